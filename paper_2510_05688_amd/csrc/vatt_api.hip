@@ -125,7 +125,6 @@ int build_plan(Plan& pl, const vatt_params& p, int q_len, int device) {
     pl.head_threads = kHeadThreadsLong;
 
   const int heads = pl.vbatch * p.n_q_heads;
-  const int want_blocks = 2 * pl.num_cus;
   // most workgroups per head that any of the gathering kernels uses (sizes the regions of their partial sums)
   pl.split_cap = std::min(32, std::max(1, (32 * pl.num_cus + heads - 1) / heads));
   // measured (gather kernel alone, us, with 4 / 8 / 16 / 32 / 64 workgroups per head): 512 heads 42.4 / 41.2 / 41.3 /
@@ -139,9 +138,22 @@ int build_plan(Plan& pl, const vatt_params& p, int q_len, int device) {
   // 122.4 us with 16 and 8; at 128 heads 8 to 16 of each are equal; at 32 heads 16 and 16 are best.)
   pl.given_splits = std::min(std::min(pl.split_cap, 16), std::max(1, (16 * pl.num_cus + heads - 1) / heads));
   pl.sparse_splits = std::min(std::min(pl.split_cap, 16), std::max(1, (32 * pl.num_cus + heads - 1) / heads));
-  const int kv_heads = pl.vbatch * p.n_kv_heads;
-  const int max_dense = std::max(1, (n_max + 255) / 256);
-  pl.dense_splits = std::min(std::min(64, max_dense), std::max(1, (2 * want_blocks + kv_heads - 1) / kv_heads));
+  // Dense attention.  The keys of the batch are dealt out to one workgroup per CU (contiguous cache: 28.3 us against
+  // 31.3 with two at batch 1 and 32K tokens, 312 against 318 at batch 16, 41 against 50 with 16 query tokens) or two
+  // (paged cache, where a workgroup also waits for its block-table entries: 200 -> 179 us for 32 ragged sequences,
+  // 55.8 -> 51.4 us for eight equal ones).  A row of the output has at most dense_splits partial sums: as many as one
+  // long sequence among short ones can use, within 34 MB of them.  Batches beyond 256 sequences fill the chip with
+  // one workgroup per sequence, KV head and round, and looking every workgroup's share up would cost more.
+  const int dense_jobs = p.n_kv_heads * dense_rounds(q_len * pl.group);
+  const int dense_wgs = (p.kv_layout == VATT_LAYOUT_PAGED ? 2 : 1) * pl.num_cus;
+  pl.dense_share = p.batch > 256 ? 0 : (dense_wgs + dense_jobs - 1) / dense_jobs;
+  pl.dense_splits = p.batch > 256 ? 1 : std::max(2, std::min({kDenseSplitsMax, pl.dense_share + 1, 65536 / heads}));
+  if (dense_dots(q_len, pl.group)) {
+    // (its workgroups are small: equal splits of every sequence, four workgroups per CU)
+    const int kv_heads = p.batch * p.n_kv_heads;
+    pl.dense_share = 0;
+    pl.dense_splits = std::min({64, std::max(1, (n_max + 255) / 256), std::max(1, (4 * pl.num_cus + kv_heads - 1) / kv_heads)});
+  }
 
   pl.fuse_splits = fused_splits_for(pl);
   pl.prework = pl.fuse_splits > 0 ? 1 : 0;

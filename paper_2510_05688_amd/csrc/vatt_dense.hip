@@ -1,12 +1,4 @@
 // Dense decode attention (Eq. 1) on the same cache, and the KV append.
-//
-// dense_kernel: grid = (KV heads, splits, sequences), KV head fastest: with 8 KV heads every XCD then streams
-// the K and V rows of one KV head front to back (measured 3 % faster at batch 4 and 16 than with the splits
-// fastest, the same at batch 1).  A workgroup owns a contiguous key range; each
-// wave walks its quarter of it, 4 (d = 128) rows per load, computing the G scores of a row with
-// the same lane layout as the score pass and keeping a running (max, sum, accumulator) per lane
-// group -- no LDS traffic inside the loop.  Lane groups, waves and finally splits are merged by
-// the usual log-sum-exp rule.  K and V are each read once: 2 * Hkv * n * d * 2 bytes per sequence.
 #include "vatt_internal.h"
 
 namespace vatt {
@@ -19,6 +11,19 @@ __device__ __forceinline__ float dot2_bf16(uint32_t a, uint32_t b, float acc) {
 }
 
 constexpr float kNegBig = -1.0e30f;
+constexpr int kDenseKeys = 32;  // keys a wave of the matrix-core kernel takes at a time
+
+typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
+typedef float f32x4_t __attribute__((ext_vector_type(4)));
+// The upper (lower) 16 bits of two words, those of `a` in the lower half.
+__device__ __forceinline__ uint32_t upper_halves(uint32_t a, uint32_t b) { return __builtin_amdgcn_perm(b, a, 0x07060302u); }
+__device__ __forceinline__ uint32_t lower_halves(uint32_t a, uint32_t b) { return __builtin_amdgcn_perm(b, a, 0x05040100u); }
+
+// 16 bytes of a K or V row; STREAM: nobody else reads them
+template <bool STREAM>
+__device__ __forceinline__ uint4 dense_load_16(const uint16_t* p) {
+  return STREAM ? load_stream_16(p) : *reinterpret_cast<const uint4*>(p);
+}
 
 struct DenseArgs {
   const uint16_t* q;
@@ -26,32 +31,392 @@ struct DenseArgs {
   const uint16_t* v;
   KVLayout Lk, Lv;
   const int32_t* seq_lens;
-  float* part;  // [B*Hq][splits][d + 4]: acc[d], max, sum
+  float* part;     // [B * q_len * Hq][splits][d]: partial sums of the weighted V rows
+  float2* part_ml;  // [B * q_len * Hq][splits]: (max, sum of the weights); the unused ones of a row come last, max kNegBig
   float* out_o;
   float* out_lse;
-  int n_max, Hq, splits;
-  int q_len;  // query tokens per sequence: blockIdx.z = sequence * q_len + query token (each one scans the cache)
+  int batch, n_max, Hq;
+  int splits;  // most partials a row of the output can have
+  int share;   // > 0: the keys of all sequences are dealt out evenly to this many workgroups per KV head and round;
+               // 0: every sequence is cut into `splits` equal ranges
+  int q_len;   // query tokens per sequence
+  int rounds;  // workgroups that take the same keys because their query vectors do not fit one
   float sm_scale;
 };
 
-// SHARE (multi-query steps): the query tokens of a sequence scan the same rows, so their workgroups for one
-// (KV head, split) are launched next to each other, eight apart in launch order and therefore on one XCD at
-// the same time, and read K and V with plain loads: the first to ask fetches a line from HBM, the others find
-// it in that XCD's L2.  blockIdx.y = split * q_len + query token, blockIdx.z = sequence.
-template <int D, int G, bool PAGED, bool SHARE>
-__global__ __launch_bounds__(kDenseThreads) void dense_kernel(DenseArgs A) {
+// How the keys of a batch are dealt out to the workgroups of a KV head.  The sequences' lengths in units of `unit`
+// keys are laid end to end and cut into runs, one per workgroup, so that ragged lengths leave no workgroup with more
+// than its share.  A run may hold the end of one sequence and the beginning of the next, at the price of draining and
+// refilling the workgroup's pipeline (about 2 us per further sequence).  Where that is not worth it (the sequences,
+// each rounded up to whole runs, need no more workgroups anyway, or a run is short) every sequence starts a new run:
+// 9 x 14846 tokens 61 us in whole runs, 52 us end to end; 8 x 0.2K .. 4K tokens 14.4 and 17.4 us.  The partial sums of
+// a sequence are numbered from its first run on.  A wave-wide computation (all lanes active) that every workgroup
+// makes for itself, 64 sequences at a time.
+struct DenseDeal {
+  uint32_t run;       // units per workgroup
+  bool whole;         // every sequence starts a new run
+  int b0;             // first of the 64 sequences at hand
+  uint32_t before;    // units laid out before it
+  int n;              // this lane's sequence: length (0 beyond the last), and units laid out up to its end
+  uint32_t u, incl;
+};
+__device__ __forceinline__ int dense_length(const DenseArgs& A, int b) {
+  return b < A.batch ? min(max(A.seq_lens[b], 1), A.n_max) : 0;
+}
+__device__ __forceinline__ void dense_lay_out(DenseDeal& d) {
+  const uint32_t laid = d.whole ? (d.u + d.run - 1) / d.run * d.run : d.u;
+  d.incl = d.before + wave_inclusive_scan_u32(laid);
+}
+template <int UNIT, int ROW_BYTES>
+__device__ __forceinline__ DenseDeal dense_deal(const DenseArgs& A) {
+  constexpr uint32_t kShortRun = 384 * 1024 / (2 * ROW_BYTES * UNIT);  // units: 384 KB of K and V
+  DenseDeal d;
+  d.b0 = 0;
+  d.before = 0;
+  d.n = dense_length(A, (int)(threadIdx.x & 63));
+  d.u = (uint32_t)(d.n + UNIT - 1) / UNIT;
+  auto units = [&](int b0) {
+    return b0 == 0 ? d.u : (uint32_t)(dense_length(A, b0 + (int)(threadIdx.x & 63)) + UNIT - 1) / UNIT;
+  };
+  uint32_t total = 0, longest = 0, whole_runs = 0;
+  for (int b0 = 0; b0 < A.batch; b0 += kWave) {
+    const uint32_t u = units(b0);
+    total += wave_sum_u32(u);
+    longest = max(longest, wave_max_u32(u));
+  }
+  d.run = (total + (uint32_t)A.share - 1) / (uint32_t)A.share;
+  // (a sequence has at most A.splits partial sums, and may touch one run more than its length fills)
+  if (longest > d.run * (uint32_t)(A.splits - 1)) d.run = (longest + (uint32_t)A.splits - 2) / (uint32_t)(A.splits - 1);
+  d.whole = d.run <= kShortRun;
+  if (!d.whole) {
+    for (int b0 = 0; b0 < A.batch; b0 += kWave) whole_runs += wave_sum_u32((units(b0) + d.run - 1) / d.run);
+    d.whole = whole_runs <= (uint32_t)A.share;
+  }
+  dense_lay_out(d);
+  return d;
+}
+
+// Dense attention with the query vectors of a KV head on the matrix cores: every K and V row is read from HBM
+// once for all query tokens of the sequence and all heads of the group.  Query vector c = t * G + g (query token
+// t, head g of the group) is a column of two products over 32 keys at a time,
+//   S [keys x vectors] = K Q^T   and   O^T [d x vectors] += V^T P^T,   P = exp(S - m),
+// both v_mfma_f32_16x16x32_bf16 (operand lane l: row or column l % 16, eight inner elements; result lane l: column
+// l % 16, rows 4 (l / 16) .. + 3).
+//   * The result layout of S is, with the inner index of the second product numbered to suit, its operand layout
+//     for P: lane group g = l / 16 holds keys 4 g + r and 16 + 4 g + r as inner elements r and 4 + r.
+//   * V needs no transposition through LDS: lane (g, i) loads d / 16 consecutive values of the eight rows of group
+//     g, which makes whole 256-byte rows per 16 lanes, and pairs them by rows in registers; row i of operand e
+//     is then column (d / 16) i + e of V.
+//   * P goes in as three bf16 terms (leading, next, last eight bits of the fp32 value), which add up to it exactly:
+//     the products and sums keep fp32 accuracy.
+//   * K rows pass through an LDS tile of the wave, as in the multi-query score kernel.
+// The running maximum of a column moves only when a score exceeds it by more than kLazy (a wave-uniform branch
+// that is rarely taken after the first rows); until then weights may exceed 1, by at most exp(kLazy).
+// What bounds it: the stream of K and V (2 * Hkv * n * d * 2 bytes per sequence), and from 64 query vectors on also the
+// vector instructions of exp and of splitting the weights.  One wave has one step's 16 KB in flight: K is requested
+// as soon as the last K rows are in the LDS tile, V as soon as the last V rows are used.  Measured against dot products
+// with one scan of the cache per query token: 4 x 32K tokens (77 us at 7 TB/s) with 1 / 2 / 4 / 8 query tokens 93 /
+// 146 / 271 / 528 -> 88 / 87 / 88 / 90 us; 1 x 32K with 16 query tokens 267 -> 43 us; 16 x 32K 350 -> 312 us;
+// 32 ragged sequences on 16-token pages 250 -> 180 us.
+// A workgroup's four waves are WQ groups of 16 NQT query vectors times 4 / WQ key ranges; waves with the same
+// key range read the same rows at about the same time (plain loads, so that the L1 and L2 serve the repeats).
+template <int D, bool PAGED, int NQT, int WQ>
+__global__ __launch_bounds__(kDenseThreads, 2) void dense_kernel(DenseArgs A) {
+  constexpr int S = D / 32;         // MFMA steps over a row of K
+  constexpr int E = D / 16;         // values of a V row per lane = MFMA tiles over the head dimension
+  constexpr int LPR = D / 8;        // lanes per K row load
+  constexpr int RPI = kWave / LPR;  // K rows per wave instruction
+  constexpr int KL = kDenseKeys / RPI;
+  constexpr int WAVES = kDenseThreads / kWave, WK = WAVES / WQ;
+  constexpr float kLazy = 6.0f;
+  constexpr float kLog2e = 1.44269504088896340736f;
+
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int i16 = lane & 15, g4 = lane >> 4, lrow = lane / LPR, lchunk = lane % LPR;
+  const int wq = wave % WQ, wk = wave / WQ;
+  constexpr int kUnit = kDenseKeys * WK;
+  const int kvh = blockIdx.x, slot = (int)blockIdx.y / A.rounds, round = (int)blockIdx.y - slot * A.rounds;
+  const int G = A.Hq / (int)gridDim.x, Q = A.q_len, QG = Q * G;
+  const int c_base = (round * WQ + wq) * 16 * NQT;
+
+  union Lds {
+    uint4 k[WAVES][kDenseKeys * (LPR + 1)];  // K tile of each wave; rows one chunk apart in the banks
+    float4 o[WAVES][4][E / 4][kWave];        // sums of one 16-vector tile of every wave, for the merge at the end
+  };
+  __shared__ Lds lds;
+  __shared__ float s_m[WAVES][16], s_l[WAVES][16];
+  uint4* kt = lds.k[wave];
+
+  DenseDeal deal = {};
+  uint32_t at = 0, at_end = 1;
+  if (A.share) {
+    deal = dense_deal<kUnit, 2 * D>(A);
+    at = (uint32_t)slot * deal.run;
+    at_end = at + deal.run;
+  }
+  while (at < at_end) {
+  int seq, n, split, u_lo, u_n, idle = 0;  // this workgroup's next piece of a sequence, in units
+  if (A.share) {
+    uint64_t here;
+    while ((here = __ballot(deal.incl > at)) == 0) {
+      if (deal.b0 + kWave >= A.batch) return;  // beyond the last sequence (the same in every wave)
+      deal.b0 += kWave;
+      deal.before = (uint32_t)__builtin_amdgcn_readlane((int)deal.incl, 63);
+      deal.n = dense_length(A, deal.b0 + lane);
+      deal.u = (uint32_t)(deal.n + kUnit - 1) / kUnit;
+      dense_lay_out(deal);
+    }
+    const int l = __ffsll((unsigned long long)here) - 1;
+    const uint32_t begin = l ? (uint32_t)__builtin_amdgcn_readlane((int)deal.incl, l - 1) : deal.before;
+    const uint32_t end = begin + (uint32_t)__builtin_amdgcn_readlane((int)deal.u, l);
+    seq = deal.b0 + l;
+    n = __builtin_amdgcn_readlane(deal.n, l);
+    split = slot - (int)(begin / deal.run);
+    u_lo = (int)(at - begin);
+    u_n = (int)(min(end, at_end) - at);
+    // the last piece of a sequence also marks the places of partial sums that the sequence has no pieces for
+    if (end <= at_end) idle = A.splits - 1 - split;
+    at = deal.whole ? at_end : end;
+  } else {
+    seq = blockIdx.z;
+    split = slot;
+    n = dense_length(A, seq);
+    u_n = ((n + kUnit - 1) / kUnit + A.splits - 1) / A.splits;
+    u_lo = split * u_n;
+    at = at_end;
+  }
+  const int blk_hi = min((u_lo + u_n) * kUnit, n);
+  const int lo = min(u_lo * kUnit + wk * u_n * kDenseKeys, n), hi = min(lo + u_n * kDenseKeys, blk_hi);
+
+  uint4 bq[NQT][S];
+  int seen[NQT];  // tokens the query of this lane's column sees
+#pragma unroll
+  for (int nt = 0; nt < NQT; ++nt) {
+    const int c = min(c_base + nt * 16 + i16, QG - 1);  // (columns beyond the last vector repeat it and are not stored)
+    const int t = c / G, g = c - t * G;
+    const uint16_t* src = A.q + (((int64_t)seq * Q + t) * A.Hq + (int64_t)kvh * G + g) * D + g4 * 8;
+#pragma unroll
+    for (int s = 0; s < S; ++s) bq[nt][s] = *reinterpret_cast<const uint4*>(src + s * 32);
+    seen[nt] = max(n - (Q - 1 - t), 1);
+  }
+  f32x4_t acc[NQT][E];
+  float mrun[NQT], lrun[NQT];
+#pragma unroll
+  for (int nt = 0; nt < NQT; ++nt) {
+    mrun[nt] = kNegBig;
+    lrun[nt] = 0.f;
+#pragma unroll
+    for (int e = 0; e < E; ++e) acc[nt][e] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+  }
+
+  uint4 kr[KL];
+  uint32_t vr[8][E / 2];
+  // (contiguous cache: a uniform address and 32-bit offsets, for at most 170752 tokens, take fewest registers)
+  auto row = [&](const uint16_t* base, const KVLayout& L, int i, int blk, int c) {
+    if constexpr (PAGED) return base + kv_row_offset_in<true>(L, seq, kvh, i, blk) + c;
+    else return base + kv_row_offset<false>(L, seq, kvh, 0) + (uint32_t)(i * D + c);
+  };
+  // (paged cache: the block-table entries of all rows first, so that no row waits for the entry of the one before)
+  auto load_k = [&](int i0) {
+    int blk[KL];
+    auto key = [&](int u) { return min(i0 + u * RPI + lrow, hi - 1); };
+#pragma unroll
+    for (int u = 0; u < KL; ++u) blk[u] = kv_block<PAGED>(A.Lk, seq, key(u));
+#pragma unroll
+    for (int u = 0; u < KL; ++u) kr[u] = dense_load_16<WQ == 1>(row(A.k, A.Lk, key(u), blk[u], lchunk * 8));
+  };
+  auto load_v = [&](int i0) {
+    int blk[8];
+    auto key = [&](int j) { return min(i0 + (j < 4 ? 0 : 12) + 4 * g4 + j, hi - 1); };
+#pragma unroll
+    for (int j = 0; j < 8; ++j) blk[j] = kv_block<PAGED>(A.Lv, seq, key(j));
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+      const uint16_t* src = row(A.v, A.Lv, key(j), blk[j], i16 * E);
+      if constexpr (D == 128) {
+        const uint4 x = dense_load_16<WQ == 1>(src);
+        vr[j][0] = x.x; vr[j][1] = x.y; vr[j][2] = x.z; vr[j][3] = x.w;
+      } else {
+        const uint2 x = *reinterpret_cast<const uint2*>(src);
+        vr[j][0] = x.x; vr[j][1] = x.y;
+      }
+    }
+  };
+  if (lo < hi) {
+    load_k(lo);
+    load_v(lo);
+  }
+  for (int i0 = lo; i0 < hi; i0 += kDenseKeys) {
+    // K rows into the tile, the next ones requested, the scores of 32 keys
+#pragma unroll
+    for (int u = 0; u < KL; ++u) kt[(u * RPI + lrow) * (LPR + 1) + lchunk] = kr[u];
+    load_k(i0 + kDenseKeys);
+    __builtin_amdgcn_wave_barrier();
+    f32x4_t sc[NQT][2];
+#pragma unroll
+    for (int t = 0; t < 2; ++t) {
+      uint4 ka[S];
+#pragma unroll
+      for (int s = 0; s < S; ++s) ka[s] = kt[(t * 16 + i16) * (LPR + 1) + s * 4 + g4];
+#pragma unroll
+      for (int nt = 0; nt < NQT; ++nt) {
+        sc[nt][t] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int s = 0; s < S; ++s)
+          sc[nt][t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, ka[s]),
+                                                              __builtin_bit_cast(bf16x8_t, bq[nt][s]), sc[nt][t], 0, 0, 0);
+      }
+    }
+    __builtin_amdgcn_wave_barrier();
+    const bool edge = i0 + kDenseKeys > min(hi, n - Q + 1);  // some column does not see all of the 32 keys
+    uint4 pb[NQT][3];
+#pragma unroll
+    for (int nt = 0; nt < NQT; ++nt) {
+      float s[8];
+#pragma unroll
+      for (int j = 0; j < 8; ++j) s[j] = sc[nt][j >> 2][j & 3] * A.sm_scale;
+      const int end = min(hi, seen[nt]) - i0 - 4 * g4;  // key j of this lane counts when its offset is below this
+      if (edge) {
+#pragma unroll
+        for (int j = 0; j < 8; ++j) s[j] = (j < 4 ? 0 : 12) + j < end ? s[j] : kNegBig;
+      }
+      float top = s[0];
+#pragma unroll
+      for (int j = 1; j < 8; ++j) top = fmaxf(top, s[j]);
+      if (__ballot(top > mrun[nt] + kLazy)) {
+        top = fmaxf(top, __shfl_xor(top, 16));
+        top = fmaxf(top, __shfl_xor(top, 32));
+        const float mnew = fmaxf(mrun[nt], top);
+        const float alpha = __expf(mrun[nt] - mnew);
+        mrun[nt] = mnew;
+        lrun[nt] *= alpha;
+#pragma unroll
+        for (int e = 0; e < E; ++e) acc[nt][e] *= alpha;
+      }
+      uint32_t w[3][8];
+#pragma unroll
+      for (int j = 0; j < 8; ++j) {
+        float p = __builtin_amdgcn_exp2f((s[j] - mrun[nt]) * kLog2e);
+        if (edge) p = (j < 4 ? 0 : 12) + j < end ? p : 0.f;
+        lrun[nt] += p;
+        const float r1 = p - __uint_as_float(__float_as_uint(p) & 0xffff0000u);
+        const float r2 = r1 - __uint_as_float(__float_as_uint(r1) & 0xffff0000u);
+        w[0][j] = __float_as_uint(p);
+        w[1][j] = __float_as_uint(r1);
+        w[2][j] = __float_as_uint(r2);
+      }
+#pragma unroll
+      for (int x = 0; x < 3; ++x)
+        pb[nt][x] = make_uint4(upper_halves(w[x][0], w[x][1]), upper_halves(w[x][2], w[x][3]),
+                               upper_halves(w[x][4], w[x][5]), upper_halves(w[x][6], w[x][7]));
+    }
+#pragma unroll
+    for (int e = 0; e < E; ++e) {
+      uint32_t a[4];
+#pragma unroll
+      for (int j = 0; j < 4; ++j)
+        a[j] = (e & 1) ? upper_halves(vr[2 * j][e / 2], vr[2 * j + 1][e / 2]) : lower_halves(vr[2 * j][e / 2], vr[2 * j + 1][e / 2]);
+      const uint4 va = make_uint4(a[0], a[1], a[2], a[3]);
+#pragma unroll
+      for (int nt = 0; nt < NQT; ++nt) {
+#pragma unroll
+        for (int x = 2; x >= 0; --x)
+          acc[nt][e] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, va),
+                                                               __builtin_bit_cast(bf16x8_t, pb[nt][x]), acc[nt][e], 0, 0, 0);
+      }
+    }
+    load_v(i0 + kDenseKeys);
+  }
+
+  // Log-sum-exp merge of the waves' key ranges, one 16-vector tile of every wave at a time.  The sums stay in
+  // the result layout throughout: wave wk finishes the result rows 4 g + r of its share of the r, which it reads
+  // from every wave with the same vectors, and stores the E consecutive columns of each.
+  constexpr int RW = 4 / WK;  // rows r per wave
+#pragma unroll
+  for (int nt = 0; nt < NQT; ++nt) {
+    float l = lrun[nt];
+    l += __shfl_xor(l, 16);
+    l += __shfl_xor(l, 32);
+    float m = mrun[nt], fac[WK];
+    fac[0] = 1.f;
+    if constexpr (WK > 1) {
+      __syncthreads();
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+#pragma unroll
+        for (int e = 0; e < E; e += 4)
+          lds.o[wave][r][e / 4][lane] = make_float4(acc[nt][e][r], acc[nt][e + 1][r], acc[nt][e + 2][r], acc[nt][e + 3][r]);
+      }
+      if (g4 == 0) {
+        s_m[wave][i16] = m;
+        s_l[wave][i16] = l;
+      }
+      __syncthreads();
+      l = 0.f;
+#pragma unroll
+      for (int w = 0; w < WK; ++w) m = fmaxf(m, s_m[w * WQ + wq][i16]);
+#pragma unroll
+      for (int w = 0; w < WK; ++w) {
+        fac[w] = __expf(s_m[w * WQ + wq][i16] - m);
+        l += s_l[w * WQ + wq][i16] * fac[w];
+      }
+    }
+    const int c = c_base + nt * 16 + i16;
+    const int tok = c / G, g = c - tok * G;
+    const int64_t place = (((int64_t)seq * Q + tok) * A.Hq + (int64_t)kvh * G + g) * A.splits + split;
+    float* part = A.part + place * D;
+#pragma unroll
+    for (int rr = 0; rr < RW; ++rr) {
+      const int r = wk * RW + rr;
+#pragma unroll
+      for (int e = 0; e < E; e += 4) {
+        float4 o;
+        if constexpr (WK > 1) {
+          o = make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll
+          for (int w = 0; w < WK; ++w) {
+            const float4 x = lds.o[w * WQ + wq][r][e / 4][lane];
+            o.x += x.x * fac[w];
+            o.y += x.y * fac[w];
+            o.z += x.z * fac[w];
+            o.w += x.w * fac[w];
+          }
+        } else {
+          o = make_float4(acc[nt][e][rr], acc[nt][e + 1][rr], acc[nt][e + 2][rr], acc[nt][e + 3][rr]);
+        }
+        if (c < QG) *reinterpret_cast<float4*>(part + E * (4 * g4 + r) + e) = o;
+      }
+    }
+    if (c < QG && wk == 0) {
+      for (int x = g4; x <= idle; x += 4) A.part_ml[place + x] = x == 0 ? make_float2(m, l) : make_float2(kNegBig, 0.f);
+    }
+  }
+  if (at < at_end) {
+    deal.n = dense_length(A, deal.b0 + lane);  // (read again rather than kept in registers across the keys)
+    deal.u = (uint32_t)(deal.n + kUnit - 1) / kUnit;
+    dense_lay_out(deal);
+    if (WK > 1) __syncthreads();  // the next piece's K tiles take the place of the sums
+  }
+  }
+}
+
+// One or two query vectors per KV head (single-token steps without or with little grouping), which would leave the
+// matrix cores' 16 columns empty: dot products.  A workgroup owns a range of a sequence's keys; each wave walks a
+// quarter of it with the lane layout of the score pass, keeping a running (max, sum, accumulator) per lane group, and
+// needs few enough registers for 16 waves per CU.  At d = 64: 16 x 9768 tokens on pages 101 us against 115 us of
+// dense_kernel, 4 x 25K ragged 38 against 42 us; with 4 vectors per KV head dense_kernel is ahead (57 against 62 us).
+template <int D, int G, bool PAGED>
+__global__ __launch_bounds__(kDenseThreads) void dense_dot_kernel(DenseArgs A) {
   constexpr int LPR = D / 8;
   constexpr int RPW = kWave / LPR;
   constexpr int WAVES = kDenseThreads / kWave;
   constexpr int U = 4;
 
   const int kvh = blockIdx.x;
-  const int split = SHARE ? (int)blockIdx.y / A.q_len : (int)blockIdx.y;
-  const int b = SHARE ? (int)blockIdx.z * A.q_len + (int)blockIdx.y % A.q_len : (int)blockIdx.z;
+  const int split = blockIdx.y, seq = blockIdx.z;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int sub = lane % LPR, rsub = lane / LPR;
-  const int seq = b / A.q_len, qtok = b - seq * A.q_len;
-  const int n = max(min(max(A.seq_lens[seq], 1), A.n_max) - (A.q_len - 1 - qtok), 1);  // clamp, then the causal cut
+  const int n = min(max(A.seq_lens[seq], 1), A.n_max);
   // key range of this workgroup, then of this wave (multiples of RPW * U rows except at the end)
   const int step = RPW * U;
   const int per_blk = ((n + A.splits - 1) / A.splits + step * WAVES - 1) / (step * WAVES) * (step * WAVES);
@@ -62,7 +427,7 @@ __global__ __launch_bounds__(kDenseThreads) void dense_kernel(DenseArgs A) {
   uint32_t qw[G][4];
 #pragma unroll
   for (int g = 0; g < G; ++g) {
-    const uint4 t = *reinterpret_cast<const uint4*>(A.q + ((int64_t)b * A.Hq + (int64_t)kvh * G + g) * D + sub * 8);
+    const uint4 t = *reinterpret_cast<const uint4*>(A.q + ((int64_t)seq * A.Hq + (int64_t)kvh * G + g) * D + sub * 8);
     qw[g][0] = t.x;
     qw[g][1] = t.y;
     qw[g][2] = t.z;
@@ -93,8 +458,8 @@ __global__ __launch_bounds__(kDenseThreads) void dense_kernel(DenseArgs A) {
       if (ok[u]) {
         const uint16_t* pk = A.k + kv_row_offset_in<PAGED>(A.Lk, seq, kvh, i, blk[u]) + sub * 8;
         const uint16_t* pv = A.v + kv_row_offset_in<PAGED>(A.Lv, seq, kvh, i, blk[u]) + sub * 8;
-        kk[u] = SHARE ? *reinterpret_cast<const uint4*>(pk) : load_stream_16(pk);
-        vv[u] = SHARE ? *reinterpret_cast<const uint4*>(pv) : load_stream_16(pv);
+        kk[u] = load_stream_16(pk);
+        vv[u] = load_stream_16(pv);
       }
     }
     float s[G][U];
@@ -179,75 +544,84 @@ __global__ __launch_bounds__(kDenseThreads) void dense_kernel(DenseArgs A) {
       a += s_acc[w][g][c] * sc;
       l += s_l[w][g] * sc;
     }
-    float* part = A.part + (((int64_t)b * A.Hq + (int64_t)kvh * G + g) * A.splits + split) * (D + 4);
-    part[c] = a;
-    if (c == 0) {
-      part[D] = mall;
-      part[D + 1] = l;
-    }
+    const int64_t place = ((int64_t)seq * A.Hq + (int64_t)kvh * G + g) * A.splits + split;
+    A.part[place * D + c] = a;
+    if (c == 0) A.part_ml[place] = make_float2(mall, l);
   }
 }
 
-// Log-sum-exp merge of the per-split partials of one head.  Two thread halves take alternate splits so
-// that their loads are independent and can be in flight together.
+// Log-sum-exp merge of the partial sums of one head.  Bound by the latency of two dependent loads: every wave loads
+// the (max, sum) pairs for itself, one (or two) per lane, so that the weights of the partial sums are a wave-wide
+// reduction and no barrier; two halves of the workgroup take alternate partial sums so that their loads are in
+// flight together, and the first ones are requested before it is known how many there are.
 template <int D>
-__global__ __launch_bounds__(2 * D) void dense_merge_kernel(const float* __restrict__ part, int splits, int Hq,
-                                                            int Hkv, float* __restrict__ out_o,
-                                                            float* __restrict__ out_lse) {
+__global__ __launch_bounds__(2 * D) void dense_merge_kernel(DenseArgs A, int Hkv) {
+  static_assert(kDenseSplitsMax == 2 * kWave, "two pairs per lane");
+  constexpr int kAhead = 4;
   // blockIdx.x runs over the KV heads first, then over the heads of a group (as in the dense kernel's grid)
-  const int h = head_of_block((int)blockIdx.x, Hq, Hkv, 1), b = blockIdx.y, bh = b * Hq + h;
-  const int c = threadIdx.x % D, half = threadIdx.x / D;
-  const float* p = part + (int64_t)bh * splits * (D + 4);
-  __shared__ float s_m[128], s_l[128], s_a[D];
-  for (int s = threadIdx.x; s < splits; s += 2 * D) {
-    s_m[s] = p[s * (D + 4) + D];
-    s_l[s] = p[s * (D + 4) + D + 1];
-  }
-  __syncthreads();
-  float mall = kNegBig;
-  for (int s = 0; s < splits; ++s) mall = fmaxf(mall, s_m[s]);
+  const int h = head_of_block((int)blockIdx.x, A.Hq, Hkv, 1), b = blockIdx.y;
+  const int64_t bh = (int64_t)b * A.Hq + h;
+  const int c = threadIdx.x % D, half = threadIdx.x / D, lane = threadIdx.x & 63;
+  const float* p = A.part + bh * A.splits * D + c;
+  const float2* ml = A.part_ml + bh * A.splits;
+  const float2 none = make_float2(kNegBig, 0.f);
+  const float2 x0 = lane < A.splits ? ml[lane] : none, x1 = kWave + lane < A.splits ? ml[kWave + lane] : none;
+  float first[kAhead];
+#pragma unroll
+  for (int u = 0; u < kAhead; ++u) first[u] = p[min(half + 2 * u, A.splits - 1) * D];
+  const int splits = (int)(__popcll(__ballot(x0.x > kNegBig)) + __popcll(__ballot(x1.x > kNegBig)));  // unused ones come last
+  const float mall = wave_max(fmaxf(x0.x, x1.x));
+  const float w0 = __expf(x0.x - mall), w1 = __expf(x1.x - mall);
+  const float l = wave_sum_f32(x0.y * w0 + x1.y * w1);
+  auto weight = [&](int s) {
+    return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(s < kWave ? w0 : w1), s & (kWave - 1)));
+  };
   float a = 0.f;
-#pragma unroll 8
-  for (int s = half; s < splits; s += 2) a += p[s * (D + 4) + c] * __expf(s_m[s] - mall);
+#pragma unroll
+  for (int u = 0; u < kAhead; ++u) {
+    const int s = half + 2 * u;
+    if (s < splits) a += first[u] * weight(s);
+  }
+  for (int s = half + 2 * kAhead; s < splits; s += 2) a += p[s * D] * weight(s);
+  __shared__ float s_a[D];
   if (half == 1) s_a[c] = a;
   __syncthreads();
   if (half == 0) {
-    float l = 0.f;
-    for (int s = 0; s < splits; ++s) l += s_l[s] * __expf(s_m[s] - mall);
-    out_o[(int64_t)bh * D + c] = (a + s_a[c]) / l;
-    if (c == 0 && out_lse) out_lse[bh] = mall + logf(l);
+    A.out_o[bh * D + c] = (a + s_a[c]) / l;
+    if (c == 0 && A.out_lse) A.out_lse[bh] = mall + logf(l);
   }
 }
 
-template <int D, int G>
-hipError_t launch_dense_dg(const Plan& pl, DenseArgs& A, hipStream_t st) {
-  const vatt_params& p = pl.p;
-  const bool paged = p.kv_layout == VATT_LAYOUT_PAGED;
-  if (pl.q_len > 1) {
-    dim3 grid(p.n_kv_heads, pl.dense_splits * pl.q_len, p.batch);
-    if (paged) hipLaunchKernelGGL((dense_kernel<D, G, true, true>), grid, dim3(kDenseThreads), 0, st, A);
-    else hipLaunchKernelGGL((dense_kernel<D, G, false, true>), grid, dim3(kDenseThreads), 0, st, A);
-  } else {
-    dim3 grid(p.n_kv_heads, pl.dense_splits, pl.vbatch);
-    if (paged) hipLaunchKernelGGL((dense_kernel<D, G, true, false>), grid, dim3(kDenseThreads), 0, st, A);
-    else hipLaunchKernelGGL((dense_kernel<D, G, false, false>), grid, dim3(kDenseThreads), 0, st, A);
-  }
-  hipError_t e = hipGetLastError();
+template <int D>
+hipError_t launch_dense_merge(const Plan& pl, DenseArgs& A, hipStream_t st) {
+  const hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL((dense_merge_kernel<D>), dim3(p.n_q_heads, pl.vbatch), dim3(2 * D), 0, st, A.part, pl.dense_splits,
-                     p.n_q_heads, p.n_kv_heads, A.out_o, A.out_lse);
+  hipLaunchKernelGGL((dense_merge_kernel<D>), dim3(pl.p.n_q_heads, pl.vbatch), dim3(2 * D), 0, st, A, pl.p.n_kv_heads);
   return hipGetLastError();
+}
+
+template <int D, bool PAGED>
+hipError_t launch_dense_p(const Plan& pl, DenseArgs& A, hipStream_t st) {
+  const vatt_params& p = pl.p;
+  const int vectors = pl.q_len * pl.group, waves = dense_vector_waves(vectors);
+  A.rounds = dense_rounds(vectors);
+  if (dense_dots(pl.q_len, pl.group)) {
+    dim3 grid(p.n_kv_heads, A.splits, p.batch);
+    if (pl.group == 1) hipLaunchKernelGGL((dense_dot_kernel<D, 1, PAGED>), grid, dim3(kDenseThreads), 0, st, A);
+    else hipLaunchKernelGGL((dense_dot_kernel<D, 2, PAGED>), grid, dim3(kDenseThreads), 0, st, A);
+    return launch_dense_merge<D>(pl, A, st);
+  }
+  dim3 grid(p.n_kv_heads, (A.share ? A.share + p.batch : A.splits) * A.rounds, A.share ? 1 : p.batch);
+  if (vectors <= 16) hipLaunchKernelGGL((dense_kernel<D, PAGED, 1, 1>), grid, dim3(kDenseThreads), 0, st, A);
+  else if (waves == 1) hipLaunchKernelGGL((dense_kernel<D, PAGED, 2, 1>), grid, dim3(kDenseThreads), 0, st, A);
+  else if (waves == 2) hipLaunchKernelGGL((dense_kernel<D, PAGED, 2, 2>), grid, dim3(kDenseThreads), 0, st, A);
+  else hipLaunchKernelGGL((dense_kernel<D, PAGED, 2, 4>), grid, dim3(kDenseThreads), 0, st, A);
+  return launch_dense_merge<D>(pl, A, st);
 }
 
 template <int D>
 hipError_t launch_dense_d(const Plan& pl, DenseArgs& A, hipStream_t st) {
-  switch (pl.group) {
-    case 1: return launch_dense_dg<D, 1>(pl, A, st);
-    case 2: return launch_dense_dg<D, 2>(pl, A, st);
-    case 4: return launch_dense_dg<D, 4>(pl, A, st);
-    case 8: return launch_dense_dg<D, 8>(pl, A, st);
-    default: return hipErrorInvalidValue;
-  }
+  return pl.p.kv_layout == VATT_LAYOUT_PAGED ? launch_dense_p<D, true>(pl, A, st) : launch_dense_p<D, false>(pl, A, st);
 }
 
 // One workgroup per sequence: all threads read the current length, then copy the new K and V rows of
@@ -285,11 +659,14 @@ hipError_t launch_dense(const Plan& pl, const void* q, const void* k, const void
   A.Lv.block_table = block_table;
   A.seq_lens = seq_lens;
   A.part = reinterpret_cast<float*>(static_cast<char*>(ws) + pl.off_dense_part);
+  A.part_ml = reinterpret_cast<float2*>(A.part + (int64_t)pl.vbatch * pl.p.n_q_heads * pl.dense_splits * pl.p.head_dim);
   A.out_o = out_o;
   A.out_lse = out_lse;
+  A.batch = pl.p.batch;
   A.n_max = pl.p.n_max;
   A.Hq = pl.p.n_q_heads;
   A.splits = pl.dense_splits;
+  A.share = pl.dense_share;
   A.q_len = pl.q_len;
   A.sm_scale = pl.sm_scale;
   if (pl.p.head_dim == 128) return launch_dense_d<128>(pl, A, st);

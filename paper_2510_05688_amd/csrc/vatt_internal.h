@@ -35,6 +35,12 @@ struct HeadRec {
                           // list places)
 };
 
+// Waves of a dense matrix-core workgroup that take different query vectors (32 each) of the same keys.
+inline int dense_vector_waves(int vectors) { return vectors <= 32 ? 1 : vectors <= 64 ? 2 : 4; }
+inline int dense_rounds(int vectors) { return (vectors + 127) / 128; }  // workgroups for all vectors of a KV head
+inline bool dense_dots(int q_len, int group) { return q_len == 1 && group <= 2; }  // too few vectors for the matrix cores
+constexpr int kDenseSplitsMax = 128;
+
 struct Plan {
   vatt_params p;
   int device;         // -1: geometry only
@@ -55,6 +61,7 @@ struct Plan {
   int head_threads;   // workgroup size of the per-head kernel
   int split_cap;  // upper bound of the four split counts below that share the partial-sum regions
   int gather_splits, dense_splits, vstat_splits, given_splits;
+  int dense_share;  // dense kernel: workgroups per KV head that the keys of the batch are dealt out to (0: equal splits)
   int given_fuse_splits;  // caller-supplied top-k: > 0, the second selection phase also gathers, with this many workgroups per head
   int sparse_splits;  // workgroups per head of the score kernel of the listed tokens when it only writes scores
   size_t idx_cap;

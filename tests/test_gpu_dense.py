@@ -1,0 +1,55 @@
+"""vatt_dense_decode against plain fp32 attention: every number of query-vector waves, ragged and large batches."""
+import numpy as np
+import pytest
+
+import workloads
+from workloads.configs import default_params
+
+pytestmark = pytest.mark.gpu
+
+CASES = [
+    # (batch, lengths low .. high, q_len, Hq, Hkv, d, page)
+    (1, 1, 1, 1, 1, 1, 64, 0), (1, 1, 2, 1, 4, 4, 128, 0), (3, 31, 33, 2, 8, 8, 64, 16),
+    (2, 127, 129, 4, 8, 2, 128, 0), (2, 300, 1500, 5, 8, 2, 128, 16), (3, 20, 900, 16, 4, 1, 128, 0),
+    (2, 100, 700, 17, 8, 2, 64, 8), (2, 200, 260, 33, 4, 1, 128, 64), (1, 300, 600, 40, 8, 1, 64, 0),
+    (1, 3000, 4001, 1, 32, 8, 128, 0), (70, 1, 400, 1, 4, 2, 128, 0), (130, 1, 90, 2, 2, 1, 64, 16),
+    (300, 1, 60, 1, 2, 1, 128, 0), (2, 5, 3000, 1, 8, 1, 128, 16), (1, 3, 3, 8, 4, 1, 128, 0),
+]
+
+
+@pytest.mark.parametrize("case", CASES, ids=lambda c: "-".join(map(str, c)))
+def test_dense_against_fp32_attention(case):
+    import torch
+    from paper_2510_05688_amd.session import DecodeSession
+
+    batch, lo, hi, q_len, hq, hkv, d, page = case
+    rng = np.random.default_rng(sum(case))
+    lens = rng.integers(lo, hi + 1, size=batch)
+    lens[0] = hi
+    n_max = -(-hi // page) * page if page else hi
+    wl = workloads.make_workload("dense", batch=batch, n_q_heads=hq, n_kv_heads=hkv, head_dim=d, n_max=n_max,
+                                 seq_lens=lens, seed=5, params=default_params(d), plant_frac=0.01)
+    q_bits = workloads.chunk_queries(wl, q_len, seed=2) if q_len > 1 else wl.q_bits
+    k_bits, v_bits, table = workloads.to_paged(wl, page) if page else (wl.k_bits, wl.v_bits, None)
+    sess = DecodeSession(dict(batch=batch, n_q_heads=hq, n_kv_heads=hkv, head_dim=d, n_max=n_max, kv_layout=1 if page else 0,
+                              page_size=page, num_blocks=k_bits.shape[0] if page else 0, sink=4, window=8, topk_abs=0,
+                              topk_frac=0.02, base_abs=0, base_frac=0.02, epsilon=0.1, delta=0.1, target=0, sm_scale=0.0,
+                              budget_cap_frac=1.0), q_len=q_len)
+    sess.upload(q_bits, k_bits, v_bits, wl.seq_lens, wl.seeds, table)
+    sess.dense()
+    torch.cuda.synchronize()
+    o, lse = sess.dense_o.cpu().double(), sess.dense_lse.cpu().double()
+    q = torch.from_numpy(workloads.bf16_bits_to_f32(q_bits)).reshape(batch, q_len, hq, d).double()
+    for b in range(batch):
+        for t in range(q_len):
+            seen = max(int(lens[b]) - (q_len - 1 - t), 1)
+            for j in range(hkv):
+                k = torch.from_numpy(wl.k_f32(b, j, seen)).double()
+                v = torch.from_numpy(wl.v_f32(b, j, seen)).double()
+                g = hq // hkv
+                s = q[b, t, j * g:(j + 1) * g] @ k.T / np.sqrt(d)
+                want = torch.softmax(s, dim=-1) @ v
+                got = o[b * q_len + t, j * g:(j + 1) * g]
+                assert float((got - want).norm() / want.norm()) < 2e-5, (b, t, j)
+                assert float((lse[b * q_len + t, j * g:(j + 1) * g] - torch.logsumexp(s, -1)).abs().max()) < 2e-5, (b, t, j)
+    sess.close()
