@@ -166,7 +166,7 @@ int build_plan(Plan& pl, const vatt_params& p, int q_len, int device) {
   pl.seg_off[4] = pl.seg_off[3] + pl.b0_max;
   pl.idx_cap = align_up((size_t)(pl.seg_off[4] + pl.b_max), 4);
   pl.head_lds_bytes = head_kernel_lds_bytes(n_max, pl.head_threads);
-  if (pl.head_lds_bytes + head_kernel_static_lds_bytes() > 160 * 1024) return VATT_E_UNSUPPORTED_SHAPE;
+  if (n_max > kCapacityMax || pl.head_lds_bytes + head_kernel_static_lds_bytes() > 160 * 1024) return VATT_E_UNSUPPORTED_SHAPE;
 
   size_t off = 0;
   auto take = [&](size_t bytes) {

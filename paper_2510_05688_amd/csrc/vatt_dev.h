@@ -21,14 +21,19 @@ __device__ __forceinline__ int head_of_block(int x, int Hq, int Hkv, int group_m
 // the shader clock at numbered points into the VATT_WS_DEBUG region of the workspace.  Compiled out
 // otherwise.
 #ifdef VATT_TIMING
+#ifdef VATT_TIMING_LAST
+#define VATT_STAMP_HERE (blockIdx.x == gridDim.x - 1 && blockIdx.y == gridDim.y - 1 && blockIdx.z == gridDim.z - 1)
+#else
+#define VATT_STAMP_HERE (blockIdx.x == 0 && blockIdx.y == 0 && blockIdx.z == 0)
+#endif
 #define VATT_STAMP(buf, id)                                                               \
   do {                                                                                    \
-    if ((buf) && threadIdx.x == 0 && blockIdx.x == 0 && blockIdx.y == 0 && blockIdx.z == 0) \
+    if ((buf) && threadIdx.x == 0 && VATT_STAMP_HERE) \
       (buf)[id] = __builtin_readcyclecounter();                                           \
   } while (0)
 #define VATT_NOTE(buf, id, val)                                                            \
   do {                                                                                    \
-    if ((buf) && threadIdx.x == 0 && blockIdx.x == 0 && blockIdx.y == 0 && blockIdx.z == 0) \
+    if ((buf) && threadIdx.x == 0 && VATT_STAMP_HERE) \
       (buf)[id] = (unsigned long long)(val);                                              \
   } while (0)
 #else

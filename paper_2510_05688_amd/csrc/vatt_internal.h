@@ -21,6 +21,7 @@ constexpr int kGatherThreads = 256;
 // Launch orders of the score pass (see the score kernel); the values of VATT_OPT_SCORE_ORDER.
 constexpr int kScoreOrderTile = 0, kScoreOrderKvHead = 1, kScoreOrderBlocks = 2;
 constexpr int kDenseThreads = 256;
+constexpr int kCapacityMax = 170752;   // tokens per sequence: what the selection kernel's LDS bitmaps are sized for
 constexpr int kCacheSlotsMax = 8192;   // slots of the random cache of base-sample rows, per (sequence, KV head)
 
 // What the per-head kernel leaves for the gather kernel.

@@ -12,6 +12,11 @@
 namespace vatt {
 
 constexpr uint32_t kInv32 = 0xffffffffu;
+// Mail slots in which the draws of repeated tokens find their earliest one (a power of two; the slot number and 8
+// more bits make a token, see kCapacityMax).
+constexpr uint32_t kMailSlots = 2048;
+// 32-bit words of a bitmap over n_max tokens: whole groups of four, which one store clears.
+__host__ __device__ constexpr int bitmap_words(int n_max) { return ((n_max + 127) >> 7) << 2; }
 
 // ---------------------------------------------------------------------------
 // Workgroup-wide exclusive scan of one uint32 per thread (DPP inside a wave, LDS across waves).
@@ -38,6 +43,30 @@ __device__ __forceinline__ uint32_t block_exclusive_scan(uint32_t v, uint32_t* t
   }
   *total = tot;
   return base + incl - v;
+}
+
+// The same with shared memory that nothing else uses in this launch: one barrier.
+template <int NT>
+__device__ __forceinline__ uint32_t block_exclusive_scan_once(uint32_t v, uint32_t* total, BlockScanSmem<NT>& sm) {
+  constexpr int SW = NT / kWave;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const uint32_t incl = wave_inclusive_scan_u32(v);
+  if (lane == kWave - 1) sm.wave_total[wave] = incl;
+  __syncthreads();
+  uint32_t base = 0, tot = 0;
+#pragma unroll
+  for (int w = 0; w < SW; ++w) {
+    const uint32_t t = sm.wave_total[w];
+    base += (w < wave) ? t : 0u;
+    tot += t;
+  }
+  *total = tot;
+  return base + incl - v;
+}
+
+// Number of the set bits of a wave's mask that belong to lower lanes.
+__device__ __forceinline__ uint32_t lanes_below(uint64_t mask) {
+  return __builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
 }
 
 // Where an accepted token goes: into the index list in global memory (dst, for the workgroup that writes the
@@ -94,12 +123,15 @@ struct HeadOps {
   struct HeadSmem {
     BlockScanSmem<NT> scan;
     double red[3][SW];
-    uint32_t again;
+    uint32_t again[2];
+    BlockScanSmem<NT> scan_once[3];  // for scans that run once in a launch and need no barrier before them
   };
 
-  // Workgroup sums of up to three doubles at once; every thread gets all of them.
+  // Workgroup sums of up to three doubles at once; every thread gets all of them.  (The sums of the waves are added
+  // by groups of 16 lanes of every wave, one group per sum, instead of by every thread.)
   template <int N>
   static __device__ __forceinline__ void block_sum(double (&v)[N], HeadSmem& sm) {
+    static_assert(N <= 4 && SW <= 16, "a row of 16 lanes per sum");
 #pragma unroll
     for (int j = 0; j < N; ++j) v[j] = wave_sum(v[j]);
     __syncthreads();
@@ -108,13 +140,15 @@ struct HeadOps {
       for (int j = 0; j < N; ++j) sm.red[j][threadIdx.x >> 6] = v[j];
     }
     __syncthreads();
+    const int row = (int)(threadIdx.x & 63) >> 4, w = (int)(threadIdx.x & 15);
+    double t = sm.red[min(row, N - 1)][min(w, SW - 1)];
+    t = w < SW ? t : 0.0;
+    t += dpp_f64<0xB1>(t);
+    t += dpp_f64<0x4E>(t);
+    t += dpp_f64<0x141>(t);
+    t += dpp_f64<0x140>(t);
 #pragma unroll
-    for (int j = 0; j < N; ++j) {
-      double t = 0.0;
-#pragma unroll
-      for (int w = 0; w < SW; ++w) t += sm.red[j][w];
-      v[j] = t;
-    }
+    for (int j = 0; j < N; ++j) v[j] = readlane_f64(t, 16 * j);
   }
 
   // Token read back from an index list, forced into [0, n): a list entry can never address outside the row.
@@ -137,13 +171,15 @@ struct HeadOps {
   }
 
   // Exclusive prefix of the set-bit counts of bm[0, words) into wpre; returns the number of set bits.
-  static __device__ uint32_t word_prefix(const uint32_t* bm, int words, uint32_t* wpre, HeadSmem& sm) {
+  // once: scan memory that nothing else uses in this launch (saves a barrier), or nullptr.
+  static __device__ uint32_t word_prefix(const uint32_t* bm, int words, uint32_t* wpre, HeadSmem& sm,
+                                         BlockScanSmem<NT>* once = nullptr) {
     const int wpt = (words + NT - 1) / NT;
     const int w0 = threadIdx.x * wpt;
     uint32_t cnt = 0;
     for (int w = w0; w < min(w0 + wpt, words); ++w) cnt += __popc(bm[w]);
     uint32_t total;
-    uint32_t pos = block_exclusive_scan<NT>(cnt, &total, sm.scan);
+    uint32_t pos = once ? block_exclusive_scan_once<NT>(cnt, &total, *once) : block_exclusive_scan<NT>(cnt, &total, sm.scan);
     for (int w = w0; w < min(w0 + wpt, words); ++w) {
       wpre[w] = pos;
       pos += __popc(bm[w]);
@@ -164,7 +200,7 @@ struct HeadOps {
   struct Sampler {
     uint32_t* taken;      // tokens proposed so far (bitmap, LDS)
     uint32_t* scratch;    // all-zero bitmap between uses (LDS)
-    uint32_t* mail;       // one slot per bitmap word, all-ones between uses (LDS)
+    uint32_t* mail;       // kMailSlots slots, free between batches (LDS)
     const uint32_t* bm_f; // top-k members (bitmap, LDS)
     uint32_t* wpre;       // word prefixes (LDS)
     const float* row;     // the head's scores
@@ -180,9 +216,12 @@ struct HeadOps {
   // proposed more than once in the batch, its earliest draw.
   //
   // Every draw that counts sets its token's bit in `taken`; a draw that finds the bit already set knows that
-  // the token is repeated and says so in `scratch`.  The draws of repeated tokens then post (draw number,
-  // bit position) with an atomic minimum into the mail slot of their bitmap word; the smallest draw number
-  // of a token wins its slot.  Two repeated tokens that share a word take turns (one more round per token).
+  // the token is repeated and says so in `scratch`.  The draws of repeated tokens then post (draw number, upper
+  // token bits) with an atomic minimum into the mail slot of their token (its lower bits); the smallest draw
+  // number of a token wins its slot.  Two repeated tokens that share a slot take turns (one more round per token).
+  // (Slots by token, not by bitmap word: 1024 draws from a thousand tokens repeat a dozen tokens in every word, and
+  // as many rounds took 22 K of the 71 K clocks of the selection kernel on a 1K-token row, more on shorter ones.
+  // Rows of up to kMailSlots tokens now need one round.)
   //
   // lt: the Philox block (relative to blk0) this thread generates, normally its thread index.  Two streams can
   // share one call, each thread working for one of them (its own S, with bitmaps, scratch and mail of that
@@ -239,31 +278,31 @@ struct HeadOps {
     // draws whose token is proposed more than once in this batch
     uint32_t unresolved = B.ok & test_bits4(S.scratch, B.tok);
     uint32_t later = 0;
-    for (;;) {
+    for (int round = 0;; ++round) {
+      // (the slots in question are cleared first; the flag alternates, so that it can be cleared here as well)
 #pragma unroll
       for (int e = 0; e < 4; ++e)
-        if ((unresolved >> e) & 1u) atomicMin(&S.mail[B.tok[e] >> 5], ((uint32_t)(tid * 4 + e) << 5) | (B.tok[e] & 31));
-      if (threadIdx.x == 0) sm.again = 0;
+        if ((unresolved >> e) & 1u) S.mail[B.tok[e] % kMailSlots] = kInv32;
+      if (threadIdx.x == 0) sm.again[round & 1] = 0;
       __syncthreads();
-      uint32_t won = 0;
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+        if ((unresolved >> e) & 1u)
+          atomicMin(&S.mail[B.tok[e] % kMailSlots], ((uint32_t)(tid * 4 + e) << 8) | (B.tok[e] / kMailSlots));
+      __syncthreads();
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
         if ((unresolved >> e) & 1u) {
-          const uint32_t v = S.mail[B.tok[e] >> 5];
-          if ((v & 31u) == (B.tok[e] & 31u)) {
-            if ((v >> 5) == (uint32_t)(tid * 4 + e)) won |= 1u << e; else later |= 1u << e;
+          const uint32_t v = S.mail[B.tok[e] % kMailSlots];
+          if ((v & 255u) == B.tok[e] / kMailSlots) {
+            if ((v >> 8) != (uint32_t)(tid * 4 + e)) later |= 1u << e;
             unresolved &= ~(1u << e);
           }
         }
       }
-      if (unresolved) sm.again = 1;
+      if (unresolved) sm.again[round & 1] = 1;
       __syncthreads();
-#pragma unroll
-      for (int e = 0; e < 4; ++e)
-        if ((won >> e) & 1u) S.mail[B.tok[e] >> 5] = kInv32;
-      const bool again = sm.again != 0;
-      __syncthreads();
-      if (!again) break;
+      if (sm.again[round & 1] == 0) break;
     }
     B.first = B.ok & ~later;
     VATT_STAMP(S.dbg, 3);
@@ -454,12 +493,27 @@ struct HeadOps {
   }
 };  // struct HeadOps
 
-// Philox blocks of the batch that is generated ahead, before the top-k set is known.
+// Philox blocks of the batch that is generated ahead, before the top-k set is known: at most ahead_blocks, and of the
+// stream of a sample that needs `most` accepted draws at most no more than it is likely to use.  While fewer than
+// `most` of the n_s residual tokens are taken a draw from the L middle tokens is accepted with a probability of at
+// least (n_s - most) / L, so `most` L / (n_s - most) draws suffice on average; six standard deviations are added (a
+// batch that falls short costs time only).
 template <int NT>
 __device__ __forceinline__ int ahead_blocks(int small_batches) {
   // (a workgroup of 1024 threads serves long rows, whose samples hold thousands of tokens)
   return small_batches ? kSmallBatchBlocks : (NT >= 1024 ? 1024 : min(NT, 256));
 }
+template <int NT>
+__device__ __forceinline__ int ahead_blocks(int small_batches, const HeadSizes& hs, int most) {
+  const int all = ahead_blocks<NT>(small_batches);
+  const int L = max(hs.mid_hi - hs.mid_lo, 1);
+  const float d = (float)most * (float)L / (float)max(hs.n_s - most, 1);
+  return max(1, min(all, (int)((d + 6.f * sqrtf(d) + 19.f) * 0.25f)));
+}
+// The most accepted draws the two samples can ask for: the smaller of the sample and its complement, the base sample
+// being known and the final sample anything from the base sample up.
+__device__ __forceinline__ int base_draws(const HeadSizes& hs) { return min(hs.b0, hs.n_s - hs.b0); }
+__device__ __forceinline__ int final_draws(const HeadSizes& hs) { return hs.n_s / 2; }
 
 // ---------------------------------------------------------------------------
 // The first batch of draws of one sampler stream of one (sequence, head), with repeated tokens resolved, made
@@ -480,10 +534,10 @@ struct PreArgs {
 
 constexpr int kPreThreads = 256;  // workgroup size of a job: the score kernel's
 
-// LDS layout of a job: HeadSmem, then three bitmaps of words_max words (drawn tokens, scratch, mail slots).
+// LDS layout of a job: HeadSmem, then two bitmaps of words_max words (drawn tokens, scratch) and the mail slots.
 __host__ __device__ inline size_t prework_lds_bytes(int n_max) {
-  const size_t words_max = ((size_t)(n_max + 63) >> 6) << 1;
-  return ((sizeof(HeadOps<kPreThreads>::HeadSmem) + 15) & ~size_t(15)) + 3 * words_max * sizeof(uint32_t);
+  const size_t words_max = (size_t)bitmap_words(n_max);
+  return ((sizeof(HeadOps<kPreThreads>::HeadSmem) + 15) & ~size_t(15)) + (2 * words_max + kMailSlots) * sizeof(uint32_t);
 }
 
 __device__ __forceinline__ void prework_job(const PreArgs& A, int b, int h, int stream, unsigned char* smem) {
@@ -492,7 +546,7 @@ __device__ __forceinline__ void prework_job(const PreArgs& A, int b, int h, int 
   const int tid = threadIdx.x, bh = b * A.Hq + h;
   const int n = max(min(max(A.seq_lens[b], 1), A.n_max), 1);
   const HeadSizes hs = head_sizes(n, A.sp);
-  const int words_max = ((A.n_max + 63) >> 6) << 1;
+  const int words_max = bitmap_words(A.n_max);
   const int words = (n + 31) >> 5;
   O::HeadSmem& sm = *reinterpret_cast<O::HeadSmem*>(smem);
   uint32_t* taken = reinterpret_cast<uint32_t*>(smem + ((sizeof(O::HeadSmem) + 15) & ~size_t(15)));
@@ -501,7 +555,6 @@ __device__ __forceinline__ void prework_job(const PreArgs& A, int b, int h, int 
   for (int w = tid; w < words; w += NT) {
     taken[w] = 0;
     scratch[w] = 0;
-    mail[w] = kInv32;
   }
   __syncthreads();
   const uint32_t L = (uint32_t)max(hs.mid_hi - hs.mid_lo, 1);
@@ -524,7 +577,8 @@ __device__ __forceinline__ void prework_job(const PreArgs& A, int b, int h, int 
   }
   S.m = 0.f;
   S.dbg = nullptr;
-  const int blocks = ahead_blocks<2 * NT>(A.small_batches);  // what the 512-thread selection kernel asks for
+  // (what the 512-thread selection kernel asks for)
+  const int blocks = ahead_blocks<2 * NT>(A.small_batches, hs, stream == 0 ? base_draws(hs) : final_draws(hs));
   const bool make = hs.n_s > 0 && hs.b0 < hs.n_s && blocks <= NT;
   DrawBatch mine = {};
   if (make) O::make_batch(mine, S, hs, 0u, blocks, false, false, sm, tid);

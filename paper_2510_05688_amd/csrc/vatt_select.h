@@ -174,7 +174,7 @@ struct CandView {
 constexpr int kBins = 2048;   // histogram bins of one pass
 constexpr int kSmall = 256;   // scores of one bin that are ranked directly
 
-struct TopkSmem {
+struct __align__(16) TopkSmem {
   uint32_t hist[kBins + 1];  // the last bin takes what is out of play
   uint64_t slist[kSmall];
   uint32_t slist_n;
@@ -205,6 +205,36 @@ struct TopkOps {
     }
     uint32_t total;
     uint32_t excl = block_exclusive_scan<NT>(sum, &total, sm.scan);
+    if (excl < r && r <= excl + sum) {
+      uint32_t cum = excl;
+      bool found = false;
+#pragma unroll
+      for (int q = 0; q < BPT; ++q) {
+        if (!found && cum + v[q] >= r) {
+          found = true;
+          ts.j = (uint32_t)(tid * BPT + q);
+          ts.below = cum;
+          ts.inbin = v[q];
+        }
+        cum += v[q];
+      }
+    }
+    __syncthreads();
+  }
+
+  // The same over a histogram of kBins counters that is complete (a barrier since the last addition), with scan memory
+  // of its own: two barriers.
+  static __device__ __forceinline__ void locate_once(uint32_t r, const uint32_t* hist, TopkSmem& ts, BlockScanSmem<NT>& scan) {
+    constexpr int BPT = kBins / NT;
+    const int tid = threadIdx.x;
+    uint32_t v[BPT], sum = 0;
+#pragma unroll
+    for (int q = 0; q < BPT; ++q) {
+      v[q] = hist[tid * BPT + q];
+      sum += v[q];
+    }
+    uint32_t total;
+    const uint32_t excl = block_exclusive_scan_once<NT>(sum, &total, scan);
     if (excl < r && r <= excl + sum) {
       uint32_t cum = excl;
       bool found = false;

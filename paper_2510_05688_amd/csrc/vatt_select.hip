@@ -5,9 +5,9 @@
 // (~order_key(score), token).  Usual path: the score kernel leaves the largest score of every 8 keys; the k-th
 // largest of those maxima is a lower bound of the k-th largest score (located to one bin of a 2048-bin LDS
 // histogram), the 8-key sub-tiles that reach it are listed, their scores loaded, and the scores at or above the
-// bound are the candidates, a few more than k.  The exact threshold among them: histogram over 2048
-// equal-width score bins, the bin that holds rank k located by a workgroup scan, its few scores ranked as
-// composites.  General path (short rows, very large k, long runs of equal scores): the same histogram selection
+// bound are the candidates, a few more than k.  The members among them: histogram over 2048 equal-width score
+// bins, the bin that holds rank k located by a workgroup scan, the bins before it taken whole and its few scores
+// ranked as composites.  General path (short rows, very large k, long runs of equal scores): the same histogram selection
 // streamed over the whole row, refined by further histograms over the integer keys when a bin holds many
 // scores, and by token order inside a run of equal scores, so the result is exact for any data.
 //
@@ -16,6 +16,13 @@
 // c > n_s / 2 they are the tokens left out).  The kernel processes the draw sequence in batches: all draws of
 // a batch are generated at once, repeated tokens are resolved to their earliest draw, and a prefix count in
 // draw order finds where the sample is complete; the result equals the sequential procedure bit for bit.
+//
+// What bounds it: a lone workgroup is one dependency chain of some 25 barriers and four dependent trips to global
+// memory, about 45 K clocks whatever the length of the row; so its time is the number of instructions and barriers on
+// that chain.  512 workgroups at 32K tokens also wait for their scattered reads (scores of the proposals, sub-tiles of
+// the candidates).  Measured before and after the mail slots by token, the first batches no longer than needed, the
+// histogram without an overflow counter, the lists by ballot and the fewer barriers of the top-k step: one head of 1K
+// tokens 32.6 -> 18 us, 256 heads of 0.5K - 7K tokens 46 -> 18 us, 1024 heads of 1K - 32K tokens 65 -> 54 us.
 //
 // Floating-point sums are taken in a fixed order, or as fixed-point integers where the order depends on
 // scheduling, so the statistics and the budget are reproducible too.
@@ -73,7 +80,7 @@ __global__ __launch_bounds__(NT, FD > 0 ? 1 : 4) void head_kernel(HeadArgs A) {
   const int seq = b / A.q_len, qtok = b - seq * A.q_len;
   const int n = max(min(max(A.seq_lens[seq], 1), A.n_max) - (A.q_len - 1 - qtok), 1);  // clamp, then the causal cut
   const HeadSizes hs = head_sizes(n, A.sp);
-  const int words_max = ((A.n_max + 63) >> 6) << 1;  // an even number of words: bitmaps are also written 64 bits at a time
+  const int words_max = bitmap_words(A.n_max);
   const int words = (n + 31) >> 5;
 
   HeadSmem& sm = *reinterpret_cast<HeadSmem*>(dyn_smem);
@@ -83,15 +90,18 @@ __global__ __launch_bounds__(NT, FD > 0 ? 1 : 4) void head_kernel(HeadArgs A) {
   uint32_t* taken0 = bm_f + words_max;
   uint32_t* taken1 = taken0 + words_max;
   uint32_t* scratch = taken1 + words_max;
-  uint32_t* wpre = scratch + words_max;
-  uint32_t* mail = wpre + words_max;
   // (the 512-thread kernel can generate the first batches of both streams at once: the final sample's stream
   // then needs a scratch bitmap and mail slots of its own)
   constexpr bool kTwoStreams = NT == kHeadThreads;
-  uint32_t* scratch1 = kTwoStreams ? mail + words_max : scratch;
-  uint32_t* mail1 = kTwoStreams ? scratch1 + words_max : mail;
+  uint32_t* scratch1 = kTwoStreams ? scratch + words_max : scratch;
+  uint32_t* wpre = scratch1 + words_max;
+  uint32_t* mail = wpre + words_max;
+  uint32_t* mail1 = kTwoStreams ? mail + kMailSlots : mail;
+  // Histogram of the candidates' scores: in the mail slots of the final sample's stream, once its first batch is made.
+  static_assert(kMailSlots == kBins, "the histogram takes the place of the mail slots");
+  uint32_t* cand_hist = mail1;
   // fused gather: this workgroup's share of I_f and of the final sample, and the cross-wave sums
-  uint32_t* glist = mail1 + words_max;
+  uint32_t* glist = mail1 + kMailSlots;
   uint32_t* dlist = glist + (kFused ? A.glist_cap : 0);
   // (the scores of the listed tokens, so that the gather requests V rows only)
   float* glist_sc = reinterpret_cast<float*>(dlist + (kFused ? A.dlist_cap : 0));
@@ -130,16 +140,14 @@ __global__ __launch_bounds__(NT, FD > 0 ? 1 : 4) void head_kernel(HeadArgs A) {
   rv.n = n;
   const float edge0 = (A.phase != 2 && tid < hs.n_sink) ? row[tid] : -INFINITY;
   const float edge1 = (A.phase != 2 && tid < hs.n_win) ? row[hs.mid_hi + tid] : -INFINITY;
-  for (int w = tid; w < words; w += NT) {
-    bm_f[w] = 0;
-    taken0[w] = 0;
-    taken1[w] = 0;
-    scratch[w] = 0;
-    mail[w] = kInv32;
-    if (kTwoStreams) {
-      scratch1[w] = 0;
-      mail1[w] = kInv32;
-    }
+  // cleared: the bitmaps bm_f .. scratch1, which follow each other, and the first histogram
+  for (int w = tid; w < (kTwoStreams ? 5 : 4) * (words_max / 4); w += NT)
+    reinterpret_cast<uint4*>(bm_f)[w] = make_uint4(0u, 0u, 0u, 0u);
+  for (int w = tid; w < kBins / 4; w += NT) reinterpret_cast<uint4*>(ts.hist)[w] = make_uint4(0u, 0u, 0u, 0u);
+  if (tid == 0) {
+    ts.cand_n = 0;
+    ts.qual_n = 0;
+    ts.slist_n = 0;
   }
   __syncthreads();
 
@@ -203,7 +211,9 @@ __global__ __launch_bounds__(NT, FD > 0 ? 1 : 4) void head_kernel(HeadArgs A) {
     // both streams at once: the lower half of the workgroup generates the first batch of the base sample,
     // the upper half that of the final sample
     const int half = tid >= NT / 2 ? 1 : 0;
-    const int blocks = ahead_blocks<NT>(A.small_batches);
+    const int blocks0 = ahead_blocks<NT>(A.small_batches, hs, base_draws(hs));
+    const int blocks1 = ahead_blocks<NT>(A.small_batches, hs, final_draws(hs));
+    const int blocks = half ? blocks1 : blocks0;
     DrawBatch mine = {};
     if (pre_made) {
       // made ahead, while the scores were computed: the proposals are marked as drawn, and the scores of the
@@ -226,15 +236,20 @@ __global__ __launch_bounds__(NT, FD > 0 ? 1 : 4) void head_kernel(HeadArgs A) {
       // their first microseconds, held every workgroup up for five microseconds at config 3)
       O::make_batch(mine, half ? S1 : S0, hs, 0u, blocks, false, kFused || !half, sm, tid - half * (NT / 2));
     }
-    spec0.blocks = spec1.blocks = blocks;
     spec0.have_sc = true;
     if (half) spec1 = mine; else spec0 = mine;
+    spec0.blocks = blocks0;
+    spec1.blocks = blocks1;
     spec1.have_sc = true;  // (the same answer in every thread; the lower half holds no draws of this stream)
     spec1_made = true;
     pair_made = true;
   } else if (want0) {
-    O::make_batch(spec0, S0, hs, 0u, ahead_blocks<NT>(A.small_batches), false, true, sm, tid);
+    O::make_batch(spec0, S0, hs, 0u, ahead_blocks<NT>(A.small_batches, hs, base_draws(hs)), false, true, sm, tid);
   }
+  auto clear_cand_hist = [&]() {
+    for (int w = tid; w < kBins / 4; w += NT) reinterpret_cast<uint4*>(cand_hist)[w] = make_uint4(0u, 0u, 0u, 0u);
+  };
+  if (kTwoStreams) clear_cand_hist();  // (make_batch ends with a barrier, and others follow before it is used)
   VATT_STAMP(A.dbg, 1);
 
   // ---- the head maximum m ----
@@ -279,8 +294,7 @@ __global__ __launch_bounds__(NT, FD > 0 ? 1 : 4) void head_kernel(HeadArgs A) {
       float sT = -INFINITY;
       uint32_t Tidx = kInv32;
       bool marked = false;
-      uint64_t T_cand = ~0ull;   // fast path: members are the candidates with composite <= T_cand
-      uint32_t n_cand_used = 0;
+      uint32_t n_cand_used = 0;  // fast path: members are the candidates marked in bm_f
       if (hs.k < mid_len) {
         // Fast path.  A lower bound of the k-th largest score: the k-th largest of the sub-tile maxima (of
         // the sub-tiles that lie entirely in the middle region) has at least k middle scores at or above it.
@@ -291,50 +305,41 @@ __global__ __launch_bounds__(NT, FD > 0 ? 1 : 4) void head_kernel(HeadArgs A) {
           float bound = lo_sub;  // every middle sub-tile maximum is at or above this
           const float scale = (float)(kBins - 1) / (m - lo_sub);
           if (m > lo_sub && scale < 1e30f) {
-            TKR::zero_hist(ts);
             each_sub_batch([&](const float (&v)[SU], int base) {
 #pragma unroll
               for (int u = 0; u < SU; ++u) {
                 const int t = base + u * NT + tid;
-                const bool in = t >= sub_lo && t < sub_hi;
-                atomicAdd(&ts.hist[in ? (uint32_t)((m - v[u]) * scale) : (uint32_t)kBins], 1u);
+                // (no counter for the others: on a short row thousands of additions to one address took 11 K clocks)
+                if (t >= sub_lo && t < sub_hi) atomicAdd(&ts.hist[(uint32_t)((m - v[u]) * scale)], 1u);
               }
             });
             __syncthreads();
-            TKR::locate((uint32_t)hs.k, ts, sm);
+            TKR::locate_once((uint32_t)hs.k, ts.hist, ts, sm.scan_once[0]);
             // the lower edge of the bin of the k-th largest maximum, a little further down for rounding
             bound = fmaxf(lo_sub, m - ((float)ts.j + 1.02f) / scale);
           }
           VATT_STAMP(A.dbg, 22);
           // sub-tiles that may hold a candidate: those that touch the middle region with a maximum at or
           // above the bound (order in the list does not matter)
-          if (tid == 0) {
-            ts.cand_n = 0;
-            ts.qual_n = 0;
-          }
-          __syncthreads();
           const int sub_first = hs.mid_lo / kSubTile, sub_last = (hs.mid_hi + kSubTile - 1) / kSubTile;
           each_sub_batch([&](const float (&v)[SU], int base) {
-            uint32_t hit = 0;
+            uint64_t mask[SU];
+            uint32_t tot = 0;
 #pragma unroll
             for (int u = 0; u < SU; ++u) {
               const int t = base + u * NT + tid;
-              hit |= ((t >= sub_first && t < sub_last && v[u] >= bound) ? 1u : 0u) << u;
+              mask[u] = __ballot(t >= sub_first && t < sub_last && v[u] >= bound);
+              tot += (uint32_t)__popcll(mask[u]);
             }
-            const uint32_t mine = (uint32_t)__popc(hit);
-            const uint32_t incl = wave_inclusive_scan_u32(mine);
-            const uint32_t wave_tot = (uint32_t)__builtin_amdgcn_readlane((int)incl, 63);
-            if (wave_tot) {
+            if (tot) {
               uint32_t at = 0;
-              if ((tid & 63) == 0) at = atomicAdd(&ts.qual_n, wave_tot);
+              if ((tid & 63) == 0) at = atomicAdd(&ts.qual_n, tot);
               at = (uint32_t)__builtin_amdgcn_readfirstlane((int)at);
-              uint32_t pos = at + incl - mine;
 #pragma unroll
               for (int u = 0; u < SU; ++u) {
-                if ((hit >> u) & 1u) {
-                  if (pos < (uint32_t)kCandCap) qual[pos] = (uint32_t)(base + u * NT + tid);
-                  ++pos;
-                }
+                const uint32_t pos = at + lanes_below(mask[u]);
+                if (((mask[u] >> (tid & 63)) & 1u) && pos < (uint32_t)kCandCap) qual[pos] = (uint32_t)(base + u * NT + tid);
+                at += (uint32_t)__popcll(mask[u]);
               }
             }
           });
@@ -343,85 +348,116 @@ __global__ __launch_bounds__(NT, FD > 0 ? 1 : 4) void head_kernel(HeadArgs A) {
           VATT_STAMP(A.dbg, 23);
           VATT_NOTE(A.dbg, 27, n_qual);
           if (n_qual <= (uint32_t)kCandCap) {
-            // candidates: the middle scores of those sub-tiles that are at or above the bound
+            // Candidates: the middle scores of those sub-tiles that are at or above the bound.  Two lanes read the
+            // eight scores of a sub-tile; the hits are listed by ballots, one score of every lane at a time (with a
+            // prefix sum of the lanes' hits instead, every score was a branch of its own); UQ loads in flight.
             static_assert(kSubTile == 8, "two 16-byte loads per sub-tile");
-            constexpr int Q = 2;  // sub-tiles a thread has in flight
-            for (uint32_t q0 = 0; q0 < n_qual; q0 += NT * Q) {
-              float sv[Q][kSubTile];
-              int tok0[Q];
+            const int mid_lo = hs.mid_lo, mid_n = hs.mid_hi - hs.mid_lo;
+            auto list_candidates = [&](uint32_t q0, auto uq) {
+              constexpr int UQ = decltype(uq)::value;
+              float sv[UQ][4];
+              int tok[UQ];
 #pragma unroll
-              for (int u = 0; u < Q; ++u) {
-                const uint32_t q = q0 + u * NT + tid;
-                const bool ok = q < n_qual;
-                tok0[u] = ok ? (int)min(qual[min(q, (uint32_t)(kCandCap - 1))], (uint32_t)(sub_last - 1)) * kSubTile : -1;
-                const float4* src = reinterpret_cast<const float4*>(row + max(tok0[u], 0));
-                const float4 x = ok ? src[0] : make_float4(0.f, 0.f, 0.f, 0.f);
-                const float4 y = ok ? src[1] : make_float4(0.f, 0.f, 0.f, 0.f);
+              for (int u = 0; u < UQ; ++u) {
+                const uint32_t q = q0 + (uint32_t)(u * (NT / 2) + tid / 2);
+                const int t = (int)min(qual[min(q, n_qual - 1)], (uint32_t)(sub_last - 1)) * kSubTile + (tid & 1) * 4;
+                const float4 x = *reinterpret_cast<const float4*>(row + t);
+                tok[u] = q < n_qual ? t : n;  // (a token past the row is no middle token)
                 sv[u][0] = x.x; sv[u][1] = x.y; sv[u][2] = x.z; sv[u][3] = x.w;
-                sv[u][4] = y.x; sv[u][5] = y.y; sv[u][6] = y.z; sv[u][7] = y.w;
               }
+              bool clear = !kTwoStreams && q0 == 0;
               if (q0 == 0 && want1 && !spec1_made) {
                 // the final sample's first batch of draws is generated while these loads are in flight
-                O::make_batch(spec1, S1, hs, 0u, ahead_blocks<NT>(A.small_batches), false, false, sm, tid);
+                O::make_batch(spec1, S1, hs, 0u, ahead_blocks<NT>(A.small_batches, hs, final_draws(hs)), false, false, sm, tid);
                 spec1_made = true;
+                clear = true;
               }
-              uint32_t hit = 0;
+              if (clear) clear_cand_hist();
+              auto hits = [&](int u, int e) {
+                return __ballot((uint32_t)(tok[u] + e - mid_lo) < (uint32_t)mid_n && sv[u][e] >= bound);
+              };
+              uint32_t tot = 0;
 #pragma unroll
-              for (int u = 0; u < Q; ++u) {
+              for (int u = 0; u < UQ; ++u) {
 #pragma unroll
-                for (int e = 0; e < kSubTile; ++e) {
-                  const int i = tok0[u] + e;
-                  hit |= ((tok0[u] >= 0 && i >= hs.mid_lo && i < hs.mid_hi && sv[u][e] >= bound) ? 1u : 0u)
-                         << (u * kSubTile + e);
-                }
+                for (int e = 0; e < 4; ++e) tot += (uint32_t)__popcll(hits(u, e));
               }
-              const uint32_t mine = (uint32_t)__popc(hit);
-              const uint32_t incl = wave_inclusive_scan_u32(mine);
-              const uint32_t wave_tot = (uint32_t)__builtin_amdgcn_readlane((int)incl, 63);
-              if (wave_tot) {
+              if (tot) {
                 uint32_t at = 0;
-                if ((tid & 63) == 0) at = atomicAdd(&ts.cand_n, wave_tot);
+                if ((tid & 63) == 0) at = atomicAdd(&ts.cand_n, tot);
                 at = (uint32_t)__builtin_amdgcn_readfirstlane((int)at);
-                uint32_t pos = at + incl - mine;
 #pragma unroll
-                for (int u = 0; u < Q; ++u) {
+                for (int u = 0; u < UQ; ++u) {
 #pragma unroll
-                  for (int e = 0; e < kSubTile; ++e) {
-                    if ((hit >> (u * kSubTile + e)) & 1u) {
-                      if (pos < (uint32_t)kCandCap)
-                        cand[pos] = ((uint64_t)(~float_order_key(sv[u][e])) << 32) | (uint32_t)(tok0[u] + e);
-                      ++pos;
-                    }
+                  for (int e = 0; e < 4; ++e) {
+                    const uint64_t mask = hits(u, e);
+                    const uint32_t pos = at + lanes_below(mask);
+                    if (((mask >> (tid & 63)) & 1u) && pos < (uint32_t)kCandCap)
+                      cand[pos] = ((uint64_t)(~float_order_key(sv[u][e])) << 32) | (uint32_t)(tok[u] + e);
+                    at += (uint32_t)__popcll(mask);
                   }
                 }
               }
-            }
+            };
+            if (n_qual <= NT / 2u) list_candidates(0u, std::integral_constant<int, 1>{});
+            else
+              for (uint32_t q0 = 0; q0 < n_qual; q0 += 4u * (NT / 2)) list_candidates(q0, std::integral_constant<int, 4>{});
             __syncthreads();
           }
           const uint32_t n_cand = n_qual <= (uint32_t)kCandCap ? ts.cand_n : 0u;
           VATT_STAMP(A.dbg, 24);
           VATT_NOTE(A.dbg, 26, n_cand);
           if (n_cand <= (uint32_t)kCandCap && n_cand >= (uint32_t)hs.k) {
-            CandView<NT> cv;
-            cv.list = cand;
-            cv.count = n_cand;
-            uint64_t T = ~0ull;
-            if (n_cand > (uint32_t)hs.k)
-              T = TKC::threshold(cv, hs, (uint32_t)hs.k, n_cand, bound, m, scratch, wpre, ts, sm, A.dbg);
-            // (the list order depends on scheduling: the members' weights are summed as 40-bit fixed-point
-            // integers, whose sum does not depend on the order; every weight is at most 1)
+            // The members, marked in the bitmap.  (The list order depends on scheduling: the members' weights are
+            // summed as 40-bit fixed-point integers, whose sum does not depend on the order; every weight is at most 1.)
             uint64_t fixed_sum = 0;
-            for (uint32_t t = tid; t < n_cand; t += NT) {
-              const uint64_t c = cand[t];
-              if (c <= T) {
-                const uint32_t i = min((uint32_t)c, (uint32_t)(n - 1));
-                atomicOr(&bm_f[i >> 5], 1u << (i & 31));
-                tau_key = max(tau_key, (uint32_t)(c >> 32));
-                fixed_sum += (uint64_t)(__expf(float_from_order_key(~(uint32_t)(c >> 32)) - m) * 1099511627776.0f);
+            auto member = [&](uint64_t c) {
+              const uint32_t i = min((uint32_t)c, (uint32_t)(n - 1));
+              atomicOr(&bm_f[i >> 5], 1u << (i & 31));
+              tau_key = max(tau_key, (uint32_t)(c >> 32));
+              fixed_sum += (uint64_t)(__expf(float_from_order_key(~(uint32_t)(c >> 32)) - m) * 1099511627776.0f);
+            };
+            const float cscale = (float)(kBins - 1) / (m - bound);
+            bool by_bin = n_cand > (uint32_t)hs.k && m > bound && cscale < 1e30f;
+            uint32_t r = (uint32_t)hs.k;
+            auto bin_of = [&](uint64_t c) { return (uint32_t)((m - float_from_order_key(~(uint32_t)(c >> 32))) * cscale); };
+            if (by_bin) {
+              for (uint32_t t = tid; t < n_cand; t += NT) atomicAdd(&cand_hist[bin_of(cand[t])], 1u);
+              __syncthreads();
+              VATT_STAMP(A.dbg, 20);
+              TKC::locate_once(r, cand_hist, ts, sm.scan_once[1]);
+              by_bin = ts.inbin <= (uint32_t)kSmall;
+            }
+            if (by_bin) {
+              // candidates in the bins before rank k's are members; those in its bin are ranked
+              const uint32_t j = ts.j;
+              r -= ts.below;
+              for (uint32_t t = tid; t < n_cand; t += NT) {
+                const uint64_t c = cand[t];
+                const uint32_t bin = bin_of(c);
+                if (bin < j) member(c);
+                if (bin == j) ts.slist[min(atomicAdd(&ts.slist_n, 1u), (uint32_t)(kSmall - 1))] = c;
               }
+              __syncthreads();
+              const uint32_t cnt = min(ts.slist_n, (uint32_t)kSmall);
+              if ((uint32_t)tid < cnt) {
+                const uint64_t mine = ts.slist[tid];
+                uint32_t below = 0;
+                for (uint32_t q = 0; q < cnt; ++q) below += (ts.slist[q] < mine) ? 1u : 0u;
+                if (below < r) member(mine);
+              }
+              VATT_STAMP(A.dbg, 21);
+            } else {
+              CandView<NT> cv;
+              cv.list = cand;
+              cv.count = n_cand;
+              uint64_t T = ~0ull;
+              if (n_cand > (uint32_t)hs.k)
+                T = TKC::threshold(cv, hs, (uint32_t)hs.k, n_cand, bound, m, scratch, wpre, ts, sm, A.dbg);
+              for (uint32_t t = tid; t < n_cand; t += NT)
+                if (cand[t] <= T) member(cand[t]);
             }
             fixed_sum = wave_sum(fixed_sum);
-            __syncthreads();
             if ((tid & 63) == 0) ts.wq[tid >> 6] = fixed_sum;
             __syncthreads();
             if (tid == 0) {
@@ -431,7 +467,6 @@ __global__ __launch_bounds__(NT, FD > 0 ? 1 : 4) void head_kernel(HeadArgs A) {
             }
             have_T = true;
             marked = true;
-            T_cand = T;
             n_cand_used = n_cand;
           }
         }
@@ -488,15 +523,16 @@ __global__ __launch_bounds__(NT, FD > 0 ? 1 : 4) void head_kernel(HeadArgs A) {
         __syncthreads();
       }
       // ascending token list from the bitmap
-      O::word_prefix(bm_f, words, wpre, sm);
+      O::word_prefix(bm_f, words, wpre, sm, &sm.scan_once[2]);
       if (marked) {
         // every member sits in the candidate list: its place in the ascending list is the number of members
         // below it, from the word prefix and the bits below its own (no thread walks a crowded word)
         for (uint32_t t = tid; t < n_cand_used; t += NT) {
           const uint64_t c = cand[t];
-          if (c <= T_cand) {
-            const uint32_t i = min((uint32_t)c, (uint32_t)(n - 1));
-            const uint32_t pos = wpre[i >> 5] + (uint32_t)__popc(bm_f[i >> 5] & ((1u << (i & 31)) - 1u));
+          const uint32_t i = min((uint32_t)c, (uint32_t)(n - 1));
+          const uint32_t word = bm_f[i >> 5], bit = 1u << (i & 31);
+          if (word & bit) {
+            const uint32_t pos = wpre[i >> 5] + (uint32_t)__popc(word & (bit - 1u));
             if (writer && pos < (uint32_t)A.k_max) idx[A.seg_topk + pos] = (int32_t)i;
             if (!kFused && pos < (uint32_t)A.k_max) place_sc[A.seg_topk + pos] = float_from_order_key(~(uint32_t)(c >> 32));
             to_glist((uint32_t)(hs.n_sink + hs.n_win) + pos, i, float_from_order_key(~(uint32_t)(c >> 32)));
@@ -605,7 +641,7 @@ __global__ __launch_bounds__(NT, FD > 0 ? 1 : 4) void head_kernel(HeadArgs A) {
   if constexpr (kFused) my_nf = (int)(g_hi - g_lo);
 
   VATT_STAMP(A.dbg, 32);
-  if (want1 && !spec1_made) O::make_batch(spec1, S1, hs, 0u, ahead_blocks<NT>(A.small_batches), false, false, sm, tid);
+  if (want1 && !spec1_made) O::make_batch(spec1, S1, hs, 0u, ahead_blocks<NT>(A.small_batches, hs, final_draws(hs)), false, false, sm, tid);
 
   // ---- I_bs (Algorithm 2, base sample) and the sums over it ----
   int flags = topk_flag;
@@ -954,11 +990,11 @@ hipError_t set_kernel_attributes(const Plan& pl) {
 }
 
 size_t head_kernel_lds_bytes(int n_max, int head_threads) {
-  const size_t words_max = ((size_t)(n_max + 63) >> 6) << 1;
+  const size_t words_max = (size_t)bitmap_words(n_max);
   const size_t fixed = head_threads == kHeadThreadsLong ? sizeof(HeadOps<kHeadThreadsLong>::HeadSmem)
                                                         : sizeof(HeadOps<kHeadThreads>::HeadSmem);
   return ((fixed + 15) & ~size_t(15)) + (size_t)kCandCap * (sizeof(uint64_t) + sizeof(uint32_t)) +
-         (head_threads == kHeadThreads ? 8 : 6) * words_max * sizeof(uint32_t);
+         (head_threads == kHeadThreads ? 6 * words_max + 2 * kMailSlots : 5 * words_max + kMailSlots) * sizeof(uint32_t);
 }
 
 // LDS entries of a workgroup's share of I_f and of the final sample when `splits` workgroups share a head.

@@ -43,7 +43,7 @@ __global__ __launch_bounds__(NT) void given_topk_kernel(HeadArgs A) {
   const int seq = b / A.q_len, qtok = b - seq * A.q_len;  // (sequence, query token) of a multi-query step
   const int n = max(min(max(A.seq_lens[seq], 1), A.n_max) - (A.q_len - 1 - qtok), 1);  // clamp, then the causal cut
   HeadSizes hs = head_sizes(n, A.sp);
-  const int words_max = ((A.n_max + 63) >> 6) << 1;
+  const int words_max = bitmap_words(A.n_max);
   const int words = (n + 31) >> 5;
   HeadSmem& sm = *reinterpret_cast<HeadSmem*>(dyn_smem);
   uint64_t* cand = reinterpret_cast<uint64_t*>(dyn_smem + ((sizeof(HeadSmem) + 15) & ~size_t(15)));
@@ -53,11 +53,11 @@ __global__ __launch_bounds__(NT) void given_topk_kernel(HeadArgs A) {
   uint32_t* wpre = scratch + words_max;
   uint32_t* mail = wpre + words_max;
   // fused gather (second phase): this workgroup's share of the final sample, and the cross-wave sums
-  uint32_t* dlist = mail + words_max;
+  uint32_t* dlist = mail + kMailSlots;
   float* g_red = reinterpret_cast<float*>(dlist + (kFused ? A.dlist_cap : 0));
   // fused scores (first phase): this workgroup's run of I_f, its share of the base sample and, for a base sample
   // from the random cache, the slots of that share
-  uint32_t* glist = mail + words_max;
+  uint32_t* glist = mail + kMailSlots;
   uint32_t* blist = glist + (kFused ? A.glist_cap : 0);
   uint32_t* bslot = blist + (kFused ? A.dlist_cap : 0);
   const int n_fix0 = 0;
@@ -69,7 +69,6 @@ __global__ __launch_bounds__(NT) void given_topk_kernel(HeadArgs A) {
     bm_f[w] = 0;
     taken[w] = 0;
     scratch[w] = 0;
-    mail[w] = kInv32;
   }
   __syncthreads();
   if (A.phase == 0) {
