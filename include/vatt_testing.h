@@ -26,9 +26,9 @@ extern "C" {
  *   VATT_OPT_HEAD_THREADS = 512 or 1024: workgroup size of the selection kernel.  The plan picks 512 for
  *     n_max <= 32768, and 1024 for longer rows when that costs no parallelism.  To be set on the plan's device.
  *   VATT_OPT_SCORE_ORDER = 0 / 1 / 2: launch order of the score pass, i.e. which of the chip's XCDs reads which
- *     tile: 0 tile by tile across the XCDs, 1 all tiles of a KV head on one XCD, 2 like 0 in blocks of 256 KiB
- *     of K.  The plan picks 1 up to n_max = 65536 when the KV head count is a multiple of 8, else 2.
- *     Multi-query plans have order 0 only (VATT_E_UNSUPPORTED_SHAPE otherwise).
+ *     piece: 0 tile by tile across the XCDs, 1 all of a KV head on one XCD, 2 like 0 in blocks of 256 KiB of K.  The
+ *     plan picks 1 below 64K tokens and 32 MB of scores per call when the KV head count is a multiple of 8, else 2.
+ *     Multi-query plans take 0 only (VATT_E_UNSUPPORTED_SHAPE otherwise) and pick their own order.
  *   VATT_OPT_FUSED_GATHER = 0, 1, 2, 4, 8 or 16: 0 keeps selection and gather in kernels of their own; S > 0
  *     runs them as one kernel with S workgroups per head (denominator target, 512-thread selection and fresh
  *     final samples only; VATT_E_UNSUPPORTED_SHAPE when the kernel's LDS does not hold that split).  The plan
@@ -36,7 +36,7 @@ extern "C" {
  *     and statistics are identical; the output sums run in another order.
  *   VATT_OPT_SCORE_PREWORK = 0 / 1: with the fused gather, whether the first batches of the sampler's draw
  *     sequences are made by the first workgroups of the score launch while the rest of it streams K (1, the
- *     default for such plans in the KV-head-major launch order) or by the selection kernel itself (0).
+ *     default for such plans) or by the selection kernel itself (0).
  *   VATT_OPT_GIVEN_SPLITS, VATT_OPT_SPARSE_SPLITS = 1 .. enough for 32 workgroups per CU (at most 32): workgroups per head of
  *     the gather kernel and of the score kernel of the listed tokens on the path with a caller-supplied top-k set
  *     (tuning aids; the plan picks both).

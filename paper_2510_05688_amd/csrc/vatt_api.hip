@@ -95,17 +95,18 @@ int build_plan(Plan& pl, const vatt_params& p, int q_len, int device) {
 
   // Workgroups go to the eight XCDs round-robin in launch order.  With a multiple of 8 KV heads the selection,
   // gather and merge kernels launch the query heads of a KV head on one XCD (they read the same sink, window and
-  // heavy V rows).  The score pass has three launch orders (see its kernel): by measurement the KV-head-major
-  // one up to 64K tokens when the KV heads can be dealt out to the XCDs evenly, the blocks order otherwise (the
-  // tile-major one is 1 - 2 % behind it and stays for tests).  The multi-query score kernel has one order of
-  // its own.
+  // heavy V rows).  The score pass has three launch orders (see vatt_score.h): by measurement the KV-head-major one below
+  // 64K tokens and 32 MB of scores when the KV heads can be dealt out to the XCDs evenly, the blocks order otherwise
+  // (whole call, KV-head-major / blocks, us: 1 x 32K 37.6 / 39.0, 8 x 16K 85.3 / 86.1, 2 x 64K 99.6 / 98.3, 8 x 32K 141 /
+  // 140, 16 x 32K 262 / 260, 4 x 128K 274 / 257; tile by tile is behind both everywhere and stays for tests).  The
+  // multi-query score kernel picks its own.
   pl.group_major = (p.n_kv_heads % 8 == 0) ? 1 : 0;
-  pl.score_order = (pl.group_major && p.n_max <= 65536) ? kScoreOrderKvHead : kScoreOrderBlocks;
+  pl.score_order = pl.group_major && p.n_max < 65536 && score_bytes(pl) < kScoreBytesLarge ? kScoreOrderKvHead : kScoreOrderBlocks;
   if (q_len != 1) pl.score_order = kScoreOrderTile;
 
   const int n_max = p.n_max;
   pl.n_pad = (int)align_up((size_t)n_max, 256);
-  pl.n_sub = (int)align_up((size_t)n_max, kScoreTilePaged) / kSubTile;  // whole tiles of either tile size
+  pl.n_sub = (int)align_up((size_t)n_max, 256) / kSubTile;
   int k_max = p.topk_abs > 0 ? p.topk_abs : (int)std::floor((double)p.topk_frac * (double)n_max);
   pl.k_max = std::min(std::max(k_max, 0), n_max);
   int b0_max = p.base_abs > 0 ? p.base_abs : (int)std::floor((double)p.base_frac * (double)n_max);

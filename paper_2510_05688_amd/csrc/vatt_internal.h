@@ -11,9 +11,6 @@
 
 namespace vatt {
 
-constexpr int kScoreTile = 64;        // keys per score-kernel workgroup (small tiles: many short workgroups fill and
-                                      // drain the chip more evenly than few long ones; measured 64 > 128 > 256 > 32)
-constexpr int kScoreTilePaged = 256;  // keys per score-kernel workgroup on a paged cache
 constexpr int kSubTile = 8;            // keys per sub-tile maximum
 constexpr int kHeadThreads = 512;      // workgroup size of the per-head kernel
 constexpr int kHeadThreadsLong = 1024; // ... for rows whose 8-key maxima do not fit the registers of 512 threads
@@ -85,6 +82,11 @@ struct Plan {
   KVLayout kv_k, kv_v;  // templates; base pointers are passed per call
 };
 
+// Bytes of score rows a call writes, and the size from which on they are taken to outgrow the last-level cache beside
+// what else passes through it.
+inline size_t score_bytes(const Plan& pl) { return (size_t)pl.vbatch * pl.p.n_q_heads * pl.p.n_max * sizeof(float); }
+constexpr size_t kScoreBytesLarge = 32000000;
+
 // Every launcher returns a hipError_t from hipGetLastError() after the launch.
 // seq_seeds: needed (may be nullptr otherwise) when score_prework(pl)
 hipError_t launch_score(const Plan& pl, const void* q, const void* k, const int32_t* block_table,
@@ -104,10 +106,10 @@ hipError_t launch_head_fused(const Plan& pl, const void* v, const int32_t* block
                              const uint64_t* seq_seeds, void* ws, int32_t* out_idx, int32_t* out_counts,
                              double* out_budget_raw, float* out_stats, bool pre_made, hipStream_t st);
 // Whether workgroups of the score launch make the sampler streams' first batches for the fused selection kernel
-// (single-token steps in the KV-head-major launch order only).
+// (single-token steps only).
 inline bool score_prework(const Plan& pl) {
   return pl.prework && pl.fuse_splits > 0 && !pl.nested_samples && !pl.ascending_samples && pl.q_len == 1 &&
-         pl.p.target == VATT_TARGET_D && pl.score_order == kScoreOrderKvHead;
+         pl.p.target == VATT_TARGET_D;
 }
 hipError_t launch_gather_merge(const Plan& pl, void* ws, int splits, float* out_o, float* out_lse, hipStream_t st);
 int fused_splits_for(const Plan& pl);           // the plan's own choice (0: separate kernels)
