@@ -37,6 +37,15 @@ struct GatherArgs {
   int q_len;  // query tokens per sequence: blockIdx.z = sequence * q_len + query token
 };
 
+// Workgroups of a head that take part, of the `splits` the grid has for it: no more than its list fills with steps.
+// A workgroup costs a chain of about four memory round trips however few rows it has, and the lengths of the lists are
+// only known here: with all 16 of them 8 sequences of 0.5K - 7K tokens (497 rows a head) took 16.7 us, with as many as there
+// are steps of 128 rows 9.4 us, with two for each step 11; long lists are as fast as before (16 x 32K tokens, 1867 rows: 40 us,
+// 6.1 TB/s of V rows).  One that takes part alone writes the result itself.
+__device__ __forceinline__ int used_splits(int splits, int total, int step_rows) {
+  return min(splits, (total + step_rows - 1) / step_rows);
+}
+
 // A head's list is walked by position: [sink | window | top-k | tail) where the tail is the final sample
 // (scaled by n_s/b) or, for the statistics pass, the base sample (unscaled).
 template <int D, bool PAGED, bool STATS>
@@ -63,7 +72,9 @@ __global__ __launch_bounds__(kGatherThreads) void gather_kernel(GatherArgs A) {
   const bool tail_by_token = r.tail_by_token != 0;               // (the same for the whole workgroup)
   const uint16_t* v_head = PAGED ? A.v : A.v + (int64_t)seq * A.L.seq_stride + (int64_t)kvh * A.L.head_stride;
   const int total = r.n_sink + r.n_win + r.k + r.b;
-  const int per = (total + A.splits - 1) / A.splits;
+  const int splits = STATS ? A.splits : used_splits(A.splits, total, RPB * U);
+  if (split >= splits) return;
+  const int per = (total + splits - 1) / splits;
   const int p_lo = split * per, p_hi = min(p_lo + per, total);
   const uint32_t seg_sink = (uint32_t)A.seg_sink, seg_win = (uint32_t)A.seg_win, seg_topk = (uint32_t)A.seg_topk;
   const uint32_t seg_tail = (uint32_t)(STATS ? A.seg_base : A.seg_dyn), last_place = (uint32_t)A.idx_cap - 1u;
@@ -226,14 +237,14 @@ __global__ __launch_bounds__(kGatherThreads) void gather_kernel(GatherArgs A) {
     float a = 0.f;
 #pragma unroll
     for (int w2 = 0; w2 < WAVES; ++w2) a += s_acc[w2][tid];
-    if (A.splits == 1) {
+    if (splits == 1) {
       A.out_o[(int64_t)bh * D + tid] = a / dtot;  // one workgroup per head: finished here
     } else {
       part[tid] = a;
     }
   }
   if (tid == 0) {
-    if (A.splits == 1) {
+    if (splits == 1) {
       if (A.out_lse) A.out_lse[bh] = r.m + logf(dtot);
     } else {
       part[D] = dtot;
@@ -241,23 +252,41 @@ __global__ __launch_bounds__(kGatherThreads) void gather_kernel(GatherArgs A) {
   }
 }
 
-// Adds the per-split partial sums of a head in split order: O = N / D, lse = m + ln D.
+// Adds the per-split partial sums of a head in split order: O = N / D, lse = m + ln D.  step_rows > 0: only the splits
+// that took part (used_splits) have written theirs, and a single one has finished the head.  Bound by the trip to memory: the
+// first eight partial sums are requested beside the head record that says how many there are.
 template <int D>
 __global__ __launch_bounds__(D) void gather_merge_kernel(const float* __restrict__ part,
                                                          const HeadRec* __restrict__ head_rec, int splits, int Hq,
                                                          float* __restrict__ out_o, float* __restrict__ out_lse,
-                                                         int group_major, int Hkv) {
+                                                         int group_major, int Hkv, int step_rows) {
   const int h = head_of_block((int)blockIdx.x, Hq, Hkv, group_major), b = blockIdx.y, bh = b * Hq + h;
   const int c = threadIdx.x;
   const float* p = part + (int64_t)bh * splits * (D + 4);
+  const HeadRec r = head_rec[bh];
+  constexpr int U = 8;
+  float v[U], w[U];
+  auto load = [&](int s0) {
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      v[u] = p[min(s0 + u, splits - 1) * (D + 4) + c];
+      w[u] = p[min(s0 + u, splits - 1) * (D + 4) + D];
+    }
+  };
+  load(0);
+  const int used = step_rows > 0 ? used_splits(splits, r.n_sink + r.n_win + r.k + r.b, step_rows) : splits;
+  if (step_rows > 0 && used == 1) return;
   float a = 0.f, dtot = 0.f;
-#pragma unroll 8
-  for (int s = 0; s < splits; ++s) {
-    a += p[s * (D + 4) + c];
-    dtot += p[s * (D + 4) + D];
+  for (int s0 = 0; s0 < used; s0 += U) {
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      a += s0 + u < used ? v[u] : 0.f;
+      dtot += s0 + u < used ? w[u] : 0.f;
+    }
+    if (s0 + U < used) load(s0 + U);
   }
   out_o[(int64_t)bh * D + c] = a / dtot;
-  if (c == 0 && out_lse) out_lse[bh] = head_rec[bh].m + logf(dtot);
+  if (c == 0 && out_lse) out_lse[bh] = r.m + logf(dtot);
 }
 
 template <int D, bool STATS>
@@ -298,7 +327,7 @@ hipError_t launch_gather_d(const Plan& pl, const void* v, const int32_t* block_t
   hipError_t e = hipGetLastError();
   if (e != hipSuccess || STATS || A.splits == 1) return e;
   hipLaunchKernelGGL((gather_merge_kernel<D>), dim3(p.n_q_heads, pl.vbatch), dim3(D), 0, st, A.part, A.head_rec,
-                     A.splits, p.n_q_heads, out_o, out_lse, pl.group_major, p.n_kv_heads);
+                     A.splits, p.n_q_heads, out_o, out_lse, pl.group_major, p.n_kv_heads, (kGatherThreads / (D / 8)) * 8);
   return hipGetLastError();
 }
 
@@ -318,10 +347,10 @@ hipError_t launch_gather_merge(const Plan& pl, void* ws, int splits, float* out_
   const HeadRec* rec = reinterpret_cast<const HeadRec*>(w + pl.off_head_rec);
   if (p.head_dim == 128)
     hipLaunchKernelGGL((gather_merge_kernel<128>), dim3(p.n_q_heads, pl.vbatch), dim3(128), 0, st, part, rec, splits,
-                       p.n_q_heads, out_o, out_lse, pl.group_major, p.n_kv_heads);
+                       p.n_q_heads, out_o, out_lse, pl.group_major, p.n_kv_heads, 0);
   else if (p.head_dim == 64)
     hipLaunchKernelGGL((gather_merge_kernel<64>), dim3(p.n_q_heads, pl.vbatch), dim3(64), 0, st, part, rec, splits,
-                       p.n_q_heads, out_o, out_lse, pl.group_major, p.n_kv_heads);
+                       p.n_q_heads, out_o, out_lse, pl.group_major, p.n_kv_heads, 0);
   else
     return hipErrorInvalidValue;
   return hipGetLastError();

@@ -1,0 +1,39 @@
+"""Gather and merge at the edges of the rows a workgroup takes per step (128 of 128 columns, 256 of 64): contexts short
+enough to be selected whole, so that the output is plain attention."""
+import numpy as np
+import pytest
+
+import workloads
+from workloads.configs import default_params
+from util import plan_params
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("paged", [False, True])
+@pytest.mark.parametrize("d", [64, 128])
+def test_whole_contexts_around_a_step(d, paged):
+    import torch
+    from paper_2510_05688_amd import binding as vb
+    from paper_2510_05688_amd.session import DecodeSession
+    lens = [1, 127, 128, 129, 255, 256, 257, 511, 513, 1025, 2048, 2049]
+    p = default_params(d, sink=16, window=48, topk_abs=2049, topk_frac=0.0, base_abs=8, base_frac=0.0)
+    n_max = 2064 if paged else 2049
+    wl = workloads.make_workload("whole", batch=len(lens), n_q_heads=4, n_kv_heads=2, head_dim=d, n_max=n_max,
+                                 seq_lens=lens, seed=3, params=p, plant_frac=0.01)
+    k_bits, v_bits, table = workloads.to_paged(wl, 16) if paged else (wl.k_bits, wl.v_bits, None)
+    sess = DecodeSession(plan_params(wl, paged=paged, num_blocks=k_bits.shape[0] if paged else 0))
+    vb.vatt_plan_set_option(sess.plan, vb.VATT_OPT_FUSED_GATHER, 0)
+    sess.upload(wl.q_bits, k_bits, v_bits, wl.seq_lens, wl.seeds, table)
+    sess.decode()
+    res = sess.results_host()
+    q = torch.from_numpy(workloads.bf16_bits_to_f32(wl.q_bits)).reshape(len(lens), 4, d).double()
+    for b, n in enumerate(lens):
+        for h in range(4):
+            assert res["counts"][b, h, :5].sum() - res["counts"][b, h, 3] == n
+            s = torch.from_numpy(wl.k_f32(b, h // 2, n)).double() @ q[b, h] / np.sqrt(d)
+            want = torch.softmax(s, 0) @ torch.from_numpy(wl.v_f32(b, h // 2, n)).double()
+            got = torch.from_numpy(res["O"][b, h]).double()
+            assert float((got - want).norm() / want.norm()) < 2e-5, (n, h)
+            assert abs(float(torch.logsumexp(s, 0)) - float(res["lse"][b, h])) < 2e-5, (n, h)
+    sess.close()
