@@ -133,12 +133,14 @@ int build_plan(Plan& pl, const vatt_params& p, int q_len, int device) {
   // 59.1 / 66.2 / 103.8 / 186.8: 16 workgroups per CU, at most 16 per head
   pl.gather_splits = std::min(16, std::max(1, (16 * pl.num_cus + heads - 1) / heads));
   pl.vstat_splits = pl.gather_splits;
-  // (the kernels of the path with a caller-supplied top-k, by measurement: its gather, which also reads K rows
-  // and carries running maxima, 16 workgroups per CU and at most 16 per head; its score kernel, which only
-  // writes scores, 32 per CU and at most 16 per head.  At 512 heads: 128.5 us per step with 8 and 2 per head,
-  // 122.4 us with 16 and 8; at 128 heads 8 to 16 of each are equal; at 32 heads 16 and 16 are best.)
+  // (the kernels of the path with a caller-supplied top-k, by measurement: 16 workgroups per CU and at most 16 per head
+  // for its gather, 32 per CU and at most 16 per head for its score kernel, which only writes scores, and there no more than the
+  // longest list has steps for.  With half as many of both 512 heads of 32K tokens take 123 us instead of 119.6, 1024
+  // heads of 1.5K tokens 75.8 instead of 79.8.)
+  const int sparse_rows = p.sink + p.window + pl.k_max + pl.b0_max, sparse_step = kGatherThreads / (p.head_dim / 8) * 8;
   pl.given_splits = std::min(std::min(pl.split_cap, 16), std::max(1, (16 * pl.num_cus + heads - 1) / heads));
-  pl.sparse_splits = std::min(std::min(pl.split_cap, 16), std::max(1, (32 * pl.num_cus + heads - 1) / heads));
+  pl.sparse_splits = std::min({pl.split_cap, 16, std::max(1, (32 * pl.num_cus + heads - 1) / heads),
+                               std::max(1, (sparse_rows + sparse_step - 1) / sparse_step)});
   // Dense attention.  The keys of the batch are dealt out to one workgroup per CU (contiguous cache: 28.3 us against
   // 31.3 with two at batch 1 and 32K tokens, 312 against 318 at batch 16, 41 against 50 with 16 query tokens) or two
   // (paged cache, where a workgroup also waits for its block-table entries: 200 -> 179 us for 32 ragged sequences,

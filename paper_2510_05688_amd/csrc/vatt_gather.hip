@@ -37,15 +37,6 @@ struct GatherArgs {
   int q_len;  // query tokens per sequence: blockIdx.z = sequence * q_len + query token
 };
 
-// Workgroups of a head that take part, of the `splits` the grid has for it: no more than its list fills with steps.
-// A workgroup costs a chain of about four memory round trips however few rows it has, and the lengths of the lists are
-// only known here: with all 16 of them 8 sequences of 0.5K - 7K tokens (497 rows a head) took 16.7 us, with as many as there
-// are steps of 128 rows 9.4 us, with two for each step 11; long lists are as fast as before (16 x 32K tokens, 1867 rows: 40 us,
-// 6.1 TB/s of V rows).  One that takes part alone writes the result itself.
-__device__ __forceinline__ int used_splits(int splits, int total, int step_rows) {
-  return min(splits, (total + step_rows - 1) / step_rows);
-}
-
 // A head's list is walked by position: [sink | window | top-k | tail) where the tail is the final sample
 // (scaled by n_s/b) or, for the statistics pass, the base sample (unscaled).
 template <int D, bool PAGED, bool STATS>

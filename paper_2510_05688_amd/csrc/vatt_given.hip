@@ -7,13 +7,19 @@
 //   given_gather_kernel   the N and D sums of Section 4.1 over [I_f, I_dyn]: scores of I_f from the sparse
 //                         list, scores of I_dyn computed here from their K rows (with nested samples the
 //                         base-sample part of I_dyn has its scores in the list already); V rows gathered as
-//                         in the dense-scored path.  No head maximum is known in advance, so every lane group keeps a
+//                         in the dense-scored path.  No head maximum is known in advance, so every wave keeps a
 //                         running maximum and rescales (online softmax), and the merge combines the splits'
 //                         (max, D, N) partials the same way.
 //
 // grid = (query heads, splits, sequences) for both, head fastest and in head_of_block order: the splits of a
 // head, and the heads of a KV head, then share an XCD and its L2 (index lists, and the K and V rows they have in
-// common); d/8 adjacent lanes read one K or V row with one 16-byte load each.
+// common); d/8 adjacent lanes read one K or V row with one 16-byte load each.  Of a head's splits only as many take
+// part as its list has steps for (used_splits).
+//
+// What bounds them: the chain record -> list entry -> row on short lists, the pace of 256-byte rows in no order (about 6 TB/s)
+// on long ones.  Whole step, us, before (every lane of a row worked out its place, its entry requested when its step came, a
+// maximum per lane group, all splits busy) and after: 16 x 32K tokens 127 -> 119.5, 16 x 4K 71.5 -> 50.4, 8 x 0.5K - 7K
+// paged 59 -> 42, 32 x 1.5K paged 97 -> 78, 1 x 9K with 16 query tokens 89 -> 72.5, 24 x 8K of 64 columns 73.7 -> 46.
 #include <type_traits>
 
 #include "vatt_internal.h"
@@ -71,12 +77,91 @@ __device__ __forceinline__ float row_score(const uint4& kv, const uint32_t (&qw)
   return group_sum<LPR>(a) * sm_scale + 0.0f;
 }
 
-// Scores of the tokens of I_f and I_bs (HeadRec.b holds |I_bs| at this point).  With STATS (targets N and
-// SDPA) the V rows of the same tokens are read as well and the numerator statistics of Algorithm 2 are
-// accumulated on the way: N_f = sum_{I_f} w V, R1 = sum_{I_bs} w V, R2 = sum_{I_bs} ||w V||^2 with
-// w = exp(s - max); no maximum is known yet, so every lane group keeps a running one and rescales.
-template <int D, bool PAGED, bool STATS>
+// Scores of the tokens of I_f and I_bs (HeadRec.b holds |I_bs| at this point), without the numerator statistics.  What
+// belongs to a row (list place, token, slot of the random cache) is done by the row's own lane, as in gather_kernel, and
+// the list entry of the next step is requested one step ahead; row and score change lanes by wave shuffles.
+template <int D, bool PAGED>
 __global__ __launch_bounds__(kGatherThreads) void sparse_score_kernel(GivenArgs A) {
+  constexpr int LPR = D / 8;
+  constexpr int RPW = kWave / LPR;
+  constexpr int WAVES = kGatherThreads / kWave;
+  constexpr int RPB = RPW * WAVES;
+  constexpr int U = 8;
+  static_assert(U <= LPR && RPW * U <= kWave, "a lane per row of a step, and one per row of a lane group");
+  const int h = head_of_block((int)blockIdx.x, A.Hq, A.Hq / A.group, A.group_major), split = blockIdx.y, b = blockIdx.z;
+  const int bh = b * A.Hq + h;
+  const int kvh = h / A.group, seq = b / A.q_len;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int sub = lane % LPR, rsub = lane / LPR;
+  const HeadRec r = A.head_rec[bh];
+  uint32_t qw[4];
+  load_q<D>(A, bh, sub, qw);
+  const int total = r.n_sink + r.n_win + r.k + r.b;
+  const int splits = used_splits(A.splits, total, RPB * U);
+  if (split >= splits) return;
+  const int per = (total + splits - 1) / splits;
+  const int p_lo = split * per, p_hi = min(p_lo + per, total);
+  const int32_t* idx = A.idx + (int64_t)bh * A.idx_cap;
+  float* sp = A.sparse + (int64_t)bh * A.idx_cap;
+  const bool cached = r.base_cached != 0;
+  const uint16_t* cache_k = cached ? reinterpret_cast<const uint16_t*>(cache_record(A.rcache, A.rc, seq, A.Hq / A.group, kvh) + A.rc.off_k) : nullptr;
+  const int32_t* slots_of = A.base_slot + (int64_t)bh * A.b0_max;
+  const uint16_t* k_head = PAGED ? A.k : A.k + (int64_t)seq * A.Lk.seq_stride + (int64_t)kvh * A.Lk.head_stride;
+  const int n_sw = r.n_sink + r.n_win, n_fix = n_sw + r.k;
+  const uint32_t seg_sink = (uint32_t)A.seg_sink, seg_win = (uint32_t)A.seg_win, seg_topk = (uint32_t)A.seg_topk;
+  const uint32_t seg_base = (uint32_t)A.seg_base;
+  const int mine = (lane / RPW) * RPB + wave * RPW + lane % RPW;  // the row of a step that this lane prepares
+  auto place_of = [&](int p0) {
+    const int pc = min(p0 + mine, p_hi - 1), t2 = pc - n_sw, t3 = pc - n_fix;
+    const uint32_t edge = pc < r.n_sink ? seg_sink + (uint32_t)pc : seg_win + (uint32_t)(pc - r.n_sink);
+    return t3 >= 0 ? seg_base + (uint32_t)t3 : t2 >= 0 ? seg_topk + (uint32_t)t2 : edge;
+  };
+  // a row in the cache is known by its slot, with the top bit set
+  auto entry_of = [&](uint32_t place) {
+    return cached && place >= seg_base ? slots_of[place - seg_base] | (int)0x80000000 : idx[place];
+  };
+  uint32_t place_next = 0;
+  int entry_next = 0;
+  if (p_lo < p_hi) entry_next = entry_of(place_next = place_of(p_lo));
+  for (int p0 = p_lo; p0 < p_hi; p0 += RPB * U) {
+    const uint32_t place = place_next;
+    const int entry = entry_next;
+    entry_next = entry_of(place_next = place_of(p0 + RPB * U));  // (beyond the range: its last place once more)
+    const bool in_cache = cached && entry < 0;
+    const int row_mine = in_cache ? min(entry & 0x7fffffff, A.rc.slots - 1) | (int)0x80000000 : min(max(entry, 0), r.n - 1);
+    int row[U], blk[U];
+    uint4 kv[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) row[u] = __shfl(row_mine, u * RPW + rsub);
+#pragma unroll
+    for (int u = 0; u < U; ++u) blk[u] = kv_block<PAGED>(A.Lk, seq, row[u] < 0 ? 0 : row[u]);
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int i = row[u] & 0x7fffffff;
+      const uint16_t* at = PAGED ? A.k + kv_row_offset_in<true>(A.Lk, seq, kvh, i, blk[u]) : k_head + (uint32_t)i * (uint32_t)D;
+      // (rows of the cache without the non-temporal hint: the group's heads share them; 115.7 -> 110.7 us for a whole step of
+      // 16 x 32K tokens)
+      if (row[u] < 0) kv[u] = *reinterpret_cast<const uint4*>(cache_k + ((uint32_t)i * (uint32_t)D + (uint32_t)(sub * 8)));
+      else kv[u] = load_stream_16(at + sub * 8);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    float s = 0.f;  // lane u of a group keeps the score of the group's row u
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const float su = row_score<LPR>(kv[u], qw, A.sm_scale);
+      s = sub == u ? su : s;
+    }
+    const int from = (sub % U) * RPW + rsub;  // the lane that prepared that row
+    const uint32_t to = (uint32_t)__shfl((int)place, from);
+    if (sub < U && p0 + sub * RPB + wave * RPW + rsub < p_hi) sp[to] = s;
+  }
+}
+
+// The same with the numerator statistics (targets N and SDPA): the V rows of the same tokens are read as well and the
+// statistics of Algorithm 2 are accumulated on the way: N_f = sum_{I_f} w V, R1 = sum_{I_bs} w V, R2 = sum_{I_bs} ||w V||^2 with
+// w = exp(s - max); no maximum is known yet, so every lane group keeps a running one and rescales.
+template <int D, bool PAGED>
+__global__ __launch_bounds__(kGatherThreads) void sparse_stats_kernel(GivenArgs A) {
   constexpr int LPR = D / 8;
   constexpr int RPW = kWave / LPR;
   constexpr int WAVES = kGatherThreads / kWave;
@@ -127,7 +212,6 @@ __global__ __launch_bounds__(kGatherThreads) void sparse_score_kernel(GivenArgs 
       for (int u = 0; u < U; ++u) {
         tok[u] = idx[place[u]];
         slot[u] = 0;
-        vv[u] = make_uint4(0u, 0u, 0u, 0u);
       }
       if (kTail && cached) {
         // the copies of the rows in the cache: rows of neighbouring slots, shared by the group's heads
@@ -137,7 +221,7 @@ __global__ __launch_bounds__(kGatherThreads) void sparse_score_kernel(GivenArgs 
         for (int u = 0; u < U; ++u) {
           const int64_t so = (int64_t)min(max(slot[u], 0), A.rc.slots - 1) * D + sub * 8;
           kv[u] = *reinterpret_cast<const uint4*>(reinterpret_cast<const uint16_t*>(cache_rec + A.rc.off_k) + so);
-          if (STATS) vv[u] = *reinterpret_cast<const uint4*>(reinterpret_cast<const uint16_t*>(cache_rec + A.rc.off_v) + so);
+          vv[u] = *reinterpret_cast<const uint4*>(reinterpret_cast<const uint16_t*>(cache_rec + A.rc.off_v) + so);
         }
       } else {
         int blk[U];
@@ -149,14 +233,14 @@ __global__ __launch_bounds__(kGatherThreads) void sparse_score_kernel(GivenArgs 
 #pragma unroll
         for (int u = 0; u < U; ++u) {
           kv[u] = load_stream_16(A.k + kv_row_offset_in<PAGED>(A.Lk, b / A.q_len, kvh, tok[u], blk[u]) + sub * 8);
-          if (STATS) vv[u] = load_stream_16(A.v + kv_row_offset_in<PAGED>(A.Lv, b / A.q_len, kvh, tok[u], blk[u]) + sub * 8);
+          vv[u] = load_stream_16(A.v + kv_row_offset_in<PAGED>(A.Lv, b / A.q_len, kvh, tok[u], blk[u]) + sub * 8);
         }
       }
 #pragma unroll
       for (int u = 0; u < U; ++u) {
         const float s = row_score<LPR>(kv[u], qw, A.sm_scale);
         if (valid[u] && sub == 0) sp[place[u]] = s;
-        if (STATS && valid[u]) {
+        if (valid[u]) {
           if (s > m_run) {
             const float f = __expf(m_run - s);  // 0 when m_run is -inf
 #pragma unroll
@@ -187,9 +271,8 @@ __global__ __launch_bounds__(kGatherThreads) void sparse_score_kernel(GivenArgs 
   };
   walk(p_lo, min(p_hi, n_fix), std::false_type{});
   walk(max(p_lo, n_fix), p_hi, std::true_type{});
-  if (!STATS) return;
   // every lane group has its own (maximum, N_f, R1, R2 share): bring them to the workgroup's maximum and add
-  __shared__ float s_f[STATS ? GROUPS : 1][STATS ? D : 1], s_b[STATS ? GROUPS : 1][STATS ? D : 1];
+  __shared__ float s_f[GROUPS][D], s_b[GROUPS][D];
   __shared__ float s_r2[GROUPS][LPR], s_m[GROUPS];
   const int g = wave * RPW + rsub;
 #pragma unroll
@@ -230,152 +313,193 @@ __global__ __launch_bounds__(kGatherThreads) void sparse_score_kernel(GivenArgs 
   }
 }
 
+// N and D over [I_f, I_dyn] by list place, in the manner of gather_kernel: what belongs to a row is done by the row's own
+// lane, list entries and known scores are requested one step ahead, all rows of a step are in flight together.  Rows of newly
+// drawn tokens bring their K row along; lane u of a group keeps the score of the group's row u and passes it to the row's
+// own lane.  A wave has one running maximum, raised once per step.
 template <int D, bool PAGED>
 __global__ __launch_bounds__(kGatherThreads) void given_gather_kernel(GivenArgs A) {
   constexpr int LPR = D / 8;
   constexpr int RPW = kWave / LPR;
   constexpr int WAVES = kGatherThreads / kWave;
   constexpr int RPB = RPW * WAVES;
-  constexpr int GROUPS = RPB;  // lane groups of a workgroup, each with its own running maximum
   constexpr int U = 8;
+  constexpr int ROWS_W = RPW * U;
+  static_assert(U <= LPR && ROWS_W <= kWave, "a lane per row of a step, and one per row of a lane group");
   const int h = head_of_block((int)blockIdx.x, A.Hq, A.Hq / A.group, A.group_major), split = blockIdx.y, b = blockIdx.z;
   const int bh = b * A.Hq + h;
-  const int kvh = h / A.group;
+  const int kvh = h / A.group, seq = b / A.q_len;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int sub = lane % LPR, rsub = lane / LPR;
   const HeadRec r = A.head_rec[bh];
-  const int32_t* idx = A.idx + (int64_t)bh * A.idx_cap;
-  const float* sp = A.sparse + (int64_t)bh * A.idx_cap;
-  const int total = r.n_sink + r.n_win + r.k + r.b;
-  const int per = (total + A.splits - 1) / A.splits;
-  const int p_lo = split * per, p_hi = min(p_lo + per, total);
-  const float tail_bias = r.scale > 0.f ? __logf(r.scale) : 0.f;  // ln(n_s / b): sampled tokens weigh n_s / b
   uint32_t qw[4];
   load_q<D>(A, bh, sub, qw);
+  const int total = r.n_sink + r.n_win + r.k + r.b;
+  const int splits = used_splits(A.splits, total, RPB * U);
+  if (split >= splits) return;
+  const int per = (total + splits - 1) / splits;
+  const int p_lo = split * per, p_hi = min(p_lo + per, total);
+  const int32_t* idx = A.idx + (int64_t)bh * A.idx_cap;
+  const float* sp = A.sparse + (int64_t)bh * A.idx_cap;
+  const uint16_t* k_head = PAGED ? A.k : A.k + (int64_t)seq * A.Lk.seq_stride + (int64_t)kvh * A.Lk.head_stride;
+  const uint16_t* v_head = PAGED ? A.v : A.v + (int64_t)seq * A.Lv.seq_stride + (int64_t)kvh * A.Lv.head_stride;
+  const float tail_bias = r.scale > 0.f ? __logf(r.scale) : 0.f;  // ln(n_s / b): sampled tokens weigh n_s / b
+  const int n_sw = r.n_sink + r.n_win, n_fix = n_sw + r.k;
+  const int n_kept = n_fix + min(max(r.b_keep, 0), r.b);  // (nested samples: these have their scores in the base sample's places)
+  const uint32_t seg_sink = (uint32_t)A.seg_sink, seg_win = (uint32_t)A.seg_win, seg_topk = (uint32_t)A.seg_topk;
+  const uint32_t seg_base = (uint32_t)A.seg_base, seg_dyn = (uint32_t)A.seg_dyn;
+  const int mine = (lane / RPW) * RPB + wave * RPW + lane % RPW;  // the row of a step that this lane prepares
+
+  int entry_next = 0;
+  float sc_next = 0.f;
+  auto request = [&](int p0) {  // (beyond the range: its last place once more)
+    const int pc = min(p0 + mine, p_hi - 1), t2 = pc - n_sw, t3 = pc - n_fix;
+    const uint32_t edge = pc < r.n_sink ? seg_sink + (uint32_t)pc : seg_win + (uint32_t)(pc - r.n_sink);
+    const uint32_t fixed = t2 >= 0 ? seg_topk + (uint32_t)t2 : edge;
+    entry_next = idx[t3 >= 0 ? seg_dyn + (uint32_t)t3 : fixed];
+    sc_next = pc < n_kept ? sp[t3 >= 0 ? seg_base + (uint32_t)t3 : fixed] : 0.f;
+  };
+  if (p_lo < p_hi) request(p_lo);
 
   float acc[8];
 #pragma unroll
   for (int c = 0; c < 8; ++c) acc[c] = 0.f;
   float dsum = 0.f, m_run = -INFINITY;
-
-  // U rows per lane group at a time, without a branch per row (places, then tokens and known scores, then
-  // rows, then the arithmetic); a slot beyond the range repeats the range's last row and adds nothing.  Three
-  // walks: I_f (scores in the sparse list), the leading entries of the final sample that repeat the base
-  // sample (nested samples: scores in the base sample's places of the sparse list), and the rest of the final
-  // sample, whose scores are computed here from their K rows.
-  const int n_fix = r.n_sink + r.n_win + r.k;
-  auto walk = [&](int lo, int hi, auto kind_tag) {
-    constexpr int kKind = decltype(kind_tag)::value;  // 0: I_f, 1: kept base-sample entries, 2: newly drawn
-    constexpr bool kTail = kKind != 0;
-    for (int p0 = lo + wave * RPW + rsub; p0 < hi; p0 += RPB * U) {
-      int64_t place[U];
-      bool valid[U];
-      int tok[U];
-      float s[U];
-      uint4 kv[U], vv[U];
+  for (int p0 = p_lo; p0 < p_hi; p0 += RPB * U) {
+    const int p = p0 + mine;
+    const bool valid = lane < ROWS_W && p < p_hi, tail = p >= n_fix, drawn = valid && p >= n_kept;
+    const int tok_mine = min(max(entry_next, 0), r.n - 1);
+    float sc = sc_next;
+    request(p0 + RPB * U);
+    int tok[U], blk[U];
+    uint4 kv[U], vv[U];
+    // (a row with its K row: the top bit of its token)
+#pragma unroll
+    for (int u = 0; u < U; ++u) tok[u] = __shfl(drawn ? tok_mine | (int)0x80000000 : tok_mine, u * RPW + rsub);
+#pragma unroll
+    for (int u = 0; u < U; ++u) blk[u] = kv_block<PAGED>(A.Lv, seq, tok[u] & 0x7fffffff);  // (K and V share the block table)
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int i = tok[u] & 0x7fffffff;
+      const int64_t o = PAGED ? kv_row_offset_in<true>(A.Lk, seq, kvh, i, blk[u]) : 0;
+      kv[u] = make_uint4(0u, 0u, 0u, 0u);
+      if (tok[u] < 0) kv[u] = load_stream_16(PAGED ? A.k + o + sub * 8 : k_head + ((uint32_t)i * (uint32_t)D + (uint32_t)(sub * 8)));
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int i = tok[u] & 0x7fffffff;
+      const int64_t o = PAGED ? kv_row_offset_in<true>(A.Lv, seq, kvh, i, blk[u]) : 0;
+      vv[u] = load_stream_16(PAGED ? A.v + o + sub * 8 : v_head + ((uint32_t)i * (uint32_t)D + (uint32_t)(sub * 8)));
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    if (__any(drawn)) {
+      float s = 0.f;
 #pragma unroll
       for (int u = 0; u < U; ++u) {
-        const int p = p0 + u * RPB;
-        valid[u] = p < hi;
-        const int pc = min(p, hi - 1);
-        place[u] = kTail ? A.seg_dyn + (pc - n_fix)
-                         : fixed_place(pc, r.n_sink, r.n_win, A.seg_sink, A.seg_win, A.seg_topk);
+        const float su = row_score<LPR>(kv[u], qw, A.sm_scale);
+        s = sub == u ? su : s;
       }
+      const float computed = __shfl(s, (lane % RPW) * LPR + (lane / RPW) % U);
+      sc = drawn ? computed : sc;
+    }
+    const float e = valid ? sc + (tail ? tail_bias : 0.f) : -INFINITY;
+    const float m_new = fmaxf(m_run, wave_max(e));
+    const float f = m_run > -INFINITY ? __expf(m_run - m_new) : 0.f;
+    const float wt_mine = e > -INFINITY ? __expf(e - m_new) : 0.f;
+    m_run = m_new;
+    dsum = dsum * f + wt_mine;
 #pragma unroll
-      for (int u = 0; u < U; ++u) {
-        tok[u] = idx[place[u]];
-        s[u] = kKind == 2 ? 0.f : sp[kKind == 1 ? A.seg_base + (place[u] - A.seg_dyn) : place[u]];
-        kv[u] = make_uint4(0u, 0u, 0u, 0u);
-      }
-      int blk[U];
+    for (int c = 0; c < 8; ++c) acc[c] *= f;
 #pragma unroll
-      for (int u = 0; u < U; ++u) {
-        tok[u] = min(max(tok[u], 0), r.n - 1);
-        blk[u] = kv_block<PAGED>(A.Lv, b / A.q_len, tok[u]);  // (K and V share the block table)
-      }
+    for (int u = 0; u < U; ++u) {
+      const float wt = __shfl(wt_mine, u * RPW + rsub);
+      const uint32_t ww[4] = {vv[u].x, vv[u].y, vv[u].z, vv[u].w};
 #pragma unroll
-      for (int u = 0; u < U; ++u) {
-        if (kKind == 2) kv[u] = load_stream_16(A.k + kv_row_offset_in<PAGED>(A.Lk, b / A.q_len, kvh, tok[u], blk[u]) + sub * 8);
-        vv[u] = load_stream_16(A.v + kv_row_offset_in<PAGED>(A.Lv, b / A.q_len, kvh, tok[u], blk[u]) + sub * 8);
-      }
-#pragma unroll
-      for (int u = 0; u < U; ++u) {
-        // (the lanes of a group stay together: every lane of the group computes the row's score)
-        if (kKind == 2) s[u] = row_score<LPR>(kv[u], qw, A.sm_scale);
-        if (valid[u]) {
-          const float e = s[u] + (kTail ? tail_bias : 0.f);
-          if (e > m_run) {
-            const float f = __expf(m_run - e);  // 0 when m_run is -inf
-#pragma unroll
-            for (int c = 0; c < 8; ++c) acc[c] *= f;
-            dsum *= f;
-            m_run = e;
-          }
-          const float wt = __expf(e - m_run);
-          const uint32_t ww[4] = {vv[u].x, vv[u].y, vv[u].z, vv[u].w};
-#pragma unroll
-          for (int c = 0; c < 4; ++c) {
-            acc[2 * c] += wt * bf16_lo(ww[c]);
-            acc[2 * c + 1] += wt * bf16_hi(ww[c]);
-          }
-          dsum += wt;
-        }
+      for (int c = 0; c < 4; ++c) {
+        acc[2 * c] += wt * bf16_lo(ww[c]);
+        acc[2 * c + 1] += wt * bf16_hi(ww[c]);
       }
     }
-  };
-  const int n_kept = n_fix + min(max(r.b_keep, 0), r.b);
-  walk(p_lo, min(p_hi, n_fix), std::integral_constant<int, 0>{});
-  walk(max(p_lo, n_fix), min(p_hi, n_kept), std::integral_constant<int, 1>{});
-  walk(max(p_lo, n_kept), p_hi, std::integral_constant<int, 2>{});
+  }
 
-  // every lane group has its own (maximum, D, N): bring them to the workgroup's maximum and add
-  __shared__ float s_acc[GROUPS][D];
-  __shared__ float s_d[GROUPS], s_m[GROUPS];
-  const int g = wave * RPW + rsub;
+  // the lane groups of a wave, then the waves, each with its maximum
 #pragma unroll
-  for (int c = 0; c < 8; ++c) s_acc[g][sub * 8 + c] = acc[c];
-  if (sub == 0) {
-    s_d[g] = dsum;
-    s_m[g] = m_run;
+  for (int o = LPR; o < kWave; o <<= 1) {
+#pragma unroll
+    for (int c = 0; c < 8; ++c) acc[c] += __shfl_xor(acc[c], o);
+  }
+  dsum = wave_sum_f32(dsum);
+  __shared__ __align__(16) float s_acc[WAVES][D];
+  __shared__ float s_d[WAVES], s_m[WAVES];
+  if (rsub == 0) {
+#pragma unroll
+    for (int c = 0; c < 8; ++c) s_acc[wave][sub * 8 + c] = acc[c];
+  }
+  if (lane == 0) {
+    s_d[wave] = dsum;
+    s_m[wave] = m_run;
   }
   __syncthreads();
   float M = -INFINITY;
 #pragma unroll
-  for (int j = 0; j < GROUPS; ++j) M = fmaxf(M, s_m[j]);
+  for (int j = 0; j < WAVES; ++j) M = fmaxf(M, s_m[j]);
   float* part = A.part + ((int64_t)bh * A.splits + split) * (D + 4);
-  if (tid < D) {
-    float a = 0.f;
+  float a = 0.f, d = 0.f;
 #pragma unroll
-    for (int j = 0; j < GROUPS; ++j) a += s_acc[j][tid] * (s_m[j] > -INFINITY ? __expf(s_m[j] - M) : 0.f);
-    part[tid] = a;
+  for (int j = 0; j < WAVES; ++j) {
+    const float f = s_m[j] > -INFINITY ? __expf(s_m[j] - M) : 0.f;
+    if (tid < D) a += s_acc[j][tid] * f;
+    d += s_d[j] * f;
   }
+  if (tid < D) part[tid] = a;
   if (tid == 0) {
-    float d = 0.f;
-#pragma unroll
-    for (int j = 0; j < GROUPS; ++j) d += s_d[j] * (s_m[j] > -INFINITY ? __expf(s_m[j] - M) : 0.f);
     part[D] = d;
     part[D + 1] = M;
   }
 }
 
-// Combines the per-split (maximum, D, N) partials of a head in split order: O = N / D, lse = M + ln D.
+// Combines the per-split (maximum, D, N) partials of a head in split order: O = N / D, lse = M + ln D.  step_rows > 0:
+// only the splits that took part (used_splits) have written theirs.  Bound
+// by the trip to memory: the first 16 are requested beside the head record.
 template <int D>
-__global__ __launch_bounds__(D) void given_merge_kernel(const float* __restrict__ part, int splits, int Hq,
-                                                        float* __restrict__ out_o, float* __restrict__ out_lse,
-                                                        int group_major, int Hkv) {
+__global__ __launch_bounds__(D) void given_merge_kernel(const float* __restrict__ part, const HeadRec* __restrict__ head_rec,
+                                                        int splits, int Hq, float* __restrict__ out_o,
+                                                        float* __restrict__ out_lse, int group_major, int Hkv, int step_rows) {
   const int h = head_of_block((int)blockIdx.x, Hq, Hkv, group_major), b = blockIdx.y, bh = b * Hq + h;
   const int c = threadIdx.x;
   const float* p = part + (int64_t)bh * splits * (D + 4);
-  float M = -INFINITY;
-#pragma unroll 8
-  for (int s = 0; s < splits; ++s) M = fmaxf(M, p[s * (D + 4) + D + 1]);
+  // lane s of every wave: (D, maximum) of split s; all lanes: their column of the splits, eight at a time
+  const float2 dm = *reinterpret_cast<const float2*>(p + min(c & (kWave - 1), splits - 1) * (D + 4) + D);
+  constexpr int U = 8;
+  float v[U], v2[U];
+  auto load = [&](float (&to)[U], int s0) {
+#pragma unroll
+    for (int u = 0; u < U; ++u) to[u] = p[min(s0 + u, splits - 1) * (D + 4) + c];
+  };
+  load(v, 0);
+  if (splits > U) load(v2, U);
+  int used = splits;
+  if (step_rows > 0) {
+    const HeadRec r = head_rec[bh];
+    used = used_splits(splits, r.n_sink + r.n_win + r.k + r.b, step_rows);
+  }
+  const bool mine = (c & (kWave - 1)) < used && dm.y > -INFINITY;
+  const float M = wave_max(mine ? dm.y : -INFINITY);
+  const float f = mine ? __expf(dm.y - M) : 0.f, df = mine ? dm.x * f : 0.f;
   float a = 0.f, dtot = 0.f;
-#pragma unroll 8
-  for (int s = 0; s < splits; ++s) {
-    const float ms = p[s * (D + 4) + D + 1];
-    const float f = ms > -INFINITY ? __expf(ms - M) : 0.f;
-    a += p[s * (D + 4) + c] * f;
-    dtot += p[s * (D + 4) + D] * f;
+  auto add = [&](const float (&from)[U], int s0) {
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const float fu = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(f), s0 + u));
+      a += fu > 0.f ? from[u] * fu : 0.f;  // (what a split without a part left behind is not looked at)
+      dtot += __int_as_float(__builtin_amdgcn_readlane(__float_as_int(df), s0 + u));
+    }
+  };
+  add(v, 0);
+  if (used > U) add(v2, U);
+  for (int s0 = 2 * U; s0 < used; s0 += U) {
+    load(v, s0);
+    add(v, s0);
   }
   out_o[(int64_t)bh * D + c] = a / dtot;
   if (c == 0 && out_lse) out_lse[bh] = M + logf(dtot);
@@ -423,18 +547,18 @@ hipError_t launch_given_d(const Plan& pl, int stage, const void* q, const void* 
   if (stage == 0 && !stats) A.splits = pl.sparse_splits;  // scores only: no partial sums, any number of workgroups
   dim3 grid(p.n_q_heads, A.splits, pl.vbatch);
   if (stage == 0) {
-    if (paged && stats) hipLaunchKernelGGL((sparse_score_kernel<D, true, true>), grid, dim3(kGatherThreads), 0, st, A);
-    else if (paged) hipLaunchKernelGGL((sparse_score_kernel<D, true, false>), grid, dim3(kGatherThreads), 0, st, A);
-    else if (stats) hipLaunchKernelGGL((sparse_score_kernel<D, false, true>), grid, dim3(kGatherThreads), 0, st, A);
-    else hipLaunchKernelGGL((sparse_score_kernel<D, false, false>), grid, dim3(kGatherThreads), 0, st, A);
+    if (paged && stats) hipLaunchKernelGGL((sparse_stats_kernel<D, true>), grid, dim3(kGatherThreads), 0, st, A);
+    else if (paged) hipLaunchKernelGGL((sparse_score_kernel<D, true>), grid, dim3(kGatherThreads), 0, st, A);
+    else if (stats) hipLaunchKernelGGL((sparse_stats_kernel<D, false>), grid, dim3(kGatherThreads), 0, st, A);
+    else hipLaunchKernelGGL((sparse_score_kernel<D, false>), grid, dim3(kGatherThreads), 0, st, A);
     return hipGetLastError();
   }
   if (paged) hipLaunchKernelGGL((given_gather_kernel<D, true>), grid, dim3(kGatherThreads), 0, st, A);
   else hipLaunchKernelGGL((given_gather_kernel<D, false>), grid, dim3(kGatherThreads), 0, st, A);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL((given_merge_kernel<D>), dim3(p.n_q_heads, pl.vbatch), dim3(D), 0, st, A.part, A.splits,
-                     p.n_q_heads, out_o, out_lse, pl.group_major, p.n_kv_heads);
+  hipLaunchKernelGGL((given_merge_kernel<D>), dim3(p.n_q_heads, pl.vbatch), dim3(D), 0, st, A.part, A.head_rec,
+                     A.splits, p.n_q_heads, out_o, out_lse, pl.group_major, p.n_kv_heads, (kGatherThreads / (D / 8)) * 8);
   return hipGetLastError();
 }
 
@@ -451,12 +575,13 @@ hipError_t launch_sparse_score(const Plan& pl, const void* q, const void* k, con
 hipError_t launch_given_merge(const Plan& pl, void* ws, int splits, float* out_o, float* out_lse, hipStream_t st) {
   const vatt_params& p = pl.p;
   const float* part = reinterpret_cast<const float*>(static_cast<char*>(ws) + pl.off_gather_part);
+  const HeadRec* rec = reinterpret_cast<const HeadRec*>(static_cast<char*>(ws) + pl.off_head_rec);
   if (p.head_dim == 128)
-    hipLaunchKernelGGL((given_merge_kernel<128>), dim3(p.n_q_heads, pl.vbatch), dim3(128), 0, st, part, splits,
-                       p.n_q_heads, out_o, out_lse, pl.group_major, p.n_kv_heads);
+    hipLaunchKernelGGL((given_merge_kernel<128>), dim3(p.n_q_heads, pl.vbatch), dim3(128), 0, st, part, rec, splits,
+                       p.n_q_heads, out_o, out_lse, pl.group_major, p.n_kv_heads, 0);
   else if (p.head_dim == 64)
-    hipLaunchKernelGGL((given_merge_kernel<64>), dim3(p.n_q_heads, pl.vbatch), dim3(64), 0, st, part, splits,
-                       p.n_q_heads, out_o, out_lse, pl.group_major, p.n_kv_heads);
+    hipLaunchKernelGGL((given_merge_kernel<64>), dim3(p.n_q_heads, pl.vbatch), dim3(64), 0, st, part, rec, splits,
+                       p.n_q_heads, out_o, out_lse, pl.group_major, p.n_kv_heads, 0);
   else
     return hipErrorInvalidValue;
   return hipGetLastError();

@@ -33,6 +33,15 @@ struct HeadRec {
                           // list places)
 };
 
+// Workgroups of a head that take part, of the `splits` the grid has for it: no more than its list fills with steps.
+// A workgroup costs a chain of about four memory round trips however few rows it has, and the lengths of the lists are
+// only known here: with all 16 of them 8 sequences of 0.5K - 7K tokens (497 rows a head) took 16.7 us, with as many as there
+// are steps of 128 rows 9.4 us, with two for each step 11; long lists are as fast as before (16 x 32K tokens, 1867 rows: 40 us,
+// 6.1 TB/s of V rows).  One that takes part alone writes the result itself.
+__device__ __forceinline__ int used_splits(int splits, int total, int step_rows) {
+  return min(splits, (total + step_rows - 1) / step_rows);
+}
+
 // Waves of a dense matrix-core workgroup that take different query vectors (32 each) of the same keys.
 inline int dense_vector_waves(int vectors) { return vectors <= 32 ? 1 : vectors <= 64 ? 2 : 4; }
 inline int dense_rounds(int vectors) { return (vectors + 127) / 128; }  // workgroups for all vectors of a KV head

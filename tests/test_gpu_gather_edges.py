@@ -10,9 +10,10 @@ from util import plan_params
 pytestmark = pytest.mark.gpu
 
 
+@pytest.mark.parametrize("given", [False, True])
 @pytest.mark.parametrize("paged", [False, True])
 @pytest.mark.parametrize("d", [64, 128])
-def test_whole_contexts_around_a_step(d, paged):
+def test_whole_contexts_around_a_step(d, paged, given):
     import torch
     from paper_2510_05688_amd import binding as vb
     from paper_2510_05688_amd.session import DecodeSession
@@ -23,9 +24,13 @@ def test_whole_contexts_around_a_step(d, paged):
                                  seq_lens=lens, seed=3, params=p, plant_frac=0.01)
     k_bits, v_bits, table = workloads.to_paged(wl, 16) if paged else (wl.k_bits, wl.v_bits, None)
     sess = DecodeSession(plan_params(wl, paged=paged, num_blocks=k_bits.shape[0] if paged else 0))
-    vb.vatt_plan_set_option(sess.plan, vb.VATT_OPT_FUSED_GATHER, 0)
+    vb.vatt_plan_set_option(sess.plan, vb.VATT_OPT_GIVEN_FUSED if given else vb.VATT_OPT_FUSED_GATHER, 0)
     sess.upload(wl.q_bits, k_bits, v_bits, wl.seq_lens, wl.seeds, table)
-    sess.decode()
+    if given:  # all tokens between sink and window
+        counts = torch.tensor([max(n - 64, 0) for n in lens], dtype=torch.int32, device="cuda")[:, None].repeat(1, 4)
+        sess.decode_given_topk((torch.arange(2049, dtype=torch.int32, device="cuda") + 16).repeat(len(lens), 4, 1), counts)
+    else:
+        sess.decode()
     res = sess.results_host()
     q = torch.from_numpy(workloads.bf16_bits_to_f32(wl.q_bits)).reshape(len(lens), 4, d).double()
     for b, n in enumerate(lens):
