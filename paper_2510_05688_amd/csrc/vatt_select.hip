@@ -295,6 +295,32 @@ __global__ __launch_bounds__(NT, FD > 0 ? 1 : 4) void head_kernel(HeadArgs A) {
       uint32_t Tidx = kInv32;
       bool marked = false;
       uint32_t n_cand_used = 0;  // fast path: members are the candidates marked in bm_f
+      // (see "more candidates than the list holds")
+      uint32_t n_wide_used = 0;
+      constexpr uint32_t kWideCap = kCandCap * 12 / sizeof(uint16_t);
+      uint16_t* wide = reinterpret_cast<uint16_t*>(cand);
+      static_assert(kCapacityMax / kSubTile < 65536, "sub-tiles as 16-bit numbers");
+      // f(score, token) for the middle scores of the listed sub-tiles, two lanes per sub-tile, four loads in flight
+      auto each_wide = [&](uint32_t count, auto&& f) {
+        for (uint32_t q0 = 0; q0 < count; q0 += 4u * (NT / 2)) {
+          float4 x[4];
+          int tok[4];
+#pragma unroll
+          for (int u = 0; u < 4; ++u) {
+            const uint32_t q = q0 + (uint32_t)(u * (NT / 2) + tid / 2);
+            const int t = (int)min((uint32_t)wide[min(q, count - 1)], (uint32_t)(n_sub - 1)) * kSubTile + (tid & 1) * 4;
+            x[u] = *reinterpret_cast<const float4*>(row + t);
+            tok[u] = q < count ? t : n;
+          }
+#pragma unroll
+          for (int u = 0; u < 4; ++u) {
+            const float sv[4] = {x[u].x, x[u].y, x[u].z, x[u].w};
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+              if (tok[u] + e >= hs.mid_lo && tok[u] + e < hs.mid_hi) f(sv[e], tok[u] + e);
+          }
+        }
+      };
       if (hs.k < mid_len) {
         // Fast path.  A lower bound of the k-th largest score: the k-th largest of the sub-tile maxima (of
         // the sub-tiles that lie entirely in the middle region) has at least k middle scores at or above it.
@@ -469,6 +495,91 @@ __global__ __launch_bounds__(NT, FD > 0 ? 1 : 4) void head_kernel(HeadArgs A) {
             marked = true;
             n_cand_used = n_cand;
           }
+          if constexpr (NT >= 1024) {
+            // More candidates than the list holds (long rows with a large top-k set): the same steps without the list.  Only
+            // the sub-tiles are listed, as 16-bit numbers in its place, and their scores are read three times: into the
+            // histogram, for the members, and (below) for the ascending list.  Bound by those reads, 100 - 200 KB a pass: with
+            // 1 x 128K tokens and k = 3276 the whole selection takes 56 us, with the passes over the whole row that follow
+            // below (for a k beyond the number of sub-tiles, or too many scores in one bin) 92 us; whole call 152 -> 116 us.
+            const float wscale = (float)(kBins - 1) / (m - bound);
+            if (!have_T && n_qual <= kWideCap && m > bound && wscale < 1e30f) {
+              __syncthreads();  // the lists and their counters are free
+              if (tid == 0) {
+                ts.qual_n = 0;
+                ts.cand_n = 0;
+              }
+              clear_cand_hist();
+              __syncthreads();
+              each_sub_batch([&](const float (&v)[SU], int base) {
+                uint64_t mask[SU];
+                uint32_t tot = 0;
+#pragma unroll
+                for (int u = 0; u < SU; ++u) {
+                  const int t = base + u * NT + tid;
+                  mask[u] = __ballot(t >= sub_first && t < sub_last && v[u] >= bound);
+                  tot += (uint32_t)__popcll(mask[u]);
+                }
+                if (tot) {
+                  uint32_t at = 0;
+                  if ((tid & 63) == 0) at = atomicAdd(&ts.qual_n, tot);
+                  at = (uint32_t)__builtin_amdgcn_readfirstlane((int)at);
+#pragma unroll
+                  for (int u = 0; u < SU; ++u) {
+                    const uint32_t pos = at + lanes_below(mask[u]);
+                    if (((mask[u] >> (tid & 63)) & 1u) && pos < kWideCap) wide[pos] = (uint16_t)(base + u * NT + tid);
+                    at += (uint32_t)__popcll(mask[u]);
+                  }
+                }
+              });
+              __syncthreads();
+              uint32_t mine = 0;
+              each_wide(n_qual, [&](float sc, int) {
+                if (sc >= bound) {
+                  atomicAdd(&cand_hist[(uint32_t)((m - sc) * wscale)], 1u);
+                  ++mine;
+                }
+              });
+              mine = wave_sum_u32(mine);
+              if ((tid & 63) == 0) atomicAdd(&ts.cand_n, mine);
+              __syncthreads();
+              TKC::locate_once((uint32_t)hs.k, cand_hist, ts, sm.scan_once[1]);
+              if (ts.cand_n >= (uint32_t)hs.k && ts.inbin <= (uint32_t)kSmall) {
+                const uint32_t j = ts.j, r = (uint32_t)hs.k - ts.below;
+                uint64_t fixed_sum = 0;
+                auto member = [&](float sc, uint32_t i) {
+                  atomicOr(&bm_f[i >> 5], 1u << (i & 31));
+                  tau_key = max(tau_key, ~float_order_key(sc));
+                  fixed_sum += (uint64_t)(__expf(sc - m) * 1099511627776.0f);
+                };
+                each_wide(n_qual, [&](float sc, int i) {
+                  const uint32_t bin = (uint32_t)((m - sc) * wscale);
+                  if (sc >= bound && bin < j) member(sc, (uint32_t)i);
+                  if (sc >= bound && bin == j)
+                    ts.slist[min(atomicAdd(&ts.slist_n, 1u), (uint32_t)(kSmall - 1))] = ((uint64_t)(~float_order_key(sc)) << 32) | (uint32_t)i;
+                });
+                __syncthreads();
+                const uint32_t cnt = min(ts.slist_n, (uint32_t)kSmall);
+                if ((uint32_t)tid < cnt) {
+                  const uint64_t mine_c = ts.slist[tid];
+                  uint32_t below = 0;
+                  for (uint32_t q = 0; q < cnt; ++q) below += (ts.slist[q] < mine_c) ? 1u : 0u;
+                  if (below < r) member(float_from_order_key(~(uint32_t)(mine_c >> 32)), (uint32_t)mine_c);
+                }
+                fixed_sum = wave_sum(fixed_sum);
+                if ((tid & 63) == 0) ts.wq[tid >> 6] = fixed_sum;
+                __syncthreads();
+                if (tid == 0) {
+                  uint64_t tot = 0;
+                  for (int w = 0; w < SW; ++w) tot += ts.wq[w];
+                  acc_f += (double)tot * (1.0 / 1099511627776.0);
+                }
+                topk_flag = kFlagTopkGeneral;
+                have_T = true;
+                marked = true;
+                n_wide_used = n_qual;
+              }
+            }
+          }
         }
         if (!have_T) {
           topk_flag = kFlagTopkGeneral;
@@ -524,7 +635,18 @@ __global__ __launch_bounds__(NT, FD > 0 ? 1 : 4) void head_kernel(HeadArgs A) {
       }
       // ascending token list from the bitmap
       O::word_prefix(bm_f, words, wpre, sm, &sm.scan_once[2]);
-      if (marked) {
+      if (NT >= 1024 && n_wide_used) {
+        each_wide(n_wide_used, [&](float sc, int i) {
+          const uint32_t word = bm_f[i >> 5], bit = 1u << (i & 31);
+          if (word & bit) {
+            const uint32_t pos = wpre[i >> 5] + (uint32_t)__popc(word & (bit - 1u));
+            if (pos < (uint32_t)A.k_max) {
+              idx[A.seg_topk + pos] = i;
+              place_sc[A.seg_topk + pos] = sc;
+            }
+          }
+        });
+      } else if (marked) {
         // every member sits in the candidate list: its place in the ascending list is the number of members
         // below it, from the word prefix and the bits below its own (no thread walks a crowded word)
         for (uint32_t t = tid; t < n_cand_used; t += NT) {

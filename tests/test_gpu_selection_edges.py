@@ -55,3 +55,17 @@ def test_equal_scores_among_the_candidates():
         assert np.array_equal(got, np.arange(4, 304)), "equal scores: the lower tokens win"
     check_all(wl, res, label="equal scores")
     sess.close()
+
+
+@pytest.mark.parametrize("k", [1900, 2048, 2049, 5500])
+def test_more_candidates_than_the_list_holds(k):
+    # long rows (1024 threads): the candidates fit the list, do not, and (5500 of 7500 sub-tiles) nearly all sub-tiles qualify
+    from paper_2510_05688_amd.session import DecodeSession
+    p = default_params(64, sink=5, window=30, topk_abs=k, topk_frac=0.0, base_abs=200, base_frac=0.0, epsilon=0.2)
+    wl = workloads.make_workload("wide", batch=2, n_q_heads=2, n_kv_heads=1, head_dim=64, n_max=60003, seq_lens=[60003, 45001],
+                                 seed=k, params=p, plant_frac=0.003)
+    sess = DecodeSession(plan_params(wl))
+    sess.upload(wl.q_bits, wl.k_bits, wl.v_bits, wl.seq_lens, wl.seeds)
+    sess.decode()
+    check_all(wl, sess.results_host(), label="wide %d" % k)
+    sess.close()
