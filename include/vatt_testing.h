@@ -32,8 +32,8 @@ extern "C" {
  *   VATT_OPT_FUSED_GATHER = 0, 1, 2, 4, 8 or 16: 0 keeps selection and gather in kernels of their own; S > 0
  *     runs them as one kernel with S workgroups per head (denominator target, 512-thread selection and fresh
  *     final samples only; VATT_E_UNSUPPORTED_SHAPE when the kernel's LDS does not hold that split).  The plan
- *     picks S > 0 for batches with fewer heads than half the chip's compute units.  The index sets, budgets
- *     and statistics are identical; the output sums run in another order.
+ *     picks S > 0 for batches with fewer heads than compute units.  The index sets, budgets and statistics are
+ *     identical; the output sums run in another order.
  *   VATT_OPT_SCORE_PREWORK = 0 / 1: with the fused gather, whether the first batches of the sampler's draw
  *     sequences are made by the first workgroups of the score launch while the rest of it streams K (1, the
  *     default for such plans) or by the selection kernel itself (0).

@@ -483,8 +483,8 @@ int vatt_decode(vatt_plan* plan, const void* q, const void* k, const void* v, co
   if (fused) {
     // small batch: selection and gather in one kernel, several workgroups per head
     VATT_LAUNCH(launch_head_fused(pl, v, block_table, seq_lens, seq_seeds, workspace, out_idx, out_counts,
-                                  out_budget_raw, out_stats, score_prework(pl), st));
-    VATT_LAUNCH(launch_gather_merge(pl, workspace, pl.fuse_splits, out_o, out_lse, st));
+                                  out_budget_raw, out_stats, out_o, out_lse, score_prework(pl), st));
+    if (pl.fuse_splits > 1) VATT_LAUNCH(launch_gather_merge(pl, workspace, pl.fuse_splits, out_o, out_lse, st));
     return VATT_OK;
   }
   if (pl.p.target == VATT_TARGET_D) {

@@ -113,7 +113,8 @@ hipError_t launch_head(const Plan& pl, int phase, const int32_t* seq_lens, const
 // of the per-workgroup partial sums.
 hipError_t launch_head_fused(const Plan& pl, const void* v, const int32_t* block_table, const int32_t* seq_lens,
                              const uint64_t* seq_seeds, void* ws, int32_t* out_idx, int32_t* out_counts,
-                             double* out_budget_raw, float* out_stats, bool pre_made, hipStream_t st);
+                             double* out_budget_raw, float* out_stats, float* out_o, float* out_lse, bool pre_made,
+                             hipStream_t st);
 // Whether workgroups of the score launch make the sampler streams' first batches for the fused selection kernel
 // (single-token steps only).
 inline bool score_prework(const Plan& pl) {

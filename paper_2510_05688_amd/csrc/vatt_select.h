@@ -68,6 +68,9 @@ struct HeadArgs {
   const uint16_t* gk;         // K cache
   KVLayout Lk;
   float sm_scale;
+  // fused gather with one workgroup per head
+  float* out_o;
+  float* out_lse;
 };
 
 

@@ -38,7 +38,9 @@ namespace {
 // of the head's list in LDS, gathers those V rows and leaves a partial (sum w V, sum w) for the merge kernel.
 // Only workgroup 0 of a head writes the index lists, counts, statistics and budget.  The rows of I_f are
 // requested as soon as the top-k set is known and are added after the samplers have run.
-template <int NT, int FD, bool PAGED>
+// ALONE: one workgroup per head, which writes the head's result itself (a branch on A.splits at the end cost the others
+// 0.4 us, and the split arithmetic these 1.4 us).
+template <int NT, int FD, bool PAGED, bool ALONE = false>
 __global__ __launch_bounds__(NT, FD > 0 ? 1 : 4) void head_kernel(HeadArgs A) {
   constexpr bool kFused = FD > 0;
   using O = HeadOps<NT>;
@@ -52,7 +54,8 @@ __global__ __launch_bounds__(NT, FD > 0 ? 1 : 4) void head_kernel(HeadArgs A) {
   const int h = head_of_block((int)blockIdx.x, A.Hq, A.Hkv, A.group_major), b = blockIdx.y;
   const int bh = b * A.Hq + h;
   const int tid = threadIdx.x;
-  const uint32_t split = kFused ? blockIdx.z : 0u, shift = kFused ? (uint32_t)A.split_shift : 0u;
+  constexpr bool kSplit = kFused && !ALONE;
+  const uint32_t split = kSplit ? blockIdx.z : 0u, shift = kSplit ? (uint32_t)A.split_shift : 0u;
   const uint32_t smask = (1u << shift) - 1u;
   const bool writer = split == 0u;  // this workgroup writes the head's outputs
   // The sub-tile maxima the score kernel left are requested first of all, before even the sequence length is
@@ -1074,9 +1077,13 @@ __global__ __launch_bounds__(NT, FD > 0 ? 1 : 4) void head_kernel(HeadArgs A) {
       float a = 0.f;
 #pragma unroll
       for (int w2 = 0; w2 < SW; ++w2) a += g_red[w2 * FD + tid];
-      part[tid] = a;
+      if (ALONE) A.out_o[(int64_t)bh * FD + tid] = a / dtot;
+      else part[tid] = a;
     }
-    if (tid == 0) part[FD] = dtot;
+    if (tid == 0) {
+      if (!ALONE) part[FD] = dtot;
+      else if (A.out_lse) A.out_lse[bh] = m + logf(dtot);
+    }
     VATT_STAMP(A.dbg, 11);
   }
 }
@@ -1085,8 +1092,12 @@ typedef void (*HeadKernel)(HeadArgs);
 // The instantiation for a plan: workgroup size; with the fused gather also head dimension and cache layout.
 HeadKernel head_kernel_for(const Plan& pl, bool fused) {
   if (fused) {
-    const bool paged = pl.p.kv_layout == VATT_LAYOUT_PAGED;
-    if (pl.p.head_dim == 128) return paged ? head_kernel<kHeadThreads, 128, true> : head_kernel<kHeadThreads, 128, false>;
+    const bool paged = pl.p.kv_layout == VATT_LAYOUT_PAGED, alone = pl.fuse_splits == 1;
+    if (pl.p.head_dim == 128) {
+      if (alone) return paged ? head_kernel<kHeadThreads, 128, true, true> : head_kernel<kHeadThreads, 128, false, true>;
+      return paged ? head_kernel<kHeadThreads, 128, true> : head_kernel<kHeadThreads, 128, false>;
+    }
+    if (alone) return paged ? head_kernel<kHeadThreads, 64, true, true> : head_kernel<kHeadThreads, 64, false, true>;
     return paged ? head_kernel<kHeadThreads, 64, true> : head_kernel<kHeadThreads, 64, false>;
   }
   return pl.head_threads == kHeadThreadsLong ? head_kernel<kHeadThreadsLong, 0, false> : head_kernel<kHeadThreads, 0, false>;
@@ -1098,14 +1109,13 @@ hipError_t set_kernel_attributes(const Plan& pl) {
   // The limit on dynamic LDS belongs to the kernel, not to the plan: it is raised to all a CU has (less the
   // kernels' static part), so that plans of different capacities can be used in any order.
   const int cap = 160 * 1024 - (int)head_kernel_static_lds_bytes();
-  const void* kernels[6] = {reinterpret_cast<const void*>(head_kernel<kHeadThreads, 0, false>),
-                            reinterpret_cast<const void*>(head_kernel<kHeadThreadsLong, 0, false>),
-                            reinterpret_cast<const void*>(head_kernel<kHeadThreads, 128, false>),
-                            reinterpret_cast<const void*>(head_kernel<kHeadThreads, 128, true>),
-                            reinterpret_cast<const void*>(head_kernel<kHeadThreads, 64, false>),
-                            reinterpret_cast<const void*>(head_kernel<kHeadThreads, 64, true>)};
-  for (const void* f : kernels) {
-    const hipError_t e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, cap);
+  const HeadKernel kernels[10] = {head_kernel<kHeadThreads, 0, false>,           head_kernel<kHeadThreadsLong, 0, false>,
+                                  head_kernel<kHeadThreads, 128, false>,        head_kernel<kHeadThreads, 128, true>,
+                                  head_kernel<kHeadThreads, 64, false>,         head_kernel<kHeadThreads, 64, true>,
+                                  head_kernel<kHeadThreads, 128, false, true>,  head_kernel<kHeadThreads, 128, true, true>,
+                                  head_kernel<kHeadThreads, 64, false, true>,   head_kernel<kHeadThreads, 64, true, true>};
+  for (const HeadKernel f : kernels) {
+    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(f), hipFuncAttributeMaxDynamicSharedMemorySize, cap);
     if (e != hipSuccess) return e;
   }
   return set_given_kernel_attributes(pl);
@@ -1149,11 +1159,24 @@ bool fused_splits_fit(const Plan& pl, int splits) {
   return fused_head_lds_bytes(pl, splits) + head_kernel_static_lds_bytes() <= 160 * 1024;
 }
 
-// Small batches only: with fewer heads than half the compute units, every head gets the largest power of two
-// of workgroups (at most 16) that the chip can run at once, one per compute unit.
+// Workgroups per head of the fused kernel, all of them at once on the chip, one per compute unit; 0: separate kernels.
+// With one per head the merge launch falls away, which is worth two to three microseconds as long as its lists are short.
+// Measured (whole call, us, separate kernels or the largest power of two that fits -> one per head; with the count of
+// workgroups a constant of the kernel, as it is now, another 0.6 to 1.5 less):
+//   more heads than half the compute units, 256 heads of 300 / 4K / 7K paged / 9K tokens: 34.7 -> 33.0, 39.8 -> 36.0, 41.5 -> 39.8,
+//     55.7 -> 51.3, none left at 12K (where the list of a final sample as long as the row no longer fits); multi-query steps,
+//     whose first draws are not made beside the scores, gain from about 200 heads on (8 query tokens, 4K: 40.1 -> 38.2, 5: 35.5 -> 37.0);
+//   fewer heads: one head of 1K 23.7 -> 21.7, 32 heads of 4K / 9K 27.5 -> 25.4, 28.2 -> 27.0, but 32 heads of 9K with a list of 1156
+//     rows 30.2 -> 30.8, of 12K (856 rows) 30.8 -> 31.2, with 4 query tokens of 2K 34.2 -> 35.3.
 int fused_splits_for(const Plan& pl) {
-  const int heads = pl.vbatch * pl.p.n_q_heads;
-  if (2 * heads > pl.num_cus) return 0;
+  const vatt_params& p = pl.p;
+  const int heads = pl.vbatch * p.n_q_heads;
+  if (2 * heads > pl.num_cus) {
+    const bool most = heads <= pl.num_cus && (pl.q_len == 1 || 4 * heads > 3 * pl.num_cus);
+    return most && fused_splits_fit(pl, 1) ? 1 : 0;
+  }
+  const int rows = p.sink + p.window + pl.k_max + pl.b0_max;  // the shortest list of the longest sequence
+  if (pl.q_len == 1 && rows <= 768 && p.n_max <= 10240 && fused_splits_fit(pl, 1)) return 1;
   int s = 1;
   while (2 * s * heads <= pl.num_cus && s < 16) s *= 2;
   while (s >= 2 && !fused_splits_fit(pl, s)) s /= 2;
@@ -1163,7 +1186,8 @@ int fused_splits_for(const Plan& pl) {
 // Selection with the fused gather (denominator target, fresh final sample): pl.fuse_splits workgroups per head.
 hipError_t launch_head_fused(const Plan& pl, const void* v, const int32_t* block_table, const int32_t* seq_lens,
                              const uint64_t* seq_seeds, void* ws, int32_t* out_idx, int32_t* out_counts,
-                             double* out_budget_raw, float* out_stats, bool pre_made, hipStream_t st) {
+                             double* out_budget_raw, float* out_stats, float* out_o, float* out_lse, bool pre_made,
+                             hipStream_t st) {
   HeadArgs A;
   fill_head_args(A, pl, 0, seq_lens, seq_seeds, ws, out_idx, out_counts, out_budget_raw, out_stats);
   const vatt_params& p = pl.p;
@@ -1175,6 +1199,8 @@ hipError_t launch_head_fused(const Plan& pl, const void* v, const int32_t* block
   A.L = pl.kv_v;
   A.L.block_table = block_table;
   A.part = reinterpret_cast<float*>(static_cast<char*>(ws) + pl.off_gather_part);
+  A.out_o = out_o;
+  A.out_lse = out_lse;
   A.splits = pl.fuse_splits;
   A.split_shift = 0;
   while ((1 << A.split_shift) < pl.fuse_splits) ++A.split_shift;

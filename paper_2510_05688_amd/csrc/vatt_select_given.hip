@@ -657,10 +657,13 @@ bool given_fused_fits(const Plan& pl, int splits) {
   return given_fused_lds_bytes(pl, splits) + head_kernel_static_lds_bytes() <= 160 * 1024;
 }
 
-// The plan's own choice: as for the scored path, when there are at most half as many heads as compute units.
+// The plan's own choice: as for the scored path, when there are at most half as many heads as compute units; and one
+// workgroup per head when most compute units get one (whole step, us, separate kernels -> fused: 256 heads of 300 / 4K / 9K
+// tokens 34.7 -> 31.1, 37.9 -> 35.9, 42.4 -> 40.3, of 4K with 64 columns 38.5 -> 34.1; 160 heads of 1K 31.7 both ways, of 6K with 5
+// query tokens 40.4 -> 43.1).
 int given_fused_splits_for(const Plan& pl) {
   const int heads = pl.vbatch * pl.p.n_q_heads;
-  if (heads * 2 > pl.num_cus) return 0;
+  if (heads * 2 > pl.num_cus) return heads <= pl.num_cus && 4 * heads > 3 * pl.num_cus && given_fused_fits(pl, 1) ? 1 : 0;
   int s2 = 1;
   while (s2 * 2 * heads <= pl.num_cus && s2 < 16) s2 *= 2;
   while (s2 >= 1 && !given_fused_fits(pl, s2)) s2 /= 2;  // (fewer workgroups per head need longer LDS lists)
