@@ -13,9 +13,21 @@ constexpr int kWave = 64;
 // (workgroups go to the XCDs round-robin in launch order, and with a KV head count that is a multiple of 8)
 // the workgroups of all query heads of KV head j run on XCD j mod 8 and share its L2 while the kernel runs:
 // they read the same sink and window rows of V and many of the same heavy tokens.
+// (Groups are 1, 2, 4 or 8 heads.  No divisions here and below: each is some 40 instructions at the start of a workgroup's chain.)
 __device__ __forceinline__ int head_of_block(int x, int Hq, int Hkv, int group_major) {
-  return group_major ? (x % Hkv) * (Hq / Hkv) + x / Hkv : x;
+  if (!group_major) return x;
+  int g = 0;
+#pragma unroll
+  for (int s = 4; s >= 1; s >>= 1) {
+    const bool above = x >= s * Hkv;
+    g += above ? s : 0;
+    x -= above ? s * Hkv : 0;
+  }
+  return (x << (__builtin_clz(Hkv) - __builtin_clz(Hq))) + g;
 }
+__device__ __forceinline__ int div_group(int h, int group) { return h >> (31 - __builtin_clz(group)); }
+// Sequence of a (sequence, query token) pair.
+__device__ __forceinline__ int seq_of_pair(int b, int q_len) { return q_len == 1 ? b : b / q_len; }
 
 // Optional phase timing for kernel development: built with -DVATT_TIMING, thread 0 of workgroup 0 stores
 // the shader clock at numbered points into the VATT_WS_DEBUG region of the workspace.  Compiled out

@@ -49,8 +49,8 @@ __global__ __launch_bounds__(kGatherThreads) void gather_kernel(GatherArgs A) {
 
   const int h = head_of_block((int)blockIdx.x, A.Hq, A.Hkv, A.group_major), split = blockIdx.y, b = blockIdx.z;
   const int bh = b * A.Hq + h;
-  const int kvh = h / A.group;
-  const int seq = b / A.q_len;  // the sequence whose cache this (sequence, query token) pair reads
+  const int kvh = div_group(h, A.group);
+  const int seq = seq_of_pair(b, A.q_len);  // the sequence whose cache this (sequence, query token) pair reads
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int sub = lane % LPR, rsub = lane / LPR;
 

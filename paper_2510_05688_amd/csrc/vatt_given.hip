@@ -88,9 +88,9 @@ __global__ __launch_bounds__(kGatherThreads) void sparse_score_kernel(GivenArgs 
   constexpr int RPB = RPW * WAVES;
   constexpr int U = 8;
   static_assert(U <= LPR && RPW * U <= kWave, "a lane per row of a step, and one per row of a lane group");
-  const int h = head_of_block((int)blockIdx.x, A.Hq, A.Hq / A.group, A.group_major), split = blockIdx.y, b = blockIdx.z;
+  const int h = head_of_block((int)blockIdx.x, A.Hq, div_group(A.Hq, A.group), A.group_major), split = blockIdx.y, b = blockIdx.z;
   const int bh = b * A.Hq + h;
-  const int kvh = h / A.group, seq = b / A.q_len;
+  const int kvh = div_group(h, A.group), seq = seq_of_pair(b, A.q_len);
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int sub = lane % LPR, rsub = lane / LPR;
   const HeadRec r = A.head_rec[bh];
@@ -104,7 +104,7 @@ __global__ __launch_bounds__(kGatherThreads) void sparse_score_kernel(GivenArgs 
   const int32_t* idx = A.idx + (int64_t)bh * A.idx_cap;
   float* sp = A.sparse + (int64_t)bh * A.idx_cap;
   const bool cached = r.base_cached != 0;
-  const uint16_t* cache_k = cached ? reinterpret_cast<const uint16_t*>(cache_record(A.rcache, A.rc, seq, A.Hq / A.group, kvh) + A.rc.off_k) : nullptr;
+  const uint16_t* cache_k = cached ? reinterpret_cast<const uint16_t*>(cache_record(A.rcache, A.rc, seq, div_group(A.Hq, A.group), kvh) + A.rc.off_k) : nullptr;
   const int32_t* slots_of = A.base_slot + (int64_t)bh * A.b0_max;
   const uint16_t* k_head = PAGED ? A.k : A.k + (int64_t)seq * A.Lk.seq_stride + (int64_t)kvh * A.Lk.head_stride;
   const int n_sw = r.n_sink + r.n_win, n_fix = n_sw + r.k;
@@ -168,9 +168,9 @@ __global__ __launch_bounds__(kGatherThreads) void sparse_stats_kernel(GivenArgs 
   constexpr int RPB = RPW * WAVES;
   constexpr int GROUPS = RPB;
   constexpr int U = 8;
-  const int h = head_of_block((int)blockIdx.x, A.Hq, A.Hq / A.group, A.group_major), split = blockIdx.y, b = blockIdx.z;
+  const int h = head_of_block((int)blockIdx.x, A.Hq, div_group(A.Hq, A.group), A.group_major), split = blockIdx.y, b = blockIdx.z;
   const int bh = b * A.Hq + h;
-  const int kvh = h / A.group;
+  const int kvh = div_group(h, A.group);
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int sub = lane % LPR, rsub = lane / LPR;
   const HeadRec r = A.head_rec[bh];
@@ -179,7 +179,7 @@ __global__ __launch_bounds__(kGatherThreads) void sparse_stats_kernel(GivenArgs 
   const int total = r.n_sink + r.n_win + r.k + r.b;
   const int per = (total + A.splits - 1) / A.splits;
   const int p_lo = split * per, p_hi = min(p_lo + per, total);
-  const unsigned char* cache_rec = r.base_cached ? cache_record(A.rcache, A.rc, b / A.q_len, A.Hq / A.group, kvh) : nullptr;
+  const unsigned char* cache_rec = r.base_cached ? cache_record(A.rcache, A.rc, seq_of_pair(b, A.q_len), div_group(A.Hq, A.group), kvh) : nullptr;
   const int32_t* slots_of = A.base_slot + (int64_t)bh * A.b0_max;
   uint32_t qw[4];
   load_q<D>(A, bh, sub, qw);
@@ -228,12 +228,12 @@ __global__ __launch_bounds__(kGatherThreads) void sparse_stats_kernel(GivenArgs 
 #pragma unroll
         for (int u = 0; u < U; ++u) {
           tok[u] = min(max(tok[u], 0), r.n - 1);
-          blk[u] = kv_block<PAGED>(A.Lk, b / A.q_len, tok[u]);  // (K and V share the block table)
+          blk[u] = kv_block<PAGED>(A.Lk, seq_of_pair(b, A.q_len), tok[u]);  // (K and V share the block table)
         }
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-          kv[u] = load_stream_16(A.k + kv_row_offset_in<PAGED>(A.Lk, b / A.q_len, kvh, tok[u], blk[u]) + sub * 8);
-          vv[u] = load_stream_16(A.v + kv_row_offset_in<PAGED>(A.Lv, b / A.q_len, kvh, tok[u], blk[u]) + sub * 8);
+          kv[u] = load_stream_16(A.k + kv_row_offset_in<PAGED>(A.Lk, seq_of_pair(b, A.q_len), kvh, tok[u], blk[u]) + sub * 8);
+          vv[u] = load_stream_16(A.v + kv_row_offset_in<PAGED>(A.Lv, seq_of_pair(b, A.q_len), kvh, tok[u], blk[u]) + sub * 8);
         }
       }
 #pragma unroll
@@ -326,9 +326,9 @@ __global__ __launch_bounds__(kGatherThreads) void given_gather_kernel(GivenArgs 
   constexpr int U = 8;
   constexpr int ROWS_W = RPW * U;
   static_assert(U <= LPR && ROWS_W <= kWave, "a lane per row of a step, and one per row of a lane group");
-  const int h = head_of_block((int)blockIdx.x, A.Hq, A.Hq / A.group, A.group_major), split = blockIdx.y, b = blockIdx.z;
+  const int h = head_of_block((int)blockIdx.x, A.Hq, div_group(A.Hq, A.group), A.group_major), split = blockIdx.y, b = blockIdx.z;
   const int bh = b * A.Hq + h;
-  const int kvh = h / A.group, seq = b / A.q_len;
+  const int kvh = div_group(h, A.group), seq = seq_of_pair(b, A.q_len);
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int sub = lane % LPR, rsub = lane / LPR;
   const HeadRec r = A.head_rec[bh];

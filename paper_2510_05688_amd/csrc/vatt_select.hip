@@ -42,6 +42,10 @@ namespace {
 // 0.4 us, and the split arithmetic these 1.4 us).
 template <int NT, int FD, bool PAGED, bool ALONE = false>
 __global__ __launch_bounds__(NT, FD > 0 ? 1 : 4) void head_kernel(HeadArgs A) {
+  if constexpr (FD > 0) {  // (what only the selection-only kernel serves: no code for it here, 0.3 us)
+    A.phase = A.nested = A.ascending = 0;
+    A.target = VATT_TARGET_D;
+  }
   constexpr bool kFused = FD > 0;
   using O = HeadOps<NT>;
   using TKR = TopkOps<NT, RowView<NT>>;
@@ -51,7 +55,9 @@ __global__ __launch_bounds__(NT, FD > 0 ? 1 : 4) void head_kernel(HeadArgs A) {
   constexpr int SW = NT / kWave;
   extern __shared__ __align__(16) unsigned char dyn_smem[];
   __shared__ TopkSmem ts;
-  const int h = head_of_block((int)blockIdx.x, A.Hq, A.Hkv, A.group_major), b = blockIdx.y;
+  // (the selection-only kernel is at its register limit: with the comparisons of head_of_block it spills six registers more)
+  const int x = (int)blockIdx.x, b = blockIdx.y;
+  const int h = kFused ? head_of_block(x, A.Hq, A.Hkv, A.group_major) : A.group_major ? (x % A.Hkv) * (A.Hq / A.Hkv) + x / A.Hkv : x;
   const int bh = b * A.Hq + h;
   const int tid = threadIdx.x;
   constexpr bool kSplit = kFused && !ALONE;
@@ -80,7 +86,7 @@ __global__ __launch_bounds__(NT, FD > 0 ? 1 : 4) void head_kernel(HeadArgs A) {
   }
   // In a multi-query step b stands for (sequence, query token); query token t of q_len sees the sequence up to
   // and including itself, which leaves out the q_len - 1 - t newer tokens.
-  const int seq = b / A.q_len, qtok = b - seq * A.q_len;
+  const int seq = seq_of_pair(b, A.q_len), qtok = b - seq * A.q_len;
   const int n = max(min(max(A.seq_lens[seq], 1), A.n_max) - (A.q_len - 1 - qtok), 1);  // clamp, then the causal cut
   const HeadSizes hs = head_sizes(n, A.sp);
   const int words_max = bitmap_words(A.n_max);
@@ -719,7 +725,7 @@ __global__ __launch_bounds__(NT, FD > 0 ? 1 : 4) void head_kernel(HeadArgs A) {
   constexpr int NG = NT / LPR;
   constexpr int UF = 8;
   const int g_sub = tid % LPR, g_grp = tid / LPR;
-  const int kvh = kFused ? h / A.group : 0;
+  const int kvh = kFused ? div_group(h, A.group) : 0;
   float gacc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
   float gdsum = 0.f;
   uint4 fv[UF];

@@ -40,7 +40,7 @@ __global__ __launch_bounds__(NT) void given_topk_kernel(HeadArgs A) {
   const int h = head_of_block((int)blockIdx.x, A.Hq, A.Hkv, A.group_major), b = blockIdx.y;
   const int bh = b * A.Hq + h;
   const int tid = threadIdx.x;
-  const int seq = b / A.q_len, qtok = b - seq * A.q_len;  // (sequence, query token) of a multi-query step
+  const int seq = seq_of_pair(b, A.q_len), qtok = b - seq * A.q_len;  // (sequence, query token) of a multi-query step
   const int n = max(min(max(A.seq_lens[seq], 1), A.n_max) - (A.q_len - 1 - qtok), 1);  // clamp, then the causal cut
   HeadSizes hs = head_sizes(n, A.sp);
   const int words_max = bitmap_words(A.n_max);
@@ -163,7 +163,7 @@ __global__ __launch_bounds__(NT) void given_topk_kernel(HeadArgs A) {
     if (hs.n_s > 0 && A.rcache) {
       // base sample = the first b0 cached tokens, in slot order, that are residual tokens of this head; the
       // cache is used only when it holds that many
-      const unsigned char* rec = cache_record(A.rcache, A.rc, seq, A.Hkv, h / A.group);
+      const unsigned char* rec = cache_record(A.rcache, A.rc, seq, A.Hkv, div_group(h, A.group));
       const int cnt = min(max(*reinterpret_cast<const int32_t*>(rec), 0), A.rc.slots);
       const int32_t* ctok = reinterpret_cast<const int32_t*>(rec + 16);
       const int per = (cnt + NT - 1) / NT;
@@ -251,7 +251,7 @@ __global__ __launch_bounds__(NT) void given_topk_kernel(HeadArgs A) {
       constexpr int NG = NT / LPR;
       constexpr int UF = 8;
       const int g_sub = tid % LPR, g_grp = tid / LPR;
-      const int kvh = h / A.group;
+      const int kvh = div_group(h, A.group);
       __syncthreads();  // the lists of this workgroup's share are complete
       float* spw = const_cast<float*>(A.sparse) + (int64_t)bh * A.idx_cap;
       uint32_t qw[4];
@@ -482,7 +482,7 @@ __global__ __launch_bounds__(NT) void given_topk_kernel(HeadArgs A) {
     constexpr int NG = NT / LPR;
     constexpr int UF = 8;
     const int g_sub = tid % LPR, g_grp = tid / LPR;
-    const int kvh = h / A.group;
+    const int kvh = div_group(h, A.group);
     __syncthreads();  // the final sample's share is complete in dlist
     uint32_t qw[4];
     {
