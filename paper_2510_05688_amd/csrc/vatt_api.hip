@@ -184,6 +184,7 @@ int build_plan(Plan& pl, const vatt_params& p, int q_len, int device) {
   pl.off_gather_part = take((size_t)heads * std::max(pl.split_cap, 16) * (p.head_dim + 4) * sizeof(float));
   pl.off_debug = take(512 * sizeof(uint64_t));
   pl.off_vstat_part = take((size_t)heads * pl.split_cap * (2 * p.head_dim + 2) * sizeof(double));
+  // (the dense kernel's partial sums, their maxima and sums of weights, and its pieces' keys, which need no more than the rest)
   pl.off_dense_part = take((size_t)heads * pl.dense_splits * (p.head_dim + 4) * sizeof(float));
   pl.off_pre_tok = take((size_t)heads * kHeadThreads * sizeof(uint4));
   pl.off_pre_flags = take((size_t)heads * kHeadThreads * sizeof(uint32_t));

@@ -25,6 +25,14 @@ __device__ __forceinline__ uint4 dense_load_16(const uint16_t* p) {
   return STREAM ? load_stream_16(p) : *reinterpret_cast<const uint4*>(p);
 }
 
+// Column c of row i (contiguous cache: a uniform address and 32-bit offsets, for at most 170752 tokens, take fewest
+// registers).
+template <int D, bool PAGED>
+__device__ __forceinline__ const uint16_t* dense_row(const uint16_t* base, const KVLayout& L, int seq, int kvh, int i, int blk, int c) {
+  if constexpr (PAGED) return base + kv_row_offset_in<true>(L, seq, kvh, i, blk) + c;
+  else return base + kv_row_offset<false>(L, seq, kvh, 0) + (uint32_t)(i * D + c);
+}
+
 struct DenseArgs {
   const uint16_t* q;
   const uint16_t* k;
@@ -33,6 +41,7 @@ struct DenseArgs {
   const int32_t* seq_lens;
   float* part;     // [B * q_len * Hq][splits][d]: partial sums of the weighted V rows
   float2* part_ml;  // [B * q_len * Hq][splits]: (max, sum of the weights); the unused ones of a row come last, max kNegBig
+  int2* keys;       // [B][splits]: keys (from, up to) of a sequence's pieces, left by dense_kernel
   float* out_o;
   float* out_lse;
   int batch, n_max, Hq;
@@ -131,7 +140,8 @@ __global__ __launch_bounds__(kDenseThreads, 2) void dense_kernel(DenseArgs A) {
   constexpr float kLazy = 6.0f;
   constexpr float kLog2e = 1.44269504088896340736f;
 
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  // (the wave's number as a scalar: its key range and the loop over it then take no vector registers)
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int i16 = lane & 15, g4 = lane >> 4, lrow = lane / LPR, lchunk = lane % LPR;
   const int wq = wave % WQ, wk = wave / WQ;
   constexpr int kUnit = kDenseKeys * WK;
@@ -186,6 +196,8 @@ __global__ __launch_bounds__(kDenseThreads, 2) void dense_kernel(DenseArgs A) {
     at = at_end;
   }
   const int blk_hi = min((u_lo + u_n) * kUnit, n);
+  // (the same for every KV head and round)
+  if (kvh == 0 && round == 0 && tid == 0) A.keys[seq * A.splits + split] = make_int2(u_lo * kUnit, blk_hi);
   const int lo = min(u_lo * kUnit + wk * u_n * kDenseKeys, n), hi = min(lo + u_n * kDenseKeys, blk_hi);
 
   uint4 bq[NQT][S];
@@ -211,10 +223,8 @@ __global__ __launch_bounds__(kDenseThreads, 2) void dense_kernel(DenseArgs A) {
 
   uint4 kr[KL];
   uint32_t vr[8][E / 2];
-  // (contiguous cache: a uniform address and 32-bit offsets, for at most 170752 tokens, take fewest registers)
   auto row = [&](const uint16_t* base, const KVLayout& L, int i, int blk, int c) {
-    if constexpr (PAGED) return base + kv_row_offset_in<true>(L, seq, kvh, i, blk) + c;
-    else return base + kv_row_offset<false>(L, seq, kvh, 0) + (uint32_t)(i * D + c);
+    return dense_row<D, PAGED>(base, L, seq, kvh, i, blk, c);
   };
   // (paged cache: the block-table entries of all rows first, so that no row waits for the entry of the one before)
   auto load_k = [&](int i0) {
@@ -550,53 +560,172 @@ __global__ __launch_bounds__(kDenseThreads) void dense_dot_kernel(DenseArgs A) {
   }
 }
 
+// Keys lo .. hi - 1 again for query vector bh, by the whole workgroup of dense_merge_kernel: dot products and a running
+// maximum per lane group, every row only where it is seen.  The sums go where dense_kernel would have left them.
+template <int D, bool PAGED>
+__device__ __forceinline__ void dense_again(const DenseArgs& A, int64_t bh, int seq, int kvh, int lo, int hi, float* part, float2* part_ml) {
+  constexpr int LPR = D / 8, RPW = kWave / LPR, WAVES = 2 * D / kWave, U = 4;
+  __shared__ float s_acc[WAVES][D], s_m[WAVES], s_l[WAVES];
+  int tid = threadIdx.x;
+  asm volatile("" : "+v"(tid));  // (nothing of this is worked out ahead: the merge has no registers to spare for it)
+  const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), sub = lane % LPR, rsub = lane / LPR;
+  const uint4 qv = *reinterpret_cast<const uint4*>(A.q + bh * D + sub * 8);
+  float m = kNegBig, l = 0.f, acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+  for (int i0 = lo + wave * RPW * U + rsub; i0 - rsub < hi; i0 += WAVES * RPW * U) {
+    int blk[U];
+    uint4 kk[U], vv[U];
+    auto key = [&](int u) { return min(i0 + u * RPW, hi - 1); };
+#pragma unroll
+    for (int u = 0; u < U; ++u) blk[u] = kv_block<PAGED>(A.Lk, seq, key(u));
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      kk[u] = *reinterpret_cast<const uint4*>(dense_row<D, PAGED>(A.k, A.Lk, seq, kvh, key(u), blk[u], sub * 8));
+      vv[u] = *reinterpret_cast<const uint4*>(dense_row<D, PAGED>(A.v, A.Lv, seq, kvh, key(u), blk[u], sub * 8));
+    }
+    float s[U], mnew = m;
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      s[u] = dot2_bf16(kk[u].x, qv.x, 0.f);
+      s[u] = dot2_bf16(kk[u].y, qv.y, s[u]);
+      s[u] = dot2_bf16(kk[u].z, qv.z, s[u]);
+      s[u] = group_sum<LPR>(dot2_bf16(kk[u].w, qv.w, s[u])) * A.sm_scale;
+      mnew = fmaxf(mnew, s[u]);  // (a row beyond the range repeats the last one)
+    }
+    const float alpha = __expf(m - mnew);
+    m = mnew;
+    l *= alpha;
+#pragma unroll
+    for (int c = 0; c < 8; ++c) acc[c] *= alpha;
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      if (i0 + u * RPW < hi) {
+        const float p = __expf(s[u] - m);
+        const uint32_t ww[4] = {vv[u].x, vv[u].y, vv[u].z, vv[u].w};
+        l += p;
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+          acc[2 * c] += p * bf16_lo(ww[c]);
+          acc[2 * c + 1] += p * bf16_hi(ww[c]);
+        }
+      }
+    }
+  }
+  float mall = m;
+#pragma unroll
+  for (int o = LPR; o < kWave; o <<= 1) mall = fmaxf(mall, __shfl_xor(mall, o));
+  const float f = __expf(m - mall);
+  l *= f;
+#pragma unroll
+  for (int c = 0; c < 8; ++c) acc[c] *= f;
+#pragma unroll
+  for (int o = LPR; o < kWave; o <<= 1) {
+    l += __shfl_xor(l, o);
+#pragma unroll
+    for (int c = 0; c < 8; ++c) acc[c] += __shfl_xor(acc[c], o);
+  }
+  if (rsub == 0) {
+#pragma unroll
+    for (int c = 0; c < 8; ++c) s_acc[wave][sub * 8 + c] = acc[c];
+  }
+  if (lane == 0) {
+    s_m[wave] = mall;
+    s_l[wave] = l;
+  }
+  __syncthreads();
+  float M = s_m[0], a = 0.f, lt = 0.f;
+#pragma unroll
+  for (int w = 1; w < WAVES; ++w) M = fmaxf(M, s_m[w]);
+#pragma unroll
+  for (int w = 0; w < WAVES; ++w) {
+    const float g = __expf(s_m[w] - M);
+    a += s_acc[w][tid % D] * g;
+    lt += s_l[w] * g;
+  }
+  if (tid < D) part[tid] = a;
+  if (tid == 0) *part_ml = make_float2(M, lt);
+  __syncthreads();
+}
+
 // Log-sum-exp merge of the partial sums of one head.  Bound by the latency of two dependent loads: every wave loads
 // the (max, sum) pairs for itself, one (or two) per lane, so that the weights of the partial sums are a wave-wide
 // reduction and no barrier; two halves of the workgroup take alternate partial sums so that their loads are in
 // flight together, and the first ones are requested before it is known how many there are.
-template <int D>
-__global__ __launch_bounds__(2 * D) void dense_merge_kernel(DenseArgs A, int Hkv) {
+// AGAIN (after dense_kernel): V rows with an Inf or a NaN.  The second product there gives every column every V row of a
+// step, with weight 0 where the column does not see the token, and in three terms of which some are 0: such a row makes a
+// NaN where it has no say (0 x Inf), which stays in the sums.  Finding it here costs dense_kernel nothing; the pieces with
+// an Inf or a NaN are then taken again for this head alone.  With such a row in every sequence, 4 x 32K tokens with 1 / 8
+// query tokens take 227 / 244 us instead of 87 / 89.  (A second loop in dense_kernel instead took so many registers that
+// those 89 us became 105.  Written as a loop around the merge, or with more than 64 registers, this kernel took 7.6 instead of
+// 4.8 us for 96 rows of 32 heads.)
+template <int D, bool PAGED, bool AGAIN>
+__global__ __launch_bounds__(2 * D, 8) void dense_merge_kernel(DenseArgs A, int Hkv) {
   static_assert(kDenseSplitsMax == 2 * kWave, "two pairs per lane");
-  constexpr int kAhead = 4;
+  constexpr int kAhead = 4, WAVES = 2 * D / kWave;
   // blockIdx.x runs over the KV heads first, then over the heads of a group (as in the dense kernel's grid)
   const int h = head_of_block((int)blockIdx.x, A.Hq, Hkv, 1), b = blockIdx.y;
   const int64_t bh = (int64_t)b * A.Hq + h;
-  const int c = threadIdx.x % D, half = threadIdx.x / D, lane = threadIdx.x & 63;
-  const float* p = A.part + bh * A.splits * D + c;
-  const float2* ml = A.part_ml + bh * A.splits;
+  const int c = threadIdx.x % D, half = threadIdx.x / D, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  float* p = A.part + bh * A.splits * D;
+  float2* ml = A.part_ml + bh * A.splits;
   const float2 none = make_float2(kNegBig, 0.f);
-  const float2 x0 = lane < A.splits ? ml[lane] : none, x1 = kWave + lane < A.splits ? ml[kWave + lane] : none;
-  float first[kAhead];
-#pragma unroll
-  for (int u = 0; u < kAhead; ++u) first[u] = p[min(half + 2 * u, A.splits - 1) * D];
-  const int splits = (int)(__popcll(__ballot(x0.x > kNegBig)) + __popcll(__ballot(x1.x > kNegBig)));  // unused ones come last
-  const float mall = wave_max(fmaxf(x0.x, x1.x));
-  const float w0 = __expf(x0.x - mall), w1 = __expf(x1.x - mall);
-  const float l = wave_sum_f32(x0.y * w0 + x1.y * w1);
-  auto weight = [&](int s) {
-    return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(s < kWave ? w0 : w1), s & (kWave - 1)));
-  };
-  float a = 0.f;
-#pragma unroll
-  for (int u = 0; u < kAhead; ++u) {
-    const int s = half + 2 * u;
-    if (s < splits) a += first[u] * weight(s);
-  }
-  for (int s = half + 2 * kAhead; s < splits; s += 2) a += p[s * D] * weight(s);
   __shared__ float s_a[D];
-  if (half == 1) s_a[c] = a;
-  __syncthreads();
+  __shared__ int s_odd[WAVES];
+  float a, l, mall;
+  int splits;
+  auto combine = [&]() __attribute__((always_inline)) {  // (ends with a barrier; whether this half's sum is finite goes to s_odd)
+    const float2 x0 = lane < A.splits ? ml[lane] : none, x1 = kWave + lane < A.splits ? ml[kWave + lane] : none;
+    float first[kAhead];
+#pragma unroll
+    for (int u = 0; u < kAhead; ++u) first[u] = p[min(half + 2 * u, A.splits - 1) * D + c];
+    splits = (int)(__popcll(__ballot(x0.x > kNegBig)) + __popcll(__ballot(x1.x > kNegBig)));  // unused ones come last
+    mall = wave_max(fmaxf(x0.x, x1.x));
+    const float w0 = __expf(x0.x - mall), w1 = __expf(x1.x - mall);
+    l = wave_sum_f32(x0.y * w0 + x1.y * w1);
+    auto weight = [&](int s) {
+      return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(s < kWave ? w0 : w1), s & (kWave - 1)));
+    };
+    a = 0.f;
+#pragma unroll
+    for (int u = 0; u < kAhead; ++u) {
+      const int s = half + 2 * u;
+      if (s < splits) a += first[u] * weight(s);
+    }
+    for (int s = half + 2 * kAhead; s < splits; s += 2) a += p[s * D + c] * weight(s);
+    if (half == 1) s_a[c] = a;
+    if (AGAIN) {
+      const uint64_t odd = __ballot(!(fabsf(a) < INFINITY));
+      if (lane == 0) s_odd[wave] = odd != 0;
+    }
+    __syncthreads();
+  };
+  combine();
+  if constexpr (AGAIN) {
+    int odd = s_odd[0];
+#pragma unroll
+    for (int w = 1; w < WAVES; ++w) odd |= s_odd[w];
+    if (__builtin_amdgcn_readfirstlane(odd)) {
+      const int seq = seq_of_pair(b, A.q_len), t = b - seq * A.q_len;
+      const int seen = max(dense_length(A, seq) - (A.q_len - 1 - t), 1);
+      for (int s = 0; s < splits; ++s) {
+        if (!__syncthreads_or(!(fabsf(p[s * D + c]) < INFINITY))) continue;
+        const int2 keys = A.keys[seq * A.splits + s];
+        dense_again<D, PAGED>(A, bh, seq, div_group(h, A.Hq / Hkv), keys.x, min(keys.y, seen), p + s * D, ml + s);
+      }
+      __syncthreads();
+      combine();
+    }
+  }
   if (half == 0) {
     A.out_o[bh * D + c] = (a + s_a[c]) / l;
     if (c == 0 && A.out_lse) A.out_lse[bh] = mall + logf(l);
   }
 }
 
-template <int D>
+template <int D, bool PAGED, bool AGAIN>
 hipError_t launch_dense_merge(const Plan& pl, DenseArgs& A, hipStream_t st) {
   const hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL((dense_merge_kernel<D>), dim3(pl.p.n_q_heads, pl.vbatch), dim3(2 * D), 0, st, A, pl.p.n_kv_heads);
+  hipLaunchKernelGGL((dense_merge_kernel<D, PAGED, AGAIN>), dim3(pl.p.n_q_heads, pl.vbatch), dim3(2 * D), 0, st, A, pl.p.n_kv_heads);
   return hipGetLastError();
 }
 
@@ -609,14 +738,14 @@ hipError_t launch_dense_p(const Plan& pl, DenseArgs& A, hipStream_t st) {
     dim3 grid(p.n_kv_heads, A.splits, p.batch);
     if (pl.group == 1) hipLaunchKernelGGL((dense_dot_kernel<D, 1, PAGED>), grid, dim3(kDenseThreads), 0, st, A);
     else hipLaunchKernelGGL((dense_dot_kernel<D, 2, PAGED>), grid, dim3(kDenseThreads), 0, st, A);
-    return launch_dense_merge<D>(pl, A, st);
+    return launch_dense_merge<D, false, false>(pl, A, st);
   }
   dim3 grid(p.n_kv_heads, (A.share ? A.share + p.batch : A.splits) * A.rounds, A.share ? 1 : p.batch);
   if (vectors <= 16) hipLaunchKernelGGL((dense_kernel<D, PAGED, 1, 1>), grid, dim3(kDenseThreads), 0, st, A);
   else if (waves == 1) hipLaunchKernelGGL((dense_kernel<D, PAGED, 2, 1>), grid, dim3(kDenseThreads), 0, st, A);
   else if (waves == 2) hipLaunchKernelGGL((dense_kernel<D, PAGED, 2, 2>), grid, dim3(kDenseThreads), 0, st, A);
   else hipLaunchKernelGGL((dense_kernel<D, PAGED, 2, 4>), grid, dim3(kDenseThreads), 0, st, A);
-  return launch_dense_merge<D>(pl, A, st);
+  return launch_dense_merge<D, PAGED, true>(pl, A, st);
 }
 
 template <int D>
@@ -660,6 +789,7 @@ hipError_t launch_dense(const Plan& pl, const void* q, const void* k, const void
   A.seq_lens = seq_lens;
   A.part = reinterpret_cast<float*>(static_cast<char*>(ws) + pl.off_dense_part);
   A.part_ml = reinterpret_cast<float2*>(A.part + (int64_t)pl.vbatch * pl.p.n_q_heads * pl.dense_splits * pl.p.head_dim);
+  A.keys = reinterpret_cast<int2*>(A.part_ml + (int64_t)pl.vbatch * pl.p.n_q_heads * pl.dense_splits);
   A.out_o = out_o;
   A.out_lse = out_lse;
   A.batch = pl.p.batch;

@@ -53,3 +53,70 @@ def test_dense_against_fp32_attention(case):
                 assert float((got - want).norm() / want.norm()) < 2e-5, (b, t, j)
                 assert float((lse[b * q_len + t, j * g:(j + 1) * g] - torch.logsumexp(s, -1)).abs().max()) < 2e-5, (b, t, j)
     sess.close()
+
+
+def _dense(batch, lens, q_len, hq, hkv, d, page, touch=None, seed=5):
+    """Outputs of one dense call and the workload's values; touch(k_bits, v_bits, b, n) edits a sequence's rows."""
+    import torch
+    from paper_2510_05688_amd.session import DecodeSession
+
+    lens = np.asarray(lens)
+    n_max = -(-int(lens.max()) // page) * page if page else int(lens.max())
+    wl = workloads.make_workload("dense", batch=batch, n_q_heads=hq, n_kv_heads=hkv, head_dim=d, n_max=n_max,
+                                 seq_lens=lens, seed=seed, params=default_params(d), plant_frac=0.01)
+    for b in range(batch if touch else 0):
+        touch(wl.k_bits, wl.v_bits, b, int(lens[b]))
+    q_bits = workloads.chunk_queries(wl, q_len, seed=2) if q_len > 1 else wl.q_bits
+    k_bits, v_bits, table = workloads.to_paged(wl, page) if page else (wl.k_bits, wl.v_bits, None)
+    sess = DecodeSession(dict(batch=batch, n_q_heads=hq, n_kv_heads=hkv, head_dim=d, n_max=n_max, kv_layout=1 if page else 0,
+                              page_size=page, num_blocks=k_bits.shape[0] if page else 0, sink=4, window=8, topk_abs=0,
+                              topk_frac=0.02, base_abs=0, base_frac=0.02, epsilon=0.1, delta=0.1, target=0, sm_scale=0.0,
+                              budget_cap_frac=1.0), q_len=q_len)
+    sess.upload(q_bits, k_bits, v_bits, wl.seq_lens, wl.seeds, table)
+    sess.dense()
+    torch.cuda.synchronize()
+    o = sess.dense_o.cpu().double().reshape(batch, q_len, hq, d)
+    lse = sess.dense_lse.cpu().double().reshape(batch, q_len, hq)
+    sess.close()
+    q = torch.from_numpy(workloads.bf16_bits_to_f32(q_bits)).reshape(batch, q_len, hq, d).double()
+    return wl, q, o, lse
+
+
+def _check(wl, q, o, lse, lens):
+    """Against attention in 64 bits over the tokens that each query sees; an Inf or a NaN where that has one, and no other."""
+    import torch
+    batch, q_len, hq, d = o.shape
+    g = hq // wl.n_kv_heads
+    for b in range(batch):
+        for j in range(wl.n_kv_heads):
+            n = int(lens[b])
+            k, v = torch.from_numpy(wl.k_f32(b, j, n)).double(), torch.from_numpy(wl.v_f32(b, j, n)).double()
+            for t in range(q_len):
+                seen = max(n - (q_len - 1 - t), 1)
+                for h in range(j * g, j * g + g):
+                    s = k[:seen] @ q[b, t, h] / np.sqrt(d)
+                    want = (torch.softmax(s, -1)[:, None] * v[:seen]).sum(0)
+                    got, fin = o[b, t, h], torch.isfinite(want)
+                    assert torch.equal(got[~fin].nan_to_num(3.0, 1.0, 2.0), want[~fin].nan_to_num(3.0, 1.0, 2.0)), (b, t, h)
+                    assert float((got - want)[fin].norm() / want[fin].norm()) < 2e-5, (b, t, h)
+                    assert abs(float(lse[b, t, h] - torch.logsumexp(s, -1))) < 2e-5, (b, t, h)
+
+
+INF, NINF, NAN = 0x7F80, 0xFF80, 0x7FC1
+
+
+@pytest.mark.parametrize("case", [
+    # (batch, length, q_len, Hq, Hkv, d, page): one and more tiles, waves and rounds of query vectors; whole and cut sequences
+    (2, 333, 4, 8, 2, 128, 0), (2, 90, 1, 4, 1, 64, 0), (1, 1500, 8, 8, 2, 128, 16), (2, 700, 12, 4, 1, 64, 16),
+    (1, 400, 33, 4, 1, 128, 0), (1, 130, 40, 8, 1, 64, 0), (3, 257, 3, 2, 2, 128, 0),
+], ids=lambda c: "-".join(map(str, c)))
+def test_rows_with_inf_and_nan_reach_only_the_queries_that_see_them(case):
+    batch, n, q_len, hq, hkv, d, page = case
+    lens = [n - 7 * b for b in range(batch)]
+
+    def touch(k, v, b, m):
+        v[b, :, m - 1, 3], v[b, :, m - 1, 4], v[b, :, m - 1, 11] = NAN, INF, INF   # the newest token, seen by the last query only
+        v[b, :, max(m - q_len // 2 - 2, 0), 11] = NINF                              # seen by some
+        v[b, 0, m // 3, 20], v[b, 0, m // 2, 21], v[b, 0, m // 2 + 1, 21] = INF, INF, NINF
+    wl, q, o, lse = _dense(batch, lens, q_len, hq, hkv, d, page, touch)
+    _check(wl, q, o, lse, lens)
