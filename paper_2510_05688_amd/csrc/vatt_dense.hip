@@ -40,7 +40,7 @@ struct DenseArgs {
   KVLayout Lk, Lv;
   const int32_t* seq_lens;
   float* part;     // [B * q_len * Hq][splits][d]: partial sums of the weighted V rows
-  float2* part_ml;  // [B * q_len * Hq][splits]: (max, sum of the weights); the unused ones of a row come last, max kNegBig
+  float2* part_ml;  // [B * q_len * Hq][splits]: (max, sum of the weights); the unused ones of a row come last, max -inf
   int2* keys;       // [B][splits]: keys (from, up to) of a sequence's pieces, left by dense_kernel
   float* out_o;
   float* out_lse;
@@ -398,7 +398,7 @@ __global__ __launch_bounds__(kDenseThreads, 2) void dense_kernel(DenseArgs A) {
       }
     }
     if (c < QG && wk == 0) {
-      for (int x = g4; x <= idle; x += 4) A.part_ml[place + x] = x == 0 ? make_float2(m, l) : make_float2(kNegBig, 0.f);
+      for (int x = g4; x <= idle; x += 4) A.part_ml[place + x] = x == 0 ? make_float2(m, l) : make_float2(-INFINITY, 0.f);
     }
   }
   if (at < at_end) {
@@ -556,7 +556,7 @@ __global__ __launch_bounds__(kDenseThreads) void dense_dot_kernel(DenseArgs A) {
     }
     const int64_t place = ((int64_t)seq * A.Hq + (int64_t)kvh * G + g) * A.splits + split;
     A.part[place * D + c] = a;
-    if (c == 0) A.part_ml[place] = make_float2(mall, l);
+    if (c == 0) A.part_ml[place] = make_float2(blk_lo < n ? mall : -INFINITY, l);
   }
 }
 
@@ -667,7 +667,7 @@ __global__ __launch_bounds__(2 * D, 8) void dense_merge_kernel(DenseArgs A, int 
   const int c = threadIdx.x % D, half = threadIdx.x / D, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   float* p = A.part + bh * A.splits * D;
   float2* ml = A.part_ml + bh * A.splits;
-  const float2 none = make_float2(kNegBig, 0.f);
+  const float2 none = make_float2(-INFINITY, 0.f);
   __shared__ float s_a[D];
   __shared__ int s_odd[WAVES];
   float a, l, mall;
@@ -677,7 +677,8 @@ __global__ __launch_bounds__(2 * D, 8) void dense_merge_kernel(DenseArgs A, int 
     float first[kAhead];
 #pragma unroll
     for (int u = 0; u < kAhead; ++u) first[u] = p[min(half + 2 * u, A.splits - 1) * D + c];
-    splits = (int)(__popcll(__ballot(x0.x > kNegBig)) + __popcll(__ballot(x1.x > kNegBig)));  // unused ones come last
+    // (unused ones come last; a piece all of whose scores are -inf has the maximum kNegBig)
+    splits = (int)(__popcll(__ballot(x0.x > -INFINITY)) + __popcll(__ballot(x1.x > -INFINITY)));
     mall = wave_max(fmaxf(x0.x, x1.x));
     const float w0 = __expf(x0.x - mall), w1 = __expf(x1.x - mall);
     l = wave_sum_f32(x0.y * w0 + x1.y * w1);

@@ -55,7 +55,7 @@ def test_dense_against_fp32_attention(case):
     sess.close()
 
 
-def _dense(batch, lens, q_len, hq, hkv, d, page, touch=None, seed=5):
+def _dense(batch, lens, q_len, hq, hkv, d, page, touch=None, seed=5, q_first=None):
     """Outputs of one dense call and the workload's values; touch(k_bits, v_bits, b, n) edits a sequence's rows."""
     import torch
     from paper_2510_05688_amd.session import DecodeSession
@@ -67,6 +67,9 @@ def _dense(batch, lens, q_len, hq, hkv, d, page, touch=None, seed=5):
     for b in range(batch if touch else 0):
         touch(wl.k_bits, wl.v_bits, b, int(lens[b]))
     q_bits = workloads.chunk_queries(wl, q_len, seed=2) if q_len > 1 else wl.q_bits
+    if q_first is not None:
+        q_bits = q_bits.copy()
+        q_bits[..., 0] = q_first
     k_bits, v_bits, table = workloads.to_paged(wl, page) if page else (wl.k_bits, wl.v_bits, None)
     sess = DecodeSession(dict(batch=batch, n_q_heads=hq, n_kv_heads=hkv, head_dim=d, n_max=n_max, kv_layout=1 if page else 0,
                               page_size=page, num_blocks=k_bits.shape[0] if page else 0, sink=4, window=8, topk_abs=0,
@@ -119,4 +122,15 @@ def test_rows_with_inf_and_nan_reach_only_the_queries_that_see_them(case):
         v[b, :, max(m - q_len // 2 - 2, 0), 11] = NINF                              # seen by some
         v[b, 0, m // 3, 20], v[b, 0, m // 2, 21], v[b, 0, m // 2 + 1, 21] = INF, INF, NINF
     wl, q, o, lse = _dense(batch, lens, q_len, hq, hkv, d, page, touch)
+    _check(wl, q, o, lse, lens)
+
+
+@pytest.mark.parametrize("hq,hkv,d,q_len,page", [(8, 2, 128, 1, 0), (4, 2, 64, 1, 0), (4, 4, 128, 1, 16), (8, 1, 64, 5, 16)])
+def test_pieces_whose_scores_are_all_minus_infinity(hq, hkv, d, q_len, page):
+    """In the middle of the sequence (its pieces are 64 to 512 keys here), and in all of it but the last keys."""
+    lens = [2300, 1100]
+
+    def touch(k, v, b, n):
+        k[b, :, (600 if b == 0 else 0):(1800 if b == 0 else n - 9), 0] = NINF
+    wl, q, o, lse = _dense(2, lens, q_len, hq, hkv, d, page, touch, q_first=0x3F80)
     _check(wl, q, o, lse, lens)
