@@ -405,7 +405,7 @@ __global__ __launch_bounds__(kGatherThreads) void given_gather_kernel(GivenArgs 
     const float e = valid ? sc + (tail ? tail_bias : 0.f) : -INFINITY;
     const float m_new = fmaxf(m_run, wave_max(e));
     const float f = m_run > -INFINITY ? __expf(m_run - m_new) : 0.f;
-    const float wt_mine = e > -INFINITY ? __expf(e - m_new) : 0.f;
+    const float wt_mine = e == -INFINITY ? 0.f : __expf(e - m_new);  // (NaN for a NaN score: the row is not left out)
     m_run = m_new;
     dsum = dsum * f + wt_mine;
 #pragma unroll
@@ -483,15 +483,16 @@ __global__ __launch_bounds__(D) void given_merge_kernel(const float* __restrict_
     const HeadRec r = head_rec[bh];
     used = used_splits(splits, r.n_sink + r.n_win + r.k + r.b, step_rows);
   }
-  const bool mine = (c & (kWave - 1)) < used && dm.y > -INFINITY;
+  const bool mine = (c & (kWave - 1)) < used;
   const float M = wave_max(mine ? dm.y : -INFINITY);
-  const float f = mine ? __expf(dm.y - M) : 0.f, df = mine ? dm.x * f : 0.f;
+  // (a split with no score but NaN has the maximum -inf and hands its NaN on, times 0)
+  const float f = mine && dm.y > -INFINITY ? __expf(dm.y - M) : 0.f, df = mine ? dm.x * f : 0.f;
   float a = 0.f, dtot = 0.f;
   auto add = [&](const float (&from)[U], int s0) {
 #pragma unroll
     for (int u = 0; u < U; ++u) {
       const float fu = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(f), s0 + u));
-      a += fu > 0.f ? from[u] * fu : 0.f;  // (what a split without a part left behind is not looked at)
+      a += s0 + u < used ? from[u] * fu : 0.f;  // (what a split without a part left behind is not looked at)
       dtot += __int_as_float(__builtin_amdgcn_readlane(__float_as_int(df), s0 + u));
     }
   };

@@ -42,3 +42,30 @@ def test_whole_contexts_around_a_step(d, paged, given):
             assert float((got - want).norm() / want.norm()) < 2e-5, (n, h)
             assert abs(float(torch.logsumexp(s, 0)) - float(res["lse"][b, h])) < 2e-5, (n, h)
     sess.close()
+
+
+@pytest.mark.parametrize("fused", [False, True])
+@pytest.mark.parametrize("d,rows", [(64, 1), (64, 700), (128, 1), (128, 400)])
+def test_a_nan_among_the_listed_scores_is_not_left_out(d, rows, fused):
+    """One K row, and enough of them to fill the whole run of a workgroup, hold a NaN: every output of the heads that list
+    them is NaN, whichever kernels take the step, and the others are as without."""
+    import torch
+    from paper_2510_05688_amd import binding as vb
+    from paper_2510_05688_amd.session import DecodeSession
+    n, first = 2000, 900
+    p = default_params(d, sink=16, window=48, topk_abs=n, topk_frac=0.0, base_abs=8, base_frac=0.0)
+    wl = workloads.make_workload("nan", batch=1, n_q_heads=4, n_kv_heads=2, head_dim=d, n_max=n, seq_lens=[n], seed=3, params=p)
+    wl.k_bits[0, 0, first:first + rows, 5] = 0x7FC0
+    sess = DecodeSession(plan_params(wl))
+    if not fused:
+        vb.vatt_plan_set_option(sess.plan, vb.VATT_OPT_GIVEN_FUSED, 0)
+    sess.upload(wl.q_bits, wl.k_bits, wl.v_bits, wl.seq_lens, wl.seeds)
+    counts = torch.full((1, 4), n - 64, dtype=torch.int32, device="cuda")
+    sess.decode_given_topk((torch.arange(n, dtype=torch.int32, device="cuda") + 16).repeat(1, 4, 1), counts)
+    res = sess.results_host()
+    assert np.isnan(res["O"][0, :2]).all() and np.isnan(res["lse"][0, :2]).all()
+    for h in (2, 3):
+        s = torch.from_numpy(wl.k_f32(0, 1, n)).double() @ torch.from_numpy(wl.q_f32()[0, h]).double() / np.sqrt(d)
+        want = torch.softmax(s, 0) @ torch.from_numpy(wl.v_f32(0, 1, n)).double()
+        assert float((torch.from_numpy(res["O"][0, h]).double() - want).norm() / want.norm()) < 2e-5
+    sess.close()
