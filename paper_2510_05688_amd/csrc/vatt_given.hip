@@ -410,6 +410,12 @@ __global__ __launch_bounds__(kGatherThreads) void given_gather_kernel(GivenArgs 
     dsum = dsum * f + wt_mine;
 #pragma unroll
     for (int c = 0; c < 8; ++c) acc[c] *= f;
+    if (p0 + RPB * U > p_hi) {
+      // (a row beyond the range repeats the last one, with weight 0; an Inf in it would make a NaN)
+#pragma unroll
+      for (int u = 0; u < U; ++u)
+        if (p0 + u * RPB + wave * RPW + rsub >= p_hi) vv[u] = make_uint4(0u, 0u, 0u, 0u);
+    }
 #pragma unroll
     for (int u = 0; u < U; ++u) {
       const float wt = __shfl(wt_mine, u * RPW + rsub);

@@ -69,3 +69,24 @@ def test_a_nan_among_the_listed_scores_is_not_left_out(d, rows, fused):
         want = torch.softmax(s, 0) @ torch.from_numpy(wl.v_f32(0, 1, n)).double()
         assert float((torch.from_numpy(res["O"][0, h]).double() - want).norm() / want.norm()) < 2e-5
     sess.close()
+
+
+@pytest.mark.parametrize("fused", [False, True])
+@pytest.mark.parametrize("d,n", [(64, 700), (128, 321), (128, 1000)])
+def test_an_inf_in_the_last_listed_row_stays_an_inf(d, n, fused):
+    """A workgroup's last step repeats its last row where it has no more; with weight 0, which must not make a NaN of it."""
+    import torch
+    from paper_2510_05688_amd import binding as vb
+    from paper_2510_05688_amd.session import DecodeSession
+    p = default_params(d, sink=16, window=48, topk_abs=n, topk_frac=0.0, base_abs=8, base_frac=0.0)
+    wl = workloads.make_workload("inf", batch=1, n_q_heads=4, n_kv_heads=2, head_dim=d, n_max=n, seq_lens=[n], seed=3, params=p)
+    wl.v_bits[0, :, n - 49, 7] = 0x7F80   # the largest token before the window: the last of the list
+    sess = DecodeSession(plan_params(wl))
+    if not fused:
+        vb.vatt_plan_set_option(sess.plan, vb.VATT_OPT_GIVEN_FUSED, 0)
+    sess.upload(wl.q_bits, wl.k_bits, wl.v_bits, wl.seq_lens, wl.seeds)
+    counts = torch.full((1, 4), n - 64, dtype=torch.int32, device="cuda")
+    sess.decode_given_topk((torch.arange(n, dtype=torch.int32, device="cuda") + 16).repeat(1, 4, 1), counts)
+    o = sess.results_host()["O"][0]
+    assert np.all(o[:, 7] == np.inf) and np.isfinite(np.delete(o, 7, axis=1)).all()
+    sess.close()
