@@ -245,7 +245,7 @@ int vatt_decode(vatt_plan* plan, const void* q, const void* k, const void* v,
  * vatt_static_scratch_bytes() = 16 MiB per GPU, which every GPU the library runs on holds until the process
  * ends.  The call allocates nothing, frees nothing and calls no allocating routine; the array's address on the
  * plan's device was looked up by vatt_plan_create.  A plan whose vatt_plan_workspace_bytes exceeds the array is
- * refused with VATT_E_WORKSPACE_TOO_SMALL (the 32K-token, batch-1 layer of 32 / 8 heads needs 12.3 MiB).
+ * refused with VATT_E_WORKSPACE_TOO_SMALL (the 32K-token, batch-1 layer of 32 / 8 heads needs 11.7 MiB).
  * All calls on one GPU share that GPU's array, which keeps the last call's contents (nothing in it has to
  * start at zero: every region is written before it is read within a call): calls that overlap on one GPU,
  * from any streams or plans, race.  Other arguments, results and errors as in vatt_decode.

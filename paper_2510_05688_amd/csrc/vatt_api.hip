@@ -145,12 +145,13 @@ int build_plan(Plan& pl, const vatt_params& p, int q_len, int device) {
   // 31.3 with two at batch 1 and 32K tokens, 312 against 318 at batch 16, 41 against 50 with 16 query tokens) or two
   // (paged cache, where a workgroup also waits for its block-table entries: 200 -> 179 us for 32 ragged sequences,
   // 55.8 -> 51.4 us for eight equal ones).  A row of the output has at most dense_splits partial sums: as many as one
-  // long sequence among short ones can use, within 34 MB of them.  Batches beyond 256 sequences fill the chip with
+  // long sequence among short ones can use, within 34 MB of them, and no more than it has units of keys.  Batches beyond 256 sequences fill the chip with
   // one workgroup per sequence, KV head and round, and looking every workgroup's share up would cost more.
   const int dense_jobs = p.n_kv_heads * dense_rounds(q_len * pl.group);
   const int dense_wgs = (p.kv_layout == VATT_LAYOUT_PAGED ? 2 : 1) * pl.num_cus;
   pl.dense_share = p.batch > 256 ? 0 : (dense_wgs + dense_jobs - 1) / dense_jobs;
-  pl.dense_splits = p.batch > 256 ? 1 : std::max(2, std::min({kDenseSplitsMax, pl.dense_share + 1, 65536 / heads}));
+  const int dense_units = (n_max + dense_unit(q_len * pl.group) - 1) / dense_unit(q_len * pl.group);
+  pl.dense_splits = p.batch > 256 ? 1 : std::min(dense_units, std::max(2, std::min({kDenseSplitsMax, pl.dense_share + 1, 65536 / heads})));
   if (dense_dots(q_len, pl.group)) {
     // (its workgroups are small: equal splits of every sequence, four workgroups per CU)
     const int kv_heads = p.batch * p.n_kv_heads;
@@ -179,17 +180,21 @@ int build_plan(Plan& pl, const vatt_params& p, int q_len, int device) {
   };
   pl.off_scores = take((size_t)heads * pl.n_pad * sizeof(float));
   pl.off_sub_max = take((size_t)heads * pl.n_sub * sizeof(float));
+  pl.off_debug = take(512 * sizeof(uint64_t));
+  const size_t step = off;  // from here on: what a decode step leaves for itself only
   pl.off_sparse = take((size_t)heads * pl.idx_cap * sizeof(float));
   pl.off_head_rec = take((size_t)heads * sizeof(HeadRec));
   pl.off_gather_part = take((size_t)heads * std::max(pl.split_cap, 16) * (p.head_dim + 4) * sizeof(float));
-  pl.off_debug = take(512 * sizeof(uint64_t));
   pl.off_vstat_part = take((size_t)heads * pl.split_cap * (2 * p.head_dim + 2) * sizeof(double));
-  // (the dense kernel's partial sums, their maxima and sums of weights, and its pieces' keys, which need no more than the rest)
-  pl.off_dense_part = take((size_t)heads * pl.dense_splits * (p.head_dim + 4) * sizeof(float));
   pl.off_pre_tok = take((size_t)heads * kHeadThreads * sizeof(uint4));
   pl.off_pre_flags = take((size_t)heads * kHeadThreads * sizeof(uint32_t));
   pl.off_base_slot = take((size_t)heads * pl.b0_max * sizeof(int32_t));
-  pl.ws_bytes = off;
+  // A dense call's partial sums, their maxima and sums of weights, and its pieces' keys (which need no more than the rest
+  // of d + 4) take the same place: a plan's workspace serves one call at a time.
+  const size_t step_end = off;
+  off = step;
+  pl.off_dense_part = take((size_t)heads * pl.dense_splits * (p.head_dim + 4) * sizeof(float));
+  pl.ws_bytes = std::max(off, step_end);
 
   KVLayout L;
   std::memset(&L, 0, sizeof(L));

@@ -11,7 +11,6 @@ __device__ __forceinline__ float dot2_bf16(uint32_t a, uint32_t b, float acc) {
 }
 
 constexpr float kNegBig = -1.0e30f;
-constexpr int kDenseKeys = 32;  // keys a wave of the matrix-core kernel takes at a time
 
 typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
 typedef float f32x4_t __attribute__((ext_vector_type(4)));
@@ -94,8 +93,9 @@ __device__ __forceinline__ DenseDeal dense_deal(const DenseArgs& A) {
     longest = max(longest, wave_max_u32(u));
   }
   d.run = (total + (uint32_t)A.share - 1) / (uint32_t)A.share;
-  // (a sequence has at most A.splits partial sums, and may touch one run more than its length fills)
-  if (longest > d.run * (uint32_t)(A.splits - 1)) d.run = (longest + (uint32_t)A.splits - 2) / (uint32_t)(A.splits - 1);
+  // (a sequence has at most A.splits partial sums, and may touch one run more than its length fills, but not more than it
+  // has units)
+  if (longest > (uint32_t)A.splits && longest > d.run * (uint32_t)(A.splits - 1)) d.run = (longest + (uint32_t)A.splits - 2) / (uint32_t)(A.splits - 1);
   d.whole = d.run <= kShortRun;
   if (!d.whole) {
     for (int b0 = 0; b0 < A.batch; b0 += kWave) whole_runs += wave_sum_u32((units(b0) + d.run - 1) / d.run);

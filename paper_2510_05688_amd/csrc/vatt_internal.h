@@ -42,8 +42,11 @@ __device__ __forceinline__ int used_splits(int splits, int total, int step_rows)
   return min(splits, (total + step_rows - 1) / step_rows);
 }
 
-// Waves of a dense matrix-core workgroup that take different query vectors (32 each) of the same keys.
+constexpr int kDenseKeys = 32;  // keys a wave of the matrix-core dense kernel takes at a time
+// Waves of a dense matrix-core workgroup that take different query vectors (32 each) of the same keys, and the keys of its
+// waves together, the unit in which keys are dealt out to workgroups.
 inline int dense_vector_waves(int vectors) { return vectors <= 32 ? 1 : vectors <= 64 ? 2 : 4; }
+inline int dense_unit(int vectors) { return kDenseKeys * (kDenseThreads / 64) / dense_vector_waves(vectors); }
 inline int dense_rounds(int vectors) { return (vectors + 127) / 128; }  // workgroups for all vectors of a KV head
 inline bool dense_dots(int q_len, int group) { return q_len == 1 && group <= 2; }  // too few vectors for the matrix cores
 constexpr int kDenseSplitsMax = 128;

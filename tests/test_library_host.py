@@ -88,6 +88,28 @@ def test_capped_budget_shrinks_index_buffer():
         vb.vatt_plan_destroy(plan)
 
 
+@pytest.mark.parametrize("shape,mib", [
+    # (batch, Hq, Hkv, d, n_max, page size, q_len), bytes of workspace at most
+    ((4, 32, 8, 128, 1024, 16, 1), 12.95), ((8, 32, 8, 64, 1024, 0, 1), 15.49), ((8, 32, 8, 64, 1024, 16, 1), 15.49),
+    ((5, 32, 8, 64, 4096, 16, 1), 14.3), ((12, 32, 8, 64, 16, 0, 1), 15.27), ((5, 32, 8, 64, 64, 0, 2), 14.39),
+    ((64, 8, 1, 128, 256, 0, 1), 27.0), ((1, 32, 8, 128, 32768, 0, 1), 12.3), ((1, 1, 1, 64, 64, 0, 1), 0.1),
+])
+def test_dense_partial_sums_take_no_room_of_their_own(shape, mib):
+    """They share theirs with what a decode step leaves behind, so that layers of these sizes fit the library's own array
+    (vatt_decode_static), which needs the room for the step alone."""
+    batch, hq, hkv, d, n_max, page, q_len = shape
+    p = _base(batch=batch, n_q_heads=hq, n_kv_heads=hkv, head_dim=d, n_max=n_max, kv_layout=1 if page else 0, page_size=page,
+              num_blocks=batch * n_max // page if page else 0)
+    plan = vb.vatt_plan_create(p, -1) if q_len == 1 else vb.vatt_plan_create_chunk(p, q_len, -1)
+    try:
+        ws = vb.vatt_plan_workspace_bytes(plan)
+        assert ws <= mib * 2 ** 20
+        assert (ws <= vb.vatt_static_scratch_bytes()) == (mib < 16)
+        assert vb.vatt_plan_workspace_offset(plan, vb.VATT_WS_SCORES) + batch * q_len * hq * n_max * 4 <= ws
+    finally:
+        vb.vatt_plan_destroy(plan)
+
+
 def test_geometry_only_plan_cannot_launch():
     plan = vb.vatt_plan_create(_base(), -1)
     try:
