@@ -140,8 +140,9 @@ __global__ __launch_bounds__(kDenseThreads, 2) void dense_kernel(DenseArgs A) {
   constexpr float kLazy = 6.0f;
   constexpr float kLog2e = 1.44269504088896340736f;
 
-  // (the wave's number as a scalar: its key range and the loop over it then take no vector registers)
-  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  // (the wave's number as a scalar: its key range and the loop over it then take no vector registers, of which there are
+  // none to spare at 128 columns; at 64 a workgroup alone with 8K tokens takes 64 us with it and 63 without)
+  const int tid = threadIdx.x, lane = tid & 63, wave = D == 128 ? __builtin_amdgcn_readfirstlane(tid >> 6) : tid >> 6;
   const int i16 = lane & 15, g4 = lane >> 4, lrow = lane / LPR, lchunk = lane % LPR;
   const int wq = wave % WQ, wk = wave / WQ;
   constexpr int kUnit = kDenseKeys * WK;
