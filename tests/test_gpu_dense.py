@@ -94,15 +94,19 @@ def _check(wl, q, o, lse, lens):
         for j in range(wl.n_kv_heads):
             n = int(lens[b])
             k, v = torch.from_numpy(wl.k_f32(b, j, n)).double(), torch.from_numpy(wl.v_f32(b, j, n)).double()
+            fin = torch.isfinite(v)
+            odd = (~fin).any(1).nonzero()[:, 0]
+            v_fin, v_odd = torch.where(fin, v, 0.0), torch.where(fin, 0.0, v)
             for t in range(q_len):
                 seen = max(n - (q_len - 1 - t), 1)
-                for h in range(j * g, j * g + g):
-                    s = k[:seen] @ q[b, t, h] / np.sqrt(d)
-                    want = (torch.softmax(s, -1)[:, None] * v[:seen]).sum(0)
-                    got, fin = o[b, t, h], torch.isfinite(want)
-                    assert torch.equal(got[~fin].nan_to_num(3.0, 1.0, 2.0), want[~fin].nan_to_num(3.0, 1.0, 2.0)), (b, t, h)
-                    assert float((got - want)[fin].norm() / want[fin].norm()) < 2e-5, (b, t, h)
-                    assert abs(float(lse[b, t, h] - torch.logsumexp(s, -1))) < 2e-5, (b, t, h)
+                s = q[b, t, j * g:(j + 1) * g] @ k[:seen].T / np.sqrt(d)
+                p, rows = torch.softmax(s, -1), odd[odd < seen]
+                want = p @ v_fin[:seen] + (p[:, rows, None] * v_odd[rows]).sum(1)
+                got, ok = o[b, t, j * g:(j + 1) * g], torch.isfinite(want)
+                assert torch.equal(got[~ok].nan_to_num(3.0, 1.0, 2.0), want[~ok].nan_to_num(3.0, 1.0, 2.0)), (b, t, j)
+                err, size = torch.where(ok, got - want, 0.0).norm(dim=1), torch.where(ok, want, 0.0).norm(dim=1)
+                assert float((err / size).max()) < 2e-5, (b, t, j)
+                assert float((lse[b, t, j * g:(j + 1) * g] - torch.logsumexp(s, -1)).abs().max()) < 2e-5, (b, t, j)
 
 
 INF, NINF, NAN = 0x7F80, 0xFF80, 0x7FC1
@@ -133,4 +137,61 @@ def test_pieces_whose_scores_are_all_minus_infinity(hq, hkv, d, q_len, page):
     def touch(k, v, b, n):
         k[b, :, (600 if b == 0 else 0):(1800 if b == 0 else n - 9), 0] = NINF
     wl, q, o, lse = _dense(2, lens, q_len, hq, hkv, d, page, touch, q_first=0x3F80)
+    _check(wl, q, o, lse, lens)
+
+
+def _deal(lens, q_len, hq, hkv, d, page):
+    """How the keys of a batch are dealt out on 256 CUs: (every sequence starts a new run, units per run, pieces of each
+    sequence), or None for equal ranges."""
+    vectors = q_len * hq // hkv
+    unit = 128 // (1 if vectors <= 32 else 2 if vectors <= 64 else 4)
+    jobs = hkv * -(-vectors // 128)
+    share = -(-(512 if page else 256) // jobs)
+    if len(lens) > 256:
+        return None
+    units = [-(-int(n) // unit) for n in lens]
+    most = -(-int(max(lens)) // unit)
+    splits = min(most, max(2, min(128, share + 1, 65536 // (len(lens) * q_len * hq))))
+    run = -(-sum(units) // share)
+    if max(units) > splits and max(units) > run * (splits - 1):
+        run = -(-max(units) // (splits - 1))
+    short = 384 * 1024 // (4 * d * unit)
+    whole = run <= short or sum(-(-u // run) for u in units) <= share
+    at, pieces = 0, []
+    for u in units:
+        pieces.append((at + u - 1) // run - at // run + 1)
+        at += -(-u // run) * run if whole else u
+    assert max(pieces) <= splits
+    return whole, run, pieces
+
+
+DEALS = [
+    # (mode, lengths, q_len, Hq, Hkv, d, page)
+    ("end to end", [1500, 1400, 1600, 1333, 1700, 1290, 1555, 1420, 1601], 1, 64, 16, 128, 0),
+    ("end to end", [150 + 37 * (i * 11 % 9) for i in range(70)], 1, 64, 16, 128, 0),       # a second group of 64 sequences
+    ("end to end", [5000, 33, 1200, 4100, 2600, 64, 700], 12, 64, 16, 128, 0),             # 48 vectors: two waves of them
+    ("end to end", [600 + 61 * (i * 5 % 8) for i in range(16)], 4, 128, 32, 128, 16),
+    ("end to end", [13000, 200, 9000, 4000], 9, 128, 16, 64, 0),                             # 72 vectors: four waves
+    ("whole runs", [6000, 100, 100, 100], 1, 8, 2, 128, 0),
+    ("whole runs", [20000, 3], 1, 4, 1, 64, 16),                                           # more units than partial sums
+    ("equal ranges", [2300] + [1 + 7 * (i % 60) for i in range(299)], 1, 4, 1, 128, 0),
+    ("equal ranges", [1 + 5 * (i % 50) for i in range(257)], 2, 8, 2, 64, 16),
+    ("equal ranges", [3000] + [1 + 3 * (i % 70) for i in range(256)], 1, 16, 4, 64, 0),
+]
+
+
+@pytest.mark.parametrize("odd", [False, True])
+@pytest.mark.parametrize("case", DEALS, ids=lambda c: "-".join([c[0].replace(" ", "_"), str(len(c[1])), str(max(c[1]))]))
+def test_every_way_the_keys_are_dealt_out(case, odd):
+    """With and without rows that hold an Inf or a NaN, whose pieces the merge takes again."""
+    mode, lens, q_len, hq, hkv, d, page = case
+    deal = _deal(lens, q_len, hq, hkv, d, page)
+    assert (deal is None) == (mode == "equal ranges")
+    if deal:
+        assert deal[0] == (mode == "whole runs") and max(deal[2]) > 1
+
+    def touch(k, v, b, n):
+        if b % 3 == 0:
+            v[b, :, n - 1, 3], v[b, :, n // 2, 11], v[b, 0, n // 3, 20] = NAN, NINF, INF
+    wl, q, o, lse = _dense(len(lens), lens, q_len, hq, hkv, d, page, touch if odd else None)
     _check(wl, q, o, lse, lens)
