@@ -145,13 +145,22 @@ int build_plan(Plan& pl, const vatt_params& p, int q_len, int device) {
   // 31.3 with two at batch 1 and 32K tokens, 312 against 318 at batch 16, 41 against 50 with 16 query tokens) or two
   // (paged cache, where a workgroup also waits for its block-table entries: 200 -> 179 us for 32 ragged sequences,
   // 55.8 -> 51.4 us for eight equal ones).  A row of the output has at most dense_splits partial sums: as many as one
-  // long sequence among short ones can use, within 34 MB of them, and no more than it has units of keys.  Batches beyond 256 sequences fill the chip with
-  // one workgroup per sequence, KV head and round, and looking every workgroup's share up would cost more.
+  // long sequence among short ones can use, within 34 MB of them, and no more than it has units of keys.  Beyond 256
+  // sequences looking every workgroup's share up costs more than it gains where they are short (512 of 200 tokens, two KV
+  // heads, 40 us dealt out and 27 in equal ranges): equal ranges of every sequence, four workgroups per CU in all, but
+  // none for less than 128 tokens of the capacity per query vector, so that the partial sums stay below 2 % of the bytes
+  // (300 of 50 to 1500 tokens, two KV heads, 4 query tokens: one range 61.5 us, two 65).  One range / these, one KV head, us:
+  // 300 of 200 tokens 13.9 / 14.1, of 1000 37.4 / 34.7, of 100 to 2000 47.5 / 38.5, one of 8K among 200s 83 / 30, one of 32K
+  // 303 / 85; 512 of 1000 48.3 / 50.7, of 100 to 2000 61 / 57, one of 8K among 200s 85 / 49; from 1024 sequences times KV
+  // heads on there is one.
   const int dense_jobs = p.n_kv_heads * dense_rounds(q_len * pl.group);
   const int dense_wgs = (p.kv_layout == VATT_LAYOUT_PAGED ? 2 : 1) * pl.num_cus;
   pl.dense_share = p.batch > 256 ? 0 : (dense_wgs + dense_jobs - 1) / dense_jobs;
   const int dense_units = (n_max + dense_unit(q_len * pl.group) - 1) / dense_unit(q_len * pl.group);
-  pl.dense_splits = p.batch > 256 ? 1 : std::min(dense_units, std::max(2, std::min({kDenseSplitsMax, pl.dense_share + 1, 65536 / heads})));
+  pl.dense_splits = std::min(dense_units, std::max(2, std::min({kDenseSplitsMax, pl.dense_share + 1, 65536 / heads})));
+  const int dense_least = 128 * q_len * pl.group;
+  if (p.batch > 256)
+    pl.dense_splits = std::min({64, (n_max + dense_least - 1) / dense_least, std::max(1, (4 * pl.num_cus + p.batch * dense_jobs - 1) / (p.batch * dense_jobs))});
   if (dense_dots(q_len, pl.group)) {
     // (its workgroups are small: equal splits of every sequence, four workgroups per CU)
     const int kv_heads = p.batch * p.n_kv_heads;
