@@ -1174,6 +1174,11 @@ bool fused_splits_fit(const Plan& pl, int splits) {
 //     whose first draws are not made beside the scores, gain from about 200 heads on (8 query tokens, 4K: 40.1 -> 38.2, 5: 35.5 -> 37.0);
 //   fewer heads: one head of 1K 23.7 -> 21.7, 32 heads of 4K / 9K 27.5 -> 25.4, 28.2 -> 27.0, but 32 heads of 9K with a list of 1156
 //     rows 30.2 -> 30.8, of 12K (856 rows) 30.8 -> 31.2, with 4 query tokens of 2K 34.2 -> 35.3.
+// That is with budgets at the base sample's size.  They grow with (z / epsilon)^2, and one workgroup then gathers all of a
+// long list: 32 heads of 8K at epsilon 0.05 / 0.03 / 0.02 / 0.01 with eight per head 26.5 / 28.8 / 32.6 / 38.2, with one 24.8 /
+// 31.6 / 40.5 / 60.9, of 2K 25.2 / 27.7 / 28.9 / 28.3 and 23.2 / 27.6 / 32.6 / 31.4, of 1K 24.7 / 28.6 / 28.2 / 28.0 and 22.5 / 27.0 / 27.3 /
+// 27.3; so a tight epsilon (0.035 at delta 0.05) takes one workgroup only for few heads' short rows.  256 heads of 7K at 0.02 /
+// 0.01: apart 53.4 / 60.9, one per head 50.4 / 65.9.
 int fused_splits_for(const Plan& pl) {
   const vatt_params& p = pl.p;
   const int heads = pl.vbatch * p.n_q_heads;
@@ -1182,7 +1187,8 @@ int fused_splits_for(const Plan& pl) {
     return most && fused_splits_fit(pl, 1) ? 1 : 0;
   }
   const int rows = p.sink + p.window + pl.k_max + pl.b0_max;  // the shortest list of the longest sequence
-  if (pl.q_len == 1 && rows <= 768 && p.n_max <= 10240 && fused_splits_fit(pl, 1)) return 1;
+  const bool tight = (pl.z_half / pl.eps) * (pl.z_half / pl.eps) > 3000.0;
+  if (pl.q_len == 1 && rows <= 768 && p.n_max <= (tight ? 1024 : 10240) && fused_splits_fit(pl, 1)) return 1;
   int s = 1;
   while (2 * s * heads <= pl.num_cus && s < 16) s *= 2;
   while (s >= 2 && !fused_splits_fit(pl, s)) s /= 2;
@@ -1197,7 +1203,7 @@ hipError_t launch_head_fused(const Plan& pl, const void* v, const int32_t* block
   HeadArgs A;
   fill_head_args(A, pl, 0, seq_lens, seq_seeds, ws, out_idx, out_counts, out_budget_raw, out_stats);
   const vatt_params& p = pl.p;
-  if (pre_made) {  // launch_prework ran for this call
+  if (pre_made) {  // workgroups of the score launch made the first batches (prework_job)
     A.pre_tok = reinterpret_cast<const uint4*>(static_cast<char*>(ws) + pl.off_pre_tok);
     A.pre_flags = reinterpret_cast<const uint32_t*>(static_cast<char*>(ws) + pl.off_pre_flags);
   }
