@@ -660,7 +660,8 @@ bool given_fused_fits(const Plan& pl, int splits) {
 // The plan's own choice: as for the scored path, when there are at most half as many heads as compute units; and one
 // workgroup per head when most compute units get one (whole step, us, separate kernels -> fused: 256 heads of 300 / 4K / 9K
 // tokens 34.7 -> 31.1, 37.9 -> 35.9, 42.4 -> 40.3, of 4K with 64 columns 38.5 -> 34.1; 160 heads of 1K 31.7 both ways, of 6K with 5
-// query tokens 40.4 -> 43.1).
+// query tokens 40.4 -> 43.1).  That is with budgets near the base sample's size: 256 heads of 7K ragged at epsilon 0.05 / 0.03 /
+// 0.02 / 0.01 36.8 / 42.2 / 56.7 / 70.3 apart, 35.2 / 43.5 / 59.3 / 92.4 fused.
 int given_fused_splits_for(const Plan& pl) {
   const int heads = pl.vbatch * pl.p.n_q_heads;
   if (heads * 2 > pl.num_cus) return heads <= pl.num_cus && 4 * heads > 3 * pl.num_cus && given_fused_fits(pl, 1) ? 1 : 0;
