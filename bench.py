@@ -27,22 +27,22 @@ HBM_PEAK_GBPS = 8000.0   # MI355X HBM3E, published
 
 # HBM bytes per score-kernel launch from two rocprofv3 --pmc runs of `bench.py --only score` (FETCH_SIZE, then
 # WRITE_SIZE, KiB per dispatch), each scaled by what the same counter reads for `bench.py --only copy`, a
-# 256 MiB device copy: FETCH_SIZE reads 131084.4 KiB for its 262144 KiB (factor 1.99981), WRITE_SIZE 262144
-# (factor 1).  Score kernel at config 2: FETCH_SIZE 32827.5, WRITE_SIZE 4608.0; at config 3: 524827.5 and
-# 73728.0.  The summaries are kept under profiles/.  Only the configurations that were measured have a figure.
-SCORE_KERNEL_TRAFFIC_BYTES = {"config2": int((32827.5 * 262144.0 / 131084.4 + 4608.0) * 1024),
-                              "config3": int((524827.5 * 262144.0 / 131084.4 + 73728.0) * 1024)}
+# 256 MiB device copy: FETCH_SIZE reads 131085.6 KiB for its 262144 KiB (factor 1.9998), WRITE_SIZE 262144
+# (factor 1).  Score kernel at config 2: FETCH_SIZE 32805.2, WRITE_SIZE 4608.0; at config 3: 524835.3 and
+# 82355.4.  The summaries are kept under profiles/.  Only the configurations that were measured have a figure.
+SCORE_KERNEL_TRAFFIC_BYTES = {"config2": int((32805.2 * 262144.0 / 131085.6 + 4608.0) * 1024),
+                              "config3": int((524835.3 * 262144.0 / 131085.6 + 82355.4) * 1024)}
 # score_chunk_kernel, same two counters and scaling (config 2 with 4 query tokens)
-SCORE_CHUNK_TRAFFIC_BYTES = {("config2", 4): int((32928.6 * 262144.0 / 131084.4 + 18432.7) * 1024)}
+SCORE_CHUNK_TRAFFIC_BYTES = {("config2", 4): int((32826.3 * 262144.0 / 131085.6 + 18433.2) * 1024)}
 # HBM bytes of all kernels of one vatt_decode step, same two counters, scaled by what they read for a 256 MiB
-# device copy (FETCH_SIZE x 1.99974, WRITE_SIZE x 1.0): profiles/decode_config{2,3,4}_kernel_stats.md
-STEP_TRAFFIC_BYTES = {"config2": 91222118, "config3": 1537473331, "config4": 1421102828}
-# rocprofv3 --kernel-trace --stats averages (us) of the kernels of one step, `python3 bench.py --no-cpu` under the
-# profiler (profiles/decode_config2_kernel_stats.md, profiles/decode_config3_kernel_stats.md)
+# device copy (FETCH_SIZE x 1.9998, WRITE_SIZE x 1.0): profiles/decode_config{2,3,4}_kernel_stats.md
+STEP_TRAFFIC_BYTES = {"config2": 91212905, "config3": 1530270507, "config4": 1423688365}
+# rocprofv3 --kernel-trace --stats averages (us) of the kernels of one step, `python3 bench.py --no-cpu --no-extra` under
+# the profiler (profiles/decode_config{2,3,4}_kernel_stats.md)
 PROFILE_KERNEL_US = {
-    "config2": {"score_kernel": 13.61, "head_kernel (selection with the gather fused in)": 23.49, "gather_merge_kernel": 4.29},
-    "config3": {"score_kernel": 181.11, "head_kernel": 31.20, "gather_kernel": 41.14, "gather_merge_kernel": 4.47},
-    "config4": {"score_kernel": 177.42, "head_kernel": 44.03, "gather_kernel": 30.33, "gather_merge_kernel": 4.40},
+    "config2": {"score_kernel": 13.19, "head_kernel (selection with the gather fused in)": 22.22, "gather_merge_kernel": 4.00},
+    "config3": {"score_kernel": 173.95, "head_kernel": 33.92, "gather_kernel": 39.31, "gather_merge_kernel": 4.39},
+    "config4": {"score_kernel": 171.38, "head_kernel": 49.83, "gather_kernel": 28.65, "gather_merge_kernel": 4.56},
 }
 LLAMA8B_LAYERS = 32
 

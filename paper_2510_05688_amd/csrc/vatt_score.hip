@@ -171,8 +171,8 @@ hipError_t launch_g(const Plan& pl, ScoreArgs& A, hipStream_t st) {
   // heads are enough to hide the time to memory: it then takes 5 us longer and the score pass 12 us less.  Whole call, plain ->
   // non-temporal, us: 16 x 32K 267.6 -> 258.7, 8 x 64K 276 -> 265, 8 x 32K 146.6 -> 143.6, 16 x 16K 160.3 -> 157.5, 32 x 8K 198.6 ->
   // 195.8, 64 x 4K 269.7 -> 265.9, 4 x 128K 255.2 -> 252.7, 32 of 1K - 33K on pages 315.5 -> 310.8, and equal at 4 x 64K (153.1,
-  // 156.3, runs 3 apart); below the limits 2 x 128K 208 -> 210, 8 x 16K 86.1 -> 86.0.  (Pieces of 64 bytes leave some lines
-  // in two writes: 82.6 MB instead of 73.7 at 16 x 32K.)
+  // 156.3, runs 3 apart); below the limits 2 x 128K 208 -> 210, 8 x 16K 86.1 -> 86.0.  (By the counters the pass then writes 84.3 MB
+  // instead of 75.5 at 16 x 32K.)
   const bool nt = score_bytes(pl) >= kScoreBytesLarge && p.batch * p.n_q_heads >= 128;
   dim3 grid = score_grid(A.grid, pl.score_order, (p.n_max + keys - 1) / keys, (size_t)keys * D * 2, p.n_kv_heads, p.batch);
   size_t lds = 0;
