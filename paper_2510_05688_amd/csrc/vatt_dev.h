@@ -272,6 +272,31 @@ __device__ __forceinline__ uint64_t wave_sum(uint64_t v) {
   return (readlane_u64(v, 0) + readlane_u64(v, 16)) + (readlane_u64(v, 32) + readlane_u64(v, 48));
 }
 
+// Adds acc[0 .. 8) over the 64 / LPR groups of LPR adjacent lanes of a wave (8 columns of a row per lane).  Two lanes that
+// hold partial sums of two columns each take one of them from both, so that every step halves what is left: 7 (LPR 16) or
+// 8 additions instead of 16 or 24 with a pass through the LDS crossbar each.  Afterwards acc[0] and acc[1] hold the sums of the
+// columns lane_groups_column(lane) and the next; with LPR 8 both halves of 16 lanes hold the same.
+template <int LPR>
+__device__ __forceinline__ void add_lane_groups(float (&acc)[8]) {
+  static_assert(LPR == 8 || LPR == 16, "rows of 64 or 128 columns");
+  float half[4];
+#pragma unroll
+  for (int c = 0; c < 4; ++c) {
+    // (lanes 32 .. 63 of the first operand change places with lanes 0 .. 31 of the second)
+    const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(acc[c]), __float_as_uint(acc[c + 4]), false, false);
+    half[c] = __uint_as_float(r[0]) + __uint_as_float(r[1]);
+  }
+#pragma unroll
+  for (int c = 0; c < 2; ++c) {
+    // (odd rows of 16 lanes of the first operand change places with even rows of the second)
+    const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(half[c]), __float_as_uint(half[c + 2]), false, false);
+    acc[c] = __uint_as_float(r[0]) + __uint_as_float(r[1]);
+    if constexpr (LPR == 8) acc[c] += dpp_f32<0x128>(acc[c]);  // row_ror:8
+  }
+}
+template <int LPR>
+__device__ __forceinline__ int lane_groups_column(int lane) { return (lane % LPR) * 8 + ((lane & 32) ? 4 : 0) + ((lane & 16) ? 2 : 0); }
+
 // ---------------------------------------------------------------------------
 // Order-preserving map fp32 -> uint32 (ascending).  -0 must have been folded into +0.
 // ---------------------------------------------------------------------------

@@ -64,6 +64,31 @@ __device__ __forceinline__ uint32_t block_exclusive_scan_once(uint32_t v, uint32
   return base + incl - v;
 }
 
+// Two of them at once: a and b become their exclusive prefixes, *total_b gets the workgroup sum of b.
+template <int NT>
+__device__ __forceinline__ void block_exclusive_scan_two_once(uint32_t& a, uint32_t& b, uint32_t* total_b, BlockScanSmem<NT>& sa,
+                                                              BlockScanSmem<NT>& sb) {
+  constexpr int SW = NT / kWave;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const uint32_t incl_a = wave_inclusive_scan_u32(a), incl_b = wave_inclusive_scan_u32(b);
+  if (lane == kWave - 1) {
+    sa.wave_total[wave] = incl_a;
+    sb.wave_total[wave] = incl_b;
+  }
+  __syncthreads();
+  uint32_t base_a = 0, base_b = 0, tot = 0;
+#pragma unroll
+  for (int w = 0; w < SW; ++w) {
+    const uint32_t ta = sa.wave_total[w], tb = sb.wave_total[w];
+    base_a += (w < wave) ? ta : 0u;
+    base_b += (w < wave) ? tb : 0u;
+    tot += tb;
+  }
+  *total_b = tot;
+  a = base_a + incl_a - a;
+  b = base_b + incl_b - b;
+}
+
 // Number of the set bits of a wave's mask that belong to lower lanes.
 __device__ __forceinline__ uint32_t lanes_below(uint64_t mask) {
   return __builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
@@ -124,22 +149,31 @@ struct HeadOps {
     BlockScanSmem<NT> scan;
     double red[3][SW];
     uint32_t again[2];
-    BlockScanSmem<NT> scan_once[3];  // for scans that run once in a launch and need no barrier before them
+    BlockScanSmem<NT> scan_once[4];  // for scans that run once in a launch and need no barrier before them
   };
 
   // Workgroup sums of up to three doubles at once; every thread gets all of them.  (The sums of the waves are added
   // by groups of 16 lanes of every wave, one group per sum, instead of by every thread.)
   template <int N>
   static __device__ __forceinline__ void block_sum(double (&v)[N], HeadSmem& sm) {
-    static_assert(N <= 4 && SW <= 16, "a row of 16 lanes per sum");
+    __syncthreads();
+    block_sum_post(v, sm);
+    __syncthreads();
+    block_sum_get(v, sm);
+  }
+  // Its two halves, for callers that have a barrier between them anyway.
+  template <int N>
+  static __device__ __forceinline__ void block_sum_post(double (&v)[N], HeadSmem& sm) {
 #pragma unroll
     for (int j = 0; j < N; ++j) v[j] = wave_sum(v[j]);
-    __syncthreads();
     if ((threadIdx.x & 63) == 0) {
 #pragma unroll
       for (int j = 0; j < N; ++j) sm.red[j][threadIdx.x >> 6] = v[j];
     }
-    __syncthreads();
+  }
+  template <int N>
+  static __device__ __forceinline__ void block_sum_get(double (&v)[N], const HeadSmem& sm) {
+    static_assert(N <= 4 && SW <= 16, "a row of 16 lanes per sum");
     const int row = (int)(threadIdx.x & 63) >> 4, w = (int)(threadIdx.x & 15);
     double t = sm.red[min(row, N - 1)][min(w, SW - 1)];
     t = w < SW ? t : 0.0;
@@ -150,7 +184,6 @@ struct HeadOps {
 #pragma unroll
     for (int j = 0; j < N; ++j) v[j] = readlane_f64(t, 16 * j);
   }
-
   // Token read back from an index list, forced into [0, n): a list entry can never address outside the row.
   static __device__ __forceinline__ int list_tok(const int32_t* idx, int64_t pos, int n) {
     return min(max(idx[pos], 0), n - 1);

@@ -447,6 +447,9 @@ __device__ __forceinline__ void add_weighted_row(float (&acc)[8], float wt, cons
   }
 }
 
+template <int V>
+using Int = std::integral_constant<int, V>;
+
 // The arguments every launch of the two kernels starts from.
 inline void fill_head_args(HeadArgs& A, const Plan& pl, int phase, const int32_t* seq_lens, const uint64_t* seq_seeds,
                            void* ws, int32_t* out_idx, int32_t* out_counts, double* out_budget_raw,

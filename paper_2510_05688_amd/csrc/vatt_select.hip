@@ -216,10 +216,10 @@ __global__ __launch_bounds__(NT, FD > 0 ? 1 : 4) void head_kernel(HeadArgs A) {
     }
   };
   bool spec1_made = false, pair_made = false;
+  const int half = tid >= NT / 2 ? 1 : 0;
   if (kTwoStreams && want0 && want1 && 2 * ahead_blocks<NT>(A.small_batches) <= NT) {
     // both streams at once: the lower half of the workgroup generates the first batch of the base sample,
     // the upper half that of the final sample
-    const int half = tid >= NT / 2 ? 1 : 0;
     const int blocks0 = ahead_blocks<NT>(A.small_batches, hs, base_draws(hs));
     const int blocks1 = ahead_blocks<NT>(A.small_batches, hs, final_draws(hs));
     const int blocks = half ? blocks1 : blocks0;
@@ -241,15 +241,19 @@ __global__ __launch_bounds__(NT, FD > 0 ? 1 : 4) void head_kernel(HeadArgs A) {
       mine.have_sc = true;
     } else {
       // (selection-only kernel, which runs with every CU full: the scores of the final sample's proposals are
-      // requested later, after the top-k step; a million scattered 4-byte reads at once, from all workgroups in
+      // requested after the top-k step; a million scattered 4-byte reads at once, from all workgroups in
       // their first microseconds, held every workgroup up for five microseconds at config 3)
       O::make_batch(mine, half ? S1 : S0, hs, 0u, blocks, false, kFused || !half, sm, tid - half * (NT / 2));
     }
-    spec0.have_sc = true;
-    if (half) spec1 = mine; else spec0 = mine;
+    // (a thread holds draws of one stream; of the other it has the same tokens, none of which counts)
+    spec0 = spec1 = mine;
+    spec0.ok = half ? 0u : mine.ok;
+    spec0.first = half ? 0u : mine.first;
+    spec1.ok = half ? mine.ok : 0u;
+    spec1.first = half ? mine.first : 0u;
     spec0.blocks = blocks0;
     spec1.blocks = blocks1;
-    spec1.have_sc = true;  // (the same answer in every thread; the lower half holds no draws of this stream)
+    spec0.have_sc = spec1.have_sc = true;
     spec1_made = true;
     pair_made = true;
   } else if (want0) {
@@ -296,40 +300,40 @@ __global__ __launch_bounds__(NT, FD > 0 ? 1 : 4) void head_kernel(HeadArgs A) {
   uint32_t tau_key = 0u;  // largest composite key (~order key: the smallest score) among this thread's top-k members
   float acc_f32 = 0.f;  // this thread's share of D_f = sum over I_f of exp(s_i - m), kept in fp32 per thread
   double acc_f = 0.0;
+  bool marked = false;  // the members' weights are in ts.wq, as integers
+  uint32_t n_cand_used = 0;  // fast path: members are the candidates marked in bm_f
+  // (see "more candidates than the list holds")
+  uint32_t n_wide_used = 0;
+  constexpr uint32_t kWideCap = kCandCap * 12 / sizeof(uint16_t);
+  uint16_t* wide = reinterpret_cast<uint16_t*>(cand);
+  static_assert(kCapacityMax / kSubTile < 65536, "sub-tiles as 16-bit numbers");
+  // f(score, token) for the middle scores of the listed sub-tiles, two lanes per sub-tile, four loads in flight
+  auto each_wide = [&](uint32_t count, auto&& f) {
+    for (uint32_t q0 = 0; q0 < count; q0 += 4u * (NT / 2)) {
+      float4 x[4];
+      int tok[4];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        const uint32_t q = q0 + (uint32_t)(u * (NT / 2) + tid / 2);
+        const int t = (int)min((uint32_t)wide[min(q, count - 1)], (uint32_t)(n_sub - 1)) * kSubTile + (tid & 1) * 4;
+        x[u] = *reinterpret_cast<const float4*>(row + t);
+        tok[u] = q < count ? t : n;
+      }
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        const float sv[4] = {x[u].x, x[u].y, x[u].z, x[u].w};
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+          if (tok[u] + e >= hs.mid_lo && tok[u] + e < hs.mid_hi) f(sv[e], tok[u] + e);
+      }
+    }
+  };
   // ---- I_t (Algorithm 1, top-k step) ----
   if (A.phase != 2) {
     const int mid_len = hs.mid_hi - hs.mid_lo;
     if (hs.k > 0) {
       float sT = -INFINITY;
       uint32_t Tidx = kInv32;
-      bool marked = false;
-      uint32_t n_cand_used = 0;  // fast path: members are the candidates marked in bm_f
-      // (see "more candidates than the list holds")
-      uint32_t n_wide_used = 0;
-      constexpr uint32_t kWideCap = kCandCap * 12 / sizeof(uint16_t);
-      uint16_t* wide = reinterpret_cast<uint16_t*>(cand);
-      static_assert(kCapacityMax / kSubTile < 65536, "sub-tiles as 16-bit numbers");
-      // f(score, token) for the middle scores of the listed sub-tiles, two lanes per sub-tile, four loads in flight
-      auto each_wide = [&](uint32_t count, auto&& f) {
-        for (uint32_t q0 = 0; q0 < count; q0 += 4u * (NT / 2)) {
-          float4 x[4];
-          int tok[4];
-#pragma unroll
-          for (int u = 0; u < 4; ++u) {
-            const uint32_t q = q0 + (uint32_t)(u * (NT / 2) + tid / 2);
-            const int t = (int)min((uint32_t)wide[min(q, count - 1)], (uint32_t)(n_sub - 1)) * kSubTile + (tid & 1) * 4;
-            x[u] = *reinterpret_cast<const float4*>(row + t);
-            tok[u] = q < count ? t : n;
-          }
-#pragma unroll
-          for (int u = 0; u < 4; ++u) {
-            const float sv[4] = {x[u].x, x[u].y, x[u].z, x[u].w};
-#pragma unroll
-            for (int e = 0; e < 4; ++e)
-              if (tok[u] + e >= hs.mid_lo && tok[u] + e < hs.mid_hi) f(sv[e], tok[u] + e);
-          }
-        }
-      };
       if (hs.k < mid_len) {
         // Fast path.  A lower bound of the k-th largest score: the k-th largest of the sub-tile maxima (of
         // the sub-tiles that lie entirely in the middle region) has at least k middle scores at or above it.
@@ -494,12 +498,6 @@ __global__ __launch_bounds__(NT, FD > 0 ? 1 : 4) void head_kernel(HeadArgs A) {
             }
             fixed_sum = wave_sum(fixed_sum);
             if ((tid & 63) == 0) ts.wq[tid >> 6] = fixed_sum;
-            __syncthreads();
-            if (tid == 0) {
-              uint64_t tot = 0;
-              for (int w = 0; w < SW; ++w) tot += ts.wq[w];
-              acc_f += (double)tot * (1.0 / 1099511627776.0);
-            }
             have_T = true;
             marked = true;
             n_cand_used = n_cand;
@@ -576,12 +574,6 @@ __global__ __launch_bounds__(NT, FD > 0 ? 1 : 4) void head_kernel(HeadArgs A) {
                 }
                 fixed_sum = wave_sum(fixed_sum);
                 if ((tid & 63) == 0) ts.wq[tid >> 6] = fixed_sum;
-                __syncthreads();
-                if (tid == 0) {
-                  uint64_t tot = 0;
-                  for (int w = 0; w < SW; ++w) tot += ts.wq[w];
-                  acc_f += (double)tot * (1.0 / 1099511627776.0);
-                }
                 topk_flag = kFlagTopkGeneral;
                 have_T = true;
                 marked = true;
@@ -640,10 +632,105 @@ __global__ __launch_bounds__(NT, FD > 0 ? 1 : 4) void head_kernel(HeadArgs A) {
             tau_key = take ? max(tau_key, ~float_order_key(s[u])) : tau_key;
           }
         });
-        __syncthreads();
       }
-      // ascending token list from the bitmap
-      O::word_prefix(bm_f, words, wpre, sm, &sm.scan_once[2]);
+      VATT_STAMP(A.dbg, 4);
+    }
+  } else {
+    // phase 2: rebuild the top-k bitmap from the list written in phase 1
+    for (int t = tid; t < hs.k; t += NT) {
+      const int i = O::list_tok(idx, A.seg_topk + t, n);
+      O::mark_bit(bm_f, (uint32_t)i);
+      acc_f += (double)__expf(row[i] - m);
+    }
+    for (int i = tid; i < hs.n_sink; i += NT) acc_f += (double)__expf(row[i] - m);
+    for (int i = tid; i < hs.n_win; i += NT) acc_f += (double)__expf(row[hs.mid_hi + i] - m);
+  }
+  VATT_STAMP(A.dbg, 30);
+  __syncthreads();
+  VATT_STAMP(A.dbg, 31);
+
+  // Fused gather, first part: the V rows (and scores) of this workgroup's share of I_f are requested now and
+  // added after the samplers have run.  LPR adjacent lanes read one row; NG rows per round, UF rounds in flight.
+  constexpr int LPR = kFused ? FD / 8 : 16;
+  constexpr int NG = NT / LPR;
+  constexpr int UF = 8;
+  const int g_sub = tid % LPR, g_grp = tid / LPR;
+  const int kvh = kFused ? div_group(h, A.group) : 0;
+  float gacc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+  float gdsum = 0.f;
+  uint4 fv[UF];
+  float fs[UF];
+  int my_nf = 0;
+  // contiguous cache: this lane's 8 columns of row 0 of the head's V slice
+  const uint16_t* v_head = (kFused && !PAGED)
+                               ? A.v + (int64_t)seq * A.L.seq_stride + (int64_t)kvh * A.L.head_stride + g_sub * 8
+                               : nullptr;
+  // UF rows of a list at once, without branches: all list entries (and their scores) are read from LDS first,
+  // then all rows are requested.  The lists are padded to whole calls, so the LDS reads need no bound; a slot
+  // beyond the list reads row 0 and gets the score -inf (weight exp(-inf - m) = 0).  (Written with a per-slot
+  // condition, every slot became a branch of its own with an LDS wait inside: sixteen serial LDS round trips.)
+  // HaveSc: the scores of the listed tokens are in LDS (list_sc), else they are read from the score row.
+  // Rounds beyond the list's end request no rows, in steps of two and four (a round costs the workgroup 128 clocks of
+  // address processing and as many of arithmetic, and most lists fill three to five of the eight: 1 x 32K tokens 36.3 -> 35.6 us,
+  // one head of 1K 20.1 -> 18.8 us per call).
+  auto load_rows = [&](const uint32_t* list, const float* list_sc, int j0, int count, float (&sc)[UF], uint4 (&vv)[UF],
+                       auto have_sc) {
+    constexpr bool HaveSc = decltype(have_sc)::value;
+    uint32_t t[UF];
+    const int jb = j0 + g_grp;
+#pragma unroll
+    for (int u = 0; u < UF; ++u) {
+      t[u] = list[jb + u * NG];
+      sc[u] = HaveSc ? list_sc[jb + u * NG] : 0.f;
+    }
+    int blk[UF];
+    bool valid[UF];
+#pragma unroll
+    for (int u = 0; u < UF; ++u) {
+      valid[u] = jb + u * NG < count;
+      t[u] = valid[u] ? min(t[u], (uint32_t)(n - 1)) : 0u;
+      blk[u] = kv_block<PAGED>(A.L, seq, (int)t[u]);  // (paged cache: all block-table entries before any row)
+    }
+    auto rows = [&](auto from, auto to) {
+#pragma unroll
+      for (int u = decltype(from)::value; u < decltype(to)::value; ++u) {
+        if constexpr (!HaveSc) sc[u] = row[t[u]];
+        if constexpr (PAGED) vv[u] = load_stream_16(A.v + kv_row_offset_in<true>(A.L, seq, kvh, (int)t[u], blk[u]) + g_sub * 8);
+        else vv[u] = load_stream_16(v_head + t[u] * (uint32_t)(kFused ? FD : 1));  // (n_max * d < 2^32)
+      }
+    };
+    rows(Int<0>{}, Int<2>{});
+    if (count > j0 + 2 * NG) rows(Int<2>{}, Int<4>{});
+    if (count > j0 + 4 * NG) rows(Int<4>{}, Int<UF>{});
+#pragma unroll
+    for (int u = 0; u < UF; ++u) sc[u] = valid[u] ? sc[u] : -INFINITY;
+  };
+  using ScInLds = std::true_type;
+  using ScInRow = std::false_type;
+  if constexpr (kFused) my_nf = (int)(g_hi - g_lo);
+
+  VATT_STAMP(A.dbg, 32);
+  if (want1 && !spec1_made) O::make_batch(spec1, S1, hs, 0u, ahead_blocks<NT>(A.small_batches, hs, final_draws(hs)), false, false, sm, tid);
+
+  // ---- I_bs (Algorithm 2, base sample) and the sums over it ----
+  int flags = topk_flag;
+  double acc_w = 0.0, acc_w2 = 0.0;
+  // Usual case (both first batches at hand, base sample neither the whole residual nor taken as a
+  // complement): the draws of both streams are tested against the top-k set and counted in draw order by ONE
+  // workgroup scan (the lower half of the workgroup holds the base sample's stream, the upper half the final
+  // sample's; the two counts travel in the halves of one word), which also counts the top-k bitmap's bits.  The base
+  // sample is complete if its first batch holds b0 accepted draws.  And since the budget is never below b0, the first b0
+  // accepted draws of the other stream belong to the final sample whatever the budget turns out to be (unless it asks for
+  // so much that the sample is taken as a complement): with the fused gather their V rows are requested now, and are in
+  // when the budget is known.  From the marked members to the budget there are four barriers where the lists, the sums and the
+  // samples, one after the other, had ten: a barrier with the scan or the sums around it is 300 - 400 clocks of the chain (1 x
+  // 32K tokens 35.6 -> 35.0 us, one head of 1K 18.8 -> 17.7 us per call).  (The sorted and the nested forms of the lists are made
+  // by the general path only.)
+  // The lists of I_f, once wpre is complete (and, with the fused gather, this workgroup's share of them in LDS).
+  auto write_lists = [&]() {
+    if (A.phase == 2) return;
+    // ascending list of the top-k tokens
+    if (hs.k > 0) {
       if (NT >= 1024 && n_wide_used) {
         each_wide(n_wide_used, [&](float sc, int i) {
           const uint32_t word = bm_f[i >> 5], bit = 1u << (i & 31);
@@ -685,12 +772,7 @@ __global__ __launch_bounds__(NT, FD > 0 ? 1 : 4) void head_kernel(HeadArgs A) {
           }
         }
       }
-      VATT_STAMP(A.dbg, 4);
     }
-    // weights of the sink and window tokens (their scores were requested at the start)
-    acc_f32 += __expf(edge0 - m) + __expf(edge1 - m);  // exp(-inf) = 0 for threads without a token
-    for (int i = tid + NT; i < hs.n_sink; i += NT) acc_f32 += __expf(row[i] - m);
-    for (int i = tid + NT; i < hs.n_win; i += NT) acc_f32 += __expf(row[hs.mid_hi + i] - m);
     for (int i = tid; i < hs.n_sink; i += NT) {
       if (writer) idx[A.seg_sink + i] = i;
       if (kFused) to_glist((uint32_t)i, (uint32_t)i, i == tid ? edge0 : row[i]);
@@ -701,111 +783,53 @@ __global__ __launch_bounds__(NT, FD > 0 ? 1 : 4) void head_kernel(HeadArgs A) {
       if (kFused) to_glist((uint32_t)(hs.n_sink + i), (uint32_t)(hs.mid_hi + i), i == tid ? edge1 : row[hs.mid_hi + i]);
       else place_sc[A.seg_win + i] = i == tid ? edge1 : row[hs.mid_hi + i];
     }
-  } else {
-    // phase 2: rebuild the top-k bitmap from the list written in phase 1
-    for (int t = tid; t < hs.k; t += NT) {
-      const int i = O::list_tok(idx, A.seg_topk + t, n);
-      O::mark_bit(bm_f, (uint32_t)i);
-      acc_f += (double)__expf(row[i] - m);
-    }
-    for (int i = tid; i < hs.n_sink; i += NT) acc_f += (double)__expf(row[i] - m);
-    for (int i = tid; i < hs.n_win; i += NT) acc_f += (double)__expf(row[hs.mid_hi + i] - m);
-  }
-  if (!kFused && pair_made && tid >= NT / 2) {  // (whole waves: the upper half holds the final sample's proposals)
-#pragma unroll
-    for (int e = 0; e < 4; ++e) spec1.sc[e] = row[spec1.tok[e]];
-  }
-  VATT_STAMP(A.dbg, 30);
-  __syncthreads();
-  VATT_STAMP(A.dbg, 31);
-
-  // Fused gather, first part: the V rows (and scores) of this workgroup's share of I_f are requested now and
-  // added after the samplers have run.  LPR adjacent lanes read one row; NG rows per round, UF rounds in flight.
-  constexpr int LPR = kFused ? FD / 8 : 16;
-  constexpr int NG = NT / LPR;
-  constexpr int UF = 8;
-  const int g_sub = tid % LPR, g_grp = tid / LPR;
-  const int kvh = kFused ? div_group(h, A.group) : 0;
-  float gacc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-  float gdsum = 0.f;
-  uint4 fv[UF];
-  float fs[UF];
-  int my_nf = 0;
-  // contiguous cache: this lane's 8 columns of row 0 of the head's V slice
-  const uint16_t* v_head = (kFused && !PAGED)
-                               ? A.v + (int64_t)seq * A.L.seq_stride + (int64_t)kvh * A.L.head_stride + g_sub * 8
-                               : nullptr;
-  // UF rows of a list at once, without branches: all list entries (and their scores) are read from LDS first,
-  // then all rows are requested.  The lists are padded to whole calls, so the LDS reads need no bound; a slot
-  // beyond the list reads row 0 and gets the score -inf (weight exp(-inf - m) = 0).  (Written with a per-slot
-  // condition, every slot became a branch of its own with an LDS wait inside: sixteen serial LDS round trips.)
-  // HaveSc: the scores of the listed tokens are in LDS (list_sc), else they are read from the score row.
-  auto load_rows = [&](const uint32_t* list, const float* list_sc, int j0, int count, float (&sc)[UF], uint4 (&vv)[UF],
-                       auto have_sc) {
-    constexpr bool HaveSc = decltype(have_sc)::value;
-    uint32_t t[UF];
-    const int jb = j0 + g_grp;
-#pragma unroll
-    for (int u = 0; u < UF; ++u) {
-      t[u] = list[jb + u * NG];
-      sc[u] = HaveSc ? list_sc[jb + u * NG] : 0.f;
-    }
-    int blk[UF];
-    bool valid[UF];
-#pragma unroll
-    for (int u = 0; u < UF; ++u) {
-      valid[u] = jb + u * NG < count;
-      t[u] = valid[u] ? min(t[u], (uint32_t)(n - 1)) : 0u;
-      blk[u] = kv_block<PAGED>(A.L, seq, (int)t[u]);  // (paged cache: all block-table entries before any row)
-    }
-#pragma unroll
-    for (int u = 0; u < UF; ++u) {
-      if constexpr (!HaveSc) sc[u] = row[t[u]];
-      if constexpr (PAGED) vv[u] = load_stream_16(A.v + kv_row_offset_in<true>(A.L, seq, kvh, (int)t[u], blk[u]) + g_sub * 8);
-      else vv[u] = load_stream_16(v_head + t[u] * (uint32_t)(kFused ? FD : 1));  // (n_max * d < 2^32)
-    }
-#pragma unroll
-    for (int u = 0; u < UF; ++u) sc[u] = valid[u] ? sc[u] : -INFINITY;
   };
-  using ScInLds = std::true_type;
-  using ScInRow = std::false_type;
-  if constexpr (kFused) my_nf = (int)(g_hi - g_lo);
-
-  VATT_STAMP(A.dbg, 32);
-  if (want1 && !spec1_made) O::make_batch(spec1, S1, hs, 0u, ahead_blocks<NT>(A.small_batches, hs, final_draws(hs)), false, false, sm, tid);
-
-  // ---- I_bs (Algorithm 2, base sample) and the sums over it ----
-  int flags = topk_flag;
-  double acc_w = 0.0, acc_w2 = 0.0;
-  // Fused gather, usual case (both first batches at hand, base sample neither the whole residual nor taken as a
-  // complement): the draws of both streams are tested against the top-k set and counted in draw order by ONE
-  // workgroup scan (the lower half of the workgroup holds the base sample's stream, the upper half the final
-  // sample's; the two counts travel in the halves of one word).  The base sample is complete if its first
-  // batch holds b0 accepted draws.  And since the budget is never below b0, the first b0 accepted draws of the
-  // other stream belong to the final sample whatever the budget turns out to be (unless it asks for so much
-  // that the sample is taken as a complement): their V rows are requested now, with those of I_f, and
-  // are in when the budget is known.
   bool fast_base = false, spec_dyn = false;
   uint32_t acc_bits = 0, acc_pos = 0, tot1 = 0;
-  const int half = tid >= NT / 2 ? 1 : 0;
   float dacc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};  // final-sample rows, before the factor n_s / b
   float ddsum = 0.f;
   uint4 dv[UF];
   float ds[UF];
   int my_spec = 0;
-  // Without the fused gather the same shortcut saves the second scan and the samplers' own passes; the sorted
-  // and the nested forms of the lists are made by the general path only.
-  if (kTwoStreams && A.phase == 0 && (kFused || (!A.ascending && !A.nested))) {
+  {
     const uint32_t ns = (uint32_t)hs.n_s, c0 = (uint32_t)hs.b0;
-    if (pair_made && hs.n_s > 0 && c0 < ns && 2u * c0 <= ns) {
+    const bool usual = kTwoStreams && A.phase == 0 && (kFused || (!A.ascending && !A.nested)) && pair_made && hs.n_s > 0 &&
+                       c0 < ns && 2u * c0 <= ns;
+    const bool listed = A.phase != 2 && hs.k > 0;
+    auto test_draws = [&]() {
       const DrawBatch& B = half ? spec1 : spec0;
       acc_bits = B.first & ~O::test_bits4(bm_f, B.tok);
-      uint32_t total;
-      const uint32_t excl = block_exclusive_scan<NT>((uint32_t)__popc(acc_bits) << (half ? 16 : 0), &total, sm.scan);
-      const uint32_t tot0 = total & 0xffffu;
+      return (uint32_t)__popc(acc_bits) << (half ? 16 : 0);
+    };
+    uint32_t taken = 0, total = 0;
+    if constexpr (kFused) {
+      const int wpt = (words + NT - 1) / NT, w0 = tid * wpt;
+      uint32_t bits = 0;
+      if (listed)
+        for (int w = w0; w < min(w0 + wpt, words); ++w) bits += __popc(bm_f[w]);
+      if (usual) taken = test_draws();
+      block_exclusive_scan_two_once<NT>(bits, taken, &total, sm.scan_once[2], sm.scan_once[3]);
+      if (listed) {
+        for (int w = w0; w < min(w0 + wpt, words); ++w) {
+          wpre[w] = bits;
+          bits += __popc(bm_f[w]);
+        }
+      }
+    } else {
+      // (the lists leave, and the final sample's scores are asked for, as early as they can: with every CU full this
+      // kernel is bound by its scattered reads, and the gather kernel behind it takes 3 us longer when they come late)
+      if (listed) O::word_prefix(bm_f, words, wpre, sm, &sm.scan_once[2]);
+      write_lists();
+      if (pair_made && half) {  // (whole waves: the upper half holds the final sample's proposals)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) spec0.sc[e] = spec1.sc[e] = row[spec1.tok[e]];
+      }
+      if (usual) taken = block_exclusive_scan_once<NT>(test_draws(), &total, sm.scan_once[3]);
+    }
+    if (usual) {
       tot1 = total >> 16;
-      acc_pos = half ? excl >> 16 : excl & 0xffffu;
-      fast_base = tot0 >= c0;
+      acc_pos = half ? taken >> 16 : taken & 0xffffu;
+      fast_base = (total & 0xffffu) >= c0;
       spec_dyn = fast_base && tot1 >= c0;
     }
     if (fast_base) {
@@ -825,18 +849,35 @@ __global__ __launch_bounds__(NT, FD > 0 ? 1 : 4) void head_kernel(HeadArgs A) {
         }
         pos += a ? 1u : 0u;
       }
-      if constexpr (kFused) {
-        __syncthreads();
-        VATT_STAMP(A.dbg, 5);
-        load_rows(glist, glist_sc, 0, my_nf, fs, fv, ScInLds{});
-        if (spec_dyn) {
-          my_spec = hs.b0 > (int)split ? (int)(((uint32_t)hs.b0 - split + smask) >> shift) : 0;
-          my_spec = min(my_spec, A.dlist_cap);
-          load_rows(dlist, dlist_sc, 0, my_spec, ds, dv, ScInLds{});
-        }
-      }
     }
   }
+  if (A.phase != 2) {
+    // weights of the sink and window tokens (their scores were requested at the start)
+    acc_f32 += __expf(edge0 - m) + __expf(edge1 - m);  // exp(-inf) = 0 for threads without a token
+    for (int i = tid + NT; i < hs.n_sink; i += NT) acc_f32 += __expf(row[i] - m);
+    for (int i = tid + NT; i < hs.n_win; i += NT) acc_f32 += __expf(row[hs.mid_hi + i] - m);
+  }
+  if (tid == NT - kWave && marked) {
+    uint64_t tot = 0;
+#pragma unroll
+    for (int w = 0; w < SW; ++w) tot += ts.wq[w];
+    acc_f += (double)tot * (1.0 / 1099511627776.0);
+  }
+  acc_f += (double)acc_f32;
+  double sums[3] = {acc_f, acc_w, acc_w2};
+  if (fast_base) O::block_sum_post(sums, sm);
+  __syncthreads();
+  VATT_STAMP(A.dbg, 5);
+  if constexpr (kFused) {
+    if (spec_dyn) {
+      my_spec = hs.b0 > (int)split ? (int)(((uint32_t)hs.b0 - split + smask) >> shift) : 0;
+      my_spec = min(my_spec, A.dlist_cap);
+      load_rows(dlist, dlist_sc, 0, my_spec, ds, dv, ScInLds{});
+    }
+  }
+  if constexpr (kFused) write_lists();
+  if (kFused || !fast_base) __syncthreads();  // (the general sampler takes the word prefixes' place)
+  if constexpr (kFused) load_rows(glist, glist_sc, 0, my_nf, fs, fv, ScInLds{});
   if (hs.n_s > 0 && !fast_base) {
     if (A.phase != 2) {
       Emit E0 = emit_to(idx + A.seg_base, (uint32_t)A.b0_max);
@@ -854,7 +895,6 @@ __global__ __launch_bounds__(NT, FD > 0 ? 1 : 4) void head_kernel(HeadArgs A) {
       }
     }
   }
-  acc_f += (double)acc_f32;
   if (A.phase == 1) {
     if (tid == 0) {
       HeadRec r;
@@ -899,8 +939,14 @@ __global__ __launch_bounds__(NT, FD > 0 ? 1 : 4) void head_kernel(HeadArgs A) {
     for (int e = 0; e < 4; ++e) spec1.sc[e] = row[min(spec1.tok[e], (uint32_t)(n - 1))];
     spec1.have_sc = true;
   }
-  double sums[3] = {acc_f, acc_w, acc_w2};
-  O::block_sum(sums, sm);
+  if (!fast_base) {
+    sums[1] = acc_w;
+    sums[2] = acc_w2;
+    __syncthreads();
+    O::block_sum_post(sums, sm);
+    __syncthreads();
+  }
+  O::block_sum_get(sums, sm);
   VATT_STAMP(A.dbg, 6);
   const double D_f = sums[0];
   double sigma2 = 0.0, b_star = 0.0, tr_sigma = 0.0, nhat_sq = 0.0;
@@ -964,9 +1010,6 @@ __global__ __launch_bounds__(NT, FD > 0 ? 1 : 4) void head_kernel(HeadArgs A) {
   // ---- I_dyn (Algorithm 1, final sample) ----
   bool fast_dyn = false;
   {
-    if constexpr (kFused) {
-      if (!fast_base) load_rows(glist, glist_sc, 0, my_nf, fs, fv, ScInLds{});
-    }
     // the first batch of draws holds the whole final sample, and it is not taken as a complement: its members
     // are the accepted draws counted above, up to the budget
     fast_dyn = spec_dyn && (uint32_t)bfin <= tot1 && 2u * (uint32_t)bfin <= (uint32_t)hs.n_s;
@@ -1041,31 +1084,37 @@ __global__ __launch_bounds__(NT, FD > 0 ? 1 : 4) void head_kernel(HeadArgs A) {
   // Fused gather, second part: add the rows of I_f that were requested above, then the rest of I_f (only long
   // lists have one), then this workgroup's share of the final sample with the weight factor n_s / b.
   if constexpr (kFused) {
-    auto add_rows = [&](float (&acc)[8], float& dsum, const float (&sc)[UF], const uint4 (&vv)[UF]) {
+    auto add_part = [&](float (&acc)[8], float& dsum, const float (&sc)[UF], const uint4 (&vv)[UF], auto from, auto to) {
 #pragma unroll
-      for (int u = 0; u < UF; ++u) {
+      for (int u = decltype(from)::value; u < decltype(to)::value; ++u) {
         const float wt = __expf(sc[u] - m);
         add_weighted_row(acc, wt, vv[u]);
         dsum += g_sub == 0 ? wt : 0.f;
       }
     };
-    add_rows(gacc, gdsum, fs, fv);
+    // (the rounds that load_rows requested for the same j0 and count)
+    auto add_rows = [&](float (&acc)[8], float& dsum, const float (&sc)[UF], const uint4 (&vv)[UF], int j0, int count) {
+      add_part(acc, dsum, sc, vv, Int<0>{}, Int<2>{});
+      if (count > j0 + 2 * NG) add_part(acc, dsum, sc, vv, Int<2>{}, Int<4>{});
+      if (count > j0 + 4 * NG) add_part(acc, dsum, sc, vv, Int<4>{}, Int<UF>{});
+    };
+    add_rows(gacc, gdsum, fs, fv, 0, my_nf);
     for (int j0 = UF * NG; j0 < my_nf; j0 += UF * NG) {
       load_rows(glist, glist_sc, j0, my_nf, fs, fv, ScInLds{});
-      add_rows(gacc, gdsum, fs, fv);
+      add_rows(gacc, gdsum, fs, fv, j0, my_nf);
     }
     int my_nd = bfin > (int)split ? (int)(((uint32_t)bfin - split + smask) >> shift) : 0;
     my_nd = min(my_nd, A.dlist_cap);
     int j_done = 0;  // entries of this workgroup's share of the final sample that are already requested
     if (fast_dyn) {
-      add_rows(dacc, ddsum, ds, dv);  // (slots beyond the list carry weight 0)
+      add_rows(dacc, ddsum, ds, dv, 0, my_spec);  // (slots beyond the list carry weight 0)
       j_done = min(UF * NG, my_spec);
       // rows requested ahead cover the first b0 tokens; what the budget adds comes after them in the list
     }
     for (int j0 = j_done; j0 < my_nd; j0 += UF * NG) {
       if (fast_dyn) load_rows(dlist, dlist_sc, j0, my_nd, ds, dv, ScInLds{});
       else load_rows(dlist, dlist_sc, j0, my_nd, ds, dv, ScInRow{});
-      add_rows(dacc, ddsum, ds, dv);
+      add_rows(dacc, ddsum, ds, dv, j0, my_nd);
     }
     const float tail_scale = bfin > 0 ? (float)((double)hs.n_s / (double)bfin) : 0.f;
 #pragma unroll
@@ -1073,17 +1122,14 @@ __global__ __launch_bounds__(NT, FD > 0 ? 1 : 4) void head_kernel(HeadArgs A) {
     gdsum += tail_scale * ddsum;
     VATT_STAMP(A.dbg, 10);
     // lane groups of a wave hold different rows: add them, then the waves through LDS
-#pragma unroll
-    for (int o = LPR; o < kWave; o <<= 1) {
-#pragma unroll
-      for (int c = 0; c < 8; ++c) gacc[c] += __shfl_xor(gacc[c], o);
-    }
-    gdsum = wave_sum_f32(gdsum);
     const int lane = tid & 63, wave = tid >> 6;
+    add_lane_groups<LPR>(gacc);
+    gdsum = wave_sum_f32(gdsum);
     float* g_d = g_red + SW * FD;
-    if (lane < LPR) {
-#pragma unroll
-      for (int c = 0; c < 8; ++c) g_red[wave * FD + lane * 8 + c] = gacc[c];
+    if (LPR == 16 || (lane & 8) == 0) {
+      const int col = lane_groups_column<LPR>(lane);
+      g_red[wave * FD + col] = gacc[0];
+      g_red[wave * FD + col + 1] = gacc[1];
     }
     if (lane == 0) g_d[wave] = gdsum;
     __syncthreads();

@@ -90,3 +90,34 @@ def test_an_inf_in_the_last_listed_row_stays_an_inf(d, n, fused):
     o = sess.results_host()["O"][0]
     assert np.all(o[:, 7] == np.inf) and np.isfinite(np.delete(o, 7, axis=1)).all()
     sess.close()
+
+
+@pytest.mark.parametrize("splits", [1, 2])
+@pytest.mark.parametrize("paged", [False, True])
+@pytest.mark.parametrize("d", [64, 128])
+def test_fused_gather_around_its_rounds(d, paged, splits):
+    """Lists that end at, before and behind a quarter, half and all of the rows that the fused gather requests at a time (64,
+    128 and 256 rows of 128 columns, twice as many of 64)."""
+    import torch
+    from paper_2510_05688_amd import binding as vb
+    from paper_2510_05688_amd.session import DecodeSession
+    lens = [m * splits + e for m in (64, 128, 256, 512) for e in (-1, 0, 1)] + [1, 640 * splits]
+    n_max = 640 * splits
+    p = default_params(d, sink=16, window=48, topk_abs=n_max, topk_frac=0.0, base_abs=8, base_frac=0.0)
+    wl = workloads.make_workload("rounds", batch=len(lens), n_q_heads=4, n_kv_heads=2, head_dim=d, n_max=n_max,
+                                 seq_lens=lens, seed=4, params=p, plant_frac=0.01)
+    k_bits, v_bits, table = workloads.to_paged(wl, 16) if paged else (wl.k_bits, wl.v_bits, None)
+    sess = DecodeSession(plan_params(wl, paged=paged, num_blocks=k_bits.shape[0] if paged else 0))
+    vb.vatt_plan_set_option(sess.plan, vb.VATT_OPT_FUSED_GATHER, splits)
+    sess.upload(wl.q_bits, k_bits, v_bits, wl.seq_lens, wl.seeds, table)
+    sess.decode()
+    res = sess.results_host()
+    q = torch.from_numpy(workloads.bf16_bits_to_f32(wl.q_bits)).reshape(len(lens), 4, d).double()
+    for b, n in enumerate(lens):
+        for h in range(4):
+            s = torch.from_numpy(wl.k_f32(b, h // 2, n)).double() @ q[b, h] / np.sqrt(d)
+            want = torch.softmax(s, 0) @ torch.from_numpy(wl.v_f32(b, h // 2, n)).double()
+            got = torch.from_numpy(res["O"][b, h]).double()
+            assert float((got - want).norm() / want.norm()) < 2e-5, (n, h)
+            assert abs(float(torch.logsumexp(s, 0)) - float(res["lse"][b, h])) < 2e-5, (n, h)
+    sess.close()
