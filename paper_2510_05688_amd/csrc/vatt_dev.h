@@ -128,6 +128,14 @@ __device__ __forceinline__ uint4 load_stream_16(const uint16_t* p) {
   return make_uint4(t.x, t.y, t.z, t.w);
 }
 
+// The two kinds of row loads, for kernels that pick one per workgroup (rows_are_shared).
+struct LoadOnce {
+  __device__ __forceinline__ uint4 operator()(const uint16_t* p) const { return load_stream_16(p); }
+};
+struct LoadShared {
+  __device__ __forceinline__ uint4 operator()(const uint16_t* p) const { return *reinterpret_cast<const uint4*>(p); }
+};
+
 // ---------------------------------------------------------------------------
 // bf16 pairs packed in a 32-bit word -> two fp32 values (exact).
 // ---------------------------------------------------------------------------

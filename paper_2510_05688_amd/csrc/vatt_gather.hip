@@ -65,6 +65,7 @@ __global__ __launch_bounds__(kGatherThreads) void gather_kernel(GatherArgs A) {
   const int total = r.n_sink + r.n_win + r.k + r.b;
   const int splits = STATS ? A.splits : used_splits(A.splits, total, RPB * U);
   if (split >= splits) return;
+  const bool shared_rows = rows_are_shared(total, A.q_len * A.group, r.n);
   const int per = (total + splits - 1) / splits;
   const int p_lo = split * per, p_hi = min(p_lo + per, total);
   const uint32_t seg_sink = (uint32_t)A.seg_sink, seg_win = (uint32_t)A.seg_win, seg_topk = (uint32_t)A.seg_topk;
@@ -139,11 +140,15 @@ __global__ __launch_bounds__(kGatherThreads) void gather_kernel(GatherArgs A) {
     }
 #pragma unroll
     for (int u = 0; u < U; ++u) blk[u] = kv_block<PAGED>(A.L, seq, tok[u]);
+    auto rows = [&](auto load) {
 #pragma unroll
-    for (int u = 0; u < U; ++u) {
-      if constexpr (PAGED) vv[u] = load_stream_16(A.v + kv_row_offset_in<true>(A.L, seq, kvh, tok[u], blk[u]) + sub * 8);
-      else vv[u] = load_stream_16(v_head + ((uint32_t)tok[u] * (uint32_t)D + (uint32_t)(sub * 8)));  // (n_max * d < 2^32)
-    }
+      for (int u = 0; u < U; ++u) {
+        if constexpr (PAGED) vv[u] = load(A.v + kv_row_offset_in<true>(A.L, seq, kvh, tok[u], blk[u]) + sub * 8);
+        else vv[u] = load(v_head + ((uint32_t)tok[u] * (uint32_t)D + (uint32_t)(sub * 8)));  // (n_max * d < 2^32)
+      }
+    };
+    if (shared_rows) rows(LoadShared{});
+    else rows(LoadOnce{});
     // (all U rows are requested before the first is used: left to itself the scheduler waits for the first rows
     // in order to reuse their registers for the later ones)
     __builtin_amdgcn_sched_barrier(0);
@@ -169,27 +174,18 @@ __global__ __launch_bounds__(kGatherThreads) void gather_kernel(GatherArgs A) {
   }
 
   // rows of one wave sit in lane groups rsub = 0 .. RPW-1: add them, then add the waves through LDS
-#pragma unroll
-  for (int o = LPR; o < kWave; o <<= 1) {
-#pragma unroll
-    for (int c = 0; c < 8; ++c) {
-      acc[c] += __shfl_xor(acc[c], o);
-      if (STATS) acc2[c] += __shfl_xor(acc2[c], o);
-    }
-  }
-#pragma unroll
-  for (int o = 32; o >= 1; o >>= 1) {
-    dsum += __shfl_xor(dsum, o);
-    if (STATS) r2 += __shfl_xor(r2, o);
-  }
+  add_lane_groups<LPR>(acc);
+  if constexpr (STATS) add_lane_groups<LPR>(acc2);
+  dsum = wave_sum_f32(dsum);
+  if constexpr (STATS) r2 = wave_sum_f32(r2);
   __shared__ float s_acc[WAVES][D];
   __shared__ float s_acc2[STATS ? WAVES : 1][STATS ? D : 1];
   __shared__ float s_d[WAVES], s_r2[WAVES];
-  if (rsub == 0) {
+  if (LPR == 16 || (lane & 8) == 0) {
 #pragma unroll
-    for (int c = 0; c < 8; ++c) {
-      s_acc[wave][sub * 8 + c] = acc[c];
-      if (STATS) s_acc2[wave][sub * 8 + c] = acc2[c];
+    for (int c = 0; c < 2; ++c) {
+      s_acc[wave][lane_groups_column<LPR>(lane) + c] = acc[c];
+      if constexpr (STATS) s_acc2[wave][lane_groups_column<LPR>(lane) + c] = acc2[c];
     }
   }
   if (lane == 0) {

@@ -99,6 +99,7 @@ __global__ __launch_bounds__(kGatherThreads) void sparse_score_kernel(GivenArgs 
   const int total = r.n_sink + r.n_win + r.k + r.b;
   const int splits = used_splits(A.splits, total, RPB * U);
   if (split >= splits) return;
+  const bool shared_rows = rows_are_shared(total, A.q_len * A.group, r.n);
   const int per = (total + splits - 1) / splits;
   const int p_lo = split * per, p_hi = min(p_lo + per, total);
   const int32_t* idx = A.idx + (int64_t)bh * A.idx_cap;
@@ -135,15 +136,19 @@ __global__ __launch_bounds__(kGatherThreads) void sparse_score_kernel(GivenArgs 
     for (int u = 0; u < U; ++u) row[u] = __shfl(row_mine, u * RPW + rsub);
 #pragma unroll
     for (int u = 0; u < U; ++u) blk[u] = kv_block<PAGED>(A.Lk, seq, row[u] < 0 ? 0 : row[u]);
+    auto rows = [&](auto load) {
 #pragma unroll
-    for (int u = 0; u < U; ++u) {
-      const int i = row[u] & 0x7fffffff;
-      const uint16_t* at = PAGED ? A.k + kv_row_offset_in<true>(A.Lk, seq, kvh, i, blk[u]) : k_head + (uint32_t)i * (uint32_t)D;
-      // (rows of the cache without the non-temporal hint: the group's heads share them; 115.7 -> 110.7 us for a whole step of
-      // 16 x 32K tokens)
-      if (row[u] < 0) kv[u] = *reinterpret_cast<const uint4*>(cache_k + ((uint32_t)i * (uint32_t)D + (uint32_t)(sub * 8)));
-      else kv[u] = load_stream_16(at + sub * 8);
-    }
+      for (int u = 0; u < U; ++u) {
+        const int i = row[u] & 0x7fffffff;
+        const uint16_t* at = PAGED ? A.k + kv_row_offset_in<true>(A.Lk, seq, kvh, i, blk[u]) : k_head + (uint32_t)i * (uint32_t)D;
+        // (rows of the cache without the non-temporal hint: the group's heads share them; 115.7 -> 110.7 us for a whole step of
+        // 16 x 32K tokens)
+        if (row[u] < 0) kv[u] = *reinterpret_cast<const uint4*>(cache_k + ((uint32_t)i * (uint32_t)D + (uint32_t)(sub * 8)));
+        else kv[u] = load(at + sub * 8);
+      }
+    };
+    if (shared_rows) rows(LoadShared{});
+    else rows(LoadOnce{});
     __builtin_amdgcn_sched_barrier(0);
     float s = 0.f;  // lane u of a group keeps the score of the group's row u
 #pragma unroll
@@ -337,6 +342,7 @@ __global__ __launch_bounds__(kGatherThreads) void given_gather_kernel(GivenArgs 
   const int total = r.n_sink + r.n_win + r.k + r.b;
   const int splits = used_splits(A.splits, total, RPB * U);
   if (split >= splits) return;
+  const bool shared_rows = rows_are_shared(total, A.q_len * A.group, r.n);
   const int per = (total + splits - 1) / splits;
   const int p_lo = split * per, p_hi = min(p_lo + per, total);
   const int32_t* idx = A.idx + (int64_t)bh * A.idx_cap;
@@ -378,19 +384,23 @@ __global__ __launch_bounds__(kGatherThreads) void given_gather_kernel(GivenArgs 
     for (int u = 0; u < U; ++u) tok[u] = __shfl(drawn ? tok_mine | (int)0x80000000 : tok_mine, u * RPW + rsub);
 #pragma unroll
     for (int u = 0; u < U; ++u) blk[u] = kv_block<PAGED>(A.Lv, seq, tok[u] & 0x7fffffff);  // (K and V share the block table)
+    auto rows = [&](auto load) {
 #pragma unroll
-    for (int u = 0; u < U; ++u) {
-      const int i = tok[u] & 0x7fffffff;
-      const int64_t o = PAGED ? kv_row_offset_in<true>(A.Lk, seq, kvh, i, blk[u]) : 0;
-      kv[u] = make_uint4(0u, 0u, 0u, 0u);
-      if (tok[u] < 0) kv[u] = load_stream_16(PAGED ? A.k + o + sub * 8 : k_head + ((uint32_t)i * (uint32_t)D + (uint32_t)(sub * 8)));
-    }
+      for (int u = 0; u < U; ++u) {
+        const int i = tok[u] & 0x7fffffff;
+        const int64_t o = PAGED ? kv_row_offset_in<true>(A.Lk, seq, kvh, i, blk[u]) : 0;
+        kv[u] = make_uint4(0u, 0u, 0u, 0u);
+        if (tok[u] < 0) kv[u] = load(PAGED ? A.k + o + sub * 8 : k_head + ((uint32_t)i * (uint32_t)D + (uint32_t)(sub * 8)));
+      }
 #pragma unroll
-    for (int u = 0; u < U; ++u) {
-      const int i = tok[u] & 0x7fffffff;
-      const int64_t o = PAGED ? kv_row_offset_in<true>(A.Lv, seq, kvh, i, blk[u]) : 0;
-      vv[u] = load_stream_16(PAGED ? A.v + o + sub * 8 : v_head + ((uint32_t)i * (uint32_t)D + (uint32_t)(sub * 8)));
-    }
+      for (int u = 0; u < U; ++u) {
+        const int i = tok[u] & 0x7fffffff;
+        const int64_t o = PAGED ? kv_row_offset_in<true>(A.Lv, seq, kvh, i, blk[u]) : 0;
+        vv[u] = load(PAGED ? A.v + o + sub * 8 : v_head + ((uint32_t)i * (uint32_t)D + (uint32_t)(sub * 8)));
+      }
+    };
+    if (shared_rows) rows(LoadShared{});
+    else rows(LoadOnce{});
     __builtin_amdgcn_sched_barrier(0);
     if (__any(drawn)) {
       float s = 0.f;
@@ -429,17 +439,13 @@ __global__ __launch_bounds__(kGatherThreads) void given_gather_kernel(GivenArgs 
   }
 
   // the lane groups of a wave, then the waves, each with its maximum
-#pragma unroll
-  for (int o = LPR; o < kWave; o <<= 1) {
-#pragma unroll
-    for (int c = 0; c < 8; ++c) acc[c] += __shfl_xor(acc[c], o);
-  }
+  add_lane_groups<LPR>(acc);
   dsum = wave_sum_f32(dsum);
   __shared__ __align__(16) float s_acc[WAVES][D];
   __shared__ float s_d[WAVES], s_m[WAVES];
-  if (rsub == 0) {
+  if (LPR == 16 || (lane & 8) == 0) {
 #pragma unroll
-    for (int c = 0; c < 8; ++c) s_acc[wave][sub * 8 + c] = acc[c];
+    for (int c = 0; c < 2; ++c) s_acc[wave][lane_groups_column<LPR>(lane) + c] = acc[c];
   }
   if (lane == 0) {
     s_d[wave] = dsum;

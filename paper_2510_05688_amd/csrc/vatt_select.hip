@@ -865,7 +865,8 @@ __global__ __launch_bounds__(NT, FD > 0 ? 1 : 4) void head_kernel(HeadArgs A) {
   }
   acc_f += (double)acc_f32;
   double sums[3] = {acc_f, acc_w, acc_w2};
-  if (fast_base) O::block_sum_post(sums, sm);
+  const bool posted = fast_base || hs.n_s == 0;  // the sums are complete
+  if (posted) O::block_sum_post(sums, sm);
   __syncthreads();
   VATT_STAMP(A.dbg, 5);
   if constexpr (kFused) {
@@ -875,9 +876,11 @@ __global__ __launch_bounds__(NT, FD > 0 ? 1 : 4) void head_kernel(HeadArgs A) {
       load_rows(dlist, dlist_sc, 0, my_spec, ds, dv, ScInLds{});
     }
   }
-  if constexpr (kFused) write_lists();
-  if (kFused || !fast_base) __syncthreads();  // (the general sampler takes the word prefixes' place)
-  if constexpr (kFused) load_rows(glist, glist_sc, 0, my_nf, fs, fv, ScInLds{});
+  if constexpr (kFused) {
+    write_lists();
+    __syncthreads();
+    load_rows(glist, glist_sc, 0, my_nf, fs, fv, ScInLds{});
+  }
   if (hs.n_s > 0 && !fast_base) {
     if (A.phase != 2) {
       Emit E0 = emit_to(idx + A.seg_base, (uint32_t)A.b0_max);
@@ -939,10 +942,9 @@ __global__ __launch_bounds__(NT, FD > 0 ? 1 : 4) void head_kernel(HeadArgs A) {
     for (int e = 0; e < 4; ++e) spec1.sc[e] = row[min(spec1.tok[e], (uint32_t)(n - 1))];
     spec1.have_sc = true;
   }
-  if (!fast_base) {
+  if (!posted) {
     sums[1] = acc_w;
     sums[2] = acc_w2;
-    __syncthreads();
     O::block_sum_post(sums, sm);
     __syncthreads();
   }
