@@ -125,9 +125,19 @@ __global__ __launch_bounds__(NT, FD > 0 ? 1 : 4) void head_kernel(HeadArgs A) {
     g_lo = min(split * run, n_f);
     g_hi = min(g_lo + run, n_f);
   }
-  auto to_glist = [&](uint32_t p, uint32_t tok, float sc) {
+  // What the lists in LDS know a row by: its token, or on a paged cache its place in the pool (pages in front of its own times
+  // the page, plus the place in it; a pool that fits the memory has fewer than 2^32).  The block-table entries are asked for
+  // where the tokens become known, long before the lists are written, so that the rows do not wait for them: 8 x 0.5K - 7K
+  // tokens 36.9 -> 35.0 us per call.
+  constexpr bool kCode = kFused && PAGED;
+  auto code_of = [&](uint32_t tok, int blk) {
+    if constexpr (!kCode) return tok;
+    else return ((uint32_t)min(max(blk, 0), A.L.num_blocks - 1) << A.L.page_shift) + (tok & ((1u << A.L.page_shift) - 1u));
+  };
+  auto row_code = [&](uint32_t tok) { return code_of(tok, kv_block<kCode>(A.L, seq, (int)tok)); };
+  auto to_glist = [&](uint32_t p, uint32_t code, float sc) {
     if (kFused && p >= g_lo && p < g_hi) {
-      glist[p - g_lo] = tok;
+      glist[p - g_lo] = code;
       glist_sc[p - g_lo] = sc;
     }
   };
@@ -149,6 +159,9 @@ __global__ __launch_bounds__(NT, FD > 0 ? 1 : 4) void head_kernel(HeadArgs A) {
   rv.n = n;
   const float edge0 = (A.phase != 2 && tid < hs.n_sink) ? row[tid] : -INFINITY;
   const float edge1 = (A.phase != 2 && tid < hs.n_win) ? row[hs.mid_hi + tid] : -INFINITY;
+  const int edge0_blk = kv_block<kCode>(A.L, seq, min(tid, n - 1));
+  const int edge1_blk = kv_block<kCode>(A.L, seq, min(hs.mid_hi + tid, n - 1));
+  const uint32_t row0_code = row_code(0u);
   // cleared: the bitmaps bm_f .. scratch1, which follow each other, and the first histogram
   for (int w = tid; w < (kTwoStreams ? 5 : 4) * (words_max / 4); w += NT)
     reinterpret_cast<uint4*>(bm_f)[w] = make_uint4(0u, 0u, 0u, 0u);
@@ -216,6 +229,7 @@ __global__ __launch_bounds__(NT, FD > 0 ? 1 : 4) void head_kernel(HeadArgs A) {
     }
   };
   bool spec1_made = false, pair_made = false;
+  int spec_blk[4] = {0, 0, 0, 0};  // block-table entries of the first batch's proposals
   const int half = tid >= NT / 2 ? 1 : 0;
   if (kTwoStreams && want0 && want1 && 2 * ahead_blocks<NT>(A.small_batches) <= NT) {
     // both streams at once: the lower half of the workgroup generates the first batch of the base sample,
@@ -245,6 +259,8 @@ __global__ __launch_bounds__(NT, FD > 0 ? 1 : 4) void head_kernel(HeadArgs A) {
       // their first microseconds, held every workgroup up for five microseconds at config 3)
       O::make_batch(mine, half ? S1 : S0, hs, 0u, blocks, false, kFused || !half, sm, tid - half * (NT / 2));
     }
+#pragma unroll
+    for (int e = 0; e < 4; ++e) spec_blk[e] = kv_block<kCode>(A.L, seq, (int)mine.tok[e]);
     // (a thread holds draws of one stream; of the other it has the same tokens, none of which counts)
     spec0 = spec1 = mine;
     spec0.ok = half ? 0u : mine.ok;
@@ -302,6 +318,8 @@ __global__ __launch_bounds__(NT, FD > 0 ? 1 : 4) void head_kernel(HeadArgs A) {
   double acc_f = 0.0;
   bool marked = false;  // the members' weights are in ts.wq, as integers
   uint32_t n_cand_used = 0;  // fast path: members are the candidates marked in bm_f
+  constexpr int CPT = kCandCap / NT;  // candidates a thread looks after
+  int cand_blk[CPT] = {};
   // (see "more candidates than the list holds")
   uint32_t n_wide_used = 0;
   constexpr uint32_t kWideCap = kCandCap * 12 / sizeof(uint16_t);
@@ -447,6 +465,13 @@ __global__ __launch_bounds__(NT, FD > 0 ? 1 : 4) void head_kernel(HeadArgs A) {
           VATT_STAMP(A.dbg, 24);
           VATT_NOTE(A.dbg, 26, n_cand);
           if (n_cand <= (uint32_t)kCandCap && n_cand >= (uint32_t)hs.k) {
+            if constexpr (kCode) {
+#pragma unroll
+              for (int j = 0; j < CPT; ++j) {
+                const uint32_t t = (uint32_t)(j * NT + tid);
+                if (t < n_cand) cand_blk[j] = kv_block<kCode>(A.L, seq, (int)min((uint32_t)cand[t], (uint32_t)(n - 1)));
+              }
+            }
             // The members, marked in the bitmap.  (The list order depends on scheduling: the members' weights are
             // summed as 40-bit fixed-point integers, whose sum does not depend on the order; every weight is at most 1.)
             uint64_t fixed_sum = 0;
@@ -665,11 +690,15 @@ __global__ __launch_bounds__(NT, FD > 0 ? 1 : 4) void head_kernel(HeadArgs A) {
   const uint16_t* v_head = (kFused && !PAGED)
                                ? A.v + (int64_t)seq * A.L.seq_stride + (int64_t)kvh * A.L.head_stride + g_sub * 8
                                : nullptr;
+  // paged cache: the same of the first block; and no code lies beyond the pool
+  const uint16_t* v_pool = kCode ? A.v + (int64_t)kvh * A.L.head_stride + g_sub * 8 : nullptr;
+  const uint32_t last_code = kCode ? (uint32_t)min(((uint64_t)A.L.num_blocks << A.L.page_shift) - 1u, (uint64_t)kInv32) : 0u;
   // UF rows of a list at once, without branches: all list entries (and their scores) are read from LDS first,
   // then all rows are requested.  The lists are padded to whole calls, so the LDS reads need no bound; a slot
   // beyond the list reads row 0 and gets the score -inf (weight exp(-inf - m) = 0).  (Written with a per-slot
   // condition, every slot became a branch of its own with an LDS wait inside: sixteen serial LDS round trips.)
-  // HaveSc: the scores of the listed tokens are in LDS (list_sc), else they are read from the score row.
+  // HaveSc: the scores of the listed tokens are in LDS (list_sc), and the list holds codes (code_of); else it holds tokens, and
+  // their scores are read from the score row.
   // Rounds beyond the list's end request no rows, in steps of two and four (a round costs the workgroup 128 clocks of
   // address processing and as many of arithmetic, and most lists fill three to five of the eight: 1 x 32K tokens 36.3 -> 35.6 us,
   // one head of 1K 20.1 -> 18.8 us per call).
@@ -688,15 +717,24 @@ __global__ __launch_bounds__(NT, FD > 0 ? 1 : 4) void head_kernel(HeadArgs A) {
 #pragma unroll
     for (int u = 0; u < UF; ++u) {
       valid[u] = jb + u * NG < count;
-      t[u] = valid[u] ? min(t[u], (uint32_t)(n - 1)) : 0u;
-      blk[u] = kv_block<PAGED>(A.L, seq, (int)t[u]);  // (paged cache: all block-table entries before any row)
+      if constexpr (HaveSc && kCode) {
+        t[u] = valid[u] ? min(t[u], last_code) : row0_code;
+      } else {
+        t[u] = valid[u] ? min(t[u], (uint32_t)(n - 1)) : 0u;
+        blk[u] = kv_block<kCode>(A.L, seq, (int)t[u]);  // (all block-table entries before any row)
+      }
     }
     auto rows = [&](auto from, auto to) {
 #pragma unroll
       for (int u = decltype(from)::value; u < decltype(to)::value; ++u) {
         if constexpr (!HaveSc) sc[u] = row[t[u]];
-        if constexpr (PAGED) vv[u] = load_stream_16(A.v + kv_row_offset_in<true>(A.L, seq, kvh, (int)t[u], blk[u]) + g_sub * 8);
-        else vv[u] = load_stream_16(v_head + t[u] * (uint32_t)(kFused ? FD : 1));  // (n_max * d < 2^32)
+        if constexpr (kCode) {
+          const uint32_t code = HaveSc ? t[u] : code_of(t[u], blk[u]);
+          const uint32_t in_page = code & ((1u << A.L.page_shift) - 1u);
+          vv[u] = load_stream_16(v_pool + (int64_t)(code >> A.L.page_shift) * A.L.block_stride + in_page * (uint32_t)(kFused ? FD : 1));
+        } else {
+          vv[u] = load_stream_16(v_head + t[u] * (uint32_t)(kFused ? FD : 1));  // (n_max * d < 2^32)
+        }
       }
     };
     rows(Int<0>{}, Int<2>{});
@@ -745,7 +783,7 @@ __global__ __launch_bounds__(NT, FD > 0 ? 1 : 4) void head_kernel(HeadArgs A) {
       } else if (marked) {
         // every member sits in the candidate list: its place in the ascending list is the number of members
         // below it, from the word prefix and the bits below its own (no thread walks a crowded word)
-        for (uint32_t t = tid; t < n_cand_used; t += NT) {
+        auto place_member = [&](uint32_t t, int blk) {
           const uint64_t c = cand[t];
           const uint32_t i = min((uint32_t)c, (uint32_t)(n - 1));
           const uint32_t word = bm_f[i >> 5], bit = 1u << (i & 31);
@@ -753,8 +791,15 @@ __global__ __launch_bounds__(NT, FD > 0 ? 1 : 4) void head_kernel(HeadArgs A) {
             const uint32_t pos = wpre[i >> 5] + (uint32_t)__popc(word & (bit - 1u));
             if (writer && pos < (uint32_t)A.k_max) idx[A.seg_topk + pos] = (int32_t)i;
             if (!kFused && pos < (uint32_t)A.k_max) place_sc[A.seg_topk + pos] = float_from_order_key(~(uint32_t)(c >> 32));
-            to_glist((uint32_t)(hs.n_sink + hs.n_win) + pos, i, float_from_order_key(~(uint32_t)(c >> 32)));
+            to_glist((uint32_t)(hs.n_sink + hs.n_win) + pos, code_of(i, blk), float_from_order_key(~(uint32_t)(c >> 32)));
           }
+        };
+        if constexpr (kCode) {
+#pragma unroll
+          for (int j = 0; j < CPT; ++j)
+            if ((uint32_t)(j * NT + tid) < n_cand_used) place_member((uint32_t)(j * NT + tid), cand_blk[j]);
+        } else {
+          for (uint32_t t = tid; t < n_cand_used; t += NT) place_member(t, 0);
         }
       } else {
         const int wpt = (words + NT - 1) / NT;
@@ -766,7 +811,7 @@ __global__ __launch_bounds__(NT, FD > 0 ? 1 : 4) void head_kernel(HeadArgs A) {
             const int i = (w << 5) + (__ffs(bits) - 1);
             bits &= bits - 1u;
             if (writer && pos < (uint32_t)A.k_max) idx[A.seg_topk + pos] = i;
-            if (kFused) to_glist((uint32_t)(hs.n_sink + hs.n_win) + pos, (uint32_t)i, row[i]);
+            if (kFused) to_glist((uint32_t)(hs.n_sink + hs.n_win) + pos, row_code((uint32_t)i), row[i]);
             else if (pos < (uint32_t)A.k_max) place_sc[A.seg_topk + pos] = row[i];
             ++pos;
           }
@@ -775,12 +820,15 @@ __global__ __launch_bounds__(NT, FD > 0 ? 1 : 4) void head_kernel(HeadArgs A) {
     }
     for (int i = tid; i < hs.n_sink; i += NT) {
       if (writer) idx[A.seg_sink + i] = i;
-      if (kFused) to_glist((uint32_t)i, (uint32_t)i, i == tid ? edge0 : row[i]);
+      if (kFused) to_glist((uint32_t)i, i == tid ? code_of((uint32_t)i, edge0_blk) : row_code((uint32_t)i), i == tid ? edge0 : row[i]);
       else place_sc[A.seg_sink + i] = i == tid ? edge0 : row[i];
     }
     for (int i = tid; i < hs.n_win; i += NT) {
       if (writer) idx[A.seg_win + i] = hs.mid_hi + i;
-      if (kFused) to_glist((uint32_t)(hs.n_sink + i), (uint32_t)(hs.mid_hi + i), i == tid ? edge1 : row[hs.mid_hi + i]);
+      if (kFused) {
+        const uint32_t tok = (uint32_t)(hs.mid_hi + i);
+        to_glist((uint32_t)(hs.n_sink + i), i == tid ? code_of(tok, edge1_blk) : row_code(tok), i == tid ? edge1 : row[tok]);
+      }
       else place_sc[A.seg_win + i] = i == tid ? edge1 : row[hs.mid_hi + i];
     }
   };
@@ -844,7 +892,7 @@ __global__ __launch_bounds__(NT, FD > 0 ? 1 : 4) void head_kernel(HeadArgs A) {
           acc_w += w;
           acc_w2 += w * w;
         } else if (kFused && spec_dyn && take && (pos & smask) == split && (pos >> shift) < (uint32_t)A.dlist_cap) {
-          dlist[pos >> shift] = spec1.tok[e];
+          dlist[pos >> shift] = code_of(spec1.tok[e], spec_blk[e]);
           dlist_sc[pos >> shift] = spec1.sc[e];
         }
         pos += a ? 1u : 0u;
@@ -1024,7 +1072,7 @@ __global__ __launch_bounds__(NT, FD > 0 ? 1 : 4) void head_kernel(HeadArgs A) {
           if (writer && pos < (uint32_t)A.b_max) idx[A.seg_dyn + pos] = (int32_t)spec1.tok[e];
           if (!kFused && pos < (uint32_t)A.b_max) place_sc[A.seg_dyn + pos] = spec1.sc[e];
           if (kFused && pos >= (uint32_t)hs.b0 && (pos & smask) == split && (pos >> shift) < (uint32_t)A.dlist_cap) {
-            dlist[pos >> shift] = spec1.tok[e];
+            dlist[pos >> shift] = code_of(spec1.tok[e], spec_blk[e]);
             dlist_sc[pos >> shift] = spec1.sc[e];
           }
         }
