@@ -65,7 +65,7 @@ __global__ __launch_bounds__(kGatherThreads) void gather_kernel(GatherArgs A) {
   const int total = r.n_sink + r.n_win + r.k + r.b;
   const int splits = STATS ? A.splits : used_splits(A.splits, total, RPB * U);
   if (split >= splits) return;
-  const bool shared_rows = rows_are_shared(total, A.q_len * A.group, r.n);
+  const bool shared_rows = rows_are_shared(total, A.group_major ? A.q_len * A.group : A.q_len, r.n);
   const int per = (total + splits - 1) / splits;
   const int p_lo = split * per, p_hi = min(p_lo + per, total);
   const uint32_t seg_sink = (uint32_t)A.seg_sink, seg_win = (uint32_t)A.seg_win, seg_topk = (uint32_t)A.seg_topk;
@@ -105,73 +105,74 @@ __global__ __launch_bounds__(kGatherThreads) void gather_kernel(GatherArgs A) {
     listed_next = idx[place0];
     sc_next = placed[place0];
   }
-  for (int p0 = p_lo; p0 < p_hi; p0 += RPB * U) {
-    const int p = p0 + u_mine * RPB + wave * RPW + g_mine;
-    const bool valid = lane < ROWS_W && p < p_hi;
-    const int pc = min(p, p_hi - 1);
-    const int t2 = pc - n_sw, t3 = t2 - r.k;
-    const bool is_tail = t3 >= 0;
-    const int listed = listed_next;
-    float sc = sc_next;
-    {
-      const uint32_t place_n = place_of(p0 + RPB * U);  // (beyond the range: the range's last place once more)
-      listed_next = idx[place_n];
-      sc_next = placed[place_n];
-    }
-    const int by_rule = pc < r.n_sink ? pc : pc + win_shift;
-    const int tok_mine = min(max(t2 >= 0 ? listed : by_rule, 0), r.n - 1);
-    if (tail_by_token) {  // a sample whose scores were not at hand when its list was written
-      const float by_token = row[tok_mine];
-      sc = is_tail ? by_token : sc;
-    }
-    const float wt_mine = valid ? __expf(sc - r.m) * (is_tail ? tail_scale : 1.0f) : 0.f;
-    if (!(STATS && is_tail)) dsum += wt_mine;
+  // (the loop twice, one for each kind of load: with the choice inside it took 15 registers and a wave per SIMD more)
+  auto walk = [&](auto load) {
+    for (int p0 = p_lo; p0 < p_hi; p0 += RPB * U) {
+      const int p = p0 + u_mine * RPB + wave * RPW + g_mine;
+      const bool valid = lane < ROWS_W && p < p_hi;
+      const int pc = min(p, p_hi - 1);
+      const int t2 = pc - n_sw, t3 = t2 - r.k;
+      const bool is_tail = t3 >= 0;
+      const int listed = listed_next;
+      float sc = sc_next;
+      {
+        const uint32_t place_n = place_of(p0 + RPB * U);  // (beyond the range: the range's last place once more)
+        listed_next = idx[place_n];
+        sc_next = placed[place_n];
+      }
+      const int by_rule = pc < r.n_sink ? pc : pc + win_shift;
+      const int tok_mine = min(max(t2 >= 0 ? listed : by_rule, 0), r.n - 1);
+      if (tail_by_token) {  // a sample whose scores were not at hand when its list was written
+        const float by_token = row[tok_mine];
+        sc = is_tail ? by_token : sc;
+      }
+      const float wt_mine = valid ? __expf(sc - r.m) * (is_tail ? tail_scale : 1.0f) : 0.f;
+      if (!(STATS && is_tail)) dsum += wt_mine;
 
-    int tok[U], blk[U];
-    float wt[U];
-    bool tail[U];
-    uint4 vv[U];
+      int tok[U], blk[U];
+      float wt[U];
+      bool tail[U];
+      uint4 vv[U];
 #pragma unroll
-    for (int u = 0; u < U; ++u) {
-      const int src = u * RPW + rsub;
-      tok[u] = __shfl(tok_mine, src);
-      wt[u] = __shfl(wt_mine, src);
-      tail[u] = STATS ? (__shfl((int)is_tail, src) != 0) : false;
-    }
+      for (int u = 0; u < U; ++u) {
+        const int src = u * RPW + rsub;
+        tok[u] = __shfl(tok_mine, src);
+        wt[u] = __shfl(wt_mine, src);
+        tail[u] = STATS ? (__shfl((int)is_tail, src) != 0) : false;
+      }
 #pragma unroll
-    for (int u = 0; u < U; ++u) blk[u] = kv_block<PAGED>(A.L, seq, tok[u]);
-    auto rows = [&](auto load) {
+      for (int u = 0; u < U; ++u) blk[u] = kv_block<PAGED>(A.L, seq, tok[u]);
 #pragma unroll
       for (int u = 0; u < U; ++u) {
         if constexpr (PAGED) vv[u] = load(A.v + kv_row_offset_in<true>(A.L, seq, kvh, tok[u], blk[u]) + sub * 8);
         else vv[u] = load(v_head + ((uint32_t)tok[u] * (uint32_t)D + (uint32_t)(sub * 8)));  // (n_max * d < 2^32)
       }
-    };
-    if (shared_rows) rows(LoadShared{});
-    else rows(LoadOnce{});
-    // (all U rows are requested before the first is used: left to itself the scheduler waits for the first rows
-    // in order to reuse their registers for the later ones)
-    __builtin_amdgcn_sched_barrier(0);
+      // (all U rows are requested before the first is used: left to itself the scheduler waits for the first rows
+      // in order to reuse their registers for the later ones)
+      __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-    for (int u = 0; u < U; ++u) {
-      const uint32_t ww[4] = {vv[u].x, vv[u].y, vv[u].z, vv[u].w};
-      if (STATS && tail[u]) {
+      for (int u = 0; u < U; ++u) {
+        const uint32_t ww[4] = {vv[u].x, vv[u].y, vv[u].z, vv[u].w};
+        if (STATS && tail[u]) {
 #pragma unroll
-        for (int c = 0; c < 4; ++c) {
-          const float a = wt[u] * bf16_lo(ww[c]), bb = wt[u] * bf16_hi(ww[c]);
-          acc2[2 * c] += a;
-          acc2[2 * c + 1] += bb;
-          r2 += a * a + bb * bb;
-        }
-      } else {
+          for (int c = 0; c < 4; ++c) {
+            const float a = wt[u] * bf16_lo(ww[c]), bb = wt[u] * bf16_hi(ww[c]);
+            acc2[2 * c] += a;
+            acc2[2 * c + 1] += bb;
+            r2 += a * a + bb * bb;
+          }
+        } else {
 #pragma unroll
-        for (int c = 0; c < 4; ++c) {
-          acc[2 * c] += wt[u] * bf16_lo(ww[c]);
-          acc[2 * c + 1] += wt[u] * bf16_hi(ww[c]);
+          for (int c = 0; c < 4; ++c) {
+            acc[2 * c] += wt[u] * bf16_lo(ww[c]);
+            acc[2 * c + 1] += wt[u] * bf16_hi(ww[c]);
+          }
         }
       }
     }
-  }
+  };
+  if (shared_rows) walk(LoadShared{});
+  else walk(LoadOnce{});
 
   // rows of one wave sit in lane groups rsub = 0 .. RPW-1: add them, then add the waves through LDS
   add_lane_groups<LPR>(acc);

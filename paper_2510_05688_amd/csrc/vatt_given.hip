@@ -81,7 +81,7 @@ __device__ __forceinline__ float row_score(const uint4& kv, const uint32_t (&qw)
 // belongs to a row (list place, token, slot of the random cache) is done by the row's own lane, as in gather_kernel, and
 // the list entry of the next step is requested one step ahead; row and score change lanes by wave shuffles.
 template <int D, bool PAGED>
-__global__ __launch_bounds__(kGatherThreads) void sparse_score_kernel(GivenArgs A) {
+__global__ __launch_bounds__(kGatherThreads, 8) void sparse_score_kernel(GivenArgs A) {
   constexpr int LPR = D / 8;
   constexpr int RPW = kWave / LPR;
   constexpr int WAVES = kGatherThreads / kWave;
@@ -99,7 +99,7 @@ __global__ __launch_bounds__(kGatherThreads) void sparse_score_kernel(GivenArgs 
   const int total = r.n_sink + r.n_win + r.k + r.b;
   const int splits = used_splits(A.splits, total, RPB * U);
   if (split >= splits) return;
-  const bool shared_rows = rows_are_shared(total, A.q_len * A.group, r.n);
+  const bool shared_rows = rows_are_shared(total, A.group_major ? A.q_len * A.group : A.q_len, r.n);
   const int per = (total + splits - 1) / splits;
   const int p_lo = split * per, p_hi = min(p_lo + per, total);
   const int32_t* idx = A.idx + (int64_t)bh * A.idx_cap;
@@ -124,19 +124,20 @@ __global__ __launch_bounds__(kGatherThreads) void sparse_score_kernel(GivenArgs 
   uint32_t place_next = 0;
   int entry_next = 0;
   if (p_lo < p_hi) entry_next = entry_of(place_next = place_of(p_lo));
-  for (int p0 = p_lo; p0 < p_hi; p0 += RPB * U) {
-    const uint32_t place = place_next;
-    const int entry = entry_next;
-    entry_next = entry_of(place_next = place_of(p0 + RPB * U));  // (beyond the range: its last place once more)
-    const bool in_cache = cached && entry < 0;
-    const int row_mine = in_cache ? min(entry & 0x7fffffff, A.rc.slots - 1) | (int)0x80000000 : min(max(entry, 0), r.n - 1);
-    int row[U], blk[U];
-    uint4 kv[U];
+  // (the loop twice, one for each kind of load: with the choice inside it took 15 registers and a wave per SIMD more)
+  auto walk = [&](auto load) {
+    for (int p0 = p_lo; p0 < p_hi; p0 += RPB * U) {
+      const uint32_t place = place_next;
+      const int entry = entry_next;
+      entry_next = entry_of(place_next = place_of(p0 + RPB * U));  // (beyond the range: its last place once more)
+      const bool in_cache = cached && entry < 0;
+      const int row_mine = in_cache ? min(entry & 0x7fffffff, A.rc.slots - 1) | (int)0x80000000 : min(max(entry, 0), r.n - 1);
+      int row[U], blk[U];
+      uint4 kv[U];
 #pragma unroll
-    for (int u = 0; u < U; ++u) row[u] = __shfl(row_mine, u * RPW + rsub);
+      for (int u = 0; u < U; ++u) row[u] = __shfl(row_mine, u * RPW + rsub);
 #pragma unroll
-    for (int u = 0; u < U; ++u) blk[u] = kv_block<PAGED>(A.Lk, seq, row[u] < 0 ? 0 : row[u]);
-    auto rows = [&](auto load) {
+      for (int u = 0; u < U; ++u) blk[u] = kv_block<PAGED>(A.Lk, seq, row[u] < 0 ? 0 : row[u]);
 #pragma unroll
       for (int u = 0; u < U; ++u) {
         const int i = row[u] & 0x7fffffff;
@@ -146,20 +147,20 @@ __global__ __launch_bounds__(kGatherThreads) void sparse_score_kernel(GivenArgs 
         if (row[u] < 0) kv[u] = *reinterpret_cast<const uint4*>(cache_k + ((uint32_t)i * (uint32_t)D + (uint32_t)(sub * 8)));
         else kv[u] = load(at + sub * 8);
       }
-    };
-    if (shared_rows) rows(LoadShared{});
-    else rows(LoadOnce{});
-    __builtin_amdgcn_sched_barrier(0);
-    float s = 0.f;  // lane u of a group keeps the score of the group's row u
+      __builtin_amdgcn_sched_barrier(0);
+      float s = 0.f;  // lane u of a group keeps the score of the group's row u
 #pragma unroll
-    for (int u = 0; u < U; ++u) {
-      const float su = row_score<LPR>(kv[u], qw, A.sm_scale);
-      s = sub == u ? su : s;
+      for (int u = 0; u < U; ++u) {
+        const float su = row_score<LPR>(kv[u], qw, A.sm_scale);
+        s = sub == u ? su : s;
+      }
+      const int from = (sub % U) * RPW + rsub;  // the lane that prepared that row
+      const uint32_t to = (uint32_t)__shfl((int)place, from);
+      if (sub < U && p0 + sub * RPB + wave * RPW + rsub < p_hi) sp[to] = s;
     }
-    const int from = (sub % U) * RPW + rsub;  // the lane that prepared that row
-    const uint32_t to = (uint32_t)__shfl((int)place, from);
-    if (sub < U && p0 + sub * RPB + wave * RPW + rsub < p_hi) sp[to] = s;
-  }
+  };
+  if (shared_rows) walk(LoadShared{});
+  else walk(LoadOnce{});
 }
 
 // The same with the numerator statistics (targets N and SDPA): the V rows of the same tokens are read as well and the
@@ -342,7 +343,7 @@ __global__ __launch_bounds__(kGatherThreads) void given_gather_kernel(GivenArgs 
   const int total = r.n_sink + r.n_win + r.k + r.b;
   const int splits = used_splits(A.splits, total, RPB * U);
   if (split >= splits) return;
-  const bool shared_rows = rows_are_shared(total, A.q_len * A.group, r.n);
+  const bool shared_rows = rows_are_shared(total, A.group_major ? A.q_len * A.group : A.q_len, r.n);
   const int per = (total + splits - 1) / splits;
   const int p_lo = split * per, p_hi = min(p_lo + per, total);
   const int32_t* idx = A.idx + (int64_t)bh * A.idx_cap;
@@ -371,20 +372,21 @@ __global__ __launch_bounds__(kGatherThreads) void given_gather_kernel(GivenArgs 
 #pragma unroll
   for (int c = 0; c < 8; ++c) acc[c] = 0.f;
   float dsum = 0.f, m_run = -INFINITY;
-  for (int p0 = p_lo; p0 < p_hi; p0 += RPB * U) {
-    const int p = p0 + mine;
-    const bool valid = lane < ROWS_W && p < p_hi, tail = p >= n_fix, drawn = valid && p >= n_kept;
-    const int tok_mine = min(max(entry_next, 0), r.n - 1);
-    float sc = sc_next;
-    request(p0 + RPB * U);
-    int tok[U], blk[U];
-    uint4 kv[U], vv[U];
-    // (a row with its K row: the top bit of its token)
+  // (the loop twice, one for each kind of load: with the choice inside it took 15 registers and a wave per SIMD more)
+  auto walk = [&](auto load) {
+    for (int p0 = p_lo; p0 < p_hi; p0 += RPB * U) {
+      const int p = p0 + mine;
+      const bool valid = lane < ROWS_W && p < p_hi, tail = p >= n_fix, drawn = valid && p >= n_kept;
+      const int tok_mine = min(max(entry_next, 0), r.n - 1);
+      float sc = sc_next;
+      request(p0 + RPB * U);
+      int tok[U], blk[U];
+      uint4 kv[U], vv[U];
+      // (a row with its K row: the top bit of its token)
 #pragma unroll
-    for (int u = 0; u < U; ++u) tok[u] = __shfl(drawn ? tok_mine | (int)0x80000000 : tok_mine, u * RPW + rsub);
+      for (int u = 0; u < U; ++u) tok[u] = __shfl(drawn ? tok_mine | (int)0x80000000 : tok_mine, u * RPW + rsub);
 #pragma unroll
-    for (int u = 0; u < U; ++u) blk[u] = kv_block<PAGED>(A.Lv, seq, tok[u] & 0x7fffffff);  // (K and V share the block table)
-    auto rows = [&](auto load) {
+      for (int u = 0; u < U; ++u) blk[u] = kv_block<PAGED>(A.Lv, seq, tok[u] & 0x7fffffff);  // (K and V share the block table)
 #pragma unroll
       for (int u = 0; u < U; ++u) {
         const int i = tok[u] & 0x7fffffff;
@@ -398,45 +400,45 @@ __global__ __launch_bounds__(kGatherThreads) void given_gather_kernel(GivenArgs 
         const int64_t o = PAGED ? kv_row_offset_in<true>(A.Lv, seq, kvh, i, blk[u]) : 0;
         vv[u] = load(PAGED ? A.v + o + sub * 8 : v_head + ((uint32_t)i * (uint32_t)D + (uint32_t)(sub * 8)));
       }
-    };
-    if (shared_rows) rows(LoadShared{});
-    else rows(LoadOnce{});
-    __builtin_amdgcn_sched_barrier(0);
-    if (__any(drawn)) {
-      float s = 0.f;
+      __builtin_amdgcn_sched_barrier(0);
+      if (__any(drawn)) {
+        float s = 0.f;
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+          const float su = row_score<LPR>(kv[u], qw, A.sm_scale);
+          s = sub == u ? su : s;
+        }
+        const float computed = __shfl(s, (lane % RPW) * LPR + (lane / RPW) % U);
+        sc = drawn ? computed : sc;
+      }
+      const float e = valid ? sc + (tail ? tail_bias : 0.f) : -INFINITY;
+      const float m_new = fmaxf(m_run, wave_max(e));
+      const float f = m_run > -INFINITY ? __expf(m_run - m_new) : 0.f;
+      const float wt_mine = e == -INFINITY ? 0.f : __expf(e - m_new);  // (NaN for a NaN score: the row is not left out)
+      m_run = m_new;
+      dsum = dsum * f + wt_mine;
+#pragma unroll
+      for (int c = 0; c < 8; ++c) acc[c] *= f;
+      if (p0 + RPB * U > p_hi) {
+        // (a row beyond the range repeats the last one, with weight 0; an Inf in it would make a NaN)
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+          if (p0 + u * RPB + wave * RPW + rsub >= p_hi) vv[u] = make_uint4(0u, 0u, 0u, 0u);
+      }
 #pragma unroll
       for (int u = 0; u < U; ++u) {
-        const float su = row_score<LPR>(kv[u], qw, A.sm_scale);
-        s = sub == u ? su : s;
-      }
-      const float computed = __shfl(s, (lane % RPW) * LPR + (lane / RPW) % U);
-      sc = drawn ? computed : sc;
-    }
-    const float e = valid ? sc + (tail ? tail_bias : 0.f) : -INFINITY;
-    const float m_new = fmaxf(m_run, wave_max(e));
-    const float f = m_run > -INFINITY ? __expf(m_run - m_new) : 0.f;
-    const float wt_mine = e == -INFINITY ? 0.f : __expf(e - m_new);  // (NaN for a NaN score: the row is not left out)
-    m_run = m_new;
-    dsum = dsum * f + wt_mine;
+        const float wt = __shfl(wt_mine, u * RPW + rsub);
+        const uint32_t ww[4] = {vv[u].x, vv[u].y, vv[u].z, vv[u].w};
 #pragma unroll
-    for (int c = 0; c < 8; ++c) acc[c] *= f;
-    if (p0 + RPB * U > p_hi) {
-      // (a row beyond the range repeats the last one, with weight 0; an Inf in it would make a NaN)
-#pragma unroll
-      for (int u = 0; u < U; ++u)
-        if (p0 + u * RPB + wave * RPW + rsub >= p_hi) vv[u] = make_uint4(0u, 0u, 0u, 0u);
-    }
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-      const float wt = __shfl(wt_mine, u * RPW + rsub);
-      const uint32_t ww[4] = {vv[u].x, vv[u].y, vv[u].z, vv[u].w};
-#pragma unroll
-      for (int c = 0; c < 4; ++c) {
-        acc[2 * c] += wt * bf16_lo(ww[c]);
-        acc[2 * c + 1] += wt * bf16_hi(ww[c]);
+        for (int c = 0; c < 4; ++c) {
+          acc[2 * c] += wt * bf16_lo(ww[c]);
+          acc[2 * c + 1] += wt * bf16_hi(ww[c]);
+        }
       }
     }
-  }
+  };
+  if (shared_rows) walk(LoadShared{});
+  else walk(LoadOnce{});
 
   // the lane groups of a wave, then the waves, each with its maximum
   add_lane_groups<LPR>(acc);

@@ -43,11 +43,13 @@ __device__ __forceinline__ int used_splits(int splits, int total, int step_rows)
 }
 
 // Whether the rows of a list are read with ordinary loads instead of non-temporal ones: `vectors` query vectors share a KV head
-// and run on one XCD, and where their lists, each about as long as this one, together are as long as half the sequence, a row that
-// one has fetched is found in the L2 by others.  Measured (gather kernel, us, non-temporal -> ordinary, and the listed rows of
-// all vectors over the length): 1 x 32K tokens with 16 query tokens 41.5 -> 31.2 (3.6), 8 22.3 -> 20.0 (1.8), 4 13.4 -> 11.6 (0.9);
-// 1 x 128K with 4 37.1 -> 36.1 (0.9), 8 x 32K with lists of 0.2 78.4 -> 75.7 (0.8); but 8 x 32K with lists of 0.06 to 0.12 31.8 ->
-// 32.7 (0.25 - 0.5), 16 x 32K 41.0 -> 44.7 (0.2), 4 x 128K 29.4 -> 32.8 (0.2).
+// and run on one XCD (all of a group in the order of head_of_block, else one per query token), and where their lists, each
+// about as long as this one, together are as long as half the sequence, a row that one has fetched is found in the L2 by others.
+// Measured (gather kernel, us, non-temporal -> ordinary, and the listed rows of all vectors over the length): 1 x 32K tokens with
+// 16 query tokens 41.5 -> 31.2 (3.6), 8 22.3 -> 20.0 (1.8), 4 13.4 -> 11.6 (0.9); 1 x 128K with 4 37.1 -> 36.1 (0.9), 8 x 32K with
+// lists of 0.2 of it 78.4 -> 75.7 (0.8); but 8 x 32K with lists of 0.06 to 0.12 31.8 -> 32.7 (0.25 - 0.5), 16 x 32K 41.0 -> 44.7
+// (0.2), 4 x 128K 29.4 -> 32.8 (0.2), and 1 x 91K with 4 KV heads, their 8 vectors on as many XCDs, and 3 query tokens 44.8 -> 48.0
+// (0.3 on each).
 __device__ __forceinline__ bool rows_are_shared(int total, int vectors, int n) { return 2ll * total * vectors > (long long)n; }
 
 constexpr int kDenseKeys = 32;  // keys a wave of the matrix-core dense kernel takes at a time
