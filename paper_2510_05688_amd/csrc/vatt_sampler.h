@@ -350,10 +350,11 @@ struct HeadOps {
   // unless `spec` carries the first batch (have_spec; made from block 0 with make_batch), `scratch` all zero.
   // Writes the token list to dst (acceptance order, or ascending when the sample is a complement) and, when
   // sum_w is given, adds exp(s_i - m) and its square over the sample to this thread's partial sums.
+  // have, blk: the first `have` tokens, from the Philox blocks before blk, are listed already (no complement).
   // Returns flag bits: 1 complement regime, 2 more than one batch, 4 draw cap reached.
   static __device__ __forceinline__ int draw_sample(const Sampler& S, const HeadSizes& hs, uint32_t c, const DrawBatch& spec, bool have_spec,
                                     int small_batches, const Emit& E, double* sum_w,
-                                    double* sum_w2, HeadSmem& sm) {
+                                    double* sum_w2, HeadSmem& sm, uint32_t have = 0u, uint32_t blk = 0u) {
     const int tid = threadIdx.x;
     const int words = (hs.n + 31) >> 5;
     const uint32_t ns = (uint32_t)hs.n_s;
@@ -368,8 +369,7 @@ struct HeadOps {
       for (int w = tid; w < words; w += NT) S.taken[w] = 0;
       __syncthreads();
     }
-    uint32_t have = 0, blk = 0;
-    int batches = 0;
+    int batches = blk > 0u ? 1 : 0;
     bool use_spec = have_spec;
     double aw = 0.0, aw2 = 0.0;
     while (have < target) {

@@ -702,11 +702,14 @@ __global__ __launch_bounds__(NT, FD > 0 ? 1 : 4) void head_kernel(HeadArgs A) {
   // Rounds beyond the list's end request no rows, in steps of two and four (a round costs the workgroup 128 clocks of
   // address processing and as many of arithmetic, and most lists fill three to five of the eight: 1 x 32K tokens 36.3 -> 35.6 us,
   // one head of 1K 20.1 -> 18.8 us per call).
-  auto load_rows = [&](const uint32_t* list, const float* list_sc, int j0, int count, float (&sc)[UF], uint4 (&vv)[UF],
+  // Places [first, count) of a list, as far as a batch reaches, which begins with first's round: place j is always read by lane
+  // group j % NG, and a group adds its rows in rising order, so that the sums do not depend on how a list was cut.
+  auto round_of = [](int first) { return first & ~(NG - 1); };
+  auto load_rows = [&](const uint32_t* list, const float* list_sc, int first, int count, float (&sc)[UF], uint4 (&vv)[UF],
                        auto have_sc) {
     constexpr bool HaveSc = decltype(have_sc)::value;
     uint32_t t[UF];
-    const int jb = j0 + g_grp;
+    const int j0 = round_of(first), jb = j0 + g_grp;
 #pragma unroll
     for (int u = 0; u < UF; ++u) {
       t[u] = list[jb + u * NG];
@@ -716,7 +719,7 @@ __global__ __launch_bounds__(NT, FD > 0 ? 1 : 4) void head_kernel(HeadArgs A) {
     bool valid[UF];
 #pragma unroll
     for (int u = 0; u < UF; ++u) {
-      valid[u] = jb + u * NG < count;
+      valid[u] = jb + u * NG >= first && jb + u * NG < count;
       if constexpr (HaveSc && kCode) {
         t[u] = valid[u] ? min(t[u], last_code) : row0_code;
       } else {
@@ -743,6 +746,8 @@ __global__ __launch_bounds__(NT, FD > 0 ? 1 : 4) void head_kernel(HeadArgs A) {
 #pragma unroll
     for (int u = 0; u < UF; ++u) sc[u] = valid[u] ? sc[u] : -INFINITY;
   };
+  // entries of this workgroup's share of the first c places of the final sample
+  auto share_of = [&](uint32_t c) { return c > split ? (int)((c - split + smask) >> shift) : 0; };
   using ScInLds = std::true_type;
   using ScInRow = std::false_type;
   if constexpr (kFused) my_nf = (int)(g_hi - g_lo);
@@ -839,6 +844,11 @@ __global__ __launch_bounds__(NT, FD > 0 ? 1 : 4) void head_kernel(HeadArgs A) {
   uint4 dv[UF];
   float ds[UF];
   int my_spec = 0;
+  // A further batch of rows under way: the second of I_f, or what the first draws add to a final sample beyond the base sample's
+  // size (2 x 20K tokens with budgets up to 2276: 45.6 -> 44.3 us per call; 8 x 0.5K - 7K, whose lists have two batches, 35.1 ->
+  // 34.4).  It takes 40 registers more, which 512 threads have.
+  uint4 ev[UF];
+  float es[UF];
   {
     const uint32_t ns = (uint32_t)hs.n_s, c0 = (uint32_t)hs.b0;
     const bool usual = kTwoStreams && A.phase == 0 && (kFused || (!A.ascending && !A.nested)) && pair_made && hs.n_s > 0 &&
@@ -919,8 +929,7 @@ __global__ __launch_bounds__(NT, FD > 0 ? 1 : 4) void head_kernel(HeadArgs A) {
   VATT_STAMP(A.dbg, 5);
   if constexpr (kFused) {
     if (spec_dyn) {
-      my_spec = hs.b0 > (int)split ? (int)(((uint32_t)hs.b0 - split + smask) >> shift) : 0;
-      my_spec = min(my_spec, A.dlist_cap);
+      my_spec = min(share_of((uint32_t)hs.b0), A.dlist_cap);
       load_rows(dlist, dlist_sc, 0, my_spec, ds, dv, ScInLds{});
     }
   }
@@ -928,6 +937,7 @@ __global__ __launch_bounds__(NT, FD > 0 ? 1 : 4) void head_kernel(HeadArgs A) {
     write_lists();
     __syncthreads();
     load_rows(glist, glist_sc, 0, my_nf, fs, fv, ScInLds{});
+    if (my_nf > UF * NG) load_rows(glist, glist_sc, UF * NG, my_nf, es, ev, ScInLds{});
   }
   if (hs.n_s > 0 && !fast_base) {
     if (A.phase != 2) {
@@ -1058,12 +1068,16 @@ __global__ __launch_bounds__(NT, FD > 0 ? 1 : 4) void head_kernel(HeadArgs A) {
 
   VATT_STAMP(A.dbg, 7);
   // ---- I_dyn (Algorithm 1, final sample) ----
-  bool fast_dyn = false;
+  bool fast_dyn = false, more_dyn = false;
+  int j_coded = 0, j_done = 0;  // fused gather: places of the share that hold codes and scores; that are requested
   {
     // the first batch of draws holds the whole final sample, and it is not taken as a complement: its members
     // are the accepted draws counted above, up to the budget
     fast_dyn = spec_dyn && (uint32_t)bfin <= tot1 && 2u * (uint32_t)bfin <= (uint32_t)hs.n_s;
-    if (fast_dyn) {
+    // the same draws begin a larger sample: fused gather, all of them are listed with their scores, and the first rows the list
+    // has beyond those of the base sample's size are requested before the further draws are made
+    more_dyn = kFused && spec_dyn && !fast_dyn && 2u * (uint32_t)bfin <= (uint32_t)hs.n_s;
+    if (fast_dyn || more_dyn) {
       uint32_t pos = acc_pos;
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
@@ -1078,7 +1092,14 @@ __global__ __launch_bounds__(NT, FD > 0 ? 1 : 4) void head_kernel(HeadArgs A) {
         }
         pos += a ? 1u : 0u;
       }
-      if (kFused) __syncthreads();
+      if constexpr (kFused) {
+        __syncthreads();
+        j_coded = min(share_of((uint32_t)min((uint32_t)bfin, tot1)), A.dlist_cap);
+        j_done = min(UF * NG, my_spec);
+        if (my_nf <= UF * NG && j_coded > j_done) {
+          load_rows(dlist, dlist_sc, j_done, j_coded, es, ev, ScInLds{});
+        }
+      }
     }
   }
   bool dyn_placed = fast_dyn;  // the final sample's scores are at its list places
@@ -1095,7 +1116,8 @@ __global__ __launch_bounds__(NT, FD > 0 ? 1 : 4) void head_kernel(HeadArgs A) {
     const int f = (!kFused && A.nested)
                       ? O::draw_nested(S1, hs, (uint32_t)hs.b0, (uint32_t)bfin, bm_f, idx + A.seg_base,
                                        idx + A.seg_dyn, (uint32_t)A.b_max, A.small_batches, sm)
-                      : O::draw_sample(S1, hs, (uint32_t)bfin, spec1, want1, A.small_batches, E1, nullptr, nullptr, sm);
+                      : O::draw_sample(S1, hs, (uint32_t)bfin, spec1, want1 && !more_dyn, A.small_batches, E1, nullptr, nullptr, sm,
+                                       more_dyn ? tot1 : 0u, more_dyn ? (uint32_t)spec1.blocks : 0u);
     flags |= ((f & 1) ? kFlagDynComplement : 0) | ((f & 2) ? kFlagDynBatches : 0) | ((f & 4) ? kFlagDrawCap : 0);
     // (one batch made ahead with its scores held the whole sample, and the list stays in acceptance order)
     dyn_placed = kEmitScores && !A.nested && !A.ascending && want1 && spec1.have_sc && f == 0;
@@ -1142,30 +1164,44 @@ __global__ __launch_bounds__(NT, FD > 0 ? 1 : 4) void head_kernel(HeadArgs A) {
         dsum += g_sub == 0 ? wt : 0.f;
       }
     };
-    // (the rounds that load_rows requested for the same j0 and count)
-    auto add_rows = [&](float (&acc)[8], float& dsum, const float (&sc)[UF], const uint4 (&vv)[UF], int j0, int count) {
+    // (the rounds that load_rows requested for the same places)
+    auto add_rows = [&](float (&acc)[8], float& dsum, const float (&sc)[UF], const uint4 (&vv)[UF], int first, int count) {
+      const int j0 = round_of(first);
       add_part(acc, dsum, sc, vv, Int<0>{}, Int<2>{});
       if (count > j0 + 2 * NG) add_part(acc, dsum, sc, vv, Int<2>{}, Int<4>{});
       if (count > j0 + 4 * NG) add_part(acc, dsum, sc, vv, Int<4>{}, Int<UF>{});
     };
-    add_rows(gacc, gdsum, fs, fv, 0, my_nf);
-    for (int j0 = UF * NG; j0 < my_nf; j0 += UF * NG) {
-      load_rows(glist, glist_sc, j0, my_nf, fs, fv, ScInLds{});
-      add_rows(gacc, gdsum, fs, fv, j0, my_nf);
+    // the rest of a list from place j0 on: a batch of rows is requested before the one in front of it is added
+    auto rest = [&](float (&acc)[8], float& dsum, const uint32_t* list, const float* list_sc, int j0, int count, auto have_sc) {
+      if (j0 >= count) return;
+      load_rows(list, list_sc, j0, count, fs, fv, have_sc);
+      for (;;) {
+        const int j1 = round_of(j0) + UF * NG, j2 = j1 + UF * NG;
+        if (j1 < count) load_rows(list, list_sc, j1, count, es, ev, have_sc);
+        add_rows(acc, dsum, fs, fv, j0, count);
+        if (j1 >= count) break;
+        if (j2 < count) load_rows(list, list_sc, j2, count, fs, fv, have_sc);
+        add_rows(acc, dsum, es, ev, j1, count);
+        if (j2 >= count) break;
+        j0 = j2;
+      }
+    };
+    if (my_nf > 0) add_rows(gacc, gdsum, fs, fv, 0, my_nf);
+    if (my_nf > UF * NG) {
+      add_rows(gacc, gdsum, es, ev, UF * NG, my_nf);
+      rest(gacc, gdsum, glist, glist_sc, 2 * UF * NG, my_nf, ScInLds{});
     }
-    int my_nd = bfin > (int)split ? (int)(((uint32_t)bfin - split + smask) >> shift) : 0;
-    my_nd = min(my_nd, A.dlist_cap);
-    int j_done = 0;  // entries of this workgroup's share of the final sample that are already requested
-    if (fast_dyn) {
-      add_rows(dacc, ddsum, ds, dv, 0, my_spec);  // (slots beyond the list carry weight 0)
-      j_done = min(UF * NG, my_spec);
-      // rows requested ahead cover the first b0 tokens; what the budget adds comes after them in the list
+    static_assert((NG & (NG - 1)) == 0, "round_of");
+    const int my_nd = min(share_of((uint32_t)bfin), A.dlist_cap);
+    if (fast_dyn || more_dyn) {
+      if (my_spec > 0) add_rows(dacc, ddsum, ds, dv, 0, my_spec);  // (slots beyond the list carry weight 0)
+      if (my_nf <= UF * NG && j_coded > j_done) {
+        add_rows(dacc, ddsum, es, ev, j_done, j_coded);
+        j_done = min(round_of(j_done) + UF * NG, j_coded);
+      }
+      rest(dacc, ddsum, dlist, dlist_sc, j_done, j_coded, ScInLds{});
     }
-    for (int j0 = j_done; j0 < my_nd; j0 += UF * NG) {
-      if (fast_dyn) load_rows(dlist, dlist_sc, j0, my_nd, ds, dv, ScInLds{});
-      else load_rows(dlist, dlist_sc, j0, my_nd, ds, dv, ScInRow{});
-      add_rows(dacc, ddsum, ds, dv, j0, my_nd);
-    }
+    rest(dacc, ddsum, dlist, dlist_sc, j_coded, my_nd, ScInRow{});
     const float tail_scale = bfin > 0 ? (float)((double)hs.n_s / (double)bfin) : 0.f;
 #pragma unroll
     for (int c = 0; c < 8; ++c) gacc[c] += tail_scale * dacc[c];

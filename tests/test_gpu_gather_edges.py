@@ -121,3 +121,34 @@ def test_fused_gather_around_its_rounds(d, paged, splits):
             assert float((got - want).norm() / want.norm()) < 2e-5, (n, h)
             assert abs(float(torch.logsumexp(s, 0)) - float(res["lse"][b, h])) < 2e-5, (n, h)
     sess.close()
+
+
+@pytest.mark.parametrize("splits", [1, 2, 4])
+@pytest.mark.parametrize("d,epsilon", [(64, 0.02), (64, 0.004), (128, 0.03), (128, 0.008)])
+def test_budgets_beyond_the_first_draws_are_paged_as_they_are_contiguous(d, epsilon, splits):
+    """Final samples that the first batch of draws holds, that need further ones and that are complements, on a paged cache
+    (whose lists name rows by their place in the pool) and on a contiguous one: the same bits."""
+    from paper_2510_05688_amd import binding as vb
+    from paper_2510_05688_amd.session import DecodeSession
+    p = default_params(d, sink=16, window=48, topk_abs=0, topk_frac=0.02, base_abs=32, base_frac=0.0, epsilon=epsilon)
+    wl = workloads.make_workload("budgets", batch=3, n_q_heads=4, n_kv_heads=2, head_dim=d, n_max=8192,
+                                 seq_lens=[8192, 5001, 700], seed=6, params=p, plant_frac=0.01)
+    got = []
+    for paged in (False, True):
+        k_bits, v_bits, table = workloads.to_paged(wl, 16) if paged else (wl.k_bits, wl.v_bits, None)
+        sess = DecodeSession(plan_params(wl, paged=paged, num_blocks=k_bits.shape[0] if paged else 0))
+        sess.upload(wl.q_bits, k_bits, v_bits, wl.seq_lens, wl.seeds, table)
+        for fused in (0, splits):
+            vb.vatt_plan_set_option(sess.plan, vb.VATT_OPT_FUSED_GATHER, fused)
+            sess.out_idx.zero_()
+            sess.decode()
+            got.append(sess.results_host())
+        sess.close()
+    assert (got[0]["counts"][..., 4] > 1024).any() or epsilon > 0.01
+    for key in ("counts", "idx", "b_star"):
+        assert all(np.array_equal(got[0][key], g[key]) for g in got[1:]), key
+    assert np.array_equal(got[1]["O"], got[3]["O"]) and np.array_equal(got[1]["lse"], got[3]["lse"])
+    for b in range(3):
+        for h in range(4):
+            want = got[0]["O"][b, h]
+            assert np.linalg.norm(got[1]["O"][b, h] - want) <= 2e-6 * np.linalg.norm(want)
