@@ -536,12 +536,14 @@ __device__ __forceinline__ int ahead_blocks(int small_batches) {
   // (a workgroup of 1024 threads serves long rows, whose samples hold thousands of tokens)
   return small_batches ? kSmallBatchBlocks : (NT >= 1024 ? 1024 : min(NT, 256));
 }
-template <int NT>
-__device__ __forceinline__ int ahead_blocks(int small_batches, const HeadSizes& hs, int most) {
-  const int all = ahead_blocks<NT>(small_batches);
+__device__ __forceinline__ int likely_blocks(int all, const HeadSizes& hs, int most) {
   const int L = max(hs.mid_hi - hs.mid_lo, 1);
   const float d = (float)most * (float)L / (float)max(hs.n_s - most, 1);
   return max(1, min(all, (int)((d + 6.f * sqrtf(d) + 19.f) * 0.25f)));
+}
+template <int NT>
+__device__ __forceinline__ int ahead_blocks(int small_batches, const HeadSizes& hs, int most) {
+  return likely_blocks(ahead_blocks<NT>(small_batches), hs, most);
 }
 // The most accepted draws the two samples can ask for: the smaller of the sample and its complement, the base sample
 // being known and the final sample anything from the base sample up.

@@ -26,7 +26,9 @@ __device__ __forceinline__ int base_count_of(int n_s, const SelectParams& p) {
 // that share and a contiguous run of I_f: scores of I_f from the sparse list, scores of the sampled tokens from
 // their K rows, V rows, running maximum per lane group (no head maximum bounds the sampled scores); one partial
 // (N, D, maximum) per workgroup for given_merge_kernel.
-template <int NT, int FD, bool PAGED>
+// PHASE is a constant of the kernel: what both phases could share is little, and values that only one of them loads would be
+// waited for where the paths meet.
+template <int NT, int FD, bool PAGED, int PHASE>
 __global__ __launch_bounds__(NT) void given_topk_kernel(HeadArgs A) {
   using O = HeadOps<NT>;
   using HeadSmem = typename O::HeadSmem;
@@ -60,10 +62,104 @@ __global__ __launch_bounds__(NT) void given_topk_kernel(HeadArgs A) {
   uint32_t* glist = mail + kMailSlots;
   uint32_t* blist = glist + (kFused ? A.glist_cap : 0);
   uint32_t* bslot = blist + (kFused ? A.dlist_cap : 0);
-  const int n_fix0 = 0;
-  (void)n_fix0;
   int32_t* idx = A.out_idx + (int64_t)bh * A.idx_cap;
+  const float* sp = A.sparse + (int64_t)bh * A.idx_cap;
   const int mid_len = hs.mid_hi - hs.mid_lo;
+  const int kvh = div_group(h, A.group);
+
+  // What can be asked for before anything is worked out comes first, and the first batch of draws, which depends on the seed,
+  // the head and the length only, is made while it is under way.
+  HeadRec rec = {};
+  uint4 pre_t = make_uint4(0u, 0u, 0u, 0u);
+  uint32_t pre_f = 0u, pre_all = 0u;
+  if constexpr (PHASE != 0) {
+    rec = A.head_rec[bh];
+    if constexpr (kFused) {
+      pre_t = A.pre_tok[(int64_t)bh * NT + tid];
+      pre_f = A.pre_flags[(int64_t)bh * NT + tid];
+      pre_all = A.pre_flags[(int64_t)bh * NT];  // (the same word for the whole workgroup)
+    }
+  }
+  const int cnt = PHASE == 0 ? min(max(A.given_cnt[bh], 0), A.k_max) : rec.k;  // entries of the list of top-k tokens
+  // (loads without a condition around them, of something valid where there is nothing to load: the list may have no room at all)
+  const int32_t* list = PHASE != 0 ? idx + A.seg_topk : A.k_max > 0 ? A.given_idx + (int64_t)bh * A.k_max : idx;
+  // (four entries per thread are read before any is used: a read behind a condition waits for the one before)
+  constexpr int U = 4;
+  auto load_list = [&](int t0, int (&g)[U]) {
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int t = max(min(t0 + u * NT + tid, cnt - 1), 0);
+      g[u] = list[t];
+    }
+  };
+  int g_first[U];
+  load_list(0, g_first);
+  // first phase: the random cache's slots, as many per thread whatever it holds
+  const unsigned char* cache_rec = PHASE == 0 && A.rcache ? cache_record(A.rcache, A.rc, seq, A.Hkv, kvh) : nullptr;
+  const int32_t* ctok = cache_rec ? reinterpret_cast<const int32_t*>(cache_rec + 16) : idx;
+  const int c_last = cache_rec ? A.rc.slots - 1 : 0;
+  const int c_per = cache_rec ? (A.rc.slots + NT - 1) / NT : 0;
+  int c_cnt = 0, c_first[U];
+  auto load_slots = [&](int sb, int (&tk)[U]) {
+#pragma unroll
+    for (int j = 0; j < U; ++j) tk[j] = ctok[min(sb + j, c_last)];
+  };
+  if constexpr (PHASE == 0) {
+    load_slots(tid * c_per, c_first);
+    if (cache_rec) c_cnt = min(max(*reinterpret_cast<const int32_t*>(cache_rec), 0), A.rc.slots);
+  }
+  // second phase: scores of [sink | window | top-k | base sample], a few per thread
+  // (places by arithmetic and loads without a condition around them, so that a thread's loads go out together;
+  // a slot beyond the list repeats the last entry and then counts as -inf)
+  const int n_fix1 = hs.n_sink + hs.n_win + rec.k, n_all = n_fix1 + (rec.n_s > 0 ? base_count_of(rec.n_s, A.sp) : 0);
+  // (what is done with a loaded value stands where it is used: next to the load it would be waited for there)
+  auto load_scores = [&](int base, float (&v)[U]) {
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int p = min(base + u * NT + tid, n_all - 1);
+      const uint32_t fixed = (uint32_t)fixed_place(p, hs.n_sink, hs.n_win, A.seg_sink, A.seg_win, A.seg_topk);
+      v[u] = sp[p < n_fix1 ? fixed : (uint32_t)A.seg_base + (uint32_t)(p - n_fix1)];
+    }
+  };
+  auto mask_scores = [&](int base, float (&v)[U]) {
+#pragma unroll
+    for (int u = 0; u < U; ++u) v[u] = base + u * NT + tid < n_all ? v[u] : -INFINITY;
+  };
+  float v_first[U];  // the first four stay in registers
+  if constexpr (PHASE != 0) load_scores(0, v_first);
+  // second phase, fused gather: the rows of this workgroup's run of I_f (LPR adjacent lanes hold one row, NG rows per round, UF
+  // rounds in flight; places, tokens, block-table entries and rows each in a loop of their own over the UF slots: no branch
+  // per row; a slot beyond the list repeats its last entry and adds nothing).  Their tokens and scores are asked for here, the
+  // rows after the draws, and they are added at the end.
+  constexpr int LPR = kFused ? FD / 8 : 16;
+  constexpr int NG = NT / LPR;
+  constexpr int UF = 8;
+  const int g_sub = tid % LPR, g_grp = tid / LPR;
+  const int run1 = (n_fix1 + (int)A.splits - 1) >> shift;
+  const int f_lo = min((int)split * run1, n_fix1), f_hi = min(f_lo + run1, n_fix1);
+  int f_tok[UF];
+  float f_sc[UF];
+  uint4 f_v[UF];
+  auto load_fixed = [&](int j0) {
+#pragma unroll
+    for (int u = 0; u < UF; ++u) {
+      const uint32_t place = (uint32_t)fixed_place(max(min(j0 + g_grp + u * NG, f_hi - 1), 0), hs.n_sink, hs.n_win, A.seg_sink, A.seg_win, A.seg_topk);
+      f_tok[u] = idx[place];
+      f_sc[u] = sp[place];
+    }
+  };
+  auto load_fixed_rows = [&]() {
+    int blk[UF];
+#pragma unroll
+    for (int u = 0; u < UF; ++u) {
+      f_tok[u] = min(max(f_tok[u], 0), n - 1);
+      blk[u] = kv_block<PAGED>(A.L, seq, f_tok[u]);
+    }
+#pragma unroll
+    for (int u = 0; u < UF; ++u)
+      f_v[u] = load_stream_16(A.v + kv_row_offset_in<PAGED>(A.L, seq, kvh, f_tok[u], blk[u]) + g_sub * 8);
+  };
+  if constexpr (kFused && PHASE != 0) load_fixed(f_lo);
 
   for (int w = tid; w < words; w += NT) {
     bm_f[w] = 0;
@@ -71,35 +167,6 @@ __global__ __launch_bounds__(NT) void given_topk_kernel(HeadArgs A) {
     scratch[w] = 0;
   }
   __syncthreads();
-  if (A.phase == 0) {
-    const int cnt = min(max(A.given_cnt[bh], 0), A.k_max);
-    const int32_t* given = A.given_idx + (int64_t)bh * A.k_max;
-    // (four entries per thread are read before any is used: a read behind a condition waits for the one before)
-    for (int t0 = 0; t0 < cnt; t0 += 4 * NT) {
-      int g[4];
-#pragma unroll
-      for (int u = 0; u < 4; ++u) g[u] = given[min(t0 + u * NT + tid, cnt - 1)];
-#pragma unroll
-      for (int u = 0; u < 4; ++u)
-        if (t0 + u * NT + tid < cnt && g[u] >= hs.mid_lo && g[u] < hs.mid_hi) O::mark_bit(bm_f, (uint32_t)g[u]);
-    }
-  } else {
-    const HeadRec r = A.head_rec[bh];
-    for (int t0 = 0; t0 < r.k; t0 += 4 * NT) {  // (four list entries per thread read together)
-      int g[4];
-#pragma unroll
-      for (int u = 0; u < 4; ++u) g[u] = O::list_tok(idx, A.seg_topk + min(t0 + u * NT + tid, r.k - 1), n);
-#pragma unroll
-      for (int u = 0; u < 4; ++u)
-        if (t0 + u * NT + tid < r.k) O::mark_bit(bm_f, (uint32_t)g[u]);
-    }
-  }
-  __syncthreads();
-  const int k_eff = A.phase == 0 ? (int)O::word_prefix(bm_f, words, wpre, sm) : A.head_rec[bh].k;
-  hs.k = k_eff;
-  hs.n_s = mid_len - k_eff;
-  hs.b0 = hs.n_s > 0 ? base_count_of(hs.n_s, A.sp) : 0;
-
   Sampler S;
   S.taken = taken;
   S.scratch = scratch;
@@ -108,45 +175,97 @@ __global__ __launch_bounds__(NT) void given_topk_kernel(HeadArgs A) {
   S.wpre = wpre;
   S.row = nullptr;
   S.seed = A.seq_seeds[seq];
-  S.stream = A.phase == 0 ? 0u : 1u;
+  S.stream = PHASE == 0 ? 0u : 1u;
   S.head = (uint32_t)h;
   S.query = (uint32_t)qtok;
   S.L = (uint32_t)max(mid_len, 1);
-  S.thr = (uint32_t)((0x100000000ull - (uint64_t)S.L) % (uint64_t)S.L);
+  S.thr = (0u - S.L) % S.L;  // 2^32 mod L
   {
     const uint64_t dflt = 64ull * (uint64_t)S.L + 4096ull;
     S.cap = (uint32_t)min(A.draw_cap ? (uint64_t)A.draw_cap : dflt, 0x80000000ull);
   }
   S.m = 0.f;
   S.dbg = nullptr;
-  const DrawBatch none = {};
+  DrawBatch spec = {};
+  bool have_spec = false;
+  // Philox blocks of the final sample's first batch: enough for the base sample's size, and for a larger sample as many as half
+  // of the threads make
+  auto final_blocks = [&](const HeadSizes& he) {
+    return max(likely_blocks(A.small_batches ? kSmallBatchBlocks : NT, he, base_draws(he)),
+               ahead_blocks<NT>(A.small_batches, he, final_draws(he)));
+  };
+  if constexpr (kFused && PHASE != 0) {
+    // made by a workgroup of the first phase, under its loads of K rows
+    have_spec = (pre_all & 256u) != 0u;
+    spec.blocks = (int)(pre_all >> 16);
+    spec.ok = pre_f & 15u;
+    spec.first = (pre_f >> 4) & 15u;
+    const uint32_t tk[4] = {pre_t.x, pre_t.y, pre_t.z, pre_t.w};
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      spec.tok[e] = min(max(tk[e], (uint32_t)hs.mid_lo), (uint32_t)max(hs.mid_hi - 1, hs.mid_lo));
+      if (have_spec && ((spec.ok >> e) & 1u)) O::mark_bit(taken, spec.tok[e]);
+    }
+  } else {
+    // (first phase: the list's length stands for the size of the set; the batch's size changes no result)
+    HeadSizes he = hs;
+    he.k = min(cnt, max(mid_len, 0));
+    he.n_s = mid_len - he.k;
+    he.b0 = he.n_s > 0 ? base_count_of(he.n_s, A.sp) : 0;
+    have_spec = he.n_s > 0 && he.b0 < he.n_s && (PHASE == 0 ? !A.rcache : !A.nested);
+    if (have_spec) {
+      const int blocks = PHASE == 0 ? likely_blocks(A.small_batches ? kSmallBatchBlocks : NT, he, base_draws(he)) : final_blocks(he);
+      O::make_batch(spec, S, hs, 0u, blocks, false, false, sm, tid);
+    }
+  }
+  if constexpr (kFused && PHASE != 0) load_fixed_rows();
+  auto mark = [&](int t0, const int (&g)[U]) {
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+      if (t0 + u * NT + tid < cnt && g[u] >= hs.mid_lo && g[u] < hs.mid_hi) O::mark_bit(bm_f, (uint32_t)g[u]);
+  };
+  mark(0, g_first);
+  for (int t0 = U * NT; t0 < cnt; t0 += U * NT) {
+    int g[U];
+    load_list(t0, g);
+    mark(t0, g);
+  }
+  __syncthreads();
+  const int k_eff = PHASE == 0 ? (int)O::word_prefix(bm_f, words, wpre, sm, &sm.scan_once[0]) : rec.k;
+  hs.k = k_eff;
+  hs.n_s = mid_len - k_eff;
+  hs.b0 = hs.n_s > 0 ? base_count_of(hs.n_s, A.sp) : 0;
+
   // (first phase fused with the scores: the run of [sink | window | top-k) this workgroup scores)
   int f0_lo = 0, f0_hi = 0;
-  if (kFused && A.phase == 0) {
+  if (kFused && PHASE == 0) {
     const int n_f = hs.n_sink + hs.n_win + k_eff;
     const int run = min((n_f + (int)A.splits - 1) >> shift, A.glist_cap);
     f0_lo = min((int)split * run, n_f);
     f0_hi = min(f0_lo + run, n_f);
   }
 
-  if (A.phase == 0) {
-    {
-      const int wpt = (words + NT - 1) / NT;
-      const int w0 = tid * wpt;
-      for (int w = w0; w < min(w0 + wpt, words); ++w) {
-        uint32_t bits = bm_f[w];
-        uint32_t pos = wpre[w];
-        while (bits) {
-          const int i = (w << 5) + (__ffs(bits) - 1);
-          bits &= bits - 1u;
-          if (writer && pos < (uint32_t)A.k_max) idx[A.seg_topk + pos] = i;
+  if constexpr (PHASE == 0) {
+    // every entry finds its own place: the members below it, from the word prefix and the bits below its own (a repeated token
+    // writes the same place twice)
+    auto place = [&](int t0, const int (&g)[U]) {
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        if (t0 + u * NT + tid < cnt && g[u] >= hs.mid_lo && g[u] < hs.mid_hi) {
+          const uint32_t pos = wpre[g[u] >> 5] + (uint32_t)__popc(bm_f[g[u] >> 5] & ((1u << (g[u] & 31)) - 1u));
+          if (writer && pos < (uint32_t)A.k_max) idx[A.seg_topk + pos] = g[u];
           if (kFused) {
             const int p = hs.n_sink + hs.n_win + (int)pos;  // place in [sink | window | top-k)
-            if (p >= f0_lo && p < f0_hi) glist[p - f0_lo] = (uint32_t)i;
+            if (p >= f0_lo && p < f0_hi) glist[p - f0_lo] = (uint32_t)g[u];
           }
-          ++pos;
         }
       }
+    };
+    place(0, g_first);
+    for (int t0 = U * NT; t0 < cnt; t0 += U * NT) {
+      int g[U];
+      load_list(t0, g);
+      place(t0, g);
     }
     for (int i = tid; i < hs.n_sink; i += NT) {
       if (writer) idx[A.seg_sink + i] = i;
@@ -157,46 +276,45 @@ __global__ __launch_bounds__(NT) void given_topk_kernel(HeadArgs A) {
       const int p = hs.n_sink + i;
       if (kFused && p >= f0_lo && p < f0_hi) glist[p - f0_lo] = (uint32_t)(hs.mid_hi + i);
     }
-    __syncthreads();
     int flags = 0;
     bool cached = false;
-    if (hs.n_s > 0 && A.rcache) {
+    if (hs.n_s > 0 && cache_rec) {
       // base sample = the first b0 cached tokens, in slot order, that are residual tokens of this head; the
       // cache is used only when it holds that many
-      const unsigned char* rec = cache_record(A.rcache, A.rc, seq, A.Hkv, div_group(h, A.group));
-      const int cnt = min(max(*reinterpret_cast<const int32_t*>(rec), 0), A.rc.slots);
-      const int32_t* ctok = reinterpret_cast<const int32_t*>(rec + 16);
-      const int per = (cnt + NT - 1) / NT;
-      const int s0 = min(tid * per, cnt), s1 = min(s0 + per, cnt);
+      const int s0 = min(tid * c_per, c_cnt), s1 = min(s0 + c_per, c_cnt);
       // a thread's slots four at a time: their tokens are read together, then their bitmap words together
       // (bit j of the result: slot sb + j holds a residual token; the token comes back in tk[j])
-      auto residual4 = [&](int sb, int (&tk)[4]) -> uint32_t {
-        uint32_t w[4], r4 = 0;
+      auto residual4 = [&](int sb, int (&tk)[U]) -> uint32_t {
+        uint32_t w[U], r4 = 0;
+        if (sb == s0) {
 #pragma unroll
-        for (int j = 0; j < 4; ++j) tk[j] = ctok[min(sb + j, cnt - 1)];
+          for (int j = 0; j < U; ++j) tk[j] = c_first[j];
+        } else {
+          load_slots(sb, tk);
+        }
 #pragma unroll
-        for (int j = 0; j < 4; ++j) w[j] = bm_f[min(max(tk[j], 0), n - 1) >> 5];  // (a token outside the sequence fails the range test below)
+        for (int j = 0; j < U; ++j) w[j] = bm_f[min(max(tk[j], 0), n - 1) >> 5];  // (a token outside the sequence fails the range test below)
 #pragma unroll
-        for (int j = 0; j < 4; ++j)
+        for (int j = 0; j < U; ++j)
           r4 |= ((sb + j < s1 && tk[j] >= hs.mid_lo && tk[j] < hs.mid_hi && !((w[j] >> (tk[j] & 31)) & 1u)) ? 1u : 0u) << j;
         return r4;
       };
       uint32_t mine = 0;
-      for (int sb = s0; sb < s1; sb += 4) {
-        int tk[4];
+      for (int sb = s0; sb < s1; sb += U) {
+        int tk[U];
         mine += (uint32_t)__popc(residual4(sb, tk));
       }
       uint32_t total;
-      uint32_t pos = block_exclusive_scan<NT>(mine, &total, sm.scan);
+      uint32_t pos = block_exclusive_scan_once<NT>(mine, &total, sm.scan_once[1]);
       cached = total >= (uint32_t)hs.b0;
       if (cached) {
         int32_t* slot_of = A.base_slot + (int64_t)bh * A.b0_max;
         const uint32_t lim = (uint32_t)min(hs.b0, A.b0_max);
-        for (int sb = s0; sb < s1 && pos < lim; sb += 4) {
-          int tk[4];
+        for (int sb = s0; sb < s1 && pos < lim; sb += U) {
+          int tk[U];
           const uint32_t r4 = residual4(sb, tk);
 #pragma unroll
-          for (int j = 0; j < 4; ++j) {
+          for (int j = 0; j < U; ++j) {
             if (((r4 >> j) & 1u) && pos < lim) {
               if (writer) {
                 idx[A.seg_base + pos] = tk[j];
@@ -214,6 +332,7 @@ __global__ __launch_bounds__(NT) void given_topk_kernel(HeadArgs A) {
       }
     }
     if (hs.n_s > 0 && !cached) {
+      __syncthreads();  // (the sampler may take the word prefixes' place)
       Emit E0 = emit_to(idx + A.seg_base, (uint32_t)A.b0_max);
       if (kFused) {
         E0.global = writer;
@@ -222,7 +341,7 @@ __global__ __launch_bounds__(NT) void given_topk_kernel(HeadArgs A) {
         E0.shift = shift;
         E0.split = split;
       }
-      const int f = O::draw_sample(S, hs, (uint32_t)hs.b0, none, false, A.small_batches, E0, nullptr, nullptr, sm);
+      const int f = O::draw_sample(S, hs, (uint32_t)hs.b0, spec, have_spec, A.small_batches, E0, nullptr, nullptr, sm);
       flags |= ((f & 1) ? kFlagBaseComplement : 0) | ((f & 2) ? kFlagBaseBatches : 0) | ((f & 4) ? kFlagDrawCap : 0);
       if (!kFused && A.ascending && !(f & 1))
         O::sort_ascending(idx + A.seg_base, (uint32_t)min(hs.b0, A.b0_max), scratch, wpre, n, sm);
@@ -247,11 +366,6 @@ __global__ __launch_bounds__(NT) void given_topk_kernel(HeadArgs A) {
       // ---- the scores of this workgroup's share of I_f and of the base sample (denominator target) ----
       // s_i = sm_scale <K[i], q>, written to the tokens' places of the sparse list; rows as in the gather below:
       // tokens, block-table entries and rows each in a loop of their own over the slots in flight
-      constexpr int LPR = FD / 8;
-      constexpr int NG = NT / LPR;
-      constexpr int UF = 8;
-      const int g_sub = tid % LPR, g_grp = tid / LPR;
-      const int kvh = div_group(h, A.group);
       __syncthreads();  // the lists of this workgroup's share are complete
       float* spw = const_cast<float*>(A.sparse) + (int64_t)bh * A.idx_cap;
       uint32_t qw[4];
@@ -271,89 +385,99 @@ __global__ __launch_bounds__(NT) void given_topk_kernel(HeadArgs A) {
         return group_sum<LPR>(a) * A.sm_scale + 0.0f;
       };
       const int my_nf = f0_hi - f0_lo;
-      for (int j0 = g_grp; j0 < my_nf; j0 += NG * UF) {
+      int my_nb = hs.n_s > 0 && hs.b0 > (int)split ? (int)(((uint32_t)hs.b0 - split + ((1u << shift) - 1u)) >> shift) : 0;
+      my_nb = min(my_nb, A.dlist_cap);
+      auto load_listed = [&](const uint32_t* list, int j0, int count, uint4 (&kv)[UF]) {
         int tok[UF], blk[UF];
-        uint4 kv[UF];
 #pragma unroll
-        for (int u = 0; u < UF; ++u) tok[u] = (int)min(glist[min(j0 + u * NG, my_nf - 1)], (uint32_t)(n - 1));
+        for (int u = 0; u < UF; ++u) tok[u] = (int)min(list[min(j0 + u * NG, count - 1)], (uint32_t)(n - 1));
 #pragma unroll
         for (int u = 0; u < UF; ++u) blk[u] = kv_block<PAGED>(A.Lk, seq, tok[u]);
 #pragma unroll
         for (int u = 0; u < UF; ++u)
           kv[u] = load_stream_16(A.gk + kv_row_offset_in<PAGED>(A.Lk, seq, kvh, tok[u], blk[u]) + g_sub * 8);
+      };
+      auto load_base = [&](int j0, uint4 (&kv)[UF]) {
+        if (cached) {
+          // the copies of the rows in the cache: rows of neighbouring slots, shared by the group's heads
+          int slot[UF];
+#pragma unroll
+          for (int u = 0; u < UF; ++u) slot[u] = (int)min(bslot[min(j0 + u * NG, my_nb - 1)], (uint32_t)(A.rc.slots - 1));
+#pragma unroll
+          for (int u = 0; u < UF; ++u)
+            kv[u] = *reinterpret_cast<const uint4*>(reinterpret_cast<const uint16_t*>(cache_rec + A.rc.off_k) +
+                                                    (int64_t)slot[u] * FD + g_sub * 8);
+        } else {
+          load_listed(blist, j0, my_nb, kv);
+        }
+      };
+      // (the first rows of both lists are under way together)
+      uint4 kf[UF], kb[UF];
+      if (my_nf > 0) load_listed(glist, g_grp, my_nf, kf);
+      if (my_nb > 0) load_base(g_grp, kb);
+      if ((int)split == A.splits - 1) {
+        // The first batch of the final sample's draws, for all workgroups of the head in the second phase, where it would
+        // stand in front of everything else.  Here it is made while the rows are on their way.
+        const bool make = hs.n_s > 0 && hs.b0 < hs.n_s;
+        DrawBatch mine = {};
+        const int blocks = final_blocks(hs);
+        if (make) {
+          for (int w = tid; w < words; w += NT) taken[w] = 0;  // (the base sample's)
+          __syncthreads();
+          Sampler S1 = S;
+          S1.stream = 1u;
+          O::make_batch(mine, S1, hs, 0u, blocks, false, false, sm, tid);
+        }
+        const int64_t at = (int64_t)bh * NT + tid;
+        const_cast<uint4*>(A.pre_tok)[at] = make_uint4(mine.tok[0], mine.tok[1], mine.tok[2], mine.tok[3]);
+        const_cast<uint32_t*>(A.pre_flags)[at] = mine.ok | mine.first << 4 | (make ? 256u : 0u) | (uint32_t)blocks << 16;
+      }
+      for (int j0 = g_grp; j0 - g_grp < my_nf; j0 += NG * UF) {
+        if (j0 != g_grp) load_listed(glist, j0, my_nf, kf);
 #pragma unroll
         for (int u = 0; u < UF; ++u) {
-          const float sc = score_of(kv[u]);
+          const float sc = score_of(kf[u]);
           const int j = j0 + u * NG;
           if (j < my_nf && g_sub == 0)
             spw[fixed_place(f0_lo + j, hs.n_sink, hs.n_win, A.seg_sink, A.seg_win, A.seg_topk)] = sc;
         }
       }
-      int my_nb = hs.n_s > 0 && hs.b0 > (int)split ? (int)(((uint32_t)hs.b0 - split + ((1u << shift) - 1u)) >> shift) : 0;
-      my_nb = min(my_nb, A.dlist_cap);
-      const unsigned char* crec = cached ? cache_record(A.rcache, A.rc, seq, A.Hkv, kvh) : nullptr;
-      for (int j0 = g_grp; j0 < my_nb; j0 += NG * UF) {
-        int tok[UF], blk[UF];
-        uint4 kv[UF];
-        if (cached) {
-          // the copies of the rows in the cache: rows of neighbouring slots, shared by the group's heads
-#pragma unroll
-          for (int u = 0; u < UF; ++u) tok[u] = (int)min(bslot[min(j0 + u * NG, my_nb - 1)], (uint32_t)(A.rc.slots - 1));
-#pragma unroll
-          for (int u = 0; u < UF; ++u)
-            kv[u] = *reinterpret_cast<const uint4*>(reinterpret_cast<const uint16_t*>(crec + A.rc.off_k) +
-                                                    (int64_t)tok[u] * FD + g_sub * 8);
-        } else {
-#pragma unroll
-          for (int u = 0; u < UF; ++u) tok[u] = (int)min(blist[min(j0 + u * NG, my_nb - 1)], (uint32_t)(n - 1));
-#pragma unroll
-          for (int u = 0; u < UF; ++u) blk[u] = kv_block<PAGED>(A.Lk, seq, tok[u]);
-#pragma unroll
-          for (int u = 0; u < UF; ++u)
-            kv[u] = load_stream_16(A.gk + kv_row_offset_in<PAGED>(A.Lk, seq, kvh, tok[u], blk[u]) + g_sub * 8);
-        }
+      for (int j0 = g_grp; j0 - g_grp < my_nb; j0 += NG * UF) {
+        if (j0 != g_grp) load_base(j0, kb);
 #pragma unroll
         for (int u = 0; u < UF; ++u) {
-          const float sc = score_of(kv[u]);
+          const float sc = score_of(kb[u]);
           const int j = j0 + u * NG;
           if (j < my_nb && g_sub == 0) spw[A.seg_base + (((int64_t)j << shift) | split)] = sc;
         }
       }
     }
-    return;
-  }
-
+  } else {
   // ---- phase 1 ----
-  // scores of [sink | window | top-k | base sample], a few per thread, requested together
-  const float* sp = A.sparse + (int64_t)bh * A.idx_cap;
-  const int n_fix = hs.n_sink + hs.n_win + k_eff, n_all = n_fix + hs.b0;
-  // (places by arithmetic and loads without a condition around them, so that a thread's loads go out together;
-  // a slot beyond the list repeats the last entry and then counts as -inf)
-  auto place_of = [&](int p) -> int64_t {
-    const int64_t fixed = fixed_place(p, hs.n_sink, hs.n_win, A.seg_sink, A.seg_win, A.seg_topk);
-    return p < n_fix ? fixed : A.seg_base + (p - n_fix);
-  };
-  constexpr int U = 4;
-  auto load_batch = [&](int base, float (&v)[U]) {
-#pragma unroll
-    for (int u = 0; u < U; ++u) v[u] = sp[place_of(min(base + u * NT + tid, n_all - 1))];
-#pragma unroll
-    for (int u = 0; u < U; ++u) v[u] = base + u * NT + tid < n_all ? v[u] : -INFINITY;
-  };
+  const int n_fix = n_fix1;
   float v_max = -INFINITY;
-  float v_first[U] = {-INFINITY, -INFINITY, -INFINITY, -INFINITY};  // the first batch stays in registers for the second pass
-  for (int base = 0; base < n_all; base += NT * U) {
-    float v[U];
-    load_batch(base, v);
+  mask_scores(0, v_first);
 #pragma unroll
-    for (int u = 0; u < U; ++u) {
-      v_max = fmaxf(v_max, v[u]);
-      if (base == 0) v_first[u] = v[u];
-    }
+  for (int u = 0; u < U; ++u) v_max = fmaxf(v_max, v_first[u]);
+  for (int base = NT * U; base < n_all; base += NT * U) {
+    float v[U];
+    load_scores(base, v);
+    mask_scores(base, v);
+#pragma unroll
+    for (int u = 0; u < U; ++u) v_max = fmaxf(v_max, v[u]);
   }
   v_max = wave_max(v_max);
   if ((tid & 63) == 0) s_wf[tid >> 6] = v_max;
-  __syncthreads();
+  // Usual case (as in the kernel of the scored path): the first batch of draws holds b0 accepted ones, which belong to the final
+  // sample whatever the budget turns out to be, unless it is taken as a complement: with the fused gather their rows are
+  // requested now.  One scan counts the accepted draws, and its barrier serves the maximum too.
+  const uint32_t smask = (1u << shift) - 1u;
+  auto share_of = [&](uint32_t c) { return c > split ? (int)((c - split + smask) >> shift) : 0; };
+  const bool usual = have_spec && 2 * hs.b0 <= hs.n_s && (kFused || !A.ascending);
+  const uint32_t acc_bits = usual ? spec.first & ~O::test_bits4(bm_f, spec.tok) : 0u;
+  uint32_t tot1;
+  const uint32_t acc_pos = block_exclusive_scan_once<NT>((uint32_t)__popc(acc_bits), &tot1, sm.scan_once[2]);
+  const bool spec_dyn = usual && tot1 >= (uint32_t)hs.b0;
   float m = s_wf[0];
 #pragma unroll
   for (int w = 1; w < SW; ++w) m = fmaxf(m, s_wf[w]);
@@ -364,7 +488,8 @@ __global__ __launch_bounds__(NT) void given_topk_kernel(HeadArgs A) {
 #pragma unroll
       for (int u = 0; u < U; ++u) v[u] = v_first[u];
     } else {
-      load_batch(base, v);  // (a second read of a few values, only for lists beyond 2048 entries)
+      load_scores(base, v);  // (a second read of a few values, only for lists beyond 2048 entries)
+      mask_scores(base, v);
     }
 #pragma unroll
     for (int u = 0; u < U; ++u) {
@@ -375,8 +500,45 @@ __global__ __launch_bounds__(NT) void given_topk_kernel(HeadArgs A) {
       acc_w2 += p < n_fix ? 0.0 : w * w;
     }
   }
+  // (accepted draws from .. to - 1 into the lists)
+  auto list_draws = [&](uint32_t lds_from, uint32_t to, bool global) {
+    uint32_t pos = acc_pos;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const bool a = (acc_bits >> e) & 1u;
+      if (a && pos < to) {
+        if (global && pos < (uint32_t)A.b_max) idx[A.seg_dyn + pos] = (int32_t)spec.tok[e];
+        if (kFused && pos >= lds_from && (pos & smask) == split && (pos >> shift) < (uint32_t)A.dlist_cap)
+          dlist[pos >> shift] = spec.tok[e];
+      }
+      pos += a ? 1u : 0u;
+    }
+  };
+  if (kFused && spec_dyn) list_draws(0u, (uint32_t)hs.b0, false);
   double sums[3] = {acc_f, acc_w, acc_w2};
-  O::block_sum(sums, sm);
+  O::block_sum_post(sums, sm);
+  __syncthreads();
+  // places [first, count) of this workgroup's share of the final sample, as far as a batch reaches: K and V rows
+  // (place j is always read by lane group j % NG, and a group adds its rows in rising order)
+  uint4 dk[UF], dv[UF];
+  auto load_drawn = [&](int first, int count) {
+    const int j0 = (first & ~(NG - 1)) + g_grp;
+    int tok[UF], blk[UF];
+#pragma unroll
+    for (int u = 0; u < UF; ++u) tok[u] = (int)min(dlist[min(j0 + u * NG, count - 1)], (uint32_t)(n - 1));
+#pragma unroll
+    for (int u = 0; u < UF; ++u) blk[u] = kv_block<PAGED>(A.L, seq, tok[u]);  // (K and V share the block table)
+#pragma unroll
+    for (int u = 0; u < UF; ++u) {
+      dk[u] = load_stream_16(A.gk + kv_row_offset_in<PAGED>(A.Lk, seq, kvh, tok[u], blk[u]) + g_sub * 8);
+      dv[u] = load_stream_16(A.v + kv_row_offset_in<PAGED>(A.L, seq, kvh, tok[u], blk[u]) + g_sub * 8);
+    }
+  };
+  const int my_spec = kFused && spec_dyn ? min(share_of((uint32_t)hs.b0), A.dlist_cap) : 0;
+  if constexpr (kFused) {
+    if (my_spec > 0) load_drawn(0, my_spec);
+  }
+  O::block_sum_get(sums, sm);
   const double D_f = sums[0];
   double sigma2 = 0.0, b_star = 0.0, D_hat = D_f, tr_sigma = 0.0, nhat_sq = 0.0;
   int bfin = 0;
@@ -420,7 +582,9 @@ __global__ __launch_bounds__(NT) void given_topk_kernel(HeadArgs A) {
     D_hat = bud.D_hat;
   }
   int flags = 0;
-  if (bfin > 0) {
+  const bool fast_dyn = spec_dyn && (uint32_t)bfin <= tot1 && 2 * bfin <= hs.n_s;  // the first batch of draws holds the sample
+  if (fast_dyn) list_draws((uint32_t)hs.b0, (uint32_t)bfin, writer);
+  if (bfin > 0 && !fast_dyn) {
     Emit E1 = emit_to(idx + A.seg_dyn, (uint32_t)A.b_max);
     if (kFused) {
       E1.global = writer;
@@ -432,7 +596,7 @@ __global__ __launch_bounds__(NT) void given_topk_kernel(HeadArgs A) {
     const int f = (!kFused && A.nested)
                       ? O::draw_nested(S, hs, (uint32_t)hs.b0, (uint32_t)bfin, bm_f, idx + A.seg_base,
                                        idx + A.seg_dyn, (uint32_t)A.b_max, A.small_batches, sm)
-                      : O::draw_sample(S, hs, (uint32_t)bfin, none, false, A.small_batches, E1, nullptr, nullptr, sm);
+                      : O::draw_sample(S, hs, (uint32_t)bfin, spec, have_spec, A.small_batches, E1, nullptr, nullptr, sm);
     flags |= ((f & 1) ? kFlagDynComplement : 0) | ((f & 2) ? kFlagDynBatches : 0) | ((f & 4) ? kFlagDrawCap : 0);
     if (!kFused && A.ascending && !A.nested && !(f & 1))
       O::sort_ascending(idx + A.seg_dyn, (uint32_t)min(bfin, A.b_max), scratch, wpre, n, sm);
@@ -475,14 +639,6 @@ __global__ __launch_bounds__(NT) void given_topk_kernel(HeadArgs A) {
 
   if constexpr (kFused) {
     // ---- the gather of this workgroup's share ----
-    // LPR adjacent lanes hold one row, NG rows per round, UF rounds in flight; places, tokens, block-table
-    // entries and rows each in a loop of their own over the UF slots (no branch per row); a slot beyond a list
-    // repeats its last entry and adds nothing.
-    constexpr int LPR = FD / 8;
-    constexpr int NG = NT / LPR;
-    constexpr int UF = 8;
-    const int g_sub = tid % LPR, g_grp = tid / LPR;
-    const int kvh = div_group(h, A.group);
     __syncthreads();  // the final sample's share is complete in dlist
     uint32_t qw[4];
     {
@@ -507,58 +663,42 @@ __global__ __launch_bounds__(NT) void given_topk_kernel(HeadArgs A) {
       dsum += wt;
     };
     // I_f: a contiguous run of [sink | window | top-k) per workgroup (the top-k part is in ascending token order)
-    const int n_fix2 = hs.n_sink + hs.n_win + k_eff;
-    const int run = (n_fix2 + (int)A.splits - 1) >> shift;
-    const int f_lo = min((int)split * run, n_fix2), f_hi = min(f_lo + run, n_fix2);
-    for (int j0 = f_lo + g_grp; j0 < f_hi; j0 += NG * UF) {
-      int64_t place[UF];
-      int tok[UF], blk[UF];
-      float sc[UF];
-      uint4 vv[UF];
-#pragma unroll
-      for (int u = 0; u < UF; ++u)
-        place[u] = fixed_place(min(j0 + u * NG, f_hi - 1), hs.n_sink, hs.n_win, A.seg_sink, A.seg_win, A.seg_topk);
-#pragma unroll
-      for (int u = 0; u < UF; ++u) {
-        tok[u] = min(max(idx[place[u]], 0), n - 1);
-        sc[u] = sp[place[u]];
+    for (int j0 = f_lo; j0 < f_hi; j0 += NG * UF) {
+      if (j0 != f_lo) {
+        load_fixed(j0);
+        load_fixed_rows();
       }
 #pragma unroll
-      for (int u = 0; u < UF; ++u) blk[u] = kv_block<PAGED>(A.L, seq, tok[u]);
-#pragma unroll
       for (int u = 0; u < UF; ++u)
-        vv[u] = load_stream_16(A.v + kv_row_offset_in<PAGED>(A.L, seq, kvh, tok[u], blk[u]) + g_sub * 8);
-#pragma unroll
-      for (int u = 0; u < UF; ++u)
-        if (j0 + u * NG < f_hi) add_row(sc[u], vv[u]);
+        if (j0 + g_grp + u * NG < f_hi) add_row(f_sc[u], f_v[u]);
     }
     // the final sample: every A.splits-th token, scores from the K rows, weights carry n_s / b
-    int my_nd = bfin > (int)split ? (int)(((uint32_t)bfin - split + ((1u << shift) - 1u)) >> shift) : 0;
-    my_nd = min(my_nd, A.dlist_cap);
+    const int my_nd = min(share_of((uint32_t)bfin), A.dlist_cap);
     const float tail_bias = bfin > 0 ? __logf((float)((double)hs.n_s / (double)bfin)) : 0.f;
-    for (int j0 = g_grp; j0 < my_nd; j0 += NG * UF) {
-      int tok[UF], blk[UF];
-      uint4 kv[UF], vv[UF];
-#pragma unroll
-      for (int u = 0; u < UF; ++u) tok[u] = (int)min(dlist[min(j0 + u * NG, my_nd - 1)], (uint32_t)(n - 1));
-#pragma unroll
-      for (int u = 0; u < UF; ++u) blk[u] = kv_block<PAGED>(A.L, seq, tok[u]);  // (K and V share the block table)
-#pragma unroll
-      for (int u = 0; u < UF; ++u) {
-        kv[u] = load_stream_16(A.gk + kv_row_offset_in<PAGED>(A.Lk, seq, kvh, tok[u], blk[u]) + g_sub * 8);
-        vv[u] = load_stream_16(A.v + kv_row_offset_in<PAGED>(A.L, seq, kvh, tok[u], blk[u]) + g_sub * 8);
-      }
+    auto add_drawn = [&](int first, int count) {
+      const int j0 = (first & ~(NG - 1)) + g_grp;
 #pragma unroll
       for (int u = 0; u < UF; ++u) {
         // (the lanes of a group stay together: every lane of the group computes the row's score)
         float a = 0.f;
-        a = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2_t, kv[u].x), __builtin_bit_cast(bf16x2_t, qw[0]), a, false);
-        a = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2_t, kv[u].y), __builtin_bit_cast(bf16x2_t, qw[1]), a, false);
-        a = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2_t, kv[u].z), __builtin_bit_cast(bf16x2_t, qw[2]), a, false);
-        a = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2_t, kv[u].w), __builtin_bit_cast(bf16x2_t, qw[3]), a, false);
+        a = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2_t, dk[u].x), __builtin_bit_cast(bf16x2_t, qw[0]), a, false);
+        a = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2_t, dk[u].y), __builtin_bit_cast(bf16x2_t, qw[1]), a, false);
+        a = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2_t, dk[u].z), __builtin_bit_cast(bf16x2_t, qw[2]), a, false);
+        a = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2_t, dk[u].w), __builtin_bit_cast(bf16x2_t, qw[3]), a, false);
         const float s_row = group_sum<LPR>(a) * A.sm_scale + 0.0f;
-        if (j0 + u * NG < my_nd) add_row(s_row + tail_bias, vv[u]);
+        const int j = j0 + u * NG;
+        if (j >= first && j < count) add_row(s_row + tail_bias, dv[u]);
       }
+    };
+    int j_done = 0;
+    if (my_spec > 0 && 2 * bfin <= hs.n_s) {  // (the rows of the first b0 tokens are at hand, unless the sample is a complement)
+      add_drawn(0, my_spec);
+      j_done = min(my_spec, UF * NG);
+    }
+    while (j_done < my_nd) {
+      load_drawn(j_done, my_nd);
+      add_drawn(j_done, my_nd);
+      j_done = (j_done & ~(NG - 1)) + UF * NG;
     }
     // the lane groups of a wave to their common maximum and added, then the waves through LDS
     float M = m_run;
@@ -570,18 +710,15 @@ __global__ __launch_bounds__(NT) void given_topk_kernel(HeadArgs A) {
       for (int c = 0; c < 8; ++c) acc[c] *= f;
       dsum *= f;
     }
+    add_lane_groups<LPR>(acc);
 #pragma unroll
-    for (int o = LPR; o < kWave; o <<= 1) {
-#pragma unroll
-      for (int c = 0; c < 8; ++c) acc[c] += __shfl_xor(acc[c], o);
-      dsum += __shfl_xor(dsum, o);
-    }
+    for (int o = LPR; o < kWave; o <<= 1) dsum += __shfl_xor(dsum, o);
     const int lane = tid & 63, wave = tid >> 6;
     float* g_d = g_red + SW * FD;
     float* g_m = g_d + SW;
-    if (lane < LPR) {
+    if (LPR == 16 || (lane & 8) == 0) {
 #pragma unroll
-      for (int c = 0; c < 8; ++c) g_red[wave * FD + lane * 8 + c] = acc[c];
+      for (int c = 0; c < 2; ++c) g_red[wave * FD + lane_groups_column<LPR>(lane) + c] = acc[c];
     }
     if (lane == 0) {
       g_d[wave] = dsum;
@@ -606,6 +743,19 @@ __global__ __launch_bounds__(NT) void given_topk_kernel(HeadArgs A) {
       part[FD + 1] = Mall;
     }
   }
+  }
+}
+
+typedef void (*GivenKernel)(HeadArgs);
+// The instantiation for a head dimension (0: selection only) and cache layout.
+template <int PHASE>
+GivenKernel given_kernel_for(int d, bool paged) {
+  if (d == 0) return given_topk_kernel<kHeadThreads, 0, false, PHASE>;
+  if (d == 128) return paged ? given_topk_kernel<kHeadThreads, 128, true, PHASE> : given_topk_kernel<kHeadThreads, 128, false, PHASE>;
+  return paged ? given_topk_kernel<kHeadThreads, 64, true, PHASE> : given_topk_kernel<kHeadThreads, 64, false, PHASE>;
+}
+GivenKernel given_kernel_for(int phase, int d, bool paged) {
+  return phase == 0 ? given_kernel_for<0>(d, paged) : given_kernel_for<1>(d, paged);
 }
 
 }  // namespace
@@ -613,15 +763,13 @@ __global__ __launch_bounds__(NT) void given_topk_kernel(HeadArgs A) {
 hipError_t set_given_kernel_attributes(const Plan& pl) {
   (void)pl;
   const int cap = 160 * 1024 - (int)head_kernel_static_lds_bytes();
-  const void* kernels[5] = {reinterpret_cast<const void*>(given_topk_kernel<kHeadThreads, 0, false>),
-                            reinterpret_cast<const void*>(given_topk_kernel<kHeadThreads, 128, false>),
-                            reinterpret_cast<const void*>(given_topk_kernel<kHeadThreads, 128, true>),
-                            reinterpret_cast<const void*>(given_topk_kernel<kHeadThreads, 64, false>),
-                            reinterpret_cast<const void*>(given_topk_kernel<kHeadThreads, 64, true>)};
-  for (const void* f : kernels) {
-    const hipError_t e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, cap);
-    if (e != hipSuccess) return e;
-  }
+  for (const int phase : {0, 1})
+    for (const int d : {0, 64, 128})
+      for (const bool paged : {false, true}) {
+        const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(given_kernel_for(phase, d, paged)),
+                                                 hipFuncAttributeMaxDynamicSharedMemorySize, cap);
+        if (e != hipSuccess) return e;
+      }
   return hipSuccess;
 }
 
@@ -635,7 +783,7 @@ hipError_t launch_given_select(const Plan& pl, int phase, const int32_t* seq_len
   A.given_cnt = given_cnt;
   A.rcache = rcache;
   A.rc = cache_layout(pl);
-  hipLaunchKernelGGL((given_topk_kernel<kHeadThreads, 0, false>), dim3(pl.p.n_q_heads, pl.vbatch), dim3(kHeadThreads),
+  hipLaunchKernelGGL(given_kernel_for(phase, 0, false), dim3(pl.p.n_q_heads, pl.vbatch), dim3(kHeadThreads),
                      pl.head_lds_bytes, st, A);
   return hipGetLastError();
 }
@@ -678,6 +826,10 @@ hipError_t launch_given_fused(const Plan& pl, int phase, const void* q, const vo
                               hipStream_t st) {
   HeadArgs A;
   fill_head_args(A, pl, phase, seq_lens, seq_seeds, ws, out_idx, out_counts, out_budget_raw, out_stats);
+  // the final sample's first batch of draws passes from the first phase to the second
+  static_assert(kHeadThreads == 2 * kPreThreads, "a thread's draws each");
+  A.pre_tok = reinterpret_cast<const uint4*>(static_cast<char*>(ws) + pl.off_pre_tok);
+  A.pre_flags = reinterpret_cast<const uint32_t*>(static_cast<char*>(ws) + pl.off_pre_flags);
   const int S = pl.given_fuse_splits;
   A.given_idx = given_idx;
   A.given_cnt = given_cnt;
@@ -700,13 +852,7 @@ hipError_t launch_given_fused(const Plan& pl, int phase, const void* q, const vo
   const dim3 grid(pl.p.n_q_heads, pl.vbatch, S);
   const size_t lds = given_fused_lds_bytes(pl, S);  // (the larger of the two phases' needs)
   const bool paged = pl.p.kv_layout == VATT_LAYOUT_PAGED;
-  if (pl.p.head_dim == 128) {
-    if (paged) hipLaunchKernelGGL((given_topk_kernel<kHeadThreads, 128, true>), grid, dim3(kHeadThreads), lds, st, A);
-    else hipLaunchKernelGGL((given_topk_kernel<kHeadThreads, 128, false>), grid, dim3(kHeadThreads), lds, st, A);
-  } else {
-    if (paged) hipLaunchKernelGGL((given_topk_kernel<kHeadThreads, 64, true>), grid, dim3(kHeadThreads), lds, st, A);
-    else hipLaunchKernelGGL((given_topk_kernel<kHeadThreads, 64, false>), grid, dim3(kHeadThreads), lds, st, A);
-  }
+  hipLaunchKernelGGL(given_kernel_for(phase, pl.p.head_dim, paged), grid, dim3(kHeadThreads), lds, st, A);
   return hipGetLastError();
 }
 
