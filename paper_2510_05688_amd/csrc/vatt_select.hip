@@ -42,6 +42,7 @@ namespace {
 // 0.4 us, and the split arithmetic these 1.4 us).
 template <int NT, int FD, bool PAGED, bool ALONE = false>
 __global__ __launch_bounds__(NT, FD > 0 ? 1 : 4) void head_kernel(HeadArgs A) {
+  touch_args<HeadArgs>();
   if constexpr (FD > 0) {  // (what only the selection-only kernel serves: no code for it here, 0.3 us)
     A.phase = A.nested = A.ascending = 0;
     A.target = VATT_TARGET_D;
