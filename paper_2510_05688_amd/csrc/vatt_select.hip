@@ -40,13 +40,19 @@ namespace {
 // requested as soon as the top-k set is known and are added after the samplers have run.
 // ALONE: one workgroup per head, which writes the head's result itself (a branch on A.splits at the end cost the others
 // 0.4 us, and the split arithmetic these 1.4 us).
-template <int NT, int FD, bool PAGED, bool ALONE = false>
+// PHASE: 0 everything (denominator target), 1 through the base sample, 2 budget and final sample (targets N and SDPA).
+// OPTIONS: a plan with an option set that the usual call does without (head_options) has a kernel of its own; without them the
+// selection-only kernel, which is at its register limit, takes 34.7 instead of 36.7 us for 16 x 32K tokens.
+template <int NT, int FD, bool PAGED, bool ALONE = false, int PHASE = 0, bool OPTIONS = true>
 __global__ __launch_bounds__(NT, FD > 0 ? 1 : 4) void head_kernel(HeadArgs A) {
   touch_args<HeadArgs>();
-  if constexpr (FD > 0) {  // (what only the selection-only kernel serves: no code for it here, 0.3 us)
-    A.phase = A.nested = A.ascending = 0;
-    A.target = VATT_TARGET_D;
+  if constexpr (FD > 0 || !OPTIONS) A.nested = A.ascending = 0;  // (in the fused kernel too: what it does not serve has no code there, 0.3 us)
+  if constexpr (!OPTIONS) {
+    A.topk_general = A.small_batches = 0;
+    A.range_factor = 0.0;
+    A.b_multiple = 1;
   }
+  if constexpr (PHASE == 0) A.target = VATT_TARGET_D;
   constexpr bool kFused = FD > 0;
   using O = HeadOps<NT>;
   using TKR = TopkOps<NT, RowView<NT>>;
@@ -158,8 +164,8 @@ __global__ __launch_bounds__(NT, FD > 0 ? 1 : 4) void head_kernel(HeadArgs A) {
   RowView<NT> rv;
   rv.row = row;
   rv.n = n;
-  const float edge0 = (A.phase != 2 && tid < hs.n_sink) ? row[tid] : -INFINITY;
-  const float edge1 = (A.phase != 2 && tid < hs.n_win) ? row[hs.mid_hi + tid] : -INFINITY;
+  const float edge0 = (PHASE != 2 && tid < hs.n_sink) ? row[tid] : -INFINITY;
+  const float edge1 = (PHASE != 2 && tid < hs.n_win) ? row[hs.mid_hi + tid] : -INFINITY;
   const int edge0_blk = kv_block<kCode>(A.L, seq, min(tid, n - 1));
   const int edge1_blk = kv_block<kCode>(A.L, seq, min(hs.mid_hi + tid, n - 1));
   const uint32_t row0_code = row_code(0u);
@@ -203,8 +209,8 @@ __global__ __launch_bounds__(NT, FD > 0 ? 1 : 4) void head_kernel(HeadArgs A) {
   S1.stream = 1u;
   S1.dbg = A.dbg ? A.dbg + 300 : nullptr;
   DrawBatch spec0 = {}, spec1 = {};
-  const bool want0 = hs.n_s > 0 && A.phase != 2 && hs.b0 < hs.n_s;
-  const bool want1 = hs.n_s > 0 && A.phase != 1 && !A.nested;  // (a nested final sample rarely draws at all)
+  const bool want0 = hs.n_s > 0 && PHASE != 2 && hs.b0 < hs.n_s;
+  const bool want1 = hs.n_s > 0 && PHASE != 1 && !A.nested;  // (a nested final sample rarely draws at all)
   const int n_sub = (n + kSubTile - 1) / kSubTile;
   const int sub_lo = (hs.mid_lo + kSubTile - 1) / kSubTile, sub_hi = hs.mid_hi / kSubTile;  // whole middle sub-tiles
   const bool sub_resident = n_sub <= SU * NT;
@@ -348,7 +354,7 @@ __global__ __launch_bounds__(NT, FD > 0 ? 1 : 4) void head_kernel(HeadArgs A) {
     }
   };
   // ---- I_t (Algorithm 1, top-k step) ----
-  if (A.phase != 2) {
+  if (PHASE != 2) {
     const int mid_len = hs.mid_hi - hs.mid_lo;
     if (hs.k > 0) {
       float sT = -INFINITY;
@@ -772,7 +778,7 @@ __global__ __launch_bounds__(NT, FD > 0 ? 1 : 4) void head_kernel(HeadArgs A) {
   // by the general path only.)
   // The lists of I_f, once wpre is complete (and, with the fused gather, this workgroup's share of them in LDS).
   auto write_lists = [&]() {
-    if (A.phase == 2) return;
+    if (PHASE == 2) return;
     // ascending list of the top-k tokens
     if (hs.k > 0) {
       if (NT >= 1024 && n_wide_used) {
@@ -852,9 +858,9 @@ __global__ __launch_bounds__(NT, FD > 0 ? 1 : 4) void head_kernel(HeadArgs A) {
   float es[UF];
   {
     const uint32_t ns = (uint32_t)hs.n_s, c0 = (uint32_t)hs.b0;
-    const bool usual = kTwoStreams && A.phase == 0 && (kFused || (!A.ascending && !A.nested)) && pair_made && hs.n_s > 0 &&
+    const bool usual = kTwoStreams && PHASE == 0 && (kFused || (!A.ascending && !A.nested)) && pair_made && hs.n_s > 0 &&
                        c0 < ns && 2u * c0 <= ns;
-    const bool listed = A.phase != 2 && hs.k > 0;
+    const bool listed = PHASE != 2 && hs.k > 0;
     auto test_draws = [&]() {
       const DrawBatch& B = half ? spec1 : spec0;
       acc_bits = B.first & ~O::test_bits4(bm_f, B.tok);
@@ -910,7 +916,7 @@ __global__ __launch_bounds__(NT, FD > 0 ? 1 : 4) void head_kernel(HeadArgs A) {
       }
     }
   }
-  if (A.phase != 2) {
+  if (PHASE != 2) {
     // weights of the sink and window tokens (their scores were requested at the start)
     acc_f32 += __expf(edge0 - m) + __expf(edge1 - m);  // exp(-inf) = 0 for threads without a token
     for (int i = tid + NT; i < hs.n_sink; i += NT) acc_f32 += __expf(row[i] - m);
@@ -941,7 +947,7 @@ __global__ __launch_bounds__(NT, FD > 0 ? 1 : 4) void head_kernel(HeadArgs A) {
     if (my_nf > UF * NG) load_rows(glist, glist_sc, UF * NG, my_nf, es, ev, ScInLds{});
   }
   if (hs.n_s > 0 && !fast_base) {
-    if (A.phase != 2) {
+    if (PHASE != 2) {
       Emit E0 = emit_to(idx + A.seg_base, (uint32_t)A.b0_max);
       E0.global = writer;
       const int f = O::draw_sample(S0, hs, (uint32_t)hs.b0, spec0, want0, A.small_batches, E0, &acc_w, &acc_w2, sm);
@@ -957,7 +963,7 @@ __global__ __launch_bounds__(NT, FD > 0 ? 1 : 4) void head_kernel(HeadArgs A) {
       }
     }
   }
-  if (A.phase == 1) {
+  if constexpr (PHASE == 1) {
     if (tid == 0) {
       HeadRec r;
       r.m = m;
@@ -1128,7 +1134,7 @@ __global__ __launch_bounds__(NT, FD > 0 ? 1 : 4) void head_kernel(HeadArgs A) {
   }
   if (tid == 0 && writer) {
     int32_t* c = A.out_counts + (int64_t)bh * 8;
-    const int prev = (A.phase == 2) ? c[7] : 0;
+    const int prev = (PHASE == 2) ? c[7] : 0;
     c[0] = hs.n_sink;
     c[1] = hs.n_win;
     c[2] = hs.k;
@@ -1241,17 +1247,27 @@ __global__ __launch_bounds__(NT, FD > 0 ? 1 : 4) void head_kernel(HeadArgs A) {
 
 typedef void (*HeadKernel)(HeadArgs);
 // The instantiation for a plan: workgroup size; with the fused gather also head dimension and cache layout.
-HeadKernel head_kernel_for(const Plan& pl, bool fused) {
-  if (fused) {
-    const bool paged = pl.p.kv_layout == VATT_LAYOUT_PAGED, alone = pl.fuse_splits == 1;
-    if (pl.p.head_dim == 128) {
-      if (alone) return paged ? head_kernel<kHeadThreads, 128, true, true> : head_kernel<kHeadThreads, 128, false, true>;
-      return paged ? head_kernel<kHeadThreads, 128, true> : head_kernel<kHeadThreads, 128, false>;
-    }
-    if (alone) return paged ? head_kernel<kHeadThreads, 64, true, true> : head_kernel<kHeadThreads, 64, false, true>;
-    return paged ? head_kernel<kHeadThreads, 64, true> : head_kernel<kHeadThreads, 64, false>;
+HeadKernel fused_kernel_for(int d, bool paged, bool alone) {
+  if (d == 128) {
+    if (alone) return paged ? head_kernel<kHeadThreads, 128, true, true> : head_kernel<kHeadThreads, 128, false, true>;
+    return paged ? head_kernel<kHeadThreads, 128, true> : head_kernel<kHeadThreads, 128, false>;
   }
-  return pl.head_threads == kHeadThreadsLong ? head_kernel<kHeadThreadsLong, 0, false> : head_kernel<kHeadThreads, 0, false>;
+  if (alone) return paged ? head_kernel<kHeadThreads, 64, true, true> : head_kernel<kHeadThreads, 64, false, true>;
+  return paged ? head_kernel<kHeadThreads, 64, true> : head_kernel<kHeadThreads, 64, false>;
+}
+template <int NT, bool OPTIONS>
+HeadKernel head_kernel_for(int phase) {
+  return phase == 0   ? head_kernel<NT, 0, false, false, 0, OPTIONS>
+         : phase == 1 ? head_kernel<NT, 0, false, false, 1, OPTIONS>
+                      : head_kernel<NT, 0, false, false, 2, OPTIONS>;
+}
+HeadKernel head_kernel_for(int threads, int phase, bool options) {
+  if (threads == kHeadThreadsLong) return options ? head_kernel_for<kHeadThreadsLong, true>(phase) : head_kernel_for<kHeadThreadsLong, false>(phase);
+  return options ? head_kernel_for<kHeadThreads, true>(phase) : head_kernel_for<kHeadThreads, false>(phase);
+}
+bool head_options(const Plan& pl) {
+  return pl.nested_samples || pl.ascending_samples || pl.topk_general_path || pl.sampler_small_batches || pl.range_factor > 0.0 ||
+         pl.budget_multiple != 1;
 }
 
 }  // namespace
@@ -1260,15 +1276,21 @@ hipError_t set_kernel_attributes(const Plan& pl) {
   // The limit on dynamic LDS belongs to the kernel, not to the plan: it is raised to all a CU has (less the
   // kernels' static part), so that plans of different capacities can be used in any order.
   const int cap = 160 * 1024 - (int)head_kernel_static_lds_bytes();
-  const HeadKernel kernels[10] = {head_kernel<kHeadThreads, 0, false>,           head_kernel<kHeadThreadsLong, 0, false>,
-                                  head_kernel<kHeadThreads, 128, false>,        head_kernel<kHeadThreads, 128, true>,
-                                  head_kernel<kHeadThreads, 64, false>,         head_kernel<kHeadThreads, 64, true>,
-                                  head_kernel<kHeadThreads, 128, false, true>,  head_kernel<kHeadThreads, 128, true, true>,
-                                  head_kernel<kHeadThreads, 64, false, true>,   head_kernel<kHeadThreads, 64, true, true>};
-  for (const HeadKernel f : kernels) {
-    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(f), hipFuncAttributeMaxDynamicSharedMemorySize, cap);
-    if (e != hipSuccess) return e;
-  }
+  auto raise = [&](HeadKernel f) {
+    return hipFuncSetAttribute(reinterpret_cast<const void*>(f), hipFuncAttributeMaxDynamicSharedMemorySize, cap);
+  };
+  for (const int threads : {kHeadThreads, kHeadThreadsLong})
+    for (const int phase : {0, 1, 2})
+      for (const bool options : {false, true}) {
+        const hipError_t e = raise(head_kernel_for(threads, phase, options));
+        if (e != hipSuccess) return e;
+      }
+  for (const int d : {64, 128})
+    for (const bool paged : {false, true})
+      for (const bool alone : {false, true}) {
+        const hipError_t e = raise(fused_kernel_for(d, paged, alone));
+        if (e != hipSuccess) return e;
+      }
   return set_given_kernel_attributes(pl);
 }
 
@@ -1300,7 +1322,7 @@ hipError_t launch_head(const Plan& pl, int phase, const int32_t* seq_lens, const
   HeadArgs A;
   fill_head_args(A, pl, phase, seq_lens, seq_seeds, ws, out_idx, out_counts, out_budget_raw, out_stats);
   const vatt_params& p = pl.p;
-  hipLaunchKernelGGL(head_kernel_for(pl, false), dim3(p.n_q_heads, pl.vbatch), dim3(pl.head_threads), pl.head_lds_bytes, st, A);
+  hipLaunchKernelGGL(head_kernel_for(pl.head_threads, phase, head_options(pl)), dim3(p.n_q_heads, pl.vbatch), dim3(pl.head_threads), pl.head_lds_bytes, st, A);
   return hipGetLastError();
 }
 
@@ -1364,7 +1386,8 @@ hipError_t launch_head_fused(const Plan& pl, const void* v, const int32_t* block
   A.group = pl.group;
   A.glist_cap = fused_glist_cap(pl, pl.fuse_splits);
   A.dlist_cap = fused_dlist_cap(pl, pl.fuse_splits);
-  hipLaunchKernelGGL(head_kernel_for(pl, true), dim3(p.n_q_heads, pl.vbatch, pl.fuse_splits), dim3(kHeadThreads),
+  const HeadKernel kernel = fused_kernel_for(p.head_dim, p.kv_layout == VATT_LAYOUT_PAGED, pl.fuse_splits == 1);
+  hipLaunchKernelGGL(kernel, dim3(p.n_q_heads, pl.vbatch, pl.fuse_splits), dim3(kHeadThreads),
                      fused_head_lds_bytes(pl, pl.fuse_splits), st, A);
   return hipGetLastError();
 }
