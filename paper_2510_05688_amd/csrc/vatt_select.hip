@@ -42,8 +42,9 @@ namespace {
 // 0.4 us, and the split arithmetic these 1.4 us).
 // PHASE: 0 everything (denominator target), 1 through the base sample, 2 budget and final sample (targets N and SDPA).
 // OPTIONS: a plan with an option set that the usual call does without (head_options) has a kernel of its own; without them the
-// selection-only kernel, which is at its register limit, takes 34.7 instead of 36.7 us for 16 x 32K tokens.
-template <int NT, int FD, bool PAGED, bool ALONE = false, int PHASE = 0, bool OPTIONS = true>
+// selection-only kernel, which is at its register limit, takes 33.6 instead of 36.5 us for 16 x 32K tokens, the fused one 20.0 instead
+// of 20.4 for 1 x 32K and 12.7 instead of 13.4 for one head of 1K.
+template <int NT, int FD, bool PAGED, bool ALONE, int PHASE, bool OPTIONS>
 __global__ __launch_bounds__(NT, FD > 0 ? 1 : 4) void head_kernel(HeadArgs A) {
   touch_args<HeadArgs>();
   if constexpr (FD > 0 || !OPTIONS) A.nested = A.ascending = 0;  // (in the fused kernel too: what it does not serve has no code there, 0.3 us)
@@ -1247,13 +1248,14 @@ __global__ __launch_bounds__(NT, FD > 0 ? 1 : 4) void head_kernel(HeadArgs A) {
 
 typedef void (*HeadKernel)(HeadArgs);
 // The instantiation for a plan: workgroup size; with the fused gather also head dimension and cache layout.
-HeadKernel fused_kernel_for(int d, bool paged, bool alone) {
-  if (d == 128) {
-    if (alone) return paged ? head_kernel<kHeadThreads, 128, true, true> : head_kernel<kHeadThreads, 128, false, true>;
-    return paged ? head_kernel<kHeadThreads, 128, true> : head_kernel<kHeadThreads, 128, false>;
-  }
-  if (alone) return paged ? head_kernel<kHeadThreads, 64, true, true> : head_kernel<kHeadThreads, 64, false, true>;
-  return paged ? head_kernel<kHeadThreads, 64, true> : head_kernel<kHeadThreads, 64, false>;
+template <int D, bool PAGED>
+HeadKernel fused_kernel_for(bool alone, bool options) {
+  if (alone) return options ? head_kernel<kHeadThreads, D, PAGED, true, 0, true> : head_kernel<kHeadThreads, D, PAGED, true, 0, false>;
+  return options ? head_kernel<kHeadThreads, D, PAGED, false, 0, true> : head_kernel<kHeadThreads, D, PAGED, false, 0, false>;
+}
+HeadKernel fused_kernel_for(int d, bool paged, bool alone, bool options) {
+  if (d == 128) return paged ? fused_kernel_for<128, true>(alone, options) : fused_kernel_for<128, false>(alone, options);
+  return paged ? fused_kernel_for<64, true>(alone, options) : fused_kernel_for<64, false>(alone, options);
 }
 template <int NT, bool OPTIONS>
 HeadKernel head_kernel_for(int phase) {
@@ -1287,10 +1289,11 @@ hipError_t set_kernel_attributes(const Plan& pl) {
       }
   for (const int d : {64, 128})
     for (const bool paged : {false, true})
-      for (const bool alone : {false, true}) {
-        const hipError_t e = raise(fused_kernel_for(d, paged, alone));
-        if (e != hipSuccess) return e;
-      }
+      for (const bool alone : {false, true})
+        for (const bool options : {false, true}) {
+          const hipError_t e = raise(fused_kernel_for(d, paged, alone, options));
+          if (e != hipSuccess) return e;
+        }
   return set_given_kernel_attributes(pl);
 }
 
@@ -1386,7 +1389,7 @@ hipError_t launch_head_fused(const Plan& pl, const void* v, const int32_t* block
   A.group = pl.group;
   A.glist_cap = fused_glist_cap(pl, pl.fuse_splits);
   A.dlist_cap = fused_dlist_cap(pl, pl.fuse_splits);
-  const HeadKernel kernel = fused_kernel_for(p.head_dim, p.kv_layout == VATT_LAYOUT_PAGED, pl.fuse_splits == 1);
+  const HeadKernel kernel = fused_kernel_for(p.head_dim, p.kv_layout == VATT_LAYOUT_PAGED, pl.fuse_splits == 1, head_options(pl));
   hipLaunchKernelGGL(kernel, dim3(p.n_q_heads, pl.vbatch, pl.fuse_splits), dim3(kHeadThreads),
                      fused_head_lds_bytes(pl, pl.fuse_splits), st, A);
   return hipGetLastError();
