@@ -149,6 +149,7 @@ struct HeadOps {
     BlockScanSmem<NT> scan;
     double red[3][SW];
     uint32_t again[2];
+    uint32_t last_block;  // Philox block that completed a sample
     BlockScanSmem<NT> scan_once[4];  // for scans that run once in a launch and need no barrier before them
   };
 
@@ -346,15 +347,22 @@ struct HeadOps {
     VATT_STAMP(S.dbg, 4);
   }
 
+  // Philox blocks of a batch when `remaining` accepted draws are asked for.
+  static __device__ __forceinline__ int first_blocks(int small_batches, uint32_t remaining) {
+    return (small_batches || remaining <= 128u) ? kSmallBatchBlocks : (remaining > 1024u ? min(NT, 1024) : min(NT, 256));
+  }
+
   // Draw a sample of c residual tokens for the stream described by S.  `taken` must be all zero on entry
   // unless `spec` carries the first batch (have_spec; made from block 0 with make_batch), `scratch` all zero.
   // Writes the token list to dst (acceptance order, or ascending when the sample is a complement) and, when
   // sum_w is given, adds exp(s_i - m) and its square over the sample to this thread's partial sums.
   // have, blk: the first `have` tokens, from the Philox blocks before blk, are listed already (no complement).
-  // Returns flag bits: 1 complement regime, 2 more than one batch, 4 draw cap reached.
+  // Returns flag bits: 1 complement regime, 2 more than one batch, 4 draw cap reached.  by_rule: bit 2 says whether the sample
+  // needs more than a first batch of first_blocks(), whatever batches it was made from.
   static __device__ __forceinline__ int draw_sample(const Sampler& S, const HeadSizes& hs, uint32_t c, const DrawBatch& spec, bool have_spec,
                                     int small_batches, const Emit& E, double* sum_w,
-                                    double* sum_w2, HeadSmem& sm, uint32_t have = 0u, uint32_t blk = 0u) {
+                                    double* sum_w2, HeadSmem& sm, uint32_t have = 0u, uint32_t blk = 0u,
+                                    bool by_rule = false) {
     const int tid = threadIdx.x;
     const int words = (hs.n + 31) >> 5;
     const uint32_t ns = (uint32_t)hs.n_s;
@@ -372,6 +380,7 @@ struct HeadOps {
     int batches = blk > 0u ? 1 : 0;
     bool use_spec = have_spec;
     double aw = 0.0, aw2 = 0.0;
+    const uint32_t rule = (uint32_t)first_blocks(small_batches, target);
     while (have < target) {
       if ((uint64_t)blk * 4ull >= (uint64_t)S.cap) break;
       DrawBatch B;
@@ -380,8 +389,7 @@ struct HeadOps {
         use_spec = false;
       } else {
         const uint32_t remaining = target - have;
-        const int blocks = (small_batches || remaining <= 128u) ? kSmallBatchBlocks
-                                                                  : (remaining > 1024u ? min(NT, 1024) : min(NT, 256));
+        const int blocks = first_blocks(small_batches, remaining);
         make_batch(B, S, hs, blk, blocks, blk > 0, false, sm, (int)threadIdx.x);
       }
       ++batches;
@@ -397,6 +405,7 @@ struct HeadOps {
       for (int e = 0; e < 4; ++e) {
         const bool a = (acc >> e) & 1u;
         const bool take = a && pos < room;
+        if (by_rule && take && pos + 1u == room) sm.last_block = blk + (uint32_t)tid;
         if (!invert) {
           if (take) emit_tok(E, have + pos, (int32_t)B.tok[e]);
           if (take && E.sc_dst && B.have_sc && have + pos < E.dst_cap) E.sc_dst[have + pos] = B.sc[e];
@@ -415,8 +424,9 @@ struct HeadOps {
       blk += (uint32_t)B.blocks;
       VATT_STAMP(S.dbg, 12);
     }
-    if (batches > 1) flags |= 2;
+    if (!by_rule && batches > 1) flags |= 2;
     __syncthreads();
+    if (by_rule && target > 0u && (have < target ? rule * 4u < S.cap : sm.last_block >= rule)) flags |= 2;
     if (have < target) {
       // draw cap reached: complete with the lowest-index residual tokens not yet accepted
       flags |= 4;

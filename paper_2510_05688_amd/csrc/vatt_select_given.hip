@@ -51,15 +51,20 @@ __global__ __launch_bounds__(NT) void given_topk_kernel(HeadArgs A) {
   uint64_t* cand = reinterpret_cast<uint64_t*>(dyn_smem + ((sizeof(HeadSmem) + 15) & ~size_t(15)));
   uint32_t* bm_f = reinterpret_cast<uint32_t*>(cand + kCandCap) + kCandCap;
   uint32_t* taken = bm_f + words_max;
-  uint32_t* scratch = taken + 2 * words_max;
-  uint32_t* wpre = scratch + words_max;
+  uint32_t* taken1 = taken + words_max;
+  uint32_t* scratch = taken1 + words_max;
+  // (the fused forms have the LDS of a 512-thread head_kernel, with a second scratch bitmap and mail slots for the final sample's
+  // stream, where the first phase makes both first batches at once; the others that of the plan's, which on long rows has one of each)
+  uint32_t* scratch1 = kFused ? scratch + words_max : scratch;
+  uint32_t* wpre = scratch1 + words_max;
   uint32_t* mail = wpre + words_max;
+  uint32_t* mail1 = kFused ? mail + kMailSlots : mail;
   // fused gather (second phase): this workgroup's share of the final sample, and the cross-wave sums
-  uint32_t* dlist = mail + kMailSlots;
+  uint32_t* dlist = mail1 + kMailSlots;
   float* g_red = reinterpret_cast<float*>(dlist + (kFused ? A.dlist_cap : 0));
   // fused scores (first phase): this workgroup's run of I_f, its share of the base sample and, for a base sample
   // from the random cache, the slots of that share
-  uint32_t* glist = mail + kMailSlots;
+  uint32_t* glist = mail1 + kMailSlots;
   uint32_t* blist = glist + (kFused ? A.glist_cap : 0);
   uint32_t* bslot = blist + (kFused ? A.dlist_cap : 0);
   int32_t* idx = A.out_idx + (int64_t)bh * A.idx_cap;
@@ -81,8 +86,9 @@ __global__ __launch_bounds__(NT) void given_topk_kernel(HeadArgs A) {
     }
   }
   const int cnt = PHASE == 0 ? min(max(A.given_cnt[bh], 0), A.k_max) : rec.k;  // entries of the list of top-k tokens
-  // (loads without a condition around them, of something valid where there is nothing to load: the list may have no room at all)
-  const int32_t* list = PHASE != 0 ? idx + A.seg_topk : A.k_max > 0 ? A.given_idx + (int64_t)bh * A.k_max : idx;
+  // (loads without a condition around them, of something valid where there is nothing to load: an empty list of the caller's may
+  // have no memory behind it)
+  const int32_t* list = PHASE != 0 ? idx + A.seg_topk : cnt > 0 ? A.given_idx + (int64_t)bh * A.k_max : idx;
   // (four entries per thread are read before any is used: a read behind a condition waits for the one before)
   constexpr int U = 4;
   auto load_list = [&](int t0, int (&g)[U]) {
@@ -165,6 +171,10 @@ __global__ __launch_bounds__(NT) void given_topk_kernel(HeadArgs A) {
     bm_f[w] = 0;
     taken[w] = 0;
     scratch[w] = 0;
+    if constexpr (kFused && PHASE == 0) {
+      taken1[w] = 0;
+      scratch1[w] = 0;
+    }
   }
   __syncthreads();
   Sampler S;
@@ -187,7 +197,14 @@ __global__ __launch_bounds__(NT) void given_topk_kernel(HeadArgs A) {
   S.m = 0.f;
   S.dbg = nullptr;
   DrawBatch spec = {};
-  bool have_spec = false;
+  bool have_spec = false, pair_made = false;
+  int blocks1 = 0;
+  // leaves a Philox block's four draws of the final sample's first batch for the second phase
+  auto store_final = [&](int block, const uint32_t (&tok)[4], uint32_t ok, uint32_t first, int blocks, bool made) {
+    const int64_t at = (int64_t)bh * NT + block;
+    const_cast<uint4*>(A.pre_tok)[at] = make_uint4(tok[0], tok[1], tok[2], tok[3]);
+    const_cast<uint32_t*>(A.pre_flags)[at] = ok | first << 4 | (made ? 256u : 0u) | (uint32_t)blocks << 16;
+  };
   // Philox blocks of the final sample's first batch: enough for the base sample's size, and for a larger sample as many as half
   // of the threads make
   auto final_blocks = [&](const HeadSizes& he) {
@@ -213,10 +230,29 @@ __global__ __launch_bounds__(NT) void given_topk_kernel(HeadArgs A) {
     he.n_s = mid_len - he.k;
     he.b0 = he.n_s > 0 ? base_count_of(he.n_s, A.sp) : 0;
     have_spec = he.n_s > 0 && he.b0 < he.n_s && (PHASE == 0 ? !A.rcache : !A.nested);
-    if (have_spec) {
-      const int blocks = PHASE == 0 ? likely_blocks(A.small_batches ? kSmallBatchBlocks : NT, he, base_draws(he)) : final_blocks(he);
-      O::make_batch(spec, S, hs, 0u, blocks, false, false, sm, tid);
+    const int blocks = PHASE == 0 ? likely_blocks(A.small_batches ? kSmallBatchBlocks : NT, he, base_draws(he)) : final_blocks(he);
+    if constexpr (kFused && PHASE == 0) {
+      // first batches of both samples at once where half of the workgroup holds each (as in the kernel of the scored path):
+      // small steps, whose rows would not cover the second one (below), 28.1 -> 25.5 us for 3 x 0.7K tokens
+      blocks1 = final_blocks(he);
+      pair_made = have_spec && blocks <= NT / 2 && blocks1 <= NT / 2;
+      if (pair_made) {
+        Sampler S1 = S;
+        S1.taken = taken1;
+        S1.scratch = scratch1;
+        S1.mail = mail1;
+        S1.stream = 1u;
+        const bool upper = tid >= NT / 2;
+        DrawBatch mine = {};
+        O::make_batch(mine, upper ? S1 : S, hs, 0u, upper ? blocks1 : blocks, false, false, sm, upper ? tid - NT / 2 : tid);
+        spec = mine;
+        spec.blocks = blocks;
+        spec.ok = upper ? 0u : mine.ok;
+        spec.first = upper ? 0u : mine.first;
+        if ((int)split == A.splits - 1) store_final(upper ? tid - NT / 2 : tid + NT / 2, mine.tok, upper ? mine.ok : 0u, upper ? mine.first : 0u, blocks1, true);
+      }
     }
+    if (have_spec && !pair_made) O::make_batch(spec, S, hs, 0u, blocks, false, false, sm, tid);
   }
   if constexpr (kFused && PHASE != 0) load_fixed_rows();
   auto mark = [&](int t0, const int (&g)[U]) {
@@ -341,7 +377,7 @@ __global__ __launch_bounds__(NT) void given_topk_kernel(HeadArgs A) {
         E0.shift = shift;
         E0.split = split;
       }
-      const int f = O::draw_sample(S, hs, (uint32_t)hs.b0, spec, have_spec, A.small_batches, E0, nullptr, nullptr, sm);
+      const int f = O::draw_sample(S, hs, (uint32_t)hs.b0, spec, have_spec, A.small_batches, E0, nullptr, nullptr, sm, 0u, 0u, true);
       flags |= ((f & 1) ? kFlagBaseComplement : 0) | ((f & 2) ? kFlagBaseBatches : 0) | ((f & 4) ? kFlagDrawCap : 0);
       if (!kFused && A.ascending && !(f & 1))
         O::sort_ascending(idx + A.seg_base, (uint32_t)min(hs.b0, A.b0_max), scratch, wpre, n, sm);
@@ -415,7 +451,7 @@ __global__ __launch_bounds__(NT) void given_topk_kernel(HeadArgs A) {
       uint4 kf[UF], kb[UF];
       if (my_nf > 0) load_listed(glist, g_grp, my_nf, kf);
       if (my_nb > 0) load_base(g_grp, kb);
-      if ((int)split == A.splits - 1) {
+      if ((int)split == A.splits - 1 && !pair_made) {
         // The first batch of the final sample's draws, for all workgroups of the head in the second phase, where it would
         // stand in front of everything else.  Here it is made while the rows are on their way.
         const bool make = hs.n_s > 0 && hs.b0 < hs.n_s;
@@ -428,9 +464,7 @@ __global__ __launch_bounds__(NT) void given_topk_kernel(HeadArgs A) {
           S1.stream = 1u;
           O::make_batch(mine, S1, hs, 0u, blocks, false, false, sm, tid);
         }
-        const int64_t at = (int64_t)bh * NT + tid;
-        const_cast<uint4*>(A.pre_tok)[at] = make_uint4(mine.tok[0], mine.tok[1], mine.tok[2], mine.tok[3]);
-        const_cast<uint32_t*>(A.pre_flags)[at] = mine.ok | mine.first << 4 | (make ? 256u : 0u) | (uint32_t)blocks << 16;
+        store_final(tid, mine.tok, mine.ok, mine.first, blocks, make);
       }
       for (int j0 = g_grp; j0 - g_grp < my_nf; j0 += NG * UF) {
         if (j0 != g_grp) load_listed(glist, j0, my_nf, kf);
@@ -583,7 +617,13 @@ __global__ __launch_bounds__(NT) void given_topk_kernel(HeadArgs A) {
   }
   int flags = 0;
   const bool fast_dyn = spec_dyn && (uint32_t)bfin <= tot1 && 2 * bfin <= hs.n_s;  // the first batch of draws holds the sample
-  if (fast_dyn) list_draws((uint32_t)hs.b0, (uint32_t)bfin, writer);
+  if (fast_dyn) {
+    list_draws((uint32_t)hs.b0, (uint32_t)bfin, writer);
+    // (a first batch of the sample's own size would not have held it: a thread makes a block, so whole waves count)
+    uint32_t held = 0;
+    for (int w = 0; w < O::first_blocks(A.small_batches, (uint32_t)bfin) / kWave; ++w) held += sm.scan_once[2].wave_total[w];
+    if (held < (uint32_t)bfin) flags |= kFlagDynBatches;
+  }
   if (bfin > 0 && !fast_dyn) {
     Emit E1 = emit_to(idx + A.seg_dyn, (uint32_t)A.b_max);
     if (kFused) {
@@ -596,7 +636,7 @@ __global__ __launch_bounds__(NT) void given_topk_kernel(HeadArgs A) {
     const int f = (!kFused && A.nested)
                       ? O::draw_nested(S, hs, (uint32_t)hs.b0, (uint32_t)bfin, bm_f, idx + A.seg_base,
                                        idx + A.seg_dyn, (uint32_t)A.b_max, A.small_batches, sm)
-                      : O::draw_sample(S, hs, (uint32_t)bfin, spec, have_spec, A.small_batches, E1, nullptr, nullptr, sm);
+                      : O::draw_sample(S, hs, (uint32_t)bfin, spec, have_spec, A.small_batches, E1, nullptr, nullptr, sm, 0u, 0u, true);
     flags |= ((f & 1) ? kFlagDynComplement : 0) | ((f & 2) ? kFlagDynBatches : 0) | ((f & 4) ? kFlagDrawCap : 0);
     if (!kFused && A.ascending && !A.nested && !(f & 1))
       O::sort_ascending(idx + A.seg_dyn, (uint32_t)min(bfin, A.b_max), scratch, wpre, n, sm);

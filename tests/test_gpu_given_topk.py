@@ -238,3 +238,29 @@ def test_given_topk_counts_out_of_range_are_clamped():
         supplied = np.empty(0, dtype=np.int64) if h % 2 == 0 else idx[0, h].astype(np.int64)
         check_head_given(wl, res, 0, h, supplied, label="clamped counts")
     sess.close()
+
+
+@pytest.mark.parametrize("paged", [False, True])
+@pytest.mark.parametrize("epsilon,base", [(0.05, 0.025), (0.02, 0.01), (0.004, 0.01), (0.05, 0.6)])
+def test_final_samples_on_both_sides_of_the_first_draws(epsilon, base, paged):
+    """Final samples that the first batch of draws holds, that need further ones, and that are complements (as is the base
+    sample of 0.6 of the residual); fused and separate kernels, against the oracle."""
+    wl = workloads.small_gqa(seed=47, batch=2, n=6000, seq_lens=[6000, 901], epsilon=epsilon, base_frac=base)
+    sess = _session(wl, paged)
+    supplied = {(b, h): _oracle_topk(wl, b, h) for b in range(wl.batch) for h in range(wl.n_q_heads)}
+    res = _run_given(sess, wl, supplied)
+    for (b, h), arr in supplied.items():
+        check_head_given(wl, res, b, h, arr, label="draws")
+    sess.close()
+
+
+def test_an_empty_list_needs_no_memory():
+    wl = workloads.small_gqa(seed=48, batch=1, n=2000)
+    sess = _session(wl)
+    res = _run_given(sess, wl, {})
+    sess.decode_given_topk(torch.zeros(1, dtype=torch.int32, device="cuda"),
+                           torch.zeros((1, wl.n_q_heads), dtype=torch.int32, device="cuda"))
+    again = sess.results_host()
+    for key in ("counts", "b_star"):
+        assert np.array_equal(res[key], again[key])
+    sess.close()
