@@ -154,16 +154,24 @@ __global__ __launch_bounds__(NT) void given_topk_kernel(HeadArgs A) {
       f_sc[u] = sp[place];
     }
   };
-  auto load_fixed_rows = [&]() {
+  // f(from, to) for the quarters of the UF rounds that a batch of `rows` rows (a whole-workgroup value) has
+  auto each_part = [](int rows, auto&& f) {
+    f(Int<0>{}, Int<UF / 4>{});
+    if (rows > UF / 4 * NG) f(Int<UF / 4>{}, Int<UF / 2>{});
+    if (rows > UF / 2 * NG) f(Int<UF / 2>{}, Int<UF>{});
+  };
+  auto load_fixed_rows = [&](int j0) {
     int blk[UF];
 #pragma unroll
     for (int u = 0; u < UF; ++u) {
       f_tok[u] = min(max(f_tok[u], 0), n - 1);
       blk[u] = kv_block<PAGED>(A.L, seq, f_tok[u]);
     }
+    each_part(f_hi - j0, [&](auto from, auto to) {
 #pragma unroll
-    for (int u = 0; u < UF; ++u)
-      f_v[u] = load_stream_16(A.v + kv_row_offset_in<PAGED>(A.L, seq, kvh, f_tok[u], blk[u]) + g_sub * 8);
+      for (int u = decltype(from)::value; u < decltype(to)::value; ++u)
+        f_v[u] = load_stream_16(A.v + kv_row_offset_in<PAGED>(A.L, seq, kvh, f_tok[u], blk[u]) + g_sub * 8);
+    });
   };
   if constexpr (kFused && PHASE != 0) load_fixed(f_lo);
 
@@ -254,7 +262,7 @@ __global__ __launch_bounds__(NT) void given_topk_kernel(HeadArgs A) {
     }
     if (have_spec && !pair_made) O::make_batch(spec, S, hs, 0u, blocks, false, false, sm, tid);
   }
-  if constexpr (kFused && PHASE != 0) load_fixed_rows();
+  if constexpr (kFused && PHASE != 0) load_fixed_rows(f_lo);
   auto mark = [&](int t0, const int (&g)[U]) {
 #pragma unroll
     for (int u = 0; u < U; ++u)
@@ -562,11 +570,13 @@ __global__ __launch_bounds__(NT) void given_topk_kernel(HeadArgs A) {
     for (int u = 0; u < UF; ++u) tok[u] = (int)min(dlist[min(j0 + u * NG, count - 1)], (uint32_t)(n - 1));
 #pragma unroll
     for (int u = 0; u < UF; ++u) blk[u] = kv_block<PAGED>(A.L, seq, tok[u]);  // (K and V share the block table)
+    each_part(count - (first & ~(NG - 1)), [&](auto from, auto to) {
 #pragma unroll
-    for (int u = 0; u < UF; ++u) {
-      dk[u] = load_stream_16(A.gk + kv_row_offset_in<PAGED>(A.Lk, seq, kvh, tok[u], blk[u]) + g_sub * 8);
-      dv[u] = load_stream_16(A.v + kv_row_offset_in<PAGED>(A.L, seq, kvh, tok[u], blk[u]) + g_sub * 8);
-    }
+      for (int u = decltype(from)::value; u < decltype(to)::value; ++u) {
+        dk[u] = load_stream_16(A.gk + kv_row_offset_in<PAGED>(A.Lk, seq, kvh, tok[u], blk[u]) + g_sub * 8);
+        dv[u] = load_stream_16(A.v + kv_row_offset_in<PAGED>(A.L, seq, kvh, tok[u], blk[u]) + g_sub * 8);
+      }
+    });
   };
   const int my_spec = kFused && spec_dyn ? min(share_of((uint32_t)hs.b0), A.dlist_cap) : 0;
   if constexpr (kFused) {
@@ -706,19 +716,22 @@ __global__ __launch_bounds__(NT) void given_topk_kernel(HeadArgs A) {
     for (int j0 = f_lo; j0 < f_hi; j0 += NG * UF) {
       if (j0 != f_lo) {
         load_fixed(j0);
-        load_fixed_rows();
+        load_fixed_rows(j0);
       }
+      each_part(f_hi - j0, [&](auto from, auto to) {
 #pragma unroll
-      for (int u = 0; u < UF; ++u)
-        if (j0 + g_grp + u * NG < f_hi) add_row(f_sc[u], f_v[u]);
+        for (int u = decltype(from)::value; u < decltype(to)::value; ++u)
+          if (j0 + g_grp + u * NG < f_hi) add_row(f_sc[u], f_v[u]);
+      });
     }
     // the final sample: every A.splits-th token, scores from the K rows, weights carry n_s / b
     const int my_nd = min(share_of((uint32_t)bfin), A.dlist_cap);
     const float tail_bias = bfin > 0 ? __logf((float)((double)hs.n_s / (double)bfin)) : 0.f;
     auto add_drawn = [&](int first, int count) {
       const int j0 = (first & ~(NG - 1)) + g_grp;
+      each_part(count - (first & ~(NG - 1)), [&](auto from, auto to) {
 #pragma unroll
-      for (int u = 0; u < UF; ++u) {
+      for (int u = decltype(from)::value; u < decltype(to)::value; ++u) {
         // (the lanes of a group stay together: every lane of the group computes the row's score)
         float a = 0.f;
         a = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2_t, dk[u].x), __builtin_bit_cast(bf16x2_t, qw[0]), a, false);
@@ -729,6 +742,7 @@ __global__ __launch_bounds__(NT) void given_topk_kernel(HeadArgs A) {
         const int j = j0 + u * NG;
         if (j >= first && j < count) add_row(s_row + tail_bias, dv[u]);
       }
+      });
     };
     int j_done = 0;
     if (my_spec > 0 && 2 * bfin <= hs.n_s) {  // (the rows of the first b0 tokens are at hand, unless the sample is a complement)
