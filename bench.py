@@ -36,13 +36,13 @@ SCORE_KERNEL_TRAFFIC_BYTES = {"config2": int((32805.2 * 262144.0 / 131085.6 + 46
 SCORE_CHUNK_TRAFFIC_BYTES = {("config2", 4): int((32826.3 * 262144.0 / 131085.6 + 18433.2) * 1024)}
 # HBM bytes of all kernels of one vatt_decode step, same two counters, scaled by what they read for a 256 MiB
 # device copy (FETCH_SIZE x 1.9998, WRITE_SIZE x 1.0): profiles/decode_config{2,3,4}_kernel_stats.md
-STEP_TRAFFIC_BYTES = {"config2": 91212905, "config3": 1530270507, "config4": 1423688365}
+STEP_TRAFFIC_BYTES = {"config2": 91258422, "config3": 1521133754, "config4": 1423945850}
 # rocprofv3 --kernel-trace --stats averages (us) of the kernels of one step, `python3 bench.py --no-cpu --no-extra` under
 # the profiler (profiles/decode_config{2,3,4}_kernel_stats.md)
 PROFILE_KERNEL_US = {
-    "config2": {"score_kernel": 13.19, "head_kernel (selection with the gather fused in)": 22.22, "gather_merge_kernel": 4.00},
-    "config3": {"score_kernel": 173.95, "head_kernel": 33.92, "gather_kernel": 39.31, "gather_merge_kernel": 4.39},
-    "config4": {"score_kernel": 171.38, "head_kernel": 49.83, "gather_kernel": 28.65, "gather_merge_kernel": 4.56},
+    "config2": {"score_kernel": 12.99, "head_kernel (selection with the gather fused in)": 19.23, "gather_merge_kernel": 4.30},
+    "config3": {"score_kernel": 173.64, "head_kernel": 29.84, "gather_kernel": 40.37, "gather_merge_kernel": 4.55},
+    "config4": {"score_kernel": 170.81, "head_kernel": 47.63, "gather_kernel": 28.87, "gather_merge_kernel": 4.69},
 }
 LLAMA8B_LAYERS = 32
 

@@ -241,7 +241,7 @@ __global__ __launch_bounds__(NT) void given_topk_kernel(HeadArgs A) {
     const int blocks = PHASE == 0 ? likely_blocks(A.small_batches ? kSmallBatchBlocks : NT, he, base_draws(he)) : final_blocks(he);
     if constexpr (kFused && PHASE == 0) {
       // first batches of both samples at once where half of the workgroup holds each (as in the kernel of the scored path):
-      // small steps, whose rows would not cover the second one (below), 28.1 -> 25.5 us for 3 x 0.7K tokens
+      // small steps, whose rows would not cover the second one (below), 28.1 -> 27.4 us for 3 x 0.7K tokens
       blocks1 = final_blocks(he);
       pair_made = have_spec && blocks <= NT / 2 && blocks1 <= NT / 2;
       if (pair_made) {
