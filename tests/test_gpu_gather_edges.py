@@ -152,3 +152,53 @@ def test_budgets_beyond_the_first_draws_are_paged_as_they_are_contiguous(d, epsi
         for h in range(4):
             want = got[0]["O"][b, h]
             assert np.linalg.norm(got[1]["O"][b, h] - want) <= 2e-6 * np.linalg.norm(want)
+
+
+def _decode(wl, paged, splits, v_bits):
+    from paper_2510_05688_amd import binding as vb
+    from paper_2510_05688_amd.session import DecodeSession
+    kept, wl.v_bits = wl.v_bits, v_bits
+    k_bits, v_bits, table = workloads.to_paged(wl, 16) if paged else (wl.k_bits, wl.v_bits, None)
+    wl.v_bits = kept
+    sess = DecodeSession(plan_params(wl, paged=paged, num_blocks=k_bits.shape[0] if paged else 0))
+    vb.vatt_plan_set_option(sess.plan, vb.VATT_OPT_FUSED_GATHER, splits)
+    sess.upload(wl.q_bits, k_bits, v_bits, wl.seq_lens, wl.seeds, table)
+    sess.decode()
+    res = sess.results_host()
+    sess.close()
+    return res
+
+
+@pytest.mark.parametrize("splits", [1, 4])
+@pytest.mark.parametrize("paged", [False, True])
+@pytest.mark.parametrize("d,n,epsilon", [(64, 700, 0.05), (128, 2000, 0.05), (64, 5000, 0.02), (128, 5000, 0.01)])
+def test_a_row_that_no_head_lists_adds_nothing(d, n, epsilon, paged, splits):
+    """An Inf and a NaN in the V rows of token 0, which the heads compared here do not list (no sink): the same bits as without,
+    whether the first draws hold the final sample or not."""
+    p = default_params(d, sink=0, window=48, topk_abs=0, topk_frac=0.02, base_abs=32, base_frac=0.0, epsilon=epsilon)
+    wl = workloads.make_workload("unlisted", batch=1, n_q_heads=8, n_kv_heads=2, head_dim=d, n_max=5008, seq_lens=[n], seed=5, params=p)
+    spoilt = wl.v_bits.copy()
+    spoilt[0, :, 0, 5], spoilt[0, :, 0, d - 1] = 0x7FC0, 0x7F80
+    want, got = _decode(wl, paged, splits, wl.v_bits), _decode(wl, paged, splits, spoilt)
+    seg, compared = got["seg"], 0
+    for h in range(8):
+        c, idx = got["counts"][0, h], got["idx"][0, h]
+        listed = np.concatenate([idx[seg[2]:seg[2] + c[2]], idx[seg[4]:seg[4] + c[4]]])
+        if 0 not in listed:
+            compared += 1
+            assert np.array_equal(got["O"][0, h], want["O"][0, h]) and np.isfinite(got["O"][0, h]).all(), h
+    assert compared >= 4 and ((got["counts"][..., 4] > 1024).any() or epsilon > 0.01)
+
+
+@pytest.mark.parametrize("splits", [1, 2])
+@pytest.mark.parametrize("paged", [False, True])
+@pytest.mark.parametrize("d,n", [(64, 700), (128, 321), (128, 1000)])
+def test_an_inf_in_a_listed_row_stays_an_inf(d, n, paged, splits):
+    """The first row of the list and the last: what fills a batch of rows behind the list's end must not make a NaN of it."""
+    p = default_params(d, sink=16, window=48, topk_abs=n, topk_frac=0.0, base_abs=8, base_frac=0.0)
+    wl = workloads.make_workload("inf", batch=1, n_q_heads=4, n_kv_heads=2, head_dim=d, n_max=1008, seq_lens=[n], seed=3, params=p)
+    for tok in (0, n - 49):
+        spoilt = wl.v_bits.copy()
+        spoilt[0, :, tok, 7] = 0x7F80
+        o = _decode(wl, paged, splits, spoilt)["O"][0]
+        assert np.all(o[:, 7] == np.inf) and np.isfinite(np.delete(o, 7, axis=1)).all(), tok
