@@ -169,7 +169,7 @@ def _decode(wl, paged, splits, v_bits):
     return res
 
 
-@pytest.mark.parametrize("splits", [1, 4])
+@pytest.mark.parametrize("splits", [0, 1, 4])
 @pytest.mark.parametrize("paged", [False, True])
 @pytest.mark.parametrize("d,n,epsilon", [(64, 700, 0.05), (128, 2000, 0.05), (64, 5000, 0.02), (128, 5000, 0.01)])
 def test_a_row_that_no_head_lists_adds_nothing(d, n, epsilon, paged, splits):
@@ -190,7 +190,7 @@ def test_a_row_that_no_head_lists_adds_nothing(d, n, epsilon, paged, splits):
     assert compared >= 4 and ((got["counts"][..., 4] > 1024).any() or epsilon > 0.01)
 
 
-@pytest.mark.parametrize("splits", [1, 2])
+@pytest.mark.parametrize("splits", [0, 1, 2])
 @pytest.mark.parametrize("paged", [False, True])
 @pytest.mark.parametrize("d,n", [(64, 700), (128, 321), (128, 1000)])
 def test_an_inf_in_a_listed_row_stays_an_inf(d, n, paged, splits):
@@ -202,3 +202,21 @@ def test_an_inf_in_a_listed_row_stays_an_inf(d, n, paged, splits):
         spoilt[0, :, tok, 7] = 0x7F80
         o = _decode(wl, paged, splits, spoilt)["O"][0]
         assert np.all(o[:, 7] == np.inf) and np.isfinite(np.delete(o, 7, axis=1)).all(), tok
+
+
+@pytest.mark.parametrize("paged", [False, True])
+@pytest.mark.parametrize("d", [64, 128])
+def test_an_inf_in_the_last_base_sample_row_stays_an_inf(d, paged):
+    """Output target: the statistics pass reads the base sample's rows last.  A base sample that is the whole residual ends
+    with the largest token before the window; an Inf in its V row makes the numerator's norm Inf, not NaN."""
+    n = 300
+    p = default_params(d, sink=16, window=48, topk_abs=8, topk_frac=0.0, base_abs=n, base_frac=0.0, target=2)
+    wl = workloads.make_workload("inf_base", batch=1, n_q_heads=4, n_kv_heads=2, head_dim=d, n_max=304, seq_lens=[n], seed=3, params=p)
+    spoilt = wl.v_bits.copy()
+    spoilt[0, :, n - 49, 7] = 0x7F80
+    res = _decode(wl, paged, 0, spoilt)
+    last = [res["idx"][0, h, res["seg"][3] + res["counts"][0, h, 3] - 1] for h in range(4)]
+    heads = [h for h in range(4) if last[h] == n - 49]
+    assert heads
+    for h in heads:
+        assert res["stats"][0, h, 3] == np.inf and res["O"][0, h, 7] == np.inf
