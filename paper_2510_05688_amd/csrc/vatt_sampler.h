@@ -15,6 +15,7 @@ constexpr uint32_t kInv32 = 0xffffffffu;
 // Mail slots in which the draws of repeated tokens find their earliest one (a power of two; the slot number and 8
 // more bits make a token, see kCapacityMax).
 constexpr uint32_t kMailSlots = 2048;
+constexpr int kMailTokens = 256;  // tokens that 8 bits tell apart in a slot
 // 32-bit words of a bitmap over n_max tokens: whole groups of four, which one store clears.
 __host__ __device__ constexpr int bitmap_words(int n_max) { return ((n_max + 127) >> 7) << 2; }
 
@@ -312,7 +313,8 @@ struct HeadOps {
     // draws whose token is proposed more than once in this batch
     uint32_t unresolved = B.ok & test_bits4(S.scratch, B.tok);
     uint32_t later = 0;
-    for (int round = 0;; ++round) {
+    // (a round settles a token of every slot in question, and no more than kMailTokens share one)
+    for (int round = 0; round < kMailTokens; ++round) {
       // (the slots in question are cleared first; the flag alternates, so that it can be cleared here as well)
 #pragma unroll
       for (int e = 0; e < 4; ++e)

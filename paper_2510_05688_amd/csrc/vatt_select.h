@@ -189,6 +189,31 @@ struct __align__(16) TopkSmem {
   uint32_t cand_n, qual_n;
 };
 
+// Where a selection workgroup of NT threads keeps what in its dynamic LDS, as offsets in 32-bit words: the kernels take their pointers
+// and the launches their sizes from here, so that the two cannot disagree.  TWO: the first batches of both sampler streams are made
+// at once, each with a scratch bitmap and mail slots of its own.  The lists of the fused kernels follow at `lists`.
+// (The kernel of the caller-supplied path has no candidates and steps over their place.)
+struct HeadLds {
+  uint32_t cand, qual, bm_f, taken0, taken1, scratch0, scratch1, wpre, mail0, mail1, lists;
+};
+template <int NT, bool TWO>
+__host__ __device__ constexpr HeadLds head_lds(int n_max) {
+  const uint32_t words = (uint32_t)bitmap_words(n_max);
+  HeadLds l{};
+  l.cand = (uint32_t)((sizeof(typename HeadOps<NT>::HeadSmem) + 15) / 16 * 4);
+  l.qual = l.cand + 2 * kCandCap;  // (candidates are 64-bit)
+  l.bm_f = l.qual + kCandCap;
+  l.taken0 = l.bm_f + words;
+  l.taken1 = l.taken0 + words;
+  l.scratch0 = l.taken1 + words;
+  l.scratch1 = TWO ? l.scratch0 + words : l.scratch0;
+  l.wpre = l.scratch1 + words;
+  l.mail0 = l.wpre + words;
+  l.mail1 = TWO ? l.mail0 + kMailSlots : l.mail0;
+  l.lists = l.mail1 + kMailSlots;
+  return l;
+}
+
 template <int NT, class View>
 struct TopkOps {
   static constexpr int SW = NT / kWave;

@@ -101,24 +101,19 @@ __global__ __launch_bounds__(NT, FD > 0 ? 1 : 4) void head_kernel(HeadArgs A) {
   const int words = (n + 31) >> 5;
 
   HeadSmem& sm = *reinterpret_cast<HeadSmem*>(dyn_smem);
-  uint64_t* cand = reinterpret_cast<uint64_t*>(dyn_smem + ((sizeof(HeadSmem) + 15) & ~size_t(15)));
-  uint32_t* qual = reinterpret_cast<uint32_t*>(cand + kCandCap);
-  uint32_t* bm_f = qual + kCandCap;
-  uint32_t* taken0 = bm_f + words_max;
-  uint32_t* taken1 = taken0 + words_max;
-  uint32_t* scratch = taken1 + words_max;
   // (the 512-thread kernel can generate the first batches of both streams at once: the final sample's stream
   // then needs a scratch bitmap and mail slots of its own)
   constexpr bool kTwoStreams = NT == kHeadThreads;
-  uint32_t* scratch1 = kTwoStreams ? scratch + words_max : scratch;
-  uint32_t* wpre = scratch1 + words_max;
-  uint32_t* mail = wpre + words_max;
-  uint32_t* mail1 = kTwoStreams ? mail + kMailSlots : mail;
+  const HeadLds at = head_lds<NT, kTwoStreams>(A.n_max);
+  uint32_t* lds = reinterpret_cast<uint32_t*>(dyn_smem);
+  uint64_t* cand = reinterpret_cast<uint64_t*>(lds + at.cand);
+  uint32_t *qual = lds + at.qual, *bm_f = lds + at.bm_f, *taken0 = lds + at.taken0, *taken1 = lds + at.taken1;
+  uint32_t *scratch = lds + at.scratch0, *scratch1 = lds + at.scratch1, *wpre = lds + at.wpre, *mail = lds + at.mail0, *mail1 = lds + at.mail1;
   // Histogram of the candidates' scores: in the mail slots of the final sample's stream, once its first batch is made.
   static_assert(kMailSlots == kBins, "the histogram takes the place of the mail slots");
   uint32_t* cand_hist = mail1;
   // fused gather: this workgroup's share of I_f and of the final sample, and the cross-wave sums
-  uint32_t* glist = mail1 + kMailSlots;
+  uint32_t* glist = lds + at.lists;
   uint32_t* dlist = glist + (kFused ? A.glist_cap : 0);
   // (the scores of the listed tokens, so that the gather requests V rows only)
   float* glist_sc = reinterpret_cast<float*>(dlist + (kFused ? A.dlist_cap : 0));
@@ -1304,11 +1299,7 @@ hipError_t set_kernel_attributes(const Plan& pl) {
 }
 
 size_t head_kernel_lds_bytes(int n_max, int head_threads) {
-  const size_t words_max = (size_t)bitmap_words(n_max);
-  const size_t fixed = head_threads == kHeadThreadsLong ? sizeof(HeadOps<kHeadThreadsLong>::HeadSmem)
-                                                        : sizeof(HeadOps<kHeadThreads>::HeadSmem);
-  return ((fixed + 15) & ~size_t(15)) + (size_t)kCandCap * (sizeof(uint64_t) + sizeof(uint32_t)) +
-         (head_threads == kHeadThreads ? 6 * words_max + 2 * kMailSlots : 5 * words_max + kMailSlots) * sizeof(uint32_t);
+  return sizeof(uint32_t) * (head_threads == kHeadThreadsLong ? head_lds<kHeadThreadsLong, false>(n_max) : head_lds<kHeadThreads, true>(n_max)).lists;
 }
 
 // LDS entries of a workgroup's share of I_f and of the final sample when `splits` workgroups share a head.

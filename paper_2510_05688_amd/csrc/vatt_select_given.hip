@@ -45,26 +45,20 @@ __global__ __launch_bounds__(NT) void given_topk_kernel(HeadArgs A) {
   const int seq = seq_of_pair(b, A.q_len), qtok = b - seq * A.q_len;  // (sequence, query token) of a multi-query step
   const int n = max(min(max(A.seq_lens[seq], 1), A.n_max) - (A.q_len - 1 - qtok), 1);  // clamp, then the causal cut
   HeadSizes hs = head_sizes(n, A.sp);
-  const int words_max = bitmap_words(A.n_max);
   const int words = (n + 31) >> 5;
   HeadSmem& sm = *reinterpret_cast<HeadSmem*>(dyn_smem);
-  uint64_t* cand = reinterpret_cast<uint64_t*>(dyn_smem + ((sizeof(HeadSmem) + 15) & ~size_t(15)));
-  uint32_t* bm_f = reinterpret_cast<uint32_t*>(cand + kCandCap) + kCandCap;
-  uint32_t* taken = bm_f + words_max;
-  uint32_t* taken1 = taken + words_max;
-  uint32_t* scratch = taken1 + words_max;
-  // (the fused forms have the LDS of a 512-thread head_kernel, with a second scratch bitmap and mail slots for the final sample's
-  // stream, where the first phase makes both first batches at once; the others that of the plan's, which on long rows has one of each)
-  uint32_t* scratch1 = kFused ? scratch + words_max : scratch;
-  uint32_t* wpre = scratch1 + words_max;
-  uint32_t* mail = wpre + words_max;
-  uint32_t* mail1 = kFused ? mail + kMailSlots : mail;
+  // (the fused forms have a second scratch bitmap and mail slots for the final sample's stream, where the first phase makes both first
+  // batches at once)
+  const HeadLds at = head_lds<NT, kFused>(A.n_max);
+  uint32_t* lds = reinterpret_cast<uint32_t*>(dyn_smem);
+  uint32_t *bm_f = lds + at.bm_f, *taken = lds + at.taken0, *taken1 = lds + at.taken1, *scratch = lds + at.scratch0, *scratch1 = lds + at.scratch1;
+  uint32_t *wpre = lds + at.wpre, *mail = lds + at.mail0, *mail1 = lds + at.mail1;
   // fused gather (second phase): this workgroup's share of the final sample, and the cross-wave sums
-  uint32_t* dlist = mail1 + kMailSlots;
+  uint32_t* dlist = lds + at.lists;
   float* g_red = reinterpret_cast<float*>(dlist + (kFused ? A.dlist_cap : 0));
   // fused scores (first phase): this workgroup's run of I_f, its share of the base sample and, for a base sample
   // from the random cache, the slots of that share
-  uint32_t* glist = mail1 + kMailSlots;
+  uint32_t* glist = lds + at.lists;
   uint32_t* blist = glist + (kFused ? A.glist_cap : 0);
   uint32_t* bslot = blist + (kFused ? A.dlist_cap : 0);
   int32_t* idx = A.out_idx + (int64_t)bh * A.idx_cap;
@@ -837,8 +831,8 @@ hipError_t launch_given_select(const Plan& pl, int phase, const int32_t* seq_len
   A.given_cnt = given_cnt;
   A.rcache = rcache;
   A.rc = cache_layout(pl);
-  hipLaunchKernelGGL(given_kernel_for(phase, 0, false), dim3(pl.p.n_q_heads, pl.vbatch), dim3(kHeadThreads),
-                     pl.head_lds_bytes, st, A);
+  const size_t lds = sizeof(uint32_t) * head_lds<kHeadThreads, false>(pl.p.n_max).lists;
+  hipLaunchKernelGGL(given_kernel_for(phase, 0, false), dim3(pl.p.n_q_heads, pl.vbatch), dim3(kHeadThreads), lds, st, A);
   return hipGetLastError();
 }
 
@@ -850,7 +844,7 @@ size_t given_fused_lds_bytes(const Plan& pl, int splits) {
   const size_t dl = (size_t)fused_dlist_cap(pl, splits);
   const size_t first = ((size_t)given_glist_cap(pl, splits) + 2 * dl) * sizeof(uint32_t);
   const size_t second = dl * sizeof(uint32_t) + (size_t)(kHeadThreads / kWave) * (pl.p.head_dim + 2) * sizeof(float);
-  return head_kernel_lds_bytes(pl.p.n_max, kHeadThreads) + std::max(first, second);
+  return sizeof(uint32_t) * head_lds<kHeadThreads, true>(pl.p.n_max).lists + std::max(first, second);
 }
 
 bool given_fused_fits(const Plan& pl, int splits) {
