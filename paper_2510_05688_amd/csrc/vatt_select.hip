@@ -696,12 +696,16 @@ __global__ __launch_bounds__(NT, FD > 0 ? 1 : 4) void head_kernel(HeadArgs A) {
   // paged cache: the same of the first block; and no code lies beyond the pool
   const uint16_t* v_pool = kCode ? A.v + (int64_t)kvh * A.L.head_stride + g_sub * 8 : nullptr;
   const uint32_t last_code = kCode ? (uint32_t)min(((uint64_t)A.L.num_blocks << A.L.page_shift) - 1u, (uint64_t)kInv32) : 0u;
+  auto v_of_code = [&](uint32_t code) {
+    const uint32_t in_page = code & ((1u << A.L.page_shift) - 1u);
+    return v_pool + (int64_t)(code >> A.L.page_shift) * A.L.block_stride + in_page * (uint32_t)(kFused ? FD : 1);
+  };
   // UF rows of a list at once, without branches: all list entries (and their scores) are read from LDS first,
   // then all rows are requested.  The lists are padded to whole calls, so the LDS reads need no bound; a slot
   // beyond the list reads row 0, which add_rows leaves out.  (Written with a per-slot
   // condition, every slot became a branch of its own with an LDS wait inside: sixteen serial LDS round trips.)
-  // HaveSc: the scores of the listed tokens are in LDS (list_sc), and the list holds codes (code_of); else it holds tokens, and
-  // their scores are read from the score row.
+  // HaveSc: the scores of the listed tokens are in LDS (list_sc), and the list holds codes (code_of); else (contiguous cache) it holds
+  // tokens, and their scores are read from the score row.
   // Rounds beyond the list's end request no rows, in steps of two and four (a round costs the workgroup 128 clocks of
   // address processing and as many of arithmetic, and most lists fill three to five of the eight: 1 x 32K tokens 36.3 -> 35.6 us,
   // one head of 1K 20.1 -> 18.8 us per call).
@@ -718,25 +722,19 @@ __global__ __launch_bounds__(NT, FD > 0 ? 1 : 4) void head_kernel(HeadArgs A) {
       t[u] = list[jb + u * NG];
       sc[u] = HaveSc ? list_sc[jb + u * NG] : 0.f;
     }
-    int blk[UF];
+    static_assert(HaveSc || !kCode, "lists of tokens on a paged cache are walked elsewhere");
 #pragma unroll
     for (int u = 0; u < UF; ++u) {
       const bool valid = jb + u * NG >= first && jb + u * NG < count;
-      if constexpr (HaveSc && kCode) {
-        t[u] = valid ? min(t[u], last_code) : row0_code;
-      } else {
-        t[u] = valid ? min(t[u], (uint32_t)(n - 1)) : 0u;
-        blk[u] = kv_block<kCode>(A.L, seq, (int)t[u]);  // (all block-table entries before any row)
-      }
+      if constexpr (kCode) t[u] = valid ? min(t[u], last_code) : row0_code;
+      else t[u] = valid ? min(t[u], (uint32_t)(n - 1)) : 0u;
     }
     auto rows = [&](auto from, auto to) {
 #pragma unroll
       for (int u = decltype(from)::value; u < decltype(to)::value; ++u) {
         if constexpr (!HaveSc) sc[u] = row[t[u]];
         if constexpr (kCode) {
-          const uint32_t code = HaveSc ? t[u] : code_of(t[u], blk[u]);
-          const uint32_t in_page = code & ((1u << A.L.page_shift) - 1u);
-          vv[u] = load_stream_16(v_pool + (int64_t)(code >> A.L.page_shift) * A.L.block_stride + in_page * (uint32_t)(kFused ? FD : 1));
+          vv[u] = load_stream_16(v_of_code(t[u]));
         } else {
           vv[u] = load_stream_16(v_head + t[u] * (uint32_t)(kFused ? FD : 1));  // (n_max * d < 2^32)
         }
@@ -1210,7 +1208,43 @@ __global__ __launch_bounds__(NT, FD > 0 ? 1 : 4) void head_kernel(HeadArgs A) {
       }
       rest(dacc, ddsum, dlist, dlist_sc, j_done, j_coded, ScInLds{});
     }
-    rest(dacc, ddsum, dlist, dlist_sc, j_coded, my_nd, ScInRow{});
+    // What further draws or a complement left is listed by token.  On a paged cache its rows wait for their block-table entries: a batch
+    // at a time, loads and sums in one piece of code (read a batch ahead in parts, as by rest, every part's sums wait for the rows
+    // just requested: 8 x 0.5K - 7K tokens with whole residuals 91 -> 81 us per call, 8 x 9K 133 -> 121; on a contiguous cache, whose
+    // rows wait for nothing else, a batch ahead is better, 67 us against 72).
+    if constexpr (kCode) {
+      int j0 = j_coded;
+      auto batch = [&](auto whole) {
+        constexpr bool Whole = decltype(whole)::value;
+        const int jb = round_of(j0) + g_grp;
+        auto listed = [&](int u) { return Whole || (uint32_t)(jb + u * NG - j0) < (uint32_t)(my_nd - j0); };
+        uint32_t t[UF];
+        int blk[UF];
+#pragma unroll
+        for (int u = 0; u < UF; ++u) t[u] = dlist[jb + u * NG];
+#pragma unroll
+        for (int u = 0; u < UF; ++u) {
+          t[u] = listed(u) ? min(t[u], (uint32_t)(n - 1)) : 0u;
+          blk[u] = kv_block<true>(A.L, seq, (int)t[u]);
+        }
+#pragma unroll
+        for (int u = 0; u < UF; ++u) {
+          fs[u] = row[t[u]];
+          fv[u] = load_stream_16(v_of_code(code_of(t[u], blk[u])));
+        }
+#pragma unroll
+        for (int u = 0; u < UF; ++u)
+          if (listed(u)) add_one(dacc, ddsum, fs[u], fv[u]);
+      };
+      if (j0 < my_nd && round_of(j0) != j0) {  // behind the places that hold codes
+        batch(std::false_type{});
+        j0 = round_of(j0) + UF * NG;
+      }
+      for (; j0 + UF * NG <= my_nd; j0 += UF * NG) batch(std::true_type{});
+      if (j0 < my_nd) batch(std::false_type{});
+    } else {
+      rest(dacc, ddsum, dlist, dlist_sc, j_coded, my_nd, ScInRow{});
+    }
     const float tail_scale = bfin > 0 ? (float)((double)hs.n_s / (double)bfin) : 0.f;
 #pragma unroll
     for (int c = 0; c < 8; ++c) gacc[c] += tail_scale * dacc[c];
