@@ -504,16 +504,16 @@ __global__ __launch_bounds__(NT) void given_topk_kernel(HeadArgs A) {
   }
   v_max = wave_max(v_max);
   if ((tid & 63) == 0) s_wf[tid >> 6] = v_max;
-  // Usual case (as in the kernel of the scored path): the first batch of draws holds b0 accepted ones, which belong to the final
-  // sample whatever the budget turns out to be, unless it is taken as a complement: with the fused gather their rows are
-  // requested now.  One scan counts the accepted draws, and its barrier serves the maximum too.
+  // The accepted ones of the first batch of draws are counted by one scan, whose barrier serves the maximum too.  (Their rows are
+  // asked for when the budget is known.  With those of the first b0, which it cannot drop unless the sample is a complement, requested
+  // before it as in the kernel of the scored path, the kernel takes 190 registers instead of 124 and a seventh more code, and every size is
+  // slower: 1 x 32K tokens 26.3 us per call instead of 26.1, 1 x 8K 23.8 instead of 22.7, 3 x 0.7K 25.7 instead of 24.3.)
   const uint32_t smask = (1u << shift) - 1u;
   auto share_of = [&](uint32_t c) { return c > split ? (int)((c - split + smask) >> shift) : 0; };
   const bool usual = have_spec && 2 * hs.b0 <= hs.n_s && (kFused || !A.ascending);
   const uint32_t acc_bits = usual ? spec.first & ~O::test_bits4(bm_f, spec.tok) : 0u;
   uint32_t tot1;
   const uint32_t acc_pos = block_exclusive_scan_once<NT>((uint32_t)__popc(acc_bits), &tot1, sm.scan_once[2]);
-  const bool spec_dyn = usual && tot1 >= (uint32_t)hs.b0;
   float m = s_wf[0];
 #pragma unroll
   for (int w = 1; w < SW; ++w) m = fmaxf(m, s_wf[w]);
@@ -536,46 +536,9 @@ __global__ __launch_bounds__(NT) void given_topk_kernel(HeadArgs A) {
       acc_w2 += p < n_fix ? 0.0 : w * w;
     }
   }
-  // (accepted draws from .. to - 1 into the lists)
-  auto list_draws = [&](uint32_t lds_from, uint32_t to, bool global) {
-    uint32_t pos = acc_pos;
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      const bool a = (acc_bits >> e) & 1u;
-      if (a && pos < to) {
-        if (global && pos < (uint32_t)A.b_max) idx[A.seg_dyn + pos] = (int32_t)spec.tok[e];
-        if (kFused && pos >= lds_from && (pos & smask) == split && (pos >> shift) < (uint32_t)A.dlist_cap)
-          dlist[pos >> shift] = spec.tok[e];
-      }
-      pos += a ? 1u : 0u;
-    }
-  };
-  if (kFused && spec_dyn) list_draws(0u, (uint32_t)hs.b0, false);
   double sums[3] = {acc_f, acc_w, acc_w2};
   O::block_sum_post(sums, sm);
   __syncthreads();
-  // places [first, count) of this workgroup's share of the final sample, as far as a batch reaches: K and V rows
-  // (place j is always read by lane group j % NG, and a group adds its rows in rising order)
-  uint4 dk[UF], dv[UF];
-  auto load_drawn = [&](int first, int count) {
-    const int j0 = (first & ~(NG - 1)) + g_grp;
-    int tok[UF], blk[UF];
-#pragma unroll
-    for (int u = 0; u < UF; ++u) tok[u] = (int)min(dlist[min(j0 + u * NG, count - 1)], (uint32_t)(n - 1));
-#pragma unroll
-    for (int u = 0; u < UF; ++u) blk[u] = kv_block<PAGED>(A.L, seq, tok[u]);  // (K and V share the block table)
-    each_part(count - (first & ~(NG - 1)), [&](auto from, auto to) {
-#pragma unroll
-      for (int u = decltype(from)::value; u < decltype(to)::value; ++u) {
-        dk[u] = load_stream_16(A.gk + kv_row_offset_in<PAGED>(A.Lk, seq, kvh, tok[u], blk[u]) + g_sub * 8);
-        dv[u] = load_stream_16(A.v + kv_row_offset_in<PAGED>(A.L, seq, kvh, tok[u], blk[u]) + g_sub * 8);
-      }
-    });
-  };
-  const int my_spec = kFused && spec_dyn ? min(share_of((uint32_t)hs.b0), A.dlist_cap) : 0;
-  if constexpr (kFused) {
-    if (my_spec > 0) load_drawn(0, my_spec);
-  }
   O::block_sum_get(sums, sm);
   const double D_f = sums[0];
   double sigma2 = 0.0, b_star = 0.0, D_hat = D_f, tr_sigma = 0.0, nhat_sq = 0.0;
@@ -620,9 +583,18 @@ __global__ __launch_bounds__(NT) void given_topk_kernel(HeadArgs A) {
     D_hat = bud.D_hat;
   }
   int flags = 0;
-  const bool fast_dyn = spec_dyn && (uint32_t)bfin <= tot1 && 2 * bfin <= hs.n_s;  // the first batch of draws holds the sample
+  const bool fast_dyn = usual && (uint32_t)bfin <= tot1 && 2 * bfin <= hs.n_s;  // the first batch of draws holds the sample
   if (fast_dyn) {
-    list_draws((uint32_t)hs.b0, (uint32_t)bfin, writer);
+    uint32_t pos = acc_pos;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const bool a = (acc_bits >> e) & 1u;
+      if (a && pos < (uint32_t)bfin) {
+        if (writer && pos < (uint32_t)A.b_max) idx[A.seg_dyn + pos] = (int32_t)spec.tok[e];
+        if (kFused && (pos & smask) == split && (pos >> shift) < (uint32_t)A.dlist_cap) dlist[pos >> shift] = spec.tok[e];
+      }
+      pos += a ? 1u : 0u;
+    }
     // (a first batch of the sample's own size would not have held it: a thread makes a block, so whole waves count)
     uint32_t held = 0;
     for (int w = 0; w < O::first_blocks(A.small_batches, (uint32_t)bfin) / kWave; ++w) held += sm.scan_once[2].wave_total[w];
@@ -721,32 +693,35 @@ __global__ __launch_bounds__(NT) void given_topk_kernel(HeadArgs A) {
     // the final sample: every A.splits-th token, scores from the K rows, weights carry n_s / b
     const int my_nd = min(share_of((uint32_t)bfin), A.dlist_cap);
     const float tail_bias = bfin > 0 ? __logf((float)((double)hs.n_s / (double)bfin)) : 0.f;
-    auto add_drawn = [&](int first, int count) {
-      const int j0 = (first & ~(NG - 1)) + g_grp;
-      each_part(count - (first & ~(NG - 1)), [&](auto from, auto to) {
+    // (place j is always read by lane group j % NG, and a group adds its rows in rising order)
+    for (int first = 0; first < my_nd; first += UF * NG) {
+      const int j0 = first + g_grp;
+      int tok[UF], blk[UF];
+      uint4 kv[UF], vv[UF];
 #pragma unroll
-      for (int u = decltype(from)::value; u < decltype(to)::value; ++u) {
-        // (the lanes of a group stay together: every lane of the group computes the row's score)
-        float a = 0.f;
-        a = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2_t, dk[u].x), __builtin_bit_cast(bf16x2_t, qw[0]), a, false);
-        a = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2_t, dk[u].y), __builtin_bit_cast(bf16x2_t, qw[1]), a, false);
-        a = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2_t, dk[u].z), __builtin_bit_cast(bf16x2_t, qw[2]), a, false);
-        a = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2_t, dk[u].w), __builtin_bit_cast(bf16x2_t, qw[3]), a, false);
-        const float s_row = group_sum<LPR>(a) * A.sm_scale + 0.0f;
-        const int j = j0 + u * NG;
-        if (j >= first && j < count) add_row(s_row + tail_bias, dv[u]);
-      }
+      for (int u = 0; u < UF; ++u) tok[u] = (int)min(dlist[min(j0 + u * NG, my_nd - 1)], (uint32_t)(n - 1));
+#pragma unroll
+      for (int u = 0; u < UF; ++u) blk[u] = kv_block<PAGED>(A.L, seq, tok[u]);  // (K and V share the block table)
+      each_part(my_nd - first, [&](auto from, auto to) {
+#pragma unroll
+        for (int u = decltype(from)::value; u < decltype(to)::value; ++u) {
+          kv[u] = load_stream_16(A.gk + kv_row_offset_in<PAGED>(A.Lk, seq, kvh, tok[u], blk[u]) + g_sub * 8);
+          vv[u] = load_stream_16(A.v + kv_row_offset_in<PAGED>(A.L, seq, kvh, tok[u], blk[u]) + g_sub * 8);
+        }
       });
-    };
-    int j_done = 0;
-    if (my_spec > 0 && 2 * bfin <= hs.n_s) {  // (the rows of the first b0 tokens are at hand, unless the sample is a complement)
-      add_drawn(0, my_spec);
-      j_done = min(my_spec, UF * NG);
-    }
-    while (j_done < my_nd) {
-      load_drawn(j_done, my_nd);
-      add_drawn(j_done, my_nd);
-      j_done = (j_done & ~(NG - 1)) + UF * NG;
+      each_part(my_nd - first, [&](auto from, auto to) {
+#pragma unroll
+        for (int u = decltype(from)::value; u < decltype(to)::value; ++u) {
+          // (the lanes of a group stay together: every lane of the group computes the row's score)
+          float a = 0.f;
+          a = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2_t, kv[u].x), __builtin_bit_cast(bf16x2_t, qw[0]), a, false);
+          a = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2_t, kv[u].y), __builtin_bit_cast(bf16x2_t, qw[1]), a, false);
+          a = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2_t, kv[u].z), __builtin_bit_cast(bf16x2_t, qw[2]), a, false);
+          a = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2_t, kv[u].w), __builtin_bit_cast(bf16x2_t, qw[3]), a, false);
+          const float s_row = group_sum<LPR>(a) * A.sm_scale + 0.0f;
+          if (j0 + u * NG < my_nd) add_row(s_row + tail_bias, vv[u]);
+        }
+      });
     }
     // the lane groups of a wave to their common maximum and added, then the waves through LDS
     float M = m_run;
