@@ -449,10 +449,11 @@ __global__ __launch_bounds__(NT) void given_topk_kernel(HeadArgs A) {
           load_listed(blist, j0, my_nb, kv);
         }
       };
-      // (the first rows of both lists are under way together)
+      // (the first rows of both lists are under way together; a lane group beyond a list's end stays out, and with it whole waves:
+      // small base samples fill one or two of eight, 3 x 0.7K tokens 24.3 -> 23.8 us per call, 1 x 4K of 64 columns 23.9 -> 22.8)
       uint4 kf[UF], kb[UF];
-      if (my_nf > 0) load_listed(glist, g_grp, my_nf, kf);
-      if (my_nb > 0) load_base(g_grp, kb);
+      if (g_grp < my_nf) load_listed(glist, g_grp, my_nf, kf);
+      if (g_grp < my_nb) load_base(g_grp, kb);
       if ((int)split == A.splits - 1 && !pair_made) {
         // The first batch of the final sample's draws, for all workgroups of the head in the second phase, where it would
         // stand in front of everything else.  Here it is made while the rows are on their way.
@@ -468,7 +469,7 @@ __global__ __launch_bounds__(NT) void given_topk_kernel(HeadArgs A) {
         }
         store_final(tid, mine.tok, mine.ok, mine.first, blocks, make);
       }
-      for (int j0 = g_grp; j0 - g_grp < my_nf; j0 += NG * UF) {
+      for (int j0 = g_grp; j0 < my_nf; j0 += NG * UF) {
         if (j0 != g_grp) load_listed(glist, j0, my_nf, kf);
 #pragma unroll
         for (int u = 0; u < UF; ++u) {
@@ -478,7 +479,7 @@ __global__ __launch_bounds__(NT) void given_topk_kernel(HeadArgs A) {
             spw[fixed_place(f0_lo + j, hs.n_sink, hs.n_win, A.seg_sink, A.seg_win, A.seg_topk)] = sc;
         }
       }
-      for (int j0 = g_grp; j0 - g_grp < my_nb; j0 += NG * UF) {
+      for (int j0 = g_grp; j0 < my_nb; j0 += NG * UF) {
         if (j0 != g_grp) load_base(j0, kb);
 #pragma unroll
         for (int u = 0; u < UF; ++u) {
