@@ -48,6 +48,7 @@ struct HeadArgs {
   int b_multiple;  // b is rounded up to a multiple of this (1: the paper's rule)
   int ascending;   // the two samples' lists are written in ascending token order (else in acceptance order)
   uint32_t draw_cap;  // 0: the default 64 L + 4096
+  int large_budgets;  // see draw_ahead
   unsigned long long* dbg;
   // fused gather (head_kernel with FD > 0): every head has `splits` workgroups, each of which repeats the
   // selection and then gathers every splits-th row of the head's token list
@@ -512,6 +513,7 @@ inline void fill_head_args(HeadArgs& A, const Plan& pl, int phase, const int32_t
   A.small_batches = pl.sampler_small_batches;
   A.topk_general = pl.topk_general_path;
   A.draw_cap = pl.sampler_draw_cap;
+  A.large_budgets = (pl.z_half / pl.eps) * (pl.z_half / pl.eps) > 5000.0;
   A.vstat_splits = pl.vstat_splits;
   A.head_dim = p.head_dim;
   A.k_max = pl.k_max;

@@ -20,6 +20,16 @@ __device__ __forceinline__ int base_count_of(int n_s, const SelectParams& p) {
   return b0 > n_s ? n_s : b0;
 }
 
+// Whether the final sample's first batch of draws is made before its budget is known.  Budgets grow with (z / epsilon)^2; where that is
+// large (epsilon below 0.028 at delta 0.05) they mostly go beyond what a batch of this size holds or take the whole residual, unless the
+// residual is so short that the batch holds half of it, and with that any sample (beyond half the complement is drawn).  There a batch
+// of the right size, made when the budget is known, is better.  Measured, us per call, ahead / when known: 1 x 8K tokens at epsilon 0.02
+// 31.7 / 30.7, 4 x 4K 44.0 / 42.6, 16 x 8K 98.2 / 95.8, 3 x 3K at 0.01 39.8 / 38.8, with the random cache 38.9 / 36.8, though 3 x 1.5K at
+// 0.02 32.7 / 33.6; at 0.03 4 x 4K 32.5 / 33.2, 1 x 32K 27.1 / 28.1; of 0.7K at 0.02 28.5 / 29.0.
+__device__ __forceinline__ bool draw_ahead(const HeadArgs& A, const HeadSizes& hs) {
+  return !A.large_budgets || likely_blocks(kHeadThreads, hs, final_draws(hs)) <= kHeadThreads / 2;
+}
+
 // FD = 0: selection only.  FD = head dimension (phase 1 only): the gather is fused in for small batches, as in
 // head_kernel: every head gets A.splits workgroups (blockIdx.z), each of which runs the whole second phase
 // (identical results in all of them), keeps every A.splits-th token of the final sample in LDS, and gathers
@@ -231,13 +241,13 @@ __global__ __launch_bounds__(NT) void given_topk_kernel(HeadArgs A) {
     he.k = min(cnt, max(mid_len, 0));
     he.n_s = mid_len - he.k;
     he.b0 = he.n_s > 0 ? base_count_of(he.n_s, A.sp) : 0;
-    have_spec = he.n_s > 0 && he.b0 < he.n_s && (PHASE == 0 ? !A.rcache : !A.nested);
+    have_spec = he.n_s > 0 && he.b0 < he.n_s && (PHASE == 0 ? !A.rcache : !A.nested && draw_ahead(A, he));
     const int blocks = PHASE == 0 ? likely_blocks(A.small_batches ? kSmallBatchBlocks : NT, he, base_draws(he)) : final_blocks(he);
     if constexpr (kFused && PHASE == 0) {
       // first batches of both samples at once where half of the workgroup holds each (as in the kernel of the scored path):
       // small steps, whose rows would not cover the second one (below), 28.1 -> 27.4 us for 3 x 0.7K tokens
       blocks1 = final_blocks(he);
-      pair_made = have_spec && blocks <= NT / 2 && blocks1 <= NT / 2;
+      pair_made = have_spec && blocks <= NT / 2 && blocks1 <= NT / 2 && draw_ahead(A, he);
       if (pair_made) {
         Sampler S1 = S;
         S1.taken = taken1;
@@ -457,7 +467,7 @@ __global__ __launch_bounds__(NT) void given_topk_kernel(HeadArgs A) {
       if ((int)split == A.splits - 1 && !pair_made) {
         // The first batch of the final sample's draws, for all workgroups of the head in the second phase, where it would
         // stand in front of everything else.  Here it is made while the rows are on their way.
-        const bool make = hs.n_s > 0 && hs.b0 < hs.n_s;
+        const bool make = hs.n_s > 0 && hs.b0 < hs.n_s && draw_ahead(A, hs);
         DrawBatch mine = {};
         const int blocks = final_blocks(hs);
         if (make) {
