@@ -562,6 +562,16 @@ __device__ __forceinline__ int ahead_blocks(int small_batches, const HeadSizes& 
 __device__ __forceinline__ int base_draws(const HeadSizes& hs) { return min(hs.b0, hs.n_s - hs.b0); }
 __device__ __forceinline__ int final_draws(const HeadSizes& hs) { return hs.n_s / 2; }
 
+// What a batch made ahead leaves of a thread's draws beside their tokens: ok (bits 0 - 3) and first (4 - 7) of DrawBatch, whether the
+// batch was made at all (8), and its Philox blocks (16 - 31; only the caller-supplied path reads them, the scored path works them out).
+__device__ __forceinline__ uint32_t pre_pack(const DrawBatch& B, bool made) {
+  return (B.ok & 15u) | (B.first & 15u) << 4 | (made ? 256u : 0u) | (uint32_t)B.blocks << 16;
+}
+__device__ __forceinline__ bool pre_made_of(uint32_t f) { return (f & 256u) != 0u; }
+__device__ __forceinline__ uint32_t pre_ok(uint32_t f) { return f & 15u; }
+__device__ __forceinline__ uint32_t pre_first(uint32_t f) { return f >> 4 & 15u; }
+__device__ __forceinline__ int pre_blocks(uint32_t f) { return (int)(f >> 16); }
+
 // ---------------------------------------------------------------------------
 // The first batch of draws of one sampler stream of one (sequence, head), with repeated tokens resolved, made
 // ahead of the selection kernel: the draw sequences depend on the seed, the head and the sequence length only,
@@ -572,7 +582,7 @@ struct PreArgs {
   const int32_t* seq_lens;
   const uint64_t* seq_seeds;
   uint4* pre_tok;       // [B*Hq][512]: the four proposed tokens of every thread of the selection kernel
-  uint32_t* pre_flags;  // [B*Hq][512]: ok | first << 4 | (made ? 256 : 0)
+  uint32_t* pre_flags;  // [B*Hq][512]: see pre_pack
   SelectParams sp;
   int n_max, Hq, small_batches;
   uint32_t draw_cap;
@@ -631,7 +641,7 @@ __device__ __forceinline__ void prework_job(const PreArgs& A, int b, int h, int 
   if (make) O::make_batch(mine, S, hs, 0u, blocks, false, false, sm, tid);
   const int64_t at = (int64_t)bh * (2 * NT) + stream * NT + tid;
   A.pre_tok[at] = make_uint4(mine.tok[0], mine.tok[1], mine.tok[2], mine.tok[3]);
-  A.pre_flags[at] = (mine.ok & 15u) | ((mine.first & 15u) << 4) | (make ? 256u : 0u);
+  A.pre_flags[at] = pre_pack(mine, make);
 }
 
 }  // namespace vatt

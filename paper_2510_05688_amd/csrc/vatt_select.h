@@ -40,7 +40,7 @@ struct HeadArgs {
   int64_t seg_topk, seg_base, seg_dyn, seg_sink, seg_win;
   int64_t idx_cap;
   int n_pad, n_max, Hq, n_sub;
-  int target, phase, small_batches, topk_general, vstat_splits, head_dim;
+  int target, small_batches, topk_general, vstat_splits, head_dim;
   int k_max, b0_max, b_max;
   int q_len;  // query tokens per sequence: blockIdx.y = sequence * q_len + query token
   int group_major, Hkv;  // see head_of_block
@@ -57,9 +57,10 @@ struct HeadArgs {
   float* part;       // [B*Hq][splits][d + 4]: partial (sum w V, sum w) of every workgroup
   int splits, split_shift, group;
   int glist_cap, dlist_cap;  // LDS entries for a workgroup's share of I_f and of the final sample
-  // first batches of both sampler streams made ahead by prework_kernel (nullptr: made here)
-  const uint4* pre_tok;       // [B*Hq][kHeadThreads]: the four proposed tokens of every thread
-  const uint32_t* pre_flags;  // [B*Hq][kHeadThreads]: ok | first << 4 | (made ? 256 : 0)
+  // first batches of draws made ahead (nullptr: made here): of both sampler streams by workgroups of the score launch, and on the
+  // caller-supplied path of the final sample's by the first phase for the second
+  uint4* pre_tok;       // [B*Hq][kHeadThreads]: the four proposed tokens of every thread
+  uint32_t* pre_flags;  // [B*Hq][kHeadThreads]: see pre_pack
   // random cache of base-sample rows (nullptr: the base sample is drawn)
   const void* rcache;
   CacheLayout rc;
@@ -477,8 +478,8 @@ template <int V>
 using Int = std::integral_constant<int, V>;
 
 // The arguments every launch of the two kernels starts from.
-inline void fill_head_args(HeadArgs& A, const Plan& pl, int phase, const int32_t* seq_lens, const uint64_t* seq_seeds,
-                           void* ws, int32_t* out_idx, int32_t* out_counts, double* out_budget_raw,
+inline void fill_head_args(HeadArgs& A, const Plan& pl, const int32_t* seq_lens, const uint64_t* seq_seeds, void* ws,
+                           int32_t* out_idx, int32_t* out_counts, double* out_budget_raw,
                            float* out_stats) {
   const vatt_params& p = pl.p;
   char* w = static_cast<char*>(ws);
@@ -509,7 +510,6 @@ inline void fill_head_args(HeadArgs& A, const Plan& pl, int phase, const int32_t
   A.n_max = p.n_max;
   A.Hq = p.n_q_heads;
   A.target = p.target;
-  A.phase = phase;
   A.small_batches = pl.sampler_small_batches;
   A.topk_general = pl.topk_general_path;
   A.draw_cap = pl.sampler_draw_cap;

@@ -63,9 +63,7 @@ __global__ __launch_bounds__(NT, FD > 0 ? 1 : 4) void head_kernel(HeadArgs A) {
   constexpr int SW = NT / kWave;
   extern __shared__ __align__(16) unsigned char dyn_smem[];
   __shared__ TopkSmem ts;
-  // (the selection-only kernel is at its register limit: with the comparisons of head_of_block it spills six registers more)
-  const int x = (int)blockIdx.x, b = blockIdx.y;
-  const int h = kFused ? head_of_block(x, A.Hq, A.Hkv, A.group_major) : A.group_major ? (x % A.Hkv) * (A.Hq / A.Hkv) + x / A.Hkv : x;
+  const int h = head_of_block((int)blockIdx.x, A.Hq, A.Hkv, A.group_major), b = blockIdx.y;
   const int bh = b * A.Hq + h;
   const int tid = threadIdx.x;
   constexpr bool kSplit = kFused && !ALONE;
@@ -90,7 +88,7 @@ __global__ __launch_bounds__(NT, FD > 0 ? 1 : 4) void head_kernel(HeadArgs A) {
   if (NT == kHeadThreads && A.pre_tok) {
     pre_t = A.pre_tok[(int64_t)bh * NT + tid];
     pre_f = A.pre_flags[(int64_t)bh * NT + tid];
-    pre_made = (A.pre_flags[(int64_t)bh * NT] & 256u) != 0u;  // one word for the whole workgroup: uniform
+    pre_made = pre_made_of(A.pre_flags[(int64_t)bh * NT]);  // one word for the whole workgroup: uniform
   }
   // In a multi-query step b stands for (sequence, query token); query token t of q_len sees the sequence up to
   // and including itself, which leaves out the q_len - 1 - t newer tokens.
@@ -246,8 +244,8 @@ __global__ __launch_bounds__(NT, FD > 0 ? 1 : 4) void head_kernel(HeadArgs A) {
       // base sample's proposals are requested
       const uint32_t tk[4] = {pre_t.x, pre_t.y, pre_t.z, pre_t.w};
       uint32_t* tk_bm = half ? taken1 : taken0;
-      mine.ok = pre_f & 15u;
-      mine.first = (pre_f >> 4) & 15u;
+      mine.ok = pre_ok(pre_f);
+      mine.first = pre_first(pre_f);
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
         mine.tok[e] = min(max(tk[e], (uint32_t)hs.mid_lo), (uint32_t)max(hs.mid_hi - 1, hs.mid_lo));
@@ -1354,7 +1352,7 @@ hipError_t launch_head(const Plan& pl, int phase, const int32_t* seq_lens, const
                        int32_t* out_idx, int32_t* out_counts, double* out_budget_raw, float* out_stats,
                        hipStream_t st) {
   HeadArgs A;
-  fill_head_args(A, pl, phase, seq_lens, seq_seeds, ws, out_idx, out_counts, out_budget_raw, out_stats);
+  fill_head_args(A, pl, seq_lens, seq_seeds, ws, out_idx, out_counts, out_budget_raw, out_stats);
   const vatt_params& p = pl.p;
   hipLaunchKernelGGL(head_kernel_for(pl.head_threads, phase, head_options(pl)), dim3(p.n_q_heads, pl.vbatch), dim3(pl.head_threads), pl.head_lds_bytes, st, A);
   return hipGetLastError();
@@ -1402,11 +1400,11 @@ hipError_t launch_head_fused(const Plan& pl, const void* v, const int32_t* block
                              double* out_budget_raw, float* out_stats, float* out_o, float* out_lse, bool pre_made,
                              hipStream_t st) {
   HeadArgs A;
-  fill_head_args(A, pl, 0, seq_lens, seq_seeds, ws, out_idx, out_counts, out_budget_raw, out_stats);
+  fill_head_args(A, pl, seq_lens, seq_seeds, ws, out_idx, out_counts, out_budget_raw, out_stats);
   const vatt_params& p = pl.p;
   if (pre_made) {  // workgroups of the score launch made the first batches (prework_job)
-    A.pre_tok = reinterpret_cast<const uint4*>(static_cast<char*>(ws) + pl.off_pre_tok);
-    A.pre_flags = reinterpret_cast<const uint32_t*>(static_cast<char*>(ws) + pl.off_pre_flags);
+    A.pre_tok = reinterpret_cast<uint4*>(static_cast<char*>(ws) + pl.off_pre_tok);
+    A.pre_flags = reinterpret_cast<uint32_t*>(static_cast<char*>(ws) + pl.off_pre_flags);
   }
   A.v = static_cast<const uint16_t*>(v);
   A.L = pl.kv_v;

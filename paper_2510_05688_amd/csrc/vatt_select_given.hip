@@ -212,10 +212,10 @@ __global__ __launch_bounds__(NT) void given_topk_kernel(HeadArgs A) {
   bool have_spec = false, pair_made = false;
   int blocks1 = 0;
   // leaves a Philox block's four draws of the final sample's first batch for the second phase
-  auto store_final = [&](int block, const uint32_t (&tok)[4], uint32_t ok, uint32_t first, int blocks, bool made) {
-    const int64_t at = (int64_t)bh * NT + block;
-    const_cast<uint4*>(A.pre_tok)[at] = make_uint4(tok[0], tok[1], tok[2], tok[3]);
-    const_cast<uint32_t*>(A.pre_flags)[at] = ok | first << 4 | (made ? 256u : 0u) | (uint32_t)blocks << 16;
+  auto store_final = [&](int block, const DrawBatch& B, bool made) {
+    const int64_t place = (int64_t)bh * NT + block;
+    A.pre_tok[place] = make_uint4(B.tok[0], B.tok[1], B.tok[2], B.tok[3]);
+    A.pre_flags[place] = pre_pack(B, made);
   };
   // Philox blocks of the final sample's first batch: enough for the base sample's size, and for a larger sample as many as half
   // of the threads make
@@ -225,10 +225,10 @@ __global__ __launch_bounds__(NT) void given_topk_kernel(HeadArgs A) {
   };
   if constexpr (kFused && PHASE != 0) {
     // made by a workgroup of the first phase, under its loads of K rows
-    have_spec = (pre_all & 256u) != 0u;
-    spec.blocks = (int)(pre_all >> 16);
-    spec.ok = pre_f & 15u;
-    spec.first = (pre_f >> 4) & 15u;
+    have_spec = pre_made_of(pre_all);
+    spec.blocks = pre_blocks(pre_all);
+    spec.ok = pre_ok(pre_f);
+    spec.first = pre_first(pre_f);
     const uint32_t tk[4] = {pre_t.x, pre_t.y, pre_t.z, pre_t.w};
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
@@ -261,7 +261,12 @@ __global__ __launch_bounds__(NT) void given_topk_kernel(HeadArgs A) {
         spec.blocks = blocks;
         spec.ok = upper ? 0u : mine.ok;
         spec.first = upper ? 0u : mine.first;
-        if ((int)split == A.splits - 1) store_final(upper ? tid - NT / 2 : tid + NT / 2, mine.tok, upper ? mine.ok : 0u, upper ? mine.first : 0u, blocks1, true);
+        if ((int)split == A.splits - 1) {
+          mine.blocks = blocks1;
+          mine.ok = upper ? mine.ok : 0u;
+          mine.first = upper ? mine.first : 0u;
+          store_final(upper ? tid - NT / 2 : tid + NT / 2, mine, true);
+        }
       }
     }
     if (have_spec && !pair_made) O::make_batch(spec, S, hs, 0u, blocks, false, false, sm, tid);
@@ -469,15 +474,14 @@ __global__ __launch_bounds__(NT) void given_topk_kernel(HeadArgs A) {
         // stand in front of everything else.  Here it is made while the rows are on their way.
         const bool make = hs.n_s > 0 && hs.b0 < hs.n_s && draw_ahead(A, hs);
         DrawBatch mine = {};
-        const int blocks = final_blocks(hs);
         if (make) {
           for (int w = tid; w < words; w += NT) taken[w] = 0;  // (the base sample's)
           __syncthreads();
           Sampler S1 = S;
           S1.stream = 1u;
-          O::make_batch(mine, S1, hs, 0u, blocks, false, false, sm, tid);
+          O::make_batch(mine, S1, hs, 0u, final_blocks(hs), false, false, sm, tid);
         }
-        store_final(tid, mine.tok, mine.ok, mine.first, blocks, make);
+        store_final(tid, mine, make);
       }
       for (int j0 = g_grp; j0 < my_nf; j0 += NG * UF) {
         if (j0 != g_grp) load_listed(glist, j0, my_nf, kf);
@@ -812,7 +816,7 @@ hipError_t launch_given_select(const Plan& pl, int phase, const int32_t* seq_len
                                int32_t* out_idx, int32_t* out_counts, double* out_budget_raw, float* out_stats,
                                hipStream_t st) {
   HeadArgs A;
-  fill_head_args(A, pl, phase, seq_lens, seq_seeds, ws, out_idx, out_counts, out_budget_raw, out_stats);
+  fill_head_args(A, pl, seq_lens, seq_seeds, ws, out_idx, out_counts, out_budget_raw, out_stats);
   A.given_idx = given_idx;
   A.given_cnt = given_cnt;
   A.rcache = rcache;
@@ -859,11 +863,11 @@ hipError_t launch_given_fused(const Plan& pl, int phase, const void* q, const vo
                               int32_t* out_idx, int32_t* out_counts, double* out_budget_raw, float* out_stats,
                               hipStream_t st) {
   HeadArgs A;
-  fill_head_args(A, pl, phase, seq_lens, seq_seeds, ws, out_idx, out_counts, out_budget_raw, out_stats);
+  fill_head_args(A, pl, seq_lens, seq_seeds, ws, out_idx, out_counts, out_budget_raw, out_stats);
   // the final sample's first batch of draws passes from the first phase to the second
   static_assert(kHeadThreads == 2 * kPreThreads, "a thread's draws each");
-  A.pre_tok = reinterpret_cast<const uint4*>(static_cast<char*>(ws) + pl.off_pre_tok);
-  A.pre_flags = reinterpret_cast<const uint32_t*>(static_cast<char*>(ws) + pl.off_pre_flags);
+  A.pre_tok = reinterpret_cast<uint4*>(static_cast<char*>(ws) + pl.off_pre_tok);
+  A.pre_flags = reinterpret_cast<uint32_t*>(static_cast<char*>(ws) + pl.off_pre_flags);
   const int S = pl.given_fuse_splits;
   A.given_idx = given_idx;
   A.given_cnt = given_cnt;
