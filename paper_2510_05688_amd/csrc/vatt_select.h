@@ -191,6 +191,13 @@ struct __align__(16) TopkSmem {
   uint32_t cand_n, qual_n;
 };
 
+// Where a list of `count` entries is read that starts `offset` entries into `lists`, and which entry stands for entry t, for loads without
+// a condition around them: of an empty list nothing is read, but the first entry of `instead`.
+__host__ __device__ constexpr const int32_t* list_or(const int32_t* lists, int64_t offset, int count, const int32_t* instead) {
+  return count > 0 ? lists + offset : instead;
+}
+__host__ __device__ constexpr int list_entry(int t, int count) { return t >= count ? (count > 0 ? count - 1 : 0) : t; }
+
 // Where a selection workgroup of NT threads keeps what in its dynamic LDS, as offsets in 32-bit words: the kernels take their pointers
 // and the launches their sizes from here, so that the two cannot disagree.  TWO: the first batches of both sampler streams are made
 // at once, each with a scratch bitmap and mail slots of its own.  The lists of the fused kernels follow at `lists`.

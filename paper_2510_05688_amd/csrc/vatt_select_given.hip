@@ -92,14 +92,13 @@ __global__ __launch_bounds__(NT) void given_topk_kernel(HeadArgs A) {
   const int cnt = PHASE == 0 ? min(max(A.given_cnt[bh], 0), A.k_max) : rec.k;  // entries of the list of top-k tokens
   // (loads without a condition around them, of something valid where there is nothing to load: an empty list of the caller's may
   // have no memory behind it)
-  const int32_t* list = PHASE != 0 ? idx + A.seg_topk : cnt > 0 ? A.given_idx + (int64_t)bh * A.k_max : idx;
+  const int32_t* list = PHASE != 0 ? idx + A.seg_topk : list_or(A.given_idx, (int64_t)bh * A.k_max, cnt, idx);
   // (four entries per thread are read before any is used: a read behind a condition waits for the one before)
   constexpr int U = 4;
   auto load_list = [&](int t0, int (&g)[U]) {
 #pragma unroll
     for (int u = 0; u < U; ++u) {
-      const int t = max(min(t0 + u * NT + tid, cnt - 1), 0);
-      g[u] = list[t];
+      g[u] = list[list_entry(t0 + u * NT + tid, cnt)];
     }
   };
   int g_first[U];

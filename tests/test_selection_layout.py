@@ -1,4 +1,5 @@
-"""The LDS layout that the selection kernels and their launch sizes share, checked at compile time for every capacity."""
+"""Checked at compile time: the LDS layout that the selection kernels and their launch sizes share, for every capacity, and where
+the kernel with the caller's top-k list reads that list."""
 import os
 import subprocess
 
@@ -29,12 +30,23 @@ constexpr bool all() {
 }
 static_assert(all(), "layout");
 static_assert(sizeof(uint32_t) * head_lds<1024, false>(kCapacityMax).lists + sizeof(TopkSmem) + 64 <= 160 * 1024, "end");
+// loads of the caller's top-k list stay inside it, and an empty one, which may have no memory, is not touched
+constexpr int32_t lists[8] = {}, other[1] = {};
+constexpr bool inside() {
+  for (int count = 1; count <= 3; ++count)
+    for (int t = 0; t < 9; ++t)
+      if (list_or(lists, 4, count, other) != lists + 4 || list_entry(t, count) != (t < count ? t : count - 1)) return false;
+  for (int t = 0; t < 9; ++t)
+    if (list_or(nullptr, 1 << 20, 0, other) != other || list_entry(t, 0) != 0) return false;
+  return true;
+}
+static_assert(inside(), "list");
 static_assert(kCapacityMax <= kMailTokens * (int)kMailSlots, "a slot's tokens");
 """
 
 
 
-def test_places_follow_each_other_at_every_capacity(tmp_path):
+def test_lds_places_and_list_reads(tmp_path):
     src = tmp_path / "layout.hip"
     src.write_text(CHECK)
     r = subprocess.run(["hipcc", "--offload-arch=gfx950", "--cuda-host-only", "-std=c++17", "-fsyntax-only", "-Wno-unused-function",
