@@ -17,12 +17,10 @@
 // a batch are generated at once, repeated tokens are resolved to their earliest draw, and a prefix count in
 // draw order finds where the sample is complete; the result equals the sequential procedure bit for bit.
 //
-// What bounds it: a lone workgroup is one dependency chain of some 25 barriers and four dependent trips to global
-// memory, about 45 K clocks whatever the length of the row; so its time is the number of instructions and barriers on
-// that chain.  512 workgroups at 32K tokens also wait for their scattered reads (scores of the proposals, sub-tiles of
-// the candidates).  Measured before and after the mail slots by token, the first batches no longer than needed, the
-// histogram without an overflow counter, the lists by ballot and the fewer barriers of the top-k step: one head of 1K
-// tokens 32.6 -> 18 us, 256 heads of 0.5K - 7K tokens 46 -> 18 us, 1024 heads of 1K - 32K tokens 65 -> 54 us.
+// What bounds it: a workgroup is one dependency chain of barriers and trips to global memory, and with few heads the chain is the time:
+// with the gather fused in, one head of 1K tokens 12.6 us, 32 heads of 32K 19.5, 256 heads of 0.5K - 7K 20.5 (rows of 32K have more
+// maxima and candidates to pass through the same steps).  Where workgroups fill the chip they also wait for their scattered reads (scores
+// of the proposals, sub-tiles of the candidates): 512 heads of 32K tokens 29 - 34 us, 1024 heads of 1K - 32K 54.
 //
 // Floating-point sums are taken in a fixed order, or as fixed-point integers where the order depends on
 // scheduling, so the statistics and the budget are reproducible too.
