@@ -343,7 +343,7 @@ __global__ __launch_bounds__(kGatherThreads) void given_gather_kernel(GivenArgs 
   const int total = r.n_sink + r.n_win + r.k + r.b;
   const int splits = used_splits(A.splits, total, RPB * U);
   if (split >= splits) return;
-  const bool shared_rows = rows_are_shared(total, A.group_major ? A.q_len * A.group : A.q_len, r.n, A.group_major ? 3 : 2);
+  const bool shared_rows = rows_are_shared(total, A.group_major ? A.q_len * A.group : A.q_len, r.n, A.group_major && A.group > 1 ? 3 : 2);
   const int per = (total + splits - 1) / splits;
   const int p_lo = split * per, p_hi = min(p_lo + per, total);
   const int32_t* idx = A.idx + (int64_t)bh * A.idx_cap;

@@ -51,10 +51,11 @@ __device__ __forceinline__ int used_splits(int splits, int total, int step_rows)
 // (0.2), 4 x 128K 29.4 -> 32.8 (0.2), and 1 x 91K with 4 KV heads, their 8 vectors on as many XCDs, and 3 query tokens 44.8 -> 48.0
 // (0.3 on each).
 // The line is `quarters` / 4.  The gather of the caller-supplied path, which reads K and V rows of the drawn tokens, none of which the
-// vectors share, takes 3 where they are whole groups: at 2 several sizes were slower than without ordinary loads (whole step, us, without
-// / at 2 / at 3: 16 x 16K at epsilon 0.02 112.3 / 113.4 / 111.5, with the random cache 108.6 / 112.2 / 107.5, 32 x 3K 79.0 / 79.9 / 75.5,
-// 2 x 32K with 3 query tokens 60.4 / 61.6 / 56.6, 8 x 16K with 2 82.4 / 86.5 / 83.2; though 16 x 4K 48.2 / 44.8 / 45.9, 24 x 4K 61.7 / 57.6 /
-// 59.7).  Where they are the query tokens of one head it stays at 2 (1 x 59K with 6 119.4 / 108.0 / 114).
+// vectors share, takes 3 where they are whole groups of several heads: at 2 several sizes were slower than without ordinary loads (whole
+// step, us, without / at 2 / at 3: 16 x 16K at epsilon 0.02 112.3 / 113.4 / 111.5, with the random cache 108.6 / 112.2 / 107.5, 32 x 3K
+// 79.0 / 79.9 / 75.5, 2 x 32K with 3 query tokens 60.4 / 61.6 / 56.6, 8 x 16K with 2 82.4 / 86.5 / 83.2; though 16 x 4K 48.2 / 44.8 / 45.9,
+// 24 x 4K 61.7 / 57.6 / 59.7).  Where they are the query tokens of one head it stays at 2 (1 x 59K with 6 119.4 / 108.0 / 114; 17 x 0.3K -
+// 5K with 2, 16 KV heads of 64 columns, at 2 50.8, at 3 51.8).
 __device__ __forceinline__ bool rows_are_shared(int total, int vectors, int n, int quarters = 2) {
   return 4ll * total * vectors > (long long)quarters * n;
 }
