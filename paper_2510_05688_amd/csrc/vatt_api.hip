@@ -507,7 +507,7 @@ int vatt_decode(vatt_plan* plan, const void* q, const void* k, const void* v, co
   } else {
     VATT_LAUNCH(launch_head(pl, 1, seq_lens, seq_seeds, workspace, out_idx, out_counts, out_budget_raw, out_stats, st));
     VATT_LAUNCH(launch_vstats(pl, v, block_table, workspace, out_idx, st));
-    VATT_LAUNCH(launch_head(pl, 2, seq_lens, seq_seeds, workspace, out_idx, out_counts, out_budget_raw, out_stats, st));
+    VATT_LAUNCH(launch_budget(pl, seq_lens, seq_seeds, workspace, out_idx, out_counts, out_budget_raw, out_stats, st));
   }
   VATT_LAUNCH(launch_gather(pl, v, block_table, workspace, out_idx, out_o, out_lse, st));
   return VATT_OK;

@@ -1,0 +1,263 @@
+// Budget and final sample of the targets N and SDPA (Algorithm 2 and the last draw of Algorithm 1), between the V-side statistics
+// and the gather.
+#include "vatt_select.h"
+
+namespace vatt {
+namespace {
+
+// LDS of budget_kernel, in 32-bit words from its start: HeadSmem, three bitmaps, word prefixes, mail slots.
+struct BudgetLds {
+  uint32_t bm_f, taken, scratch, wpre, mail, end;
+};
+template <int NT>
+__host__ __device__ constexpr BudgetLds budget_lds(int n_max) {
+  const uint32_t words = (uint32_t)bitmap_words(n_max);
+  BudgetLds l{};
+  l.bm_f = (uint32_t)((sizeof(typename HeadOps<NT>::HeadSmem) + 15) / 16 * 4);
+  l.taken = l.bm_f + words;
+  l.scratch = l.taken + words;
+  l.wpre = l.scratch + words;
+  l.mail = l.wpre + words;
+  l.end = l.mail + kMailSlots;
+  return l;
+}
+
+// Targets N and SDPA, behind the V-side statistics: budget and final sample of every head (Algorithm 2; Algorithm 1, final
+// sample).  The weights are those of the lists that phase 1 left, and so is the top-k bitmap.  D_f and N_f stay for the merge:
+// the gather then reads the rows of the final sample only.
+// What bounds it: one chain per head.  Everything that the budget waits for is asked for ahead of the first batch of draws, which
+// is as large as the workgroup can make it: budgets of these targets go well beyond the base sample.
+// Kernel and whole call, us, before (the selection kernel with its top-k step left out, then a gather of all listed rows) -> now:
+// 4 x 16K tokens 19.1 -> 13, 86.8 -> 82.5; whole call 16 x 32K 373 -> 358, 32 x 8K 324 -> 311, 4 x 128K 353 -> 333, 8 x 4K paged
+// 82.4 -> 82.0, one of 2K 37.4 -> 37.2.
+template <int NT, bool OPTIONS>
+__global__ __launch_bounds__(NT, 4) void budget_kernel(HeadArgs A) {
+  touch_args<HeadArgs>();
+  if constexpr (!OPTIONS) {
+    A.nested = A.ascending = A.small_batches = 0;
+    A.range_factor = 0.0;
+    A.b_multiple = 1;
+  }
+  using O = HeadOps<NT>;
+  extern __shared__ __align__(16) unsigned char dyn_smem[];
+  typename O::HeadSmem& sm = *reinterpret_cast<typename O::HeadSmem*>(dyn_smem);
+  const BudgetLds at = budget_lds<NT>(A.n_max);
+  uint32_t* lds = reinterpret_cast<uint32_t*>(dyn_smem);
+  uint32_t* bm_f = lds + at.bm_f;
+  const int h = head_of_block((int)blockIdx.x, A.Hq, A.Hkv, A.group_major), b = blockIdx.y;
+  const int bh = b * A.Hq + h, tid = threadIdx.x;
+  const int seq = seq_of_pair(b, A.q_len);
+  // everything that can be asked for before the sizes are known
+  const HeadRec rec = A.head_rec[bh];
+  const uint64_t seed = A.seq_seeds[seq];
+  int32_t* c = A.out_counts + (int64_t)bh * 8;
+  int flags = c[7];
+  int32_t* idx = A.out_idx + (int64_t)bh * A.idx_cap;
+  // (list entries of the first two rounds, whatever the lists hold: no list is longer than what follows its start)
+  constexpr int U = 2;
+  const int64_t last = A.idx_cap - 1;
+  int top[U], base[U];
+#pragma unroll
+  for (int u = 0; u < U; ++u) {
+    top[u] = idx[min(A.seg_topk + u * NT + tid, last)];
+    base[u] = idx[min(A.seg_base + u * NT + tid, last)];
+  }
+  // Numerator statistics from the V pass, per split {N_f[d], R1[d], R2, pad}: a thread per column, and one per split for R2.
+  const int d = A.head_dim, stride = 2 * d + 2;
+  const double* vp = A.vstat_part + (int64_t)bh * A.vstat_splits * stride;
+  constexpr int VS = 8;
+  double x[VS], y[VS], nf = 0.0, r1 = 0.0, r2 = 0.0;
+  auto ask = [&](int s0) {
+#pragma unroll
+    for (int u = 0; u < VS; ++u) {
+      const int from = min(s0 + u, A.vstat_splits - 1) * stride + tid;
+      x[u] = vp[from];
+      y[u] = vp[from + d];
+    }
+  };
+  auto take = [&](int s0) {
+#pragma unroll
+    for (int u = 0; u < VS; ++u) {
+      nf += s0 + u < A.vstat_splits ? x[u] : 0.0;
+      r1 += s0 + u < A.vstat_splits ? y[u] : 0.0;
+    }
+  };
+  if (tid < d) ask(0);
+  else if (tid - d < A.vstat_splits) r2 = vp[(tid - d) * stride + 2 * d];  // (at most 32)
+  for (int w = tid; w < 3 * (bitmap_words(A.n_max) / 4); w += NT)
+    reinterpret_cast<uint4*>(bm_f)[w] = make_uint4(0u, 0u, 0u, 0u);  // the three bitmaps follow each other
+  const int n = rec.n;
+  const HeadSizes hs = head_sizes(n, A.sp);
+  const float* row = A.scores + (int64_t)bh * A.n_pad;
+  // scores of the listed tokens, -inf where a thread has none (exp(-inf) = 0)
+  const int n_base = hs.n_s > 0 ? hs.b0 : 0;
+  float sc_top[U], sc_base[U];
+#pragma unroll
+  for (int u = 0; u < U; ++u) {
+    top[u] = min(max(top[u], 0), n - 1);
+    sc_top[u] = row[top[u]];
+    sc_base[u] = row[min(max(base[u], 0), n - 1)];
+  }
+  const float sc_sink = row[min(tid, n - 1)], sc_win = row[min(hs.mid_hi + tid, n - 1)];
+  __syncthreads();
+#pragma unroll
+  for (int u = 0; u < U; ++u)
+    if (u * NT + tid < hs.k) O::mark_bit(bm_f, (uint32_t)top[u]);
+  for (int t = tid + U * NT; t < hs.k; t += NT) O::mark_bit(bm_f, (uint32_t)O::list_tok(idx, A.seg_topk + t, n));
+  if (tid < d) {
+    take(0);
+    if (A.vstat_splits > VS) ask(VS);
+  }
+
+  typename O::Sampler S;
+  S.taken = lds + at.taken;
+  S.scratch = lds + at.scratch;
+  S.mail = lds + at.mail;
+  S.bm_f = bm_f;
+  S.wpre = lds + at.wpre;
+  S.row = row;
+  S.seed = seed;
+  S.stream = 1u;
+  S.head = (uint32_t)h;
+  S.query = (uint32_t)(b - seq * A.q_len);
+  S.L = (uint32_t)max(hs.mid_hi - hs.mid_lo, 1);
+  S.thr = (0u - S.L) % S.L;  // 2^32 mod L
+  {
+    const uint64_t dflt = 64ull * (uint64_t)S.L + 4096ull;
+    S.cap = (uint32_t)min(A.draw_cap ? (uint64_t)A.draw_cap : dflt, 0x80000000ull);
+  }
+  S.m = rec.m;
+  S.dbg = nullptr;
+  DrawBatch spec = {};
+  // From 12K residual tokens on, 512 threads make 2048 draws at first, where the other targets' kernel has 1024; fewer tokens are drawn
+  // too often for that (us per call, 1024 / 2048 draws: 4 x 16K tokens 86.4 / 84.4, 32 x 8K 311 / 308, but 8 x 4K 85.1 / 85.3, 2 x 9K
+  // 53.1 / 53.9; workgroups of 1024 threads with 4096 draws 84.9, 334, 88.2, 56.5).
+  const int plan_batch = ahead_blocks<NT>(A.small_batches, hs, final_draws(hs));
+  const int first_batch = OPTIONS || hs.n_s < 12288 ? plan_batch : likely_blocks(NT, hs, final_draws(hs));
+  const bool want = hs.n_s > 0 && !A.nested;  // (a nested final sample rarely draws at all)
+  if (want) O::make_batch(spec, S, hs, 0u, first_batch, false, false, sm, tid);
+  constexpr bool kPlace = NT >= 1024;  // (as in the selection-only kernel)
+  if (want && kPlace) {
+#pragma unroll
+    for (int e = 0; e < 4; ++e) spec.sc[e] = row[min(spec.tok[e], (uint32_t)(n - 1))];
+    spec.have_sc = true;
+  }
+
+  double sums[3] = {0.0, 0.0, 0.0};  // D_f, and the base sample's weights and their squares
+  auto fixed = [&](float sc) { sums[0] += (double)__expf(sc - rec.m); };
+  auto sampled = [&](float sc) {
+    const double w = (double)__expf(sc - rec.m);
+    sums[1] += w;
+    sums[2] += w * w;
+  };
+#pragma unroll
+  for (int u = 0; u < U; ++u) {
+    fixed(u * NT + tid < hs.k ? sc_top[u] : -INFINITY);
+    sampled(u * NT + tid < n_base ? sc_base[u] : -INFINITY);
+  }
+  for (int t = tid + U * NT; t < hs.k; t += NT) fixed(row[O::list_tok(idx, A.seg_topk + t, n)]);
+  for (int t = tid + U * NT; t < n_base; t += NT) sampled(row[O::list_tok(idx, A.seg_base + t, n)]);
+  fixed(tid < hs.n_sink ? sc_sink : -INFINITY);
+  fixed(tid < hs.n_win ? sc_win : -INFINITY);
+  for (int i = tid + NT; i < hs.n_sink; i += NT) fixed(row[i]);
+  for (int i = tid + NT; i < hs.n_win; i += NT) fixed(row[hs.mid_hi + i]);
+  O::block_sum(sums, sm);
+  const double D_f = sums[0];
+  if (tid < d) {
+    if (A.vstat_splits > VS) take(VS);
+    for (int s0 = 2 * VS; s0 < A.vstat_splits; s0 += VS) {
+      ask(s0);
+      take(s0);
+    }
+    A.fixed_sums[(int64_t)bh * kFixedSums + 1 + tid] = nf;
+  }
+  if (tid == 0) A.fixed_sums[(int64_t)bh * kFixedSums] = D_f;
+  double sigma2 = 0.0, b_star = 0.0, tr_sigma = 0.0, nhat_sq = 0.0, D_hat = D_f;
+  int bfin = 0;
+  if (hs.n_s > 0) {
+    const double ns = (double)hs.n_s;
+    const double nh = nf + ns * r1 / (double)hs.b0;
+    double t3[3] = {nh * nh, r1 * r1, r2};  // (zero where a thread has no column)
+    O::block_sum(t3, sm);
+    nhat_sq = t3[0];
+    const double rho_N = numerator_rho(hs.n_s, hs.b0, t3[1], t3[2], nhat_sq, &tr_sigma);
+    const Budget bud = algorithm2_budget(A, hs.n_s, hs.b0, D_f, sums[1], sums[2], rho_N, 1.0);
+    sigma2 = bud.sigma2;
+    b_star = bud.b_star;
+    bfin = bud.b;
+    D_hat = bud.D_hat;
+  }
+  if (tid == 0 && A.out_stats) {
+    float* st = A.out_stats + (int64_t)bh * 4;
+    st[0] = (float)D_hat;
+    st[1] = (float)sigma2;
+    st[2] = (float)tr_sigma;
+    st[3] = (float)nhat_sq;
+  }
+
+  // ---- I_dyn (Algorithm 1, final sample) ----
+  bool dyn_placed = false;
+  if (bfin > 0) {
+    Emit E = emit_to(idx + A.seg_dyn, (uint32_t)A.b_max);
+    if (kPlace) E.sc_dst = A.place_sc + (int64_t)bh * A.idx_cap + A.seg_dyn;
+    // (the flag of further batches goes by the size that the first batch has elsewhere)
+    const int f = A.nested ? O::draw_nested(S, hs, (uint32_t)hs.b0, (uint32_t)bfin, bm_f, idx + A.seg_base, idx + A.seg_dyn,
+                                            (uint32_t)A.b_max, A.small_batches, sm)
+                           : O::draw_sample(S, hs, (uint32_t)bfin, spec, want, A.small_batches, E, nullptr, nullptr, sm, 0u, 0u,
+                                            !OPTIONS, plan_batch);
+    flags |= ((f & 1) ? kFlagDynComplement : 0) | ((f & 2) ? kFlagDynBatches : 0) | ((f & 4) ? kFlagDrawCap : 0);
+    // (one batch made ahead with its scores held the whole sample, and the list stays in acceptance order)
+    dyn_placed = kPlace && !A.nested && !A.ascending && want && f == 0;
+    if (A.ascending && !A.nested && !(f & 1))
+      O::sort_ascending(idx + A.seg_dyn, (uint32_t)min(bfin, A.b_max), S.scratch, S.wpre, n, sm);
+  }
+  if (tid == 0) {
+    c[0] = hs.n_sink;
+    c[1] = hs.n_win;
+    c[2] = hs.k;
+    c[3] = hs.n_s > 0 ? hs.b0 : 0;
+    c[4] = bfin;
+    c[5] = hs.n_s;
+    c[6] = n;
+    c[7] = flags;
+    if (A.out_budget_raw) A.out_budget_raw[bh] = b_star;
+    HeadRec r = rec;
+    r.scale = bfin > 0 ? (float)((double)hs.n_s / (double)bfin) : 0.f;
+    r.b = bfin;
+    r.b_keep = (A.nested && bfin > 0) ? hs.b0 : 0;
+    r.tail_by_token = dyn_placed ? 0 : 1;
+    A.head_rec[bh] = r;
+  }
+}
+
+typedef void (*BudgetKernel)(HeadArgs);
+BudgetKernel budget_kernel_for(int threads, bool options) {
+  if (threads == kHeadThreadsLong) return options ? budget_kernel<kHeadThreadsLong, true> : budget_kernel<kHeadThreadsLong, false>;
+  return options ? budget_kernel<kHeadThreads, true> : budget_kernel<kHeadThreads, false>;
+}
+
+}  // namespace
+
+hipError_t set_budget_kernel_attributes() {
+  // (as for the selection kernels: the limit belongs to the kernel, so it is raised to all a CU has)
+  for (const int threads : {kHeadThreads, kHeadThreadsLong})
+    for (const bool options : {false, true}) {
+      const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(budget_kernel_for(threads, options)),
+                                               hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
+      if (e != hipSuccess) return e;
+    }
+  return hipSuccess;
+}
+
+hipError_t launch_budget(const Plan& pl, const int32_t* seq_lens, const uint64_t* seq_seeds, void* ws, int32_t* out_idx,
+                         int32_t* out_counts, double* out_budget_raw, float* out_stats, hipStream_t st) {
+  HeadArgs A;
+  fill_head_args(A, pl, seq_lens, seq_seeds, ws, out_idx, out_counts, out_budget_raw, out_stats);
+  const vatt_params& p = pl.p;
+  const int threads = pl.head_threads;
+  const size_t lds = sizeof(uint32_t) * (threads == kHeadThreadsLong ? budget_lds<kHeadThreadsLong>(p.n_max) : budget_lds<kHeadThreads>(p.n_max)).end;
+  hipLaunchKernelGGL(budget_kernel_for(threads, head_options(pl)), dim3(p.n_q_heads, pl.vbatch), dim3(threads), lds, st, A);
+  return hipGetLastError();
+}
+
+}  // namespace vatt

@@ -39,8 +39,13 @@ struct GatherArgs {
 
 // A head's list is walked by position: [sink | window | top-k | tail) where the tail is the final sample
 // (scaled by n_s/b) or, for the statistics pass, the base sample (unscaled).
-template <int D, bool PAGED, bool STATS>
-__global__ __launch_bounds__(kGatherThreads) void gather_kernel(GatherArgs A) {
+// PART: the whole list; the statistics pass; or the tail alone, behind a statistics pass that has summed I_f already (targets N
+// and SDPA: its rows are not read again, the merge adds its sums; 4 x 16K tokens 18.1 -> 14.8 us).  The tail on a paged cache is held
+// to the registers of six waves per SIMD: left to itself it takes 88 and five (8 x 4K tokens 23.0 -> 21.7 us).
+enum Part { kWhole, kStats, kTail };
+template <int D, bool PAGED, int PART>
+__global__ __launch_bounds__(kGatherThreads, PAGED && PART == kTail ? 6 : 1) void gather_kernel(GatherArgs A) {
+  constexpr bool STATS = PART == kStats;
   constexpr int LPR = D / 8;
   constexpr int RPW = kWave / LPR;
   constexpr int WAVES = kGatherThreads / kWave;
@@ -54,7 +59,8 @@ __global__ __launch_bounds__(kGatherThreads) void gather_kernel(GatherArgs A) {
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int sub = lane % LPR, rsub = lane / LPR;
 
-  const HeadRec r = A.head_rec[bh];
+  HeadRec r = A.head_rec[bh];
+  if constexpr (PART == kTail) r.n_sink = r.n_win = r.k = 0;
   // (pointers that are the same for the whole workgroup, indexed with 32-bit offsets: address arithmetic in 64
   // bits for every row was most of this kernel's instructions, and the kernel was bound by issuing them)
   const int32_t* idx = A.idx + (int64_t)bh * A.idx_cap;
@@ -64,7 +70,7 @@ __global__ __launch_bounds__(kGatherThreads) void gather_kernel(GatherArgs A) {
   const uint16_t* v_head = PAGED ? A.v : A.v + (int64_t)seq * A.L.seq_stride + (int64_t)kvh * A.L.head_stride;
   const int total = r.n_sink + r.n_win + r.k + r.b;
   const int splits = STATS ? A.splits : used_splits(A.splits, total, RPB * U);
-  if (split >= splits) return;
+  if (split >= splits) return;  // (all of them where a tail is empty)
   const bool shared_rows = rows_are_shared(total, A.group_major ? A.q_len * A.group : A.q_len, r.n);
   const int per = (total + splits - 1) / splits;
   const int p_lo = split * per, p_hi = min(p_lo + per, total);
@@ -228,14 +234,14 @@ __global__ __launch_bounds__(kGatherThreads) void gather_kernel(GatherArgs A) {
     float a = 0.f;
 #pragma unroll
     for (int w2 = 0; w2 < WAVES; ++w2) a += s_acc[w2][tid];
-    if (splits == 1) {
+    if (PART != kTail && splits == 1) {
       A.out_o[(int64_t)bh * D + tid] = a / dtot;  // one workgroup per head: finished here
     } else {
       part[tid] = a;
     }
   }
   if (tid == 0) {
-    if (splits == 1) {
+    if (PART != kTail && splits == 1) {
       if (A.out_lse) A.out_lse[bh] = r.m + logf(dtot);
     } else {
       part[D] = dtot;
@@ -280,7 +286,39 @@ __global__ __launch_bounds__(D) void gather_merge_kernel(const float* __restrict
   if (c == 0 && out_lse) out_lse[bh] = r.m + logf(dtot);
 }
 
-template <int D, bool STATS>
+// The same for targets N and SDPA: the parts are the final sample's, and the sums over I_f are those that the budget
+// kernel left.  All partial sums are requested together.
+template <int D>
+__global__ __launch_bounds__(D) void tail_merge_kernel(const float* __restrict__ part, const double* __restrict__ fixed_sums,
+                                                       const HeadRec* __restrict__ head_rec, int splits, int Hq,
+                                                       float* __restrict__ out_o, float* __restrict__ out_lse,
+                                                       int group_major, int Hkv, int step_rows) {
+  const int h = head_of_block((int)blockIdx.x, Hq, Hkv, group_major), b = blockIdx.y, bh = b * Hq + h;
+  const int c = threadIdx.x;
+  const float* p = part + (int64_t)bh * splits * (D + 4);
+  const double* fixed = fixed_sums + (int64_t)bh * kFixedSums;
+  const HeadRec r = head_rec[bh];
+  constexpr int U = 16;
+  double dtot = fixed[0], a = fixed[1 + c];
+  const int used = used_splits(splits, r.b, step_rows);  // (those that took part: none where the sample is empty)
+  for (int s0 = 0; s0 < splits; s0 += U) {
+    float v[U], w[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      v[u] = p[min(s0 + u, splits - 1) * (D + 4) + c];
+      w[u] = p[min(s0 + u, splits - 1) * (D + 4) + D];
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      a += s0 + u < used ? (double)v[u] : 0.0;
+      dtot += s0 + u < used ? (double)w[u] : 0.0;
+    }
+  }
+  out_o[(int64_t)bh * D + c] = (float)(a / dtot);
+  if (c == 0 && out_lse) out_lse[bh] = r.m + logf((float)dtot);
+}
+
+template <int D, int PART>
 hipError_t launch_gather_d(const Plan& pl, const void* v, const int32_t* block_table, void* ws,
                            const int32_t* out_idx, float* out_o, float* out_lse, hipStream_t st) {
   const vatt_params& p = pl.p;
@@ -306,19 +344,26 @@ hipError_t launch_gather_d(const Plan& pl, const void* v, const int32_t* block_t
   A.n_pad = pl.n_pad;
   A.Hq = p.n_q_heads;
   A.group = pl.group;
-  A.splits = STATS ? pl.vstat_splits : pl.gather_splits;
+  A.splits = PART == kStats ? pl.vstat_splits : pl.gather_splits;
   A.q_len = pl.q_len;
   A.group_major = pl.group_major;
   A.Hkv = p.n_kv_heads;
   dim3 grid(p.n_q_heads, A.splits, pl.vbatch);
   if (p.kv_layout == VATT_LAYOUT_PAGED)
-    hipLaunchKernelGGL((gather_kernel<D, true, STATS>), grid, dim3(kGatherThreads), 0, st, A);
+    hipLaunchKernelGGL((gather_kernel<D, true, PART>), grid, dim3(kGatherThreads), 0, st, A);
   else
-    hipLaunchKernelGGL((gather_kernel<D, false, STATS>), grid, dim3(kGatherThreads), 0, st, A);
+    hipLaunchKernelGGL((gather_kernel<D, false, PART>), grid, dim3(kGatherThreads), 0, st, A);
   hipError_t e = hipGetLastError();
-  if (e != hipSuccess || STATS || A.splits == 1) return e;
+  if (e != hipSuccess || PART == kStats || (PART == kWhole && A.splits == 1)) return e;
+  constexpr int step_rows = (kGatherThreads / (D / 8)) * 8;
+  if constexpr (PART == kTail) {
+    hipLaunchKernelGGL((tail_merge_kernel<D>), dim3(p.n_q_heads, pl.vbatch), dim3(D), 0, st, A.part,
+                       reinterpret_cast<const double*>(w + pl.off_pre_tok), A.head_rec, A.splits, p.n_q_heads, out_o, out_lse,
+                       pl.group_major, p.n_kv_heads, step_rows);
+    return hipGetLastError();
+  }
   hipLaunchKernelGGL((gather_merge_kernel<D>), dim3(p.n_q_heads, pl.vbatch), dim3(D), 0, st, A.part, A.head_rec,
-                     A.splits, p.n_q_heads, out_o, out_lse, pl.group_major, p.n_kv_heads, (kGatherThreads / (D / 8)) * 8);
+                     A.splits, p.n_q_heads, out_o, out_lse, pl.group_major, p.n_kv_heads, step_rows);
   return hipGetLastError();
 }
 
@@ -326,8 +371,13 @@ hipError_t launch_gather_d(const Plan& pl, const void* v, const int32_t* block_t
 
 hipError_t launch_gather(const Plan& pl, const void* v, const int32_t* block_table, void* ws,
                          const int32_t* out_idx, float* out_o, float* out_lse, hipStream_t st) {
-  if (pl.p.head_dim == 128) return launch_gather_d<128, false>(pl, v, block_table, ws, out_idx, out_o, out_lse, st);
-  if (pl.p.head_dim == 64) return launch_gather_d<64, false>(pl, v, block_table, ws, out_idx, out_o, out_lse, st);
+  const bool tail = pl.p.target != VATT_TARGET_D;
+  if (pl.p.head_dim == 128)
+    return tail ? launch_gather_d<128, kTail>(pl, v, block_table, ws, out_idx, out_o, out_lse, st)
+                : launch_gather_d<128, kWhole>(pl, v, block_table, ws, out_idx, out_o, out_lse, st);
+  if (pl.p.head_dim == 64)
+    return tail ? launch_gather_d<64, kTail>(pl, v, block_table, ws, out_idx, out_o, out_lse, st)
+                : launch_gather_d<64, kWhole>(pl, v, block_table, ws, out_idx, out_o, out_lse, st);
   return hipErrorInvalidValue;
 }
 
@@ -349,8 +399,8 @@ hipError_t launch_gather_merge(const Plan& pl, void* ws, int splits, float* out_
 
 hipError_t launch_vstats(const Plan& pl, const void* v, const int32_t* block_table, void* ws,
                          const int32_t* out_idx, hipStream_t st) {
-  if (pl.p.head_dim == 128) return launch_gather_d<128, true>(pl, v, block_table, ws, out_idx, nullptr, nullptr, st);
-  if (pl.p.head_dim == 64) return launch_gather_d<64, true>(pl, v, block_table, ws, out_idx, nullptr, nullptr, st);
+  if (pl.p.head_dim == 128) return launch_gather_d<128, kStats>(pl, v, block_table, ws, out_idx, nullptr, nullptr, st);
+  if (pl.p.head_dim == 64) return launch_gather_d<64, kStats>(pl, v, block_table, ws, out_idx, nullptr, nullptr, st);
   return hipErrorInvalidValue;
 }
 

@@ -15,6 +15,9 @@ constexpr int kSubTile = 8;            // keys per sub-tile maximum
 constexpr int kHeadThreads = 512;      // workgroup size of the per-head kernel
 constexpr int kHeadThreadsLong = 1024; // ... for rows whose 8-key maxima do not fit the registers of 512 threads
 constexpr int kGatherThreads = 256;
+// Targets N and SDPA: the doubles that the budget kernel leaves of a head for the merge: D_f, and N_f from the second on.
+constexpr int kFixedSums = 1 + 128;
+static_assert(kFixedSums * sizeof(double) <= kHeadThreads * sizeof(uint4), "it lies in the region of the draws made ahead");
 // Launch orders of the score pass (see the score kernel); the values of VATT_OPT_SCORE_ORDER.
 constexpr int kScoreOrderTile = 0, kScoreOrderKvHead = 1, kScoreOrderBlocks = 2;
 constexpr int kDenseThreads = 256;
@@ -124,7 +127,7 @@ hipError_t launch_score(const Plan& pl, const void* q, const void* k, const int3
 // The score pass of a multi-query step (q_len > 1): all query tokens and group heads share one read of K.
 hipError_t launch_score_chunk(const Plan& pl, const void* q, const void* k, const int32_t* block_table,
                               const int32_t* seq_lens, void* ws, hipStream_t st);
-// phase 0: everything (target D); phase 1: through the base sample; phase 2: budget and final sample.
+// phase 0: everything (target D); phase 1: through the base sample.
 hipError_t launch_head(const Plan& pl, int phase, const int32_t* seq_lens, const uint64_t* seq_seeds, void* ws,
                        int32_t* out_idx, int32_t* out_counts, double* out_budget_raw, float* out_stats,
                        hipStream_t st);
@@ -181,6 +184,9 @@ hipError_t launch_given_gather(const Plan& pl, const void* q, const void* k, con
                                float* out_lse, hipStream_t st);
 hipError_t launch_vstats(const Plan& pl, const void* v, const int32_t* block_table, void* ws,
                          const int32_t* out_idx, hipStream_t st);
+// Targets N and SDPA: budget and final sample, behind phase 1 and the V-side statistics.
+hipError_t launch_budget(const Plan& pl, const int32_t* seq_lens, const uint64_t* seq_seeds, void* ws, int32_t* out_idx,
+                         int32_t* out_counts, double* out_budget_raw, float* out_stats, hipStream_t st);
 hipError_t launch_gather(const Plan& pl, const void* v, const int32_t* block_table, void* ws,
                          const int32_t* out_idx, float* out_o, float* out_lse, hipStream_t st);
 hipError_t launch_dense(const Plan& pl, const void* q, const void* k, const void* v, const int32_t* block_table,
@@ -188,6 +194,7 @@ hipError_t launch_dense(const Plan& pl, const void* q, const void* k, const void
 hipError_t launch_append(const Plan& pl, const void* k_new, const void* v_new, void* k, void* v,
                          const int32_t* block_table, int32_t* seq_lens, hipStream_t st);
 hipError_t set_kernel_attributes(const Plan& pl);        // every selection kernel: dynamic LDS limit
+hipError_t set_budget_kernel_attributes();
 hipError_t set_given_kernel_attributes(const Plan& pl);  // (its part for the caller-supplied-top-k kernels)
 // Dynamic and static LDS of the selection kernels, and the LDS list entries of the fused gathers.
 size_t head_kernel_lds_bytes(int n_max, int head_threads);

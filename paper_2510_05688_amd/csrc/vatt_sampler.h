@@ -360,11 +360,11 @@ struct HeadOps {
   // sum_w is given, adds exp(s_i - m) and its square over the sample to this thread's partial sums.
   // have, blk: the first `have` tokens, from the Philox blocks before blk, are listed already (no complement).
   // Returns flag bits: 1 complement regime, 2 more than one batch, 4 draw cap reached.  by_rule: bit 2 says whether the sample
-  // needs more than a first batch of first_blocks(), whatever batches it was made from.
+  // needs more than a first batch of rule_blocks (0: first_blocks()), whatever batches it was made from.
   static __device__ __forceinline__ int draw_sample(const Sampler& S, const HeadSizes& hs, uint32_t c, const DrawBatch& spec, bool have_spec,
                                     int small_batches, const Emit& E, double* sum_w,
                                     double* sum_w2, HeadSmem& sm, uint32_t have = 0u, uint32_t blk = 0u,
-                                    bool by_rule = false) {
+                                    bool by_rule = false, int rule_blocks = 0) {
     const int tid = threadIdx.x;
     const int words = (hs.n + 31) >> 5;
     const uint32_t ns = (uint32_t)hs.n_s;
@@ -382,7 +382,7 @@ struct HeadOps {
     int batches = blk > 0u ? 1 : 0;
     bool use_spec = have_spec;
     double aw = 0.0, aw2 = 0.0;
-    const uint32_t rule = (uint32_t)first_blocks(small_batches, target);
+    const uint32_t rule = (uint32_t)(rule_blocks > 0 ? rule_blocks : first_blocks(small_batches, target));
     while (have < target) {
       if ((uint64_t)blk * 4ull >= (uint64_t)S.cap) break;
       DrawBatch B;
@@ -544,9 +544,9 @@ struct HeadOps {
 // least (n_s - most) / L, so `most` L / (n_s - most) draws suffice on average; six standard deviations are added (a
 // batch that falls short costs time only).
 template <int NT>
-__device__ __forceinline__ int ahead_blocks(int small_batches) {
+__host__ __device__ constexpr int ahead_blocks(int small_batches) {
   // (a workgroup of 1024 threads serves long rows, whose samples hold thousands of tokens)
-  return small_batches ? kSmallBatchBlocks : (NT >= 1024 ? 1024 : min(NT, 256));
+  return small_batches ? kSmallBatchBlocks : (NT >= 1024 ? 1024 : NT < 256 ? NT : 256);
 }
 __device__ __forceinline__ int likely_blocks(int all, const HeadSizes& hs, int most) {
   const int L = max(hs.mid_hi - hs.mid_lo, 1);

@@ -28,6 +28,7 @@ struct HeadArgs {
   const uint64_t* seq_seeds;
   HeadRec* head_rec;
   const double* vstat_part;  // [B*Hq][vstat_splits][2d+2] (targets N, SDPA)
+  double* fixed_sums;        // [B*Hq][kFixedSums]: see there (targets N, SDPA)
   const float* given_vstat;  // [B*Hq][given_splits][2d+4]: N_f[d], R1[d], R2, maximum (given-top-k path)
   int given_splits;
   int32_t* out_idx;
@@ -484,7 +485,13 @@ __device__ __forceinline__ void add_weighted_row(float (&acc)[8], float wt, cons
 template <int V>
 using Int = std::integral_constant<int, V>;
 
-// The arguments every launch of the two kernels starts from.
+// Whether a plan has an option set that the usual call does without (the kernels have a form without them).
+inline bool head_options(const Plan& pl) {
+  return pl.nested_samples || pl.ascending_samples || pl.topk_general_path || pl.sampler_small_batches || pl.range_factor > 0.0 ||
+         pl.budget_multiple != 1;
+}
+
+// The arguments every launch of the kernels starts from.
 inline void fill_head_args(HeadArgs& A, const Plan& pl, const int32_t* seq_lens, const uint64_t* seq_seeds, void* ws,
                            int32_t* out_idx, int32_t* out_counts, double* out_budget_raw,
                            float* out_stats) {
@@ -522,6 +529,7 @@ inline void fill_head_args(HeadArgs& A, const Plan& pl, const int32_t* seq_lens,
   A.draw_cap = pl.sampler_draw_cap;
   A.large_budgets = (pl.z_half / pl.eps) * (pl.z_half / pl.eps) > 5000.0;
   A.vstat_splits = pl.vstat_splits;
+  A.fixed_sums = reinterpret_cast<double*>(w + pl.off_pre_tok);  // (those targets have no batches made ahead)
   A.head_dim = p.head_dim;
   A.k_max = pl.k_max;
   A.b0_max = pl.b0_max;

@@ -38,7 +38,7 @@ namespace {
 // requested as soon as the top-k set is known and are added after the samplers have run.
 // ALONE: one workgroup per head, which writes the head's result itself (a branch on A.splits at the end cost the others
 // 0.4 us, and the split arithmetic these 1.4 us).
-// PHASE: 0 everything (denominator target), 1 through the base sample, 2 budget and final sample (targets N and SDPA).
+// PHASE: 0 everything (denominator target), 1 through the base sample (targets N and SDPA; budget_kernel has the rest).
 // OPTIONS: a plan with an option set that the usual call does without (head_options) has a kernel of its own; without them the
 // selection-only kernel, which is at its register limit, takes 33.6 instead of 36.5 us for 16 x 32K tokens, the fused one 20.0 instead
 // of 20.4 for 1 x 32K and 12.7 instead of 13.4 for one head of 1K.
@@ -156,8 +156,8 @@ __global__ __launch_bounds__(NT, FD > 0 ? 1 : 4) void head_kernel(HeadArgs A) {
   RowView<NT> rv;
   rv.row = row;
   rv.n = n;
-  const float edge0 = (PHASE != 2 && tid < hs.n_sink) ? row[tid] : -INFINITY;
-  const float edge1 = (PHASE != 2 && tid < hs.n_win) ? row[hs.mid_hi + tid] : -INFINITY;
+  const float edge0 = tid < hs.n_sink ? row[tid] : -INFINITY;
+  const float edge1 = tid < hs.n_win ? row[hs.mid_hi + tid] : -INFINITY;
   const int edge0_blk = kv_block<kCode>(A.L, seq, min(tid, n - 1));
   const int edge1_blk = kv_block<kCode>(A.L, seq, min(hs.mid_hi + tid, n - 1));
   const uint32_t row0_code = row_code(0u);
@@ -201,7 +201,7 @@ __global__ __launch_bounds__(NT, FD > 0 ? 1 : 4) void head_kernel(HeadArgs A) {
   S1.stream = 1u;
   S1.dbg = A.dbg ? A.dbg + 300 : nullptr;
   DrawBatch spec0 = {}, spec1 = {};
-  const bool want0 = hs.n_s > 0 && PHASE != 2 && hs.b0 < hs.n_s;
+  const bool want0 = hs.n_s > 0 && hs.b0 < hs.n_s;
   const bool want1 = hs.n_s > 0 && PHASE != 1 && !A.nested;  // (a nested final sample rarely draws at all)
   const int n_sub = (n + kSubTile - 1) / kSubTile;
   const int sub_lo = (hs.mid_lo + kSubTile - 1) / kSubTile, sub_hi = hs.mid_hi / kSubTile;  // whole middle sub-tiles
@@ -346,7 +346,7 @@ __global__ __launch_bounds__(NT, FD > 0 ? 1 : 4) void head_kernel(HeadArgs A) {
     }
   };
   // ---- I_t (Algorithm 1, top-k step) ----
-  if (PHASE != 2) {
+  {
     const int mid_len = hs.mid_hi - hs.mid_lo;
     if (hs.k > 0) {
       float sT = -INFINITY;
@@ -659,15 +659,6 @@ __global__ __launch_bounds__(NT, FD > 0 ? 1 : 4) void head_kernel(HeadArgs A) {
       }
       VATT_STAMP(A.dbg, 4);
     }
-  } else {
-    // phase 2: rebuild the top-k bitmap from the list written in phase 1
-    for (int t = tid; t < hs.k; t += NT) {
-      const int i = O::list_tok(idx, A.seg_topk + t, n);
-      O::mark_bit(bm_f, (uint32_t)i);
-      acc_f += (double)__expf(row[i] - m);
-    }
-    for (int i = tid; i < hs.n_sink; i += NT) acc_f += (double)__expf(row[i] - m);
-    for (int i = tid; i < hs.n_win; i += NT) acc_f += (double)__expf(row[hs.mid_hi + i] - m);
   }
   VATT_STAMP(A.dbg, 30);
   __syncthreads();
@@ -765,7 +756,6 @@ __global__ __launch_bounds__(NT, FD > 0 ? 1 : 4) void head_kernel(HeadArgs A) {
   // by the general path only.)
   // The lists of I_f, once wpre is complete (and, with the fused gather, this workgroup's share of them in LDS).
   auto write_lists = [&]() {
-    if (PHASE == 2) return;
     // ascending list of the top-k tokens
     if (hs.k > 0) {
       if (NT >= 1024 && n_wide_used) {
@@ -847,7 +837,7 @@ __global__ __launch_bounds__(NT, FD > 0 ? 1 : 4) void head_kernel(HeadArgs A) {
     const uint32_t ns = (uint32_t)hs.n_s, c0 = (uint32_t)hs.b0;
     const bool usual = kTwoStreams && PHASE == 0 && (kFused || (!A.ascending && !A.nested)) && pair_made && hs.n_s > 0 &&
                        c0 < ns && 2u * c0 <= ns;
-    const bool listed = PHASE != 2 && hs.k > 0;
+    const bool listed = hs.k > 0;
     auto test_draws = [&]() {
       const DrawBatch& B = half ? spec1 : spec0;
       acc_bits = B.first & ~O::test_bits4(bm_f, B.tok);
@@ -903,12 +893,10 @@ __global__ __launch_bounds__(NT, FD > 0 ? 1 : 4) void head_kernel(HeadArgs A) {
       }
     }
   }
-  if (PHASE != 2) {
-    // weights of the sink and window tokens (their scores were requested at the start)
-    acc_f32 += __expf(edge0 - m) + __expf(edge1 - m);  // exp(-inf) = 0 for threads without a token
-    for (int i = tid + NT; i < hs.n_sink; i += NT) acc_f32 += __expf(row[i] - m);
-    for (int i = tid + NT; i < hs.n_win; i += NT) acc_f32 += __expf(row[hs.mid_hi + i] - m);
-  }
+  // weights of the sink and window tokens (their scores were requested at the start)
+  acc_f32 += __expf(edge0 - m) + __expf(edge1 - m);  // exp(-inf) = 0 for threads without a token
+  for (int i = tid + NT; i < hs.n_sink; i += NT) acc_f32 += __expf(row[i] - m);
+  for (int i = tid + NT; i < hs.n_win; i += NT) acc_f32 += __expf(row[hs.mid_hi + i] - m);
   if (tid == NT - kWave && marked) {
     uint64_t tot = 0;
 #pragma unroll
@@ -934,21 +922,13 @@ __global__ __launch_bounds__(NT, FD > 0 ? 1 : 4) void head_kernel(HeadArgs A) {
     if (my_nf > UF * NG) load_rows(glist, glist_sc, UF * NG, my_nf, es, ev, ScInLds{});
   }
   if (hs.n_s > 0 && !fast_base) {
-    if (PHASE != 2) {
-      Emit E0 = emit_to(idx + A.seg_base, (uint32_t)A.b0_max);
-      E0.global = writer;
-      const int f = O::draw_sample(S0, hs, (uint32_t)hs.b0, spec0, want0, A.small_batches, E0, &acc_w, &acc_w2, sm);
-      flags |= ((f & 1) ? kFlagBaseComplement : 0) | ((f & 2) ? kFlagBaseBatches : 0) | ((f & 4) ? kFlagDrawCap : 0);
-      if (A.ascending && !(f & 1))
-        O::sort_ascending(idx + A.seg_base, (uint32_t)min(hs.b0, A.b0_max), scratch, wpre, n, sm);
-      VATT_STAMP(A.dbg, 5);
-    } else {
-      for (int t = tid; t < hs.b0; t += NT) {
-        const double wgt = (double)__expf(row[O::list_tok(idx, A.seg_base + t, n)] - m);
-        acc_w += wgt;
-        acc_w2 += wgt * wgt;
-      }
-    }
+    Emit E0 = emit_to(idx + A.seg_base, (uint32_t)A.b0_max);
+    E0.global = writer;
+    const int f = O::draw_sample(S0, hs, (uint32_t)hs.b0, spec0, want0, A.small_batches, E0, &acc_w, &acc_w2, sm);
+    flags |= ((f & 1) ? kFlagBaseComplement : 0) | ((f & 2) ? kFlagBaseBatches : 0) | ((f & 4) ? kFlagDrawCap : 0);
+    if (A.ascending && !(f & 1))
+      O::sort_ascending(idx + A.seg_base, (uint32_t)min(hs.b0, A.b0_max), scratch, wpre, n, sm);
+    VATT_STAMP(A.dbg, 5);
   }
   if constexpr (PHASE == 1) {
     if (tid == 0) {
@@ -1003,56 +983,18 @@ __global__ __launch_bounds__(NT, FD > 0 ? 1 : 4) void head_kernel(HeadArgs A) {
   O::block_sum_get(sums, sm);
   VATT_STAMP(A.dbg, 6);
   const double D_f = sums[0];
-  double sigma2 = 0.0, b_star = 0.0, tr_sigma = 0.0, nhat_sq = 0.0;
+  double b_star = 0.0;
   int bfin = 0;
   if (hs.n_s > 0) {
-    const double b0d = (double)hs.b0, ns = (double)hs.n_s;
-    double rho_N = 0.0;
-    if (A.target != VATT_TARGET_D) {
-      // numerator statistics from the V pass: per split {N_f[d], R1[d], R2, pad}
-      const int d = A.head_dim;
-      const int stride = 2 * d + 2;
-      const double* vp = A.vstat_part + (int64_t)bh * A.vstat_splits * stride;
-      double t3[3] = {0.0, 0.0, 0.0};
-      if (tid < d) {
-        // (eight splits requested together: one after the other they took 10 us of this kernel's 25 with 16 splits)
-        constexpr int VS = 8;
-        double nf = 0.0, r1 = 0.0;
-        for (int s0 = 0; s0 < A.vstat_splits; s0 += VS) {
-          double x[VS], y[VS];
-#pragma unroll
-          for (int u = 0; u < VS; ++u) {
-            const int at = min(s0 + u, A.vstat_splits - 1) * stride + tid;
-            x[u] = vp[at];
-            y[u] = vp[at + d];
-          }
-#pragma unroll
-          for (int u = 0; u < VS; ++u) {
-            nf += s0 + u < A.vstat_splits ? x[u] : 0.0;
-            r1 += s0 + u < A.vstat_splits ? y[u] : 0.0;
-          }
-        }
-        const double nh = nf + ns * r1 / b0d;
-        t3[0] = nh * nh;
-        t3[1] = r1 * r1;
-      } else if (tid - d < A.vstat_splits) {  // (at most 32)
-        t3[2] = vp[(tid - d) * stride + 2 * d];
-      }
-      O::block_sum(t3, sm);
-      nhat_sq = t3[0];
-      rho_N = numerator_rho(hs.n_s, hs.b0, t3[1], t3[2], nhat_sq, &tr_sigma);
-    }
-    const Budget bud = algorithm2_budget(A, hs.n_s, hs.b0, D_f, sums[1], sums[2], rho_N, w_range);
-    sigma2 = bud.sigma2;
+    const Budget bud = algorithm2_budget(A, hs.n_s, hs.b0, D_f, sums[1], sums[2], 0.0, w_range);
     b_star = bud.b_star;
     bfin = bud.b;
     const double D_hat = bud.D_hat;
     if (tid == 0 && writer && A.out_stats) {
       float* st = A.out_stats + (int64_t)bh * 4;
       st[0] = (float)D_hat;
-      st[1] = (float)sigma2;
-      st[2] = (float)tr_sigma;
-      st[3] = (float)nhat_sq;
+      st[1] = (float)bud.sigma2;
+      st[2] = st[3] = 0.f;
     }
   } else if (tid == 0 && writer && A.out_stats) {
     float* st = A.out_stats + (int64_t)bh * 4;
@@ -1121,7 +1063,6 @@ __global__ __launch_bounds__(NT, FD > 0 ? 1 : 4) void head_kernel(HeadArgs A) {
   }
   if (tid == 0 && writer) {
     int32_t* c = A.out_counts + (int64_t)bh * 8;
-    const int prev = (PHASE == 2) ? c[7] : 0;
     c[0] = hs.n_sink;
     c[1] = hs.n_win;
     c[2] = hs.k;
@@ -1129,7 +1070,7 @@ __global__ __launch_bounds__(NT, FD > 0 ? 1 : 4) void head_kernel(HeadArgs A) {
     c[4] = bfin;
     c[5] = hs.n_s;
     c[6] = n;
-    c[7] = prev | flags;
+    c[7] = flags;
     if (A.out_budget_raw) A.out_budget_raw[bh] = b_star;
     HeadRec r;
     r.m = m;
@@ -1290,17 +1231,11 @@ HeadKernel fused_kernel_for(int d, bool paged, bool alone, bool options) {
 }
 template <int NT, bool OPTIONS>
 HeadKernel head_kernel_for(int phase) {
-  return phase == 0   ? head_kernel<NT, 0, false, false, 0, OPTIONS>
-         : phase == 1 ? head_kernel<NT, 0, false, false, 1, OPTIONS>
-                      : head_kernel<NT, 0, false, false, 2, OPTIONS>;
+  return phase == 0 ? head_kernel<NT, 0, false, false, 0, OPTIONS> : head_kernel<NT, 0, false, false, 1, OPTIONS>;
 }
 HeadKernel head_kernel_for(int threads, int phase, bool options) {
   if (threads == kHeadThreadsLong) return options ? head_kernel_for<kHeadThreadsLong, true>(phase) : head_kernel_for<kHeadThreadsLong, false>(phase);
   return options ? head_kernel_for<kHeadThreads, true>(phase) : head_kernel_for<kHeadThreads, false>(phase);
-}
-bool head_options(const Plan& pl) {
-  return pl.nested_samples || pl.ascending_samples || pl.topk_general_path || pl.sampler_small_batches || pl.range_factor > 0.0 ||
-         pl.budget_multiple != 1;
 }
 
 }  // namespace
@@ -1313,7 +1248,7 @@ hipError_t set_kernel_attributes(const Plan& pl) {
     return hipFuncSetAttribute(reinterpret_cast<const void*>(f), hipFuncAttributeMaxDynamicSharedMemorySize, cap);
   };
   for (const int threads : {kHeadThreads, kHeadThreadsLong})
-    for (const int phase : {0, 1, 2})
+    for (const int phase : {0, 1})
       for (const bool options : {false, true}) {
         const hipError_t e = raise(head_kernel_for(threads, phase, options));
         if (e != hipSuccess) return e;
@@ -1325,7 +1260,8 @@ hipError_t set_kernel_attributes(const Plan& pl) {
           const hipError_t e = raise(fused_kernel_for(d, paged, alone, options));
           if (e != hipSuccess) return e;
         }
-  return set_given_kernel_attributes(pl);
+  const hipError_t e = set_budget_kernel_attributes();
+  return e != hipSuccess ? e : set_given_kernel_attributes(pl);
 }
 
 size_t head_kernel_lds_bytes(int n_max, int head_threads) {
