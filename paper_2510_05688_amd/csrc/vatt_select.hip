@@ -67,7 +67,18 @@ __global__ __launch_bounds__(NT, FD > 0 ? 1 : 4) void head_kernel(HeadArgs A) {
   constexpr bool kSplit = kFused && !ALONE;
   const uint32_t split = kSplit ? blockIdx.z : 0u, shift = kSplit ? (uint32_t)A.split_shift : 0u;
   const uint32_t smask = (1u << shift) - 1u;
-  const bool writer = split == 0u;  // this workgroup writes the head's outputs
+  // Long rows, no more heads than half the compute units: a second workgroup per head (A.splits == 2) repeats the top-k step and
+  // writes what the first would make the base sample wait for, the lists of I_f, and what it would make the budget wait for, the
+  // scores of the final sample's proposals at the list places.  Nothing is exchanged: it writes the scores of all accepted draws of the
+  // first batch, and the first workgroup says in the record whether the sample is the beginning of them.  A compute unit takes
+  // four to five clocks per scattered 4-byte read, and with one workgroup per head half of the units pulled all of them.
+  // Whole call, us, one -> two: 4 x 128K tokens 250.5 -> 245.0, 1 x 128K 113.6 -> 103.0, 2 of 9K - 100K paged 108.5 -> 99.1, 4 x 50K with
+  // k and b0 of 5 % 151.6 -> 145.4, 1 x 60K at epsilon 0.02 59.5 -> 57.3, 1 x 91K with 3 query tokens 109.4 -> 99.1.
+  constexpr bool kPair = !kFused && NT >= 1024 && PHASE == 0 && !OPTIONS;
+  const bool paired = kPair && A.splits == 2;
+  const bool second = paired && blockIdx.z == 1u;
+  const bool lister = !paired || second;            // this workgroup writes the lists of I_f
+  const bool writer = split == 0u && !second;       // this workgroup writes the head's other outputs
   // The sub-tile maxima the score kernel left are requested first of all, before even the sequence length is
   // known (what lies beyond the row's own sub-tiles is masked once it is): the kernel starts with a chain of
   // dependent loads, and this takes one link out of it.  Rows of up to 8 * NT sub-tiles keep the maxima in
@@ -201,7 +212,7 @@ __global__ __launch_bounds__(NT, FD > 0 ? 1 : 4) void head_kernel(HeadArgs A) {
   S1.stream = 1u;
   S1.dbg = A.dbg ? A.dbg + 300 : nullptr;
   DrawBatch spec0 = {}, spec1 = {};
-  const bool want0 = hs.n_s > 0 && hs.b0 < hs.n_s;
+  const bool want0 = hs.n_s > 0 && hs.b0 < hs.n_s && !second;
   const bool want1 = hs.n_s > 0 && PHASE != 1 && !A.nested;  // (a nested final sample rarely draws at all)
   const int n_sub = (n + kSubTile - 1) / kSubTile;
   const int sub_lo = (hs.mid_lo + kSubTile - 1) / kSubTile, sub_hi = hs.mid_hi / kSubTile;  // whole middle sub-tiles
@@ -273,6 +284,9 @@ __global__ __launch_bounds__(NT, FD > 0 ? 1 : 4) void head_kernel(HeadArgs A) {
     pair_made = true;
   } else if (want0) {
     O::make_batch(spec0, S0, hs, 0u, ahead_blocks<NT>(A.small_batches, hs, base_draws(hs)), false, true, sm, tid);
+  } else if (second && want1) {
+    O::make_batch(spec1, S1, hs, 0u, ahead_blocks<NT>(A.small_batches, hs, final_draws(hs)), false, true, sm, tid);
+    spec1_made = true;
   }
   auto clear_cand_hist = [&]() {
     for (int w = tid; w < kBins / 4; w += NT) reinterpret_cast<uint4*>(cand_hist)[w] = make_uint4(0u, 0u, 0u, 0u);
@@ -778,7 +792,7 @@ __global__ __launch_bounds__(NT, FD > 0 ? 1 : 4) void head_kernel(HeadArgs A) {
           const uint32_t word = bm_f[i >> 5], bit = 1u << (i & 31);
           if (word & bit) {
             const uint32_t pos = wpre[i >> 5] + (uint32_t)__popc(word & (bit - 1u));
-            if (writer && pos < (uint32_t)A.k_max) idx[A.seg_topk + pos] = (int32_t)i;
+            if ((kFused ? writer : lister) && pos < (uint32_t)A.k_max) idx[A.seg_topk + pos] = (int32_t)i;
             if (!kFused && pos < (uint32_t)A.k_max) place_sc[A.seg_topk + pos] = float_from_order_key(~(uint32_t)(c >> 32));
             to_glist((uint32_t)(hs.n_sink + hs.n_win) + pos, code_of(i, blk), float_from_order_key(~(uint32_t)(c >> 32)));
           }
@@ -799,7 +813,7 @@ __global__ __launch_bounds__(NT, FD > 0 ? 1 : 4) void head_kernel(HeadArgs A) {
           while (bits) {
             const int i = (w << 5) + (__ffs(bits) - 1);
             bits &= bits - 1u;
-            if (writer && pos < (uint32_t)A.k_max) idx[A.seg_topk + pos] = i;
+            if ((kFused ? writer : lister) && pos < (uint32_t)A.k_max) idx[A.seg_topk + pos] = i;
             if (kFused) to_glist((uint32_t)(hs.n_sink + hs.n_win) + pos, row_code((uint32_t)i), row[i]);
             else if (pos < (uint32_t)A.k_max) place_sc[A.seg_topk + pos] = row[i];
             ++pos;
@@ -808,12 +822,12 @@ __global__ __launch_bounds__(NT, FD > 0 ? 1 : 4) void head_kernel(HeadArgs A) {
       }
     }
     for (int i = tid; i < hs.n_sink; i += NT) {
-      if (writer) idx[A.seg_sink + i] = i;
+      if (kFused ? writer : lister) idx[A.seg_sink + i] = i;
       if (kFused) to_glist((uint32_t)i, i == tid ? code_of((uint32_t)i, edge0_blk) : row_code((uint32_t)i), i == tid ? edge0 : row[i]);
       else place_sc[A.seg_sink + i] = i == tid ? edge0 : row[i];
     }
     for (int i = tid; i < hs.n_win; i += NT) {
-      if (writer) idx[A.seg_win + i] = hs.mid_hi + i;
+      if (kFused ? writer : lister) idx[A.seg_win + i] = hs.mid_hi + i;
       if (kFused) {
         const uint32_t tok = (uint32_t)(hs.mid_hi + i);
         to_glist((uint32_t)(hs.n_sink + i), i == tid ? code_of(tok, edge1_blk) : row_code(tok), i == tid ? edge1 : row[tok]);
@@ -860,8 +874,21 @@ __global__ __launch_bounds__(NT, FD > 0 ? 1 : 4) void head_kernel(HeadArgs A) {
     } else {
       // (the lists leave, and the final sample's scores are asked for, as early as they can: with every CU full this
       // kernel is bound by its scattered reads, and the gather kernel behind it takes 3 us longer when they come late)
-      if (listed) O::word_prefix(bm_f, words, wpre, sm, &sm.scan_once[2]);
-      write_lists();
+      if (lister) {
+        if (listed) O::word_prefix(bm_f, words, wpre, sm, &sm.scan_once[2]);
+        write_lists();
+      }
+      if (second) {
+        const uint32_t acc = spec1.first & ~O::test_bits4(bm_f, spec1.tok);
+        uint32_t unused, pos = block_exclusive_scan_once<NT>((uint32_t)__popc(acc), &unused, sm.scan_once[3]);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const bool a = (acc >> e) & 1u;
+          if (a && pos < (uint32_t)A.b_max) place_sc[A.seg_dyn + pos] = spec1.sc[e];
+          pos += a ? 1u : 0u;
+        }
+        return;
+      }
       if (pair_made && half) {  // (whole waves: the upper half holds the final sample's proposals)
 #pragma unroll
         for (int e = 0; e < 4; ++e) spec0.sc[e] = spec1.sc[e] = row[spec1.tok[e]];
@@ -969,7 +996,7 @@ __global__ __launch_bounds__(NT, FD > 0 ? 1 : 4) void head_kernel(HeadArgs A) {
   // short of registers, the same cost more than the gather gains: a sample that its shortcut above does not
   // cover is read by token.)
   constexpr bool kEmitScores = !kFused && NT >= 1024;
-  if (kEmitScores && want1 && !spec1.have_sc) {
+  if (kEmitScores && want1 && !spec1.have_sc && !paired) {
 #pragma unroll
     for (int e = 0; e < 4; ++e) spec1.sc[e] = row[min(spec1.tok[e], (uint32_t)(n - 1))];
     spec1.have_sc = true;
@@ -1056,7 +1083,7 @@ __global__ __launch_bounds__(NT, FD > 0 ? 1 : 4) void head_kernel(HeadArgs A) {
                                        more_dyn ? tot1 : 0u, more_dyn ? (uint32_t)spec1.blocks : 0u);
     flags |= ((f & 1) ? kFlagDynComplement : 0) | ((f & 2) ? kFlagDynBatches : 0) | ((f & 4) ? kFlagDrawCap : 0);
     // (one batch made ahead with its scores held the whole sample, and the list stays in acceptance order)
-    dyn_placed = kEmitScores && !A.nested && !A.ascending && want1 && spec1.have_sc && f == 0;
+    dyn_placed = kEmitScores && !A.nested && !A.ascending && want1 && (spec1.have_sc || paired) && f == 0;
     if (!kFused && A.ascending && !A.nested && !(f & 1))
       O::sort_ascending(idx + A.seg_dyn, (uint32_t)min(bfin, A.b_max), scratch, wpre, n, sm);
     VATT_STAMP(A.dbg, 8);
@@ -1288,7 +1315,10 @@ hipError_t launch_head(const Plan& pl, int phase, const int32_t* seq_lens, const
   HeadArgs A;
   fill_head_args(A, pl, seq_lens, seq_seeds, ws, out_idx, out_counts, out_budget_raw, out_stats);
   const vatt_params& p = pl.p;
-  hipLaunchKernelGGL(head_kernel_for(pl.head_threads, phase, head_options(pl)), dim3(p.n_q_heads, pl.vbatch), dim3(pl.head_threads), pl.head_lds_bytes, st, A);
+  const bool options = head_options(pl);
+  // (a second workgroup per head as long as all of them have a compute unit, of which each fills one)
+  if (phase == 0 && !options && pl.head_threads == kHeadThreadsLong && 2 * pl.vbatch * p.n_q_heads <= pl.num_cus) A.splits = 2;
+  hipLaunchKernelGGL(head_kernel_for(pl.head_threads, phase, options), dim3(p.n_q_heads, pl.vbatch, A.splits), dim3(pl.head_threads), pl.head_lds_bytes, st, A);
   return hipGetLastError();
 }
 

@@ -69,3 +69,33 @@ def test_more_candidates_than_the_list_holds(k):
     sess.decode()
     check_all(wl, sess.results_host(), label="wide %d" % k)
     sess.close()
+
+
+# (longest row, shortest row, k, b0, epsilon): samples within the first batch of draws, of several batches, complements, whole
+# residuals, no residual; top-k sets from the candidate list, from the wide list and from the general path
+@pytest.mark.parametrize("case", [(45, 33, 6, 3, 0.3), (1200, 700, 64, 32, 0.05), (9001, 8200, 200, 300, 0.05), (9001, 5000, 2300, 40, 0.02),
+                                  (16003, 12000, 400, 100, 0.006), (33001, 30000, 5000, 300, 0.1)], ids=lambda c: "-".join(map(str, c)))
+def test_two_workgroups_per_head_leave_what_one_leaves(case):
+    from paper_2510_05688_amd import binding as vb
+    from paper_2510_05688_amd.session import DecodeSession
+    hi, lo, k, b0, eps = case
+    p = default_params(64, sink=4, window=28, topk_abs=k, topk_frac=0.0, base_abs=b0, base_frac=0.0, epsilon=eps)
+    wl = workloads.make_workload("pair", batch=2, n_q_heads=4, n_kv_heads=2, head_dim=64, n_max=hi, seq_lens=[hi, lo],
+                                 seed=sum(map(int, case[:4])), params=p, plant_frac=0.003)
+    got = []
+    for repeat in (1, 20):  # 8 heads; 160, more than half of the compute units: one workgroup each
+        sess = DecodeSession(dict(plan_params(wl), batch=wl.batch * repeat))
+        vb.vatt_plan_set_option(sess.plan, vb.VATT_OPT_HEAD_THREADS, 1024)
+        tile = lambda a: np.concatenate([a] * repeat)
+        sess.upload(tile(wl.q_bits), tile(wl.k_bits), tile(wl.v_bits), tile(wl.seq_lens), tile(wl.seeds))
+        sess.workspace.fill_(0xff)  # (scores that nobody left would be NaN)
+        sess.out_idx.zero_()
+        sess.decode()
+        got.append(sess.results_host())
+        sess.close()
+    one, many = got
+    check_all(wl, one, label="pair %s" % (case,))
+    for name in ("idx", "counts", "b_star", "stats"):
+        assert np.array_equal(many[name][:wl.batch], one[name]), name
+    # (another number of partial sums of the same 32-bit products)
+    np.testing.assert_allclose(many["O"][:wl.batch], one["O"], rtol=0, atol=4e-6 * np.abs(one["O"]).max())
