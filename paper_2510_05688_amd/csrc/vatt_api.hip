@@ -297,11 +297,11 @@ static int decode_given(const vatt::Plan& pl, const void* q, const void* k, cons
     VATT_LAUNCH(launch_given_merge(pl, workspace, pl.given_fuse_splits, out_o, out_lse, st));
     return VATT_OK;
   }
-  VATT_LAUNCH(launch_given_select(pl, 0, seq_lens, seq_seeds, topk_idx, topk_cnt, rcache, workspace, out_idx,
+  VATT_LAUNCH(launch_given_select(pl, seq_lens, seq_seeds, topk_idx, topk_cnt, rcache, workspace, out_idx,
                                   out_counts, out_budget_raw, out_stats, st));
   VATT_LAUNCH(launch_sparse_score(pl, q, k, v, block_table, rcache, workspace, out_idx, st));
-  VATT_LAUNCH(launch_given_select(pl, 1, seq_lens, seq_seeds, topk_idx, topk_cnt, nullptr, workspace, out_idx,
-                                  out_counts, out_budget_raw, out_stats, st));
+  VATT_LAUNCH(launch_given_budget(pl, v, block_table, seq_lens, seq_seeds, workspace, out_idx, out_counts, out_budget_raw,
+                                  out_stats, st));
   VATT_LAUNCH(launch_given_gather(pl, q, k, v, block_table, workspace, out_idx, out_o, out_lse, st));
   return VATT_OK;
 }

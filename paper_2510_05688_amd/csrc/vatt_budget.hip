@@ -5,23 +5,6 @@
 namespace vatt {
 namespace {
 
-// LDS of budget_kernel, in 32-bit words from its start: HeadSmem, three bitmaps, word prefixes, mail slots.
-struct BudgetLds {
-  uint32_t bm_f, taken, scratch, wpre, mail, end;
-};
-template <int NT>
-__host__ __device__ constexpr BudgetLds budget_lds(int n_max) {
-  const uint32_t words = (uint32_t)bitmap_words(n_max);
-  BudgetLds l{};
-  l.bm_f = (uint32_t)((sizeof(typename HeadOps<NT>::HeadSmem) + 15) / 16 * 4);
-  l.taken = l.bm_f + words;
-  l.scratch = l.taken + words;
-  l.wpre = l.scratch + words;
-  l.mail = l.wpre + words;
-  l.end = l.mail + kMailSlots;
-  return l;
-}
-
 // Targets N and SDPA, behind the V-side statistics: budget and final sample of every head (Algorithm 2; Algorithm 1, final
 // sample).  The weights are those of the lists that phase 1 left, and so is the top-k bitmap.  D_f and N_f stay for the merge:
 // the gather then reads the rows of the final sample only.
@@ -41,7 +24,7 @@ __global__ __launch_bounds__(NT, 4) void budget_kernel(HeadArgs A) {
   using O = HeadOps<NT>;
   extern __shared__ __align__(16) unsigned char dyn_smem[];
   typename O::HeadSmem& sm = *reinterpret_cast<typename O::HeadSmem*>(dyn_smem);
-  const BudgetLds at = budget_lds<NT>(A.n_max);
+  const SamplerLds at = sampler_lds<NT>(A.n_max);
   uint32_t* lds = reinterpret_cast<uint32_t*>(dyn_smem);
   uint32_t* bm_f = lds + at.bm_f;
   const int h = head_of_block((int)blockIdx.x, A.Hq, A.Hkv, A.group_major), b = blockIdx.y;
@@ -255,7 +238,7 @@ hipError_t launch_budget(const Plan& pl, const int32_t* seq_lens, const uint64_t
   fill_head_args(A, pl, seq_lens, seq_seeds, ws, out_idx, out_counts, out_budget_raw, out_stats);
   const vatt_params& p = pl.p;
   const int threads = pl.head_threads;
-  const size_t lds = sizeof(uint32_t) * (threads == kHeadThreadsLong ? budget_lds<kHeadThreadsLong>(p.n_max) : budget_lds<kHeadThreads>(p.n_max)).end;
+  const size_t lds = sizeof(uint32_t) * (threads == kHeadThreadsLong ? sampler_lds<kHeadThreadsLong>(p.n_max) : sampler_lds<kHeadThreads>(p.n_max)).end;
   hipLaunchKernelGGL(budget_kernel_for(threads, head_options(pl)), dim3(p.n_q_heads, pl.vbatch), dim3(threads), lds, st, A);
   return hipGetLastError();
 }

@@ -48,6 +48,7 @@ struct GivenArgs {
   float* out_lse;
   int64_t seg_sink, seg_win, seg_topk, seg_base, seg_dyn, idx_cap;
   int Hq, group, splits;
+  int part_slots, first_slot;  // partial sums of a head in all; the first of this kernel's
   int group_major;  // see head_of_block (the KV head count is Hq / group)
   int q_len;  // query tokens per sequence: blockIdx.z = sequence * q_len + query token
   float sm_scale;
@@ -319,7 +320,8 @@ __global__ __launch_bounds__(kGatherThreads) void sparse_stats_kernel(GivenArgs 
   }
 }
 
-// N and D over [I_f, I_dyn] by list place, in the manner of gather_kernel: what belongs to a row is done by the row's own
+// N and D over [I_f, I_dyn], or I_dyn alone where the sums over I_f are made beside the second selection phase, by list place, in the
+// manner of gather_kernel: what belongs to a row is done by the row's own
 // lane, list entries and known scores are requested one step ahead, all rows of a step are in flight together.  Rows of newly
 // drawn tokens bring their K row along; lane u of a group keeps the score of the group's row u and passes it to the row's
 // own lane.  A wave has one running maximum, raised once per step.
@@ -340,18 +342,19 @@ __global__ __launch_bounds__(kGatherThreads) void given_gather_kernel(GivenArgs 
   const HeadRec r = A.head_rec[bh];
   uint32_t qw[4];
   load_q<D>(A, bh, sub, qw);
-  const int total = r.n_sink + r.n_win + r.k + r.b;
-  const int splits = used_splits(A.splits, total, RPB * U);
+  const int n_fix = r.n_sink + r.n_win + r.k, total = n_fix + r.b;
+  const int first = A.first_slot > 0 ? n_fix : 0, count = total - first;
+  const int splits = used_splits(A.splits, count, RPB * U);
   if (split >= splits) return;
   const bool shared_rows = rows_are_shared(total, A.group_major ? A.q_len * A.group : A.q_len, r.n, A.group_major && A.group > 1 ? 3 : 2);
-  const int per = (total + splits - 1) / splits;
-  const int p_lo = split * per, p_hi = min(p_lo + per, total);
+  const int per = (count + splits - 1) / splits;
+  const int p_lo = first + split * per, p_hi = min(p_lo + per, total);
   const int32_t* idx = A.idx + (int64_t)bh * A.idx_cap;
   const float* sp = A.sparse + (int64_t)bh * A.idx_cap;
   const uint16_t* k_head = PAGED ? A.k : A.k + (int64_t)seq * A.Lk.seq_stride + (int64_t)kvh * A.Lk.head_stride;
   const uint16_t* v_head = PAGED ? A.v : A.v + (int64_t)seq * A.Lv.seq_stride + (int64_t)kvh * A.Lv.head_stride;
   const float tail_bias = r.scale > 0.f ? __logf(r.scale) : 0.f;  // ln(n_s / b): sampled tokens weigh n_s / b
-  const int n_sw = r.n_sink + r.n_win, n_fix = n_sw + r.k;
+  const int n_sw = r.n_sink + r.n_win;
   const int n_kept = n_fix + min(max(r.b_keep, 0), r.b);  // (nested samples: these have their scores in the base sample's places)
   const uint32_t seg_sink = (uint32_t)A.seg_sink, seg_win = (uint32_t)A.seg_win, seg_topk = (uint32_t)A.seg_topk;
   const uint32_t seg_base = (uint32_t)A.seg_base, seg_dyn = (uint32_t)A.seg_dyn;
@@ -457,7 +460,7 @@ __global__ __launch_bounds__(kGatherThreads) void given_gather_kernel(GivenArgs 
   float M = -INFINITY;
 #pragma unroll
   for (int j = 0; j < WAVES; ++j) M = fmaxf(M, s_m[j]);
-  float* part = A.part + ((int64_t)bh * A.splits + split) * (D + 4);
+  float* part = A.part + ((int64_t)bh * A.part_slots + A.first_slot + split) * (D + 4);
   float a = 0.f, d = 0.f;
 #pragma unroll
   for (int j = 0; j < WAVES; ++j) {
@@ -472,16 +475,17 @@ __global__ __launch_bounds__(kGatherThreads) void given_gather_kernel(GivenArgs 
   }
 }
 
-// Combines the per-split (maximum, D, N) partials of a head in split order: O = N / D, lse = M + ln D.  step_rows > 0:
-// only the splits that took part (used_splits) have written theirs.  Bound
-// by the trip to memory: the first 16 are requested beside the head record.
+// Combines the per-split (maximum, D, N) partials of a head in split order: O = N / D, lse = M + ln D.  step_rows > 0: the first
+// fixed_splits are those of I_f (from workgroups twice the size), the others the final sample's, and only those that took part
+// (used_splits) have written theirs.  Bound by the trip to memory: the first 16 are requested beside the head record.
 template <int D>
 __global__ __launch_bounds__(D) void given_merge_kernel(const float* __restrict__ part, const HeadRec* __restrict__ head_rec,
                                                         int splits, int Hq, float* __restrict__ out_o,
-                                                        float* __restrict__ out_lse, int group_major, int Hkv, int step_rows) {
+                                                        float* __restrict__ out_lse, int group_major, int Hkv, int step_rows,
+                                                        int fixed_splits, int part_slots) {
   const int h = head_of_block((int)blockIdx.x, Hq, Hkv, group_major), b = blockIdx.y, bh = b * Hq + h;
   const int c = threadIdx.x;
-  const float* p = part + (int64_t)bh * splits * (D + 4);
+  const float* p = part + (int64_t)bh * part_slots * (D + 4);
   // lane s of every wave: (D, maximum) of split s; all lanes: their column of the splits, eight at a time
   const float2 dm = *reinterpret_cast<const float2*>(p + min(c & (kWave - 1), splits - 1) * (D + 4) + D);
   constexpr int U = 8;
@@ -492,12 +496,15 @@ __global__ __launch_bounds__(D) void given_merge_kernel(const float* __restrict_
   };
   load(v, 0);
   if (splits > U) load(v2, U);
-  int used = splits;
+  const int s = c & (kWave - 1);
+  bool mine = s < splits;
   if (step_rows > 0) {
     const HeadRec r = head_rec[bh];
-    used = used_splits(splits, r.n_sink + r.n_win + r.k + r.b, step_rows);
+    const int n_fix = r.n_sink + r.n_win + r.k;
+    mine = s < fixed_splits ? s < used_splits(fixed_splits, n_fix, 2 * step_rows)
+                            : s - fixed_splits < used_splits(splits - fixed_splits, fixed_splits > 0 ? r.b : n_fix + r.b, step_rows) && s < splits;
   }
-  const bool mine = (c & (kWave - 1)) < used;
+  const uint64_t took_part = __ballot(mine);
   const float M = wave_max(mine ? dm.y : -INFINITY);
   // (a split with no score but NaN has the maximum -inf and hands its NaN on, times 0)
   const float f = mine && dm.y > -INFINITY ? __expf(dm.y - M) : 0.f, df = mine ? dm.x * f : 0.f;
@@ -506,13 +513,13 @@ __global__ __launch_bounds__(D) void given_merge_kernel(const float* __restrict_
 #pragma unroll
     for (int u = 0; u < U; ++u) {
       const float fu = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(f), s0 + u));
-      a += s0 + u < used ? from[u] * fu : 0.f;  // (what a split without a part left behind is not looked at)
+      a += (took_part >> (s0 + u)) & 1u ? from[u] * fu : 0.f;  // (what a split without a part left behind is not looked at)
       dtot += __int_as_float(__builtin_amdgcn_readlane(__float_as_int(df), s0 + u));
     }
   };
   add(v, 0);
-  if (used > U) add(v2, U);
-  for (int s0 = 2 * U; s0 < used; s0 += U) {
+  if (splits > U) add(v2, U);
+  for (int s0 = 2 * U; s0 < splits; s0 += U) {
     load(v, s0);
     add(v, s0);
   }
@@ -549,7 +556,10 @@ hipError_t launch_given_d(const Plan& pl, int stage, const void* q, const void* 
   A.idx_cap = (int64_t)pl.idx_cap;
   A.Hq = p.n_q_heads;
   A.group = pl.group;
-  A.splits = pl.given_splits;
+  A.splits = stage == 0 ? pl.given_splits : given_tail_splits(pl);
+  A.first_slot = given_fixed_splits(pl);
+  A.part_slots = given_part_slots(pl);
+  if (stage != 0) A.head_rec = given_rec_of(pl, ws);
   A.q_len = pl.q_len;
   A.group_major = pl.group_major;
   A.sm_scale = pl.sm_scale;
@@ -573,7 +583,8 @@ hipError_t launch_given_d(const Plan& pl, int stage, const void* q, const void* 
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL((given_merge_kernel<D>), dim3(p.n_q_heads, pl.vbatch), dim3(D), 0, st, A.part, A.head_rec,
-                     A.splits, p.n_q_heads, out_o, out_lse, pl.group_major, p.n_kv_heads, (kGatherThreads / (D / 8)) * 8);
+                     A.first_slot + A.splits, p.n_q_heads, out_o, out_lse, pl.group_major, p.n_kv_heads, (kGatherThreads / (D / 8)) * 8,
+                     A.first_slot, A.part_slots);
   return hipGetLastError();
 }
 
@@ -593,10 +604,10 @@ hipError_t launch_given_merge(const Plan& pl, void* ws, int splits, float* out_o
   const HeadRec* rec = reinterpret_cast<const HeadRec*>(static_cast<char*>(ws) + pl.off_head_rec);
   if (p.head_dim == 128)
     hipLaunchKernelGGL((given_merge_kernel<128>), dim3(p.n_q_heads, pl.vbatch), dim3(128), 0, st, part, rec, splits,
-                       p.n_q_heads, out_o, out_lse, pl.group_major, p.n_kv_heads, 0);
+                       p.n_q_heads, out_o, out_lse, pl.group_major, p.n_kv_heads, 0, 0, splits);
   else if (p.head_dim == 64)
     hipLaunchKernelGGL((given_merge_kernel<64>), dim3(p.n_q_heads, pl.vbatch), dim3(64), 0, st, part, rec, splits,
-                       p.n_q_heads, out_o, out_lse, pl.group_major, p.n_kv_heads, 0);
+                       p.n_q_heads, out_o, out_lse, pl.group_major, p.n_kv_heads, 0, 0, splits);
   else
     return hipErrorInvalidValue;
   return hipGetLastError();

@@ -115,6 +115,27 @@ struct Plan {
   KVLayout kv_k, kv_v;  // templates; base pointers are passed per call
 };
 
+// Caller-supplied top-k, gather apart: workgroups per head that gather I_f beside the second selection phase, in its launch (0: the
+// gather behind it takes the whole list), and workgroups of the gather behind it; their partial sums share a region of at least 16 per
+// head.  Beside it where every head's phase has a compute unit to itself: with two of them on each, the rows wait for their slots
+// and the launch takes as long as the two one after the other.  Whole step, us, behind -> beside: 128 heads of 128K tokens 99.6 -> 94.2,
+// 192 of 32K (3 query tokens) 56.1 -> 52.1; but 512 heads of 32K 111.0 -> 113.2, of 4K 47.8 -> 49.0, 1024 of 0.3K - 1.5K paged 61.3 ->
+// 65.4 (though of 9K with 16 query tokens 59.7 -> 56.2).
+inline int given_part_slots(const Plan& pl) { return pl.split_cap > 16 ? pl.split_cap : 16; }
+inline bool given_beside(const Plan& pl) { return pl.vbatch * pl.p.n_q_heads <= pl.num_cus; }
+inline int given_tail_splits(const Plan& pl) {
+  if (!given_beside(pl)) return pl.given_splits;
+  return pl.given_splits < given_part_slots(pl) ? pl.given_splits : given_part_slots(pl) - 1;
+}
+inline int given_fixed_splits(const Plan& pl) {
+  if (!given_beside(pl)) return 0;
+  const int left = given_part_slots(pl) - given_tail_splits(pl);
+  return pl.given_splits < left ? pl.given_splits : left;
+}
+// Where the second phase leaves its record.
+inline HeadRec* given_rec_of(const Plan& pl, void* ws) { return reinterpret_cast<HeadRec*>(static_cast<char*>(ws) + pl.off_pre_flags); }
+static_assert(sizeof(HeadRec) <= kHeadThreads * sizeof(uint32_t), "it lies in the region of the draws made ahead");
+
 // Bytes of score rows a call writes, and the size from which on they are taken to outgrow the last-level cache beside
 // what else passes through it.
 inline size_t score_bytes(const Plan& pl) { return (size_t)pl.vbatch * pl.p.n_q_heads * pl.p.n_max * sizeof(float); }
@@ -150,7 +171,7 @@ int fused_splits_for(const Plan& pl);           // the plan's own choice (0: sep
 bool fused_splits_fit(const Plan& pl, int splits);  // whether the fused kernel can run with that many
 // rcache (may be nullptr): random cache the base sample is taken from when it holds enough residual tokens;
 // the score kernel of the listed tokens then reads those tokens' rows from the cache.
-hipError_t launch_given_select(const Plan& pl, int phase, const int32_t* seq_lens, const uint64_t* seq_seeds,
+hipError_t launch_given_select(const Plan& pl, const int32_t* seq_lens, const uint64_t* seq_seeds,
                                const int32_t* given_idx, const int32_t* given_cnt, const void* rcache, void* ws,
                                int32_t* out_idx, int32_t* out_counts, double* out_budget_raw, float* out_stats,
                                hipStream_t st);
@@ -162,6 +183,10 @@ hipError_t launch_given_fused(const Plan& pl, int phase, const void* q, const vo
                               const int32_t* given_idx, const int32_t* given_cnt, const void* rcache, void* ws,
                               int32_t* out_idx, int32_t* out_counts, double* out_budget_raw, float* out_stats,
                               hipStream_t st);
+// The second selection phase with the gather of I_f beside it, in one launch.
+hipError_t launch_given_budget(const Plan& pl, const void* v, const int32_t* block_table, const int32_t* seq_lens,
+                               const uint64_t* seq_seeds, void* ws, int32_t* out_idx, int32_t* out_counts, double* out_budget_raw,
+                               float* out_stats, hipStream_t st);
 hipError_t launch_given_merge(const Plan& pl, void* ws, int splits, float* out_o, float* out_lse, hipStream_t st);
 int given_fused_splits_for(const Plan& pl);
 bool given_fused_fits(const Plan& pl, int splits);

@@ -27,6 +27,7 @@ struct HeadArgs {
   const int32_t* seq_lens;
   const uint64_t* seq_seeds;
   HeadRec* head_rec;
+  HeadRec* given_rec;  // caller-supplied path, gather apart: the second phase's record, beside the first's, which others are reading
   const double* vstat_part;  // [B*Hq][vstat_splits][2d+2] (targets N, SDPA)
   double* fixed_sums;        // [B*Hq][kFixedSums]: see there (targets N, SDPA)
   const float* given_vstat;  // [B*Hq][given_splits][2d+4]: N_f[d], R1[d], R2, maximum (given-top-k path)
@@ -57,6 +58,7 @@ struct HeadArgs {
   KVLayout L;
   float* part;       // [B*Hq][splits][d + 4]: partial (sum w V, sum w) of every workgroup
   int splits, split_shift, group;
+  int fixed_splits, part_slots;  // caller-supplied path: workgroups per head for I_f, and partial sums of a head in all
   int glist_cap, dlist_cap;  // LDS entries for a workgroup's share of I_f and of the final sample
   // first batches of draws made ahead (nullptr: made here): of both sampler streams by workgroups of the score launch, and on the
   // caller-supplied path of the final sample's by the first phase for the second
@@ -221,6 +223,23 @@ __host__ __device__ constexpr HeadLds head_lds(int n_max) {
   l.mail0 = l.wpre + words;
   l.mail1 = TWO ? l.mail0 + kMailSlots : l.mail0;
   l.lists = l.mail1 + kMailSlots;
+  return l;
+}
+
+// LDS of a kernel that samples and selects nothing, in 32-bit words from its start: HeadSmem, three bitmaps, word prefixes, mail slots.
+struct SamplerLds {
+  uint32_t bm_f, taken, scratch, wpre, mail, end;
+};
+template <int NT>
+__host__ __device__ constexpr SamplerLds sampler_lds(int n_max) {
+  const uint32_t words = (uint32_t)bitmap_words(n_max);
+  SamplerLds l{};
+  l.bm_f = (uint32_t)((sizeof(typename HeadOps<NT>::HeadSmem) + 15) / 16 * 4);
+  l.taken = l.bm_f + words;
+  l.scratch = l.taken + words;
+  l.wpre = l.scratch + words;
+  l.mail = l.wpre + words;
+  l.end = l.mail + kMailSlots;
   return l;
 }
 
@@ -503,6 +522,7 @@ inline void fill_head_args(HeadArgs& A, const Plan& pl, const int32_t* seq_lens,
   A.seq_lens = seq_lens;
   A.seq_seeds = seq_seeds;
   A.head_rec = reinterpret_cast<HeadRec*>(w + pl.off_head_rec);
+  A.given_rec = given_rec_of(pl, ws);
   A.vstat_part = reinterpret_cast<const double*>(w + pl.off_vstat_part);
   A.out_idx = out_idx;
   A.out_counts = out_counts;
@@ -552,6 +572,7 @@ inline void fill_head_args(HeadArgs& A, const Plan& pl, const int32_t* seq_lens,
   A.part = nullptr;
   A.splits = 1;
   A.split_shift = 0;
+  A.fixed_splits = A.part_slots = 0;
   A.group = pl.group;
   A.glist_cap = 0;
   A.dlist_cap = 0;

@@ -39,7 +39,7 @@ __device__ __forceinline__ bool draw_ahead(const HeadArgs& A, const HeadSizes& h
 // PHASE is a constant of the kernel: what both phases could share is little, and values that only one of them loads would be
 // waited for where the paths meet.
 template <int NT, int FD, bool PAGED, int PHASE>
-__global__ __launch_bounds__(NT) void given_topk_kernel(HeadArgs A) {
+__device__ __forceinline__ void given_topk(const HeadArgs& A) {
   using O = HeadOps<NT>;
   using HeadSmem = typename O::HeadSmem;
   using Sampler = typename O::Sampler;
@@ -60,9 +60,11 @@ __global__ __launch_bounds__(NT) void given_topk_kernel(HeadArgs A) {
   // (the fused forms have a second scratch bitmap and mail slots for the final sample's stream, where the first phase makes both first
   // batches at once)
   const HeadLds at = head_lds<NT, kFused>(A.n_max);
+  const SamplerLds apart = sampler_lds<NT>(A.n_max);
   uint32_t* lds = reinterpret_cast<uint32_t*>(dyn_smem);
-  uint32_t *bm_f = lds + at.bm_f, *taken = lds + at.taken0, *taken1 = lds + at.taken1, *scratch = lds + at.scratch0, *scratch1 = lds + at.scratch1;
-  uint32_t *wpre = lds + at.wpre, *mail = lds + at.mail0, *mail1 = lds + at.mail1;
+  uint32_t *bm_f = lds + (kFused ? at.bm_f : apart.bm_f), *taken = lds + (kFused ? at.taken0 : apart.taken), *taken1 = lds + at.taken1;
+  uint32_t *scratch = lds + (kFused ? at.scratch0 : apart.scratch), *scratch1 = lds + at.scratch1;
+  uint32_t *wpre = lds + (kFused ? at.wpre : apart.wpre), *mail = lds + (kFused ? at.mail0 : apart.mail), *mail1 = lds + at.mail1;
   // fused gather (second phase): this workgroup's share of the final sample, and the cross-wave sums
   uint32_t* dlist = lds + at.lists;
   float* g_red = reinterpret_cast<float*>(dlist + (kFused ? A.dlist_cap : 0));
@@ -79,10 +81,12 @@ __global__ __launch_bounds__(NT) void given_topk_kernel(HeadArgs A) {
   // What can be asked for before anything is worked out comes first, and the first batch of draws, which depends on the seed,
   // the head and the length only, is made while it is under way.
   HeadRec rec = {};
+  int flags_before = 0;
   uint4 pre_t = make_uint4(0u, 0u, 0u, 0u);
   uint32_t pre_f = 0u, pre_all = 0u;
   if constexpr (PHASE != 0) {
     rec = A.head_rec[bh];
+    flags_before = A.out_counts[(int64_t)bh * 8 + 7];  // (at the end it would be a trip of its own)
     if constexpr (kFused) {
       pre_t = A.pre_tok[(int64_t)bh * NT + tid];
       pre_f = A.pre_flags[(int64_t)bh * NT + tid];
@@ -640,7 +644,7 @@ __global__ __launch_bounds__(NT) void given_topk_kernel(HeadArgs A) {
     c[4] = bfin;
     c[5] = hs.n_s;
     c[6] = n;
-    c[7] = c[7] | flags;
+    c[7] = flags_before | flags;
     if (A.out_budget_raw) A.out_budget_raw[bh] = b_star;
     if (A.out_stats) {
       float* st = A.out_stats + (int64_t)bh * 4;
@@ -664,7 +668,7 @@ __global__ __launch_bounds__(NT) void given_topk_kernel(HeadArgs A) {
     r.tail_by_token = 0;
     // (with the gather fused in nothing reads the record again, and the head's other workgroups may still be
     // reading the first phase's)
-    if (!kFused) A.head_rec[bh] = r;
+    if (!kFused) A.given_rec[bh] = r;
   }
 
   if constexpr (kFused) {
@@ -783,7 +787,125 @@ __global__ __launch_bounds__(NT) void given_topk_kernel(HeadArgs A) {
   }
 }
 
+template <int NT, int FD, bool PAGED, int PHASE>
+__global__ __launch_bounds__(NT) void given_topk_kernel(HeadArgs A) {
+  given_topk<NT, FD, PAGED, PHASE>(A);
+}
+
+// Partial sums (N, D, maximum) over a share of [sink | window | top-k): scores from the sparse list, V rows, in the manner of
+// given_gather_kernel and with its running maximum, which needs nothing of the second phase.
+template <int D, bool PAGED>
+__device__ __forceinline__ void gather_fixed(const HeadArgs& A, int split) {
+  constexpr int LPR = D / 8, RPW = kWave / LPR, WAVES = kHeadThreads / kWave, RPB = RPW * WAVES, U = 8, ROWS_W = RPW * U;
+  const int h = head_of_block((int)blockIdx.x, A.Hq, A.Hkv, A.group_major), b = blockIdx.y;
+  const int bh = b * A.Hq + h, kvh = div_group(h, A.group), seq = seq_of_pair(b, A.q_len);
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int sub = lane % LPR, rsub = lane / LPR;
+  const HeadRec r = A.head_rec[bh];  // the first phase's: b is the size of the base sample
+  const int n_fix = r.n_sink + r.n_win + r.k;
+  const int splits = used_splits(A.fixed_splits, n_fix, RPB * U);
+  if (split >= splits) return;
+  const bool shared_rows = rows_are_shared(n_fix + r.b, A.group_major ? A.q_len * A.group : A.q_len, r.n, A.group_major && A.group > 1 ? 3 : 2);
+  const int per = (n_fix + splits - 1) / splits;
+  const int p_lo = split * per, p_hi = min(p_lo + per, n_fix);
+  const int32_t* idx = A.out_idx + (int64_t)bh * A.idx_cap;
+  const float* sp = A.sparse + (int64_t)bh * A.idx_cap;
+  const uint16_t* v_head = PAGED ? A.v : A.v + (int64_t)seq * A.L.seq_stride + (int64_t)kvh * A.L.head_stride;
+  const int mine = (lane / RPW) * RPB + wave * RPW + lane % RPW;  // the row of a step that this lane prepares
+  int entry_next = 0;
+  float sc_next = 0.f;
+  auto request = [&](int p0) {  // (beyond the range: its last place once more)
+    const uint32_t place = (uint32_t)fixed_place(min(p0 + mine, p_hi - 1), r.n_sink, r.n_win, A.seg_sink, A.seg_win, A.seg_topk);
+    entry_next = idx[place];
+    sc_next = sp[place];
+  };
+  if (p_lo < p_hi) request(p_lo);
+  float acc[8];
+#pragma unroll
+  for (int c = 0; c < 8; ++c) acc[c] = 0.f;
+  float dsum = 0.f, m_run = -INFINITY;
+  auto walk = [&](auto load) {
+    for (int p0 = p_lo; p0 < p_hi; p0 += RPB * U) {
+      const bool valid = lane < ROWS_W && p0 + mine < p_hi;
+      const int tok_mine = min(max(entry_next, 0), r.n - 1);
+      const float e = valid ? sc_next : -INFINITY;
+      request(p0 + RPB * U);
+      int tok[U], blk[U];
+      uint4 vv[U];
+#pragma unroll
+      for (int u = 0; u < U; ++u) tok[u] = __shfl(tok_mine, u * RPW + rsub);
+#pragma unroll
+      for (int u = 0; u < U; ++u) blk[u] = kv_block<PAGED>(A.L, seq, tok[u]);
+#pragma unroll
+      for (int u = 0; u < U; ++u)
+        vv[u] = load(PAGED ? A.v + kv_row_offset_in<true>(A.L, seq, kvh, tok[u], blk[u]) + sub * 8 : v_head + ((uint32_t)tok[u] * (uint32_t)D + (uint32_t)(sub * 8)));
+      __builtin_amdgcn_sched_barrier(0);
+      const float m_new = fmaxf(m_run, wave_max(e));
+      const float f = m_run > -INFINITY ? __expf(m_run - m_new) : 0.f;
+      const float wt_mine = e == -INFINITY ? 0.f : __expf(e - m_new);  // (NaN for a NaN score: the row is not left out)
+      m_run = m_new;
+      dsum = dsum * f + wt_mine;
+#pragma unroll
+      for (int c = 0; c < 8; ++c) acc[c] *= f;
+      if (p0 + RPB * U > p_hi) {
+        // (a row beyond the range repeats the last one, with weight 0; an Inf in it would make a NaN)
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+          if (p0 + u * RPB + wave * RPW + rsub >= p_hi) vv[u] = make_uint4(0u, 0u, 0u, 0u);
+      }
+#pragma unroll
+      for (int u = 0; u < U; ++u) add_weighted_row(acc, __shfl(wt_mine, u * RPW + rsub), vv[u]);
+    }
+  };
+  if (shared_rows) walk(LoadShared{});
+  else walk(LoadOnce{});
+
+  // the lane groups of a wave, then the waves, each with its maximum
+  add_lane_groups<LPR>(acc);
+  dsum = wave_sum_f32(dsum);
+  __shared__ __align__(16) float s_acc[WAVES][D];
+  __shared__ float s_d[WAVES], s_m[WAVES];
+  if (LPR == 16 || (lane & 8) == 0) {
+#pragma unroll
+    for (int c = 0; c < 2; ++c) s_acc[wave][lane_groups_column<LPR>(lane) + c] = acc[c];
+  }
+  if (lane == 0) {
+    s_d[wave] = dsum;
+    s_m[wave] = m_run;
+  }
+  __syncthreads();
+  float M = -INFINITY;
+#pragma unroll
+  for (int j = 0; j < WAVES; ++j) M = fmaxf(M, s_m[j]);
+  float* part = A.part + ((int64_t)bh * A.part_slots + split) * (D + 4);
+  float a = 0.f, d = 0.f;
+#pragma unroll
+  for (int j = 0; j < WAVES; ++j) {
+    const float f = s_m[j] > -INFINITY ? __expf(s_m[j] - M) : 0.f;
+    if (tid < D) a += s_acc[j][tid] * f;
+    d += s_d[j] * f;
+  }
+  if (tid < D) part[tid] = a;
+  if (tid == 0) {
+    part[D] = d;
+    part[D + 1] = M;
+  }
+}
+
+// The second phase of a step whose gather is apart (given_fixed_splits), and beside it, in the same launch and behind the workgroups of
+// the phase, the first of the third grid dimension, the gather of I_f, which waits for nothing that the phase finds out: a phase
+// is a chain of 9 us that leaves memory idle.
+template <int D, bool PAGED>
+__global__ __launch_bounds__(kHeadThreads) void given_budget_kernel(HeadArgs A) {
+  if (blockIdx.z == 0) given_topk<kHeadThreads, 0, false, 1>(A);
+  else gather_fixed<D, PAGED>(A, (int)blockIdx.z - 1);
+}
+
 typedef void (*GivenKernel)(HeadArgs);
+GivenKernel given_budget_kernel_for(int d, bool paged) {
+  if (d == 128) return paged ? given_budget_kernel<128, true> : given_budget_kernel<128, false>;
+  return paged ? given_budget_kernel<64, true> : given_budget_kernel<64, false>;
+}
 // The instantiation for a head dimension (0: selection only) and cache layout.
 template <int PHASE>
 GivenKernel given_kernel_for(int d, bool paged) {
@@ -807,10 +929,16 @@ hipError_t set_given_kernel_attributes(const Plan& pl) {
                                                  hipFuncAttributeMaxDynamicSharedMemorySize, cap);
         if (e != hipSuccess) return e;
       }
+  for (const int d : {64, 128})
+    for (const bool paged : {false, true}) {
+      const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(given_budget_kernel_for(d, paged)),
+                                               hipFuncAttributeMaxDynamicSharedMemorySize, cap);
+      if (e != hipSuccess) return e;
+    }
   return hipSuccess;
 }
 
-hipError_t launch_given_select(const Plan& pl, int phase, const int32_t* seq_lens, const uint64_t* seq_seeds,
+hipError_t launch_given_select(const Plan& pl, const int32_t* seq_lens, const uint64_t* seq_seeds,
                                const int32_t* given_idx, const int32_t* given_cnt, const void* rcache, void* ws,
                                int32_t* out_idx, int32_t* out_counts, double* out_budget_raw, float* out_stats,
                                hipStream_t st) {
@@ -820,8 +948,25 @@ hipError_t launch_given_select(const Plan& pl, int phase, const int32_t* seq_len
   A.given_cnt = given_cnt;
   A.rcache = rcache;
   A.rc = cache_layout(pl);
-  const size_t lds = sizeof(uint32_t) * head_lds<kHeadThreads, false>(pl.p.n_max).lists;
-  hipLaunchKernelGGL(given_kernel_for(phase, 0, false), dim3(pl.p.n_q_heads, pl.vbatch), dim3(kHeadThreads), lds, st, A);
+  const size_t lds = sizeof(uint32_t) * sampler_lds<kHeadThreads>(pl.p.n_max).end;
+  hipLaunchKernelGGL(given_kernel_for(0, 0, false), dim3(pl.p.n_q_heads, pl.vbatch), dim3(kHeadThreads), lds, st, A);
+  return hipGetLastError();
+}
+
+hipError_t launch_given_budget(const Plan& pl, const void* v, const int32_t* block_table, const int32_t* seq_lens,
+                               const uint64_t* seq_seeds, void* ws, int32_t* out_idx, int32_t* out_counts, double* out_budget_raw,
+                               float* out_stats, hipStream_t st) {
+  HeadArgs A;
+  fill_head_args(A, pl, seq_lens, seq_seeds, ws, out_idx, out_counts, out_budget_raw, out_stats);
+  A.v = static_cast<const uint16_t*>(v);
+  A.L = pl.kv_v;
+  A.L.block_table = block_table;
+  A.part = reinterpret_cast<float*>(static_cast<char*>(ws) + pl.off_gather_part);
+  A.fixed_splits = given_fixed_splits(pl);
+  A.part_slots = given_part_slots(pl);
+  const size_t lds = sizeof(uint32_t) * sampler_lds<kHeadThreads>(pl.p.n_max).end;
+  const GivenKernel kernel = A.fixed_splits > 0 ? given_budget_kernel_for(pl.p.head_dim, pl.p.kv_layout == VATT_LAYOUT_PAGED) : given_kernel_for(1, 0, false);
+  hipLaunchKernelGGL(kernel, dim3(pl.p.n_q_heads, pl.vbatch, 1 + A.fixed_splits), dim3(kHeadThreads), lds, st, A);
   return hipGetLastError();
 }
 

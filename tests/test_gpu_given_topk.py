@@ -7,6 +7,7 @@ import workloads
 from oracle import vatt_oracle as vo
 from parity import check_head_given, gpu_segments, head_inputs, say
 from util import plan_params
+from workloads.configs import default_params
 
 pytestmark = pytest.mark.gpu
 
@@ -265,3 +266,58 @@ def test_an_empty_list_is_not_interpreted():
     for key in ("counts", "b_star", "idx", "O", "lse", "stats"):
         assert np.array_equal(res[key], again[key]), key
     sess.close()
+
+
+# (tokens, sink, window, k, b0, epsilon): I_f empty, around one step of a 512-thread workgroup (256 rows of 128 columns), of many steps;
+# no residual; a whole residual
+@pytest.mark.parametrize("paged", [False, True])
+@pytest.mark.parametrize("case", [(900, 0, 0, 0, 40, 0.1), (2000, 100, 100, 55, 64, 0.05), (2000, 100, 100, 56, 64, 0.05), (2000, 100, 100, 57, 64, 0.05),
+                                  (300, 150, 150, 9, 8, 0.1), (6000, 128, 900, 2500, 300, 0.005)], ids=lambda c: "-".join(map(str, c)))
+def test_gather_of_the_fixed_set_beside_the_budget_and_behind_it(case, paged):
+    from paper_2510_05688_amd import binding as vb
+    from paper_2510_05688_amd.session import DecodeSession
+    n, sink, window, k, b0, eps = case
+    p = default_params(128, sink=sink, window=window, topk_abs=k, topk_frac=0.0, base_abs=b0, base_frac=0.0, epsilon=eps)
+    wl = workloads.make_workload("beside", batch=1, n_q_heads=4, n_kv_heads=2, head_dim=128, n_max=n, seq_lens=[n], seed=n + k, params=p,
+                                 plant_frac=0.003)
+    supplied = {h: _oracle_topk(wl, 0, h) for h in range(4)}
+    got = []
+    for batch in (1, 70):  # 4 heads: beside the second phase; 280, more than the card has compute units: behind it
+        params = dict(plan_params(wl), batch=batch)
+        tile = lambda a: np.concatenate([a] * batch)
+        if paged:
+            page, pages = 16, -(-n // 16)
+            params.update(kv_layout=vb.VATT_LAYOUT_PAGED, page_size=page, num_blocks=batch * pages)
+            table = np.random.default_rng(n).permutation(batch * pages).astype(np.int32).reshape(batch, pages)
+
+            def pool(bits):
+                rows = np.zeros((2, pages * page, 128), dtype=bits.dtype)
+                rows[:, :n] = bits[0]
+                out = np.empty((batch * pages, 2, page, 128), dtype=bits.dtype)
+                for b in range(batch):
+                    out[table[b]] = rows.reshape(2, pages, page, 128).transpose(1, 0, 2, 3)
+                return out
+            kk, vv = pool(wl.k_bits), pool(wl.v_bits)
+        else:
+            kk, vv, table = tile(wl.k_bits), tile(wl.v_bits), None
+        sess = DecodeSession(params)
+        vb.vatt_plan_set_option(sess.plan, vb.VATT_OPT_GIVEN_FUSED, 0)
+        sess.upload(tile(wl.q_bits), kk, vv, tile(wl.seq_lens), tile(wl.seeds), table)
+        sess.workspace.fill_(0xff)  # (a partial sum that nobody left would be NaN)
+        idx = np.zeros((batch, 4, max(_k_max(sess), 1)), dtype=np.int32)
+        cnt = np.zeros((batch, 4), dtype=np.int32)
+        for h, toks in supplied.items():
+            idx[:, h, :len(toks)] = toks
+            cnt[:, h] = len(toks)
+        sess.decode_given_topk(torch.from_numpy(idx).to(sess.device), torch.from_numpy(cnt).to(sess.device))
+        got.append(sess.results_host())
+        sess.close()
+    one, many = got
+    for h in range(4):
+        check_head_given(wl, one, 0, h, supplied[h], label="beside")
+    for row in (0, 69):
+        for name in ("counts", "b_star", "stats"):
+            assert np.array_equal(many[name][row], one[name][0]), name
+        # (the same 32-bit products in partial sums cut at other places)
+        np.testing.assert_allclose(many["O"][row], one["O"][0], rtol=0, atol=4e-6 * np.abs(one["O"]).max())
+        np.testing.assert_allclose(many["lse"][row], one["lse"][0], rtol=0, atol=2e-5)
