@@ -120,9 +120,14 @@ struct Plan {
 // head.  Beside it where every head's phase has a compute unit to itself: with two of them on each, the rows wait for their slots
 // and the launch takes as long as the two one after the other.  Whole step, us, behind -> beside: 128 heads of 128K tokens 99.6 -> 94.2,
 // 192 of 32K (3 query tokens) 56.1 -> 52.1; but 512 heads of 32K 111.0 -> 113.2, of 4K 47.8 -> 49.0, 1024 of 0.3K - 1.5K paged 61.3 ->
-// 65.4 (though of 9K with 16 query tokens 59.7 -> 56.2).
+// 65.4.  Where query tokens share the rows, two of them on a unit still gain on longer rows: 512 heads of 9K (16 query tokens) 58.5 ->
+// 55.5, 32K (16) 85.9 -> 84.6, 16K (2) 76.5 -> 74.2, 20K (4) at epsilon 0.02 164 -> 156; but of 1K (16) 44.1 -> 44.7, 960 of 3K (3)
+// 84.9 -> 86.2, 1024 of 8K (8) 88.1 -> 89.2.
 inline int given_part_slots(const Plan& pl) { return pl.split_cap > 16 ? pl.split_cap : 16; }
-inline bool given_beside(const Plan& pl) { return pl.vbatch * pl.p.n_q_heads <= pl.num_cus; }
+inline bool given_beside(const Plan& pl) {
+  const int heads = pl.vbatch * pl.p.n_q_heads;
+  return heads <= pl.num_cus || (pl.q_len > 1 && heads <= 2 * pl.num_cus && pl.p.n_max >= 4096);
+}
 inline int given_tail_splits(const Plan& pl) {
   if (!given_beside(pl)) return pl.given_splits;
   return pl.given_splits < given_part_slots(pl) ? pl.given_splits : given_part_slots(pl) - 1;
