@@ -120,7 +120,7 @@ __global__ __launch_bounds__(NT, 4) void budget_kernel(HeadArgs A) {
   const bool want = hs.n_s > 0 && !A.nested;  // (a nested final sample rarely draws at all)
   if (want) O::make_batch(spec, S, hs, 0u, first_batch, false, false, sm, tid);
   constexpr bool kPlace = NT >= 1024;  // (as in the selection-only kernel)
-  if (want && kPlace) {
+  if (want && kPlace && A.splits == 1) {  // (else the second workgroup of phase 1 has left them)
 #pragma unroll
     for (int e = 0; e < 4; ++e) spec.sc[e] = row[min(spec.tok[e], (uint32_t)(n - 1))];
     spec.have_sc = true;
@@ -238,6 +238,7 @@ hipError_t launch_budget(const Plan& pl, const int32_t* seq_lens, const uint64_t
   fill_head_args(A, pl, seq_lens, seq_seeds, ws, out_idx, out_counts, out_budget_raw, out_stats);
   const vatt_params& p = pl.p;
   const int threads = pl.head_threads;
+  A.splits = head_pair(pl, 1) ? 2 : 1;
   const size_t lds = sizeof(uint32_t) * (threads == kHeadThreadsLong ? sampler_lds<kHeadThreadsLong>(p.n_max) : sampler_lds<kHeadThreads>(p.n_max)).end;
   hipLaunchKernelGGL(budget_kernel_for(threads, head_options(pl)), dim3(p.n_q_heads, pl.vbatch), dim3(threads), lds, st, A);
   return hipGetLastError();

@@ -510,6 +510,12 @@ inline bool head_options(const Plan& pl) {
          pl.budget_multiple != 1;
 }
 
+// Whether the selection-only kernel has a second workgroup per head: as long as all of them have a compute unit to themselves, for long
+// rows and for the first phase of the targets N and SDPA.
+inline bool head_pair(const Plan& pl, int phase) {
+  return !head_options(pl) && (pl.head_threads == kHeadThreadsLong || phase == 1) && 2 * pl.vbatch * pl.p.n_q_heads <= pl.num_cus;
+}
+
 // The arguments every launch of the kernels starts from.
 inline void fill_head_args(HeadArgs& A, const Plan& pl, const int32_t* seq_lens, const uint64_t* seq_seeds, void* ws,
                            int32_t* out_idx, int32_t* out_counts, double* out_budget_raw,

@@ -67,14 +67,15 @@ __global__ __launch_bounds__(NT, FD > 0 ? 1 : 4) void head_kernel(HeadArgs A) {
   constexpr bool kSplit = kFused && !ALONE;
   const uint32_t split = kSplit ? blockIdx.z : 0u, shift = kSplit ? (uint32_t)A.split_shift : 0u;
   const uint32_t smask = (1u << shift) - 1u;
-  // Long rows, no more heads than half the compute units: a second workgroup per head (A.splits == 2) repeats the top-k step and
+  // No more heads than half the compute units, and long rows or the first phase (head_pair): a second workgroup per head (A.splits == 2) repeats the top-k step and
   // writes what the first would make the base sample wait for, the lists of I_f, and what it would make the budget wait for, the
   // scores of the final sample's proposals at the list places.  Nothing is exchanged: it writes the scores of all accepted draws of the
   // first batch, and the first workgroup says in the record whether the sample is the beginning of them.  A compute unit takes
   // four to five clocks per scattered 4-byte read, and with one workgroup per head half of the units pulled all of them.
   // Whole call, us, one -> two: 4 x 128K tokens 250.5 -> 245.0, 1 x 128K 113.6 -> 103.0, 2 of 9K - 100K paged 108.5 -> 99.1, 4 x 50K with
   // k and b0 of 5 % 151.6 -> 145.4, 1 x 60K at epsilon 0.02 59.5 -> 57.3, 1 x 91K with 3 query tokens 109.4 -> 99.1.
-  constexpr bool kPair = !kFused && NT >= 1024 && PHASE == 0 && !OPTIONS;
+  // Targets N and SDPA: 4 x 16K 82.5 -> 80.5, 1 x 32K 86.8 -> 84.4, 2 x 9K of 16 heads 50.7 -> 47.8, 4 x 128K 333 -> 327, 1 x 100K 155 -> 152.7.
+  constexpr bool kPair = !kFused && !OPTIONS && (NT >= 1024 || PHASE == 1);
   const bool paired = kPair && A.splits == 2;
   const bool second = paired && blockIdx.z == 1u;
   const bool lister = !paired || second;            // this workgroup writes the lists of I_f
@@ -213,7 +214,7 @@ __global__ __launch_bounds__(NT, FD > 0 ? 1 : 4) void head_kernel(HeadArgs A) {
   S1.dbg = A.dbg ? A.dbg + 300 : nullptr;
   DrawBatch spec0 = {}, spec1 = {};
   const bool want0 = hs.n_s > 0 && hs.b0 < hs.n_s && !second;
-  const bool want1 = hs.n_s > 0 && PHASE != 1 && !A.nested;  // (a nested final sample rarely draws at all)
+  const bool want1 = hs.n_s > 0 && (PHASE != 1 || (NT >= 1024 && second)) && !A.nested;  // (a nested final sample rarely draws at all)
   const int n_sub = (n + kSubTile - 1) / kSubTile;
   const int sub_lo = (hs.mid_lo + kSubTile - 1) / kSubTile, sub_hi = hs.mid_hi / kSubTile;  // whole middle sub-tiles
   const bool sub_resident = n_sub <= SU * NT;
@@ -1316,8 +1317,7 @@ hipError_t launch_head(const Plan& pl, int phase, const int32_t* seq_lens, const
   fill_head_args(A, pl, seq_lens, seq_seeds, ws, out_idx, out_counts, out_budget_raw, out_stats);
   const vatt_params& p = pl.p;
   const bool options = head_options(pl);
-  // (a second workgroup per head as long as all of them have a compute unit, of which each fills one)
-  if (phase == 0 && !options && pl.head_threads == kHeadThreadsLong && 2 * pl.vbatch * p.n_q_heads <= pl.num_cus) A.splits = 2;
+  A.splits = head_pair(pl, phase) ? 2 : 1;
   hipLaunchKernelGGL(head_kernel_for(pl.head_threads, phase, options), dim3(p.n_q_heads, pl.vbatch, A.splits), dim3(pl.head_threads), pl.head_lds_bytes, st, A);
   return hipGetLastError();
 }

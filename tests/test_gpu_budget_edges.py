@@ -1,5 +1,6 @@
 """Budget and final sample of the targets N and SDPA at the edges of their sizes: samples that the first batch of draws holds, that take
-several, complements, whole residuals and none; every head against the oracle, and both workgroup sizes against each other."""
+several, complements, whole residuals and none; every head against the oracle, and few heads, which have two workgroups each in the first
+selection phase, against many."""
 import numpy as np
 import pytest
 
@@ -18,32 +19,35 @@ CASES = [
 ]
 
 
-def _run(wl, repeat=1):
+def _run(wl, threads, repeat=1):
+    from paper_2510_05688_amd import binding as vb
     from paper_2510_05688_amd.session import DecodeSession
     params = dict(plan_params(wl), batch=wl.batch * repeat)
     sess = DecodeSession(params)
+    vb.vatt_plan_set_option(sess.plan, vb.VATT_OPT_HEAD_THREADS, threads)
     tile = lambda a: np.concatenate([a] * repeat)
     sess.upload(tile(wl.q_bits), tile(wl.k_bits), tile(wl.v_bits), tile(wl.seq_lens), tile(wl.seeds))
+    sess.workspace.fill_(0xff)  # (scores and sums that nobody left would be NaN)
+    sess.out_idx.zero_()
     sess.decode()
     res = sess.results_host()
     sess.close()
     return res
 
 
-@pytest.mark.parametrize("head_dim", [64, 128])
+@pytest.mark.parametrize("head_dim, threads", [(64, 512), (128, 512), (128, 1024)])
 @pytest.mark.parametrize("case", CASES, ids=lambda c: "-".join(map(str, c)))
-def test_budgets_at_the_edges_of_their_sizes(case, head_dim):
+def test_budgets_at_the_edges_of_their_sizes(case, head_dim, threads):
     hi, lo, k, b0, eps, target = case
     p = default_params(head_dim, sink=4, window=28, topk_abs=k, topk_frac=0.0, base_abs=b0, base_frac=0.0, epsilon=eps, target=target)
     wl = workloads.make_workload("budgets", batch=2, n_q_heads=4, n_kv_heads=2, head_dim=head_dim, n_max=hi, seq_lens=[hi, lo],
                                  seed=sum(map(int, case[:4])), params=p, v_mean=1.0, plant_frac=0.003)
-    res = _run(wl)
+    res = _run(wl, threads)
     check_all(wl, res, label="budgets %s" % (case,))
-    # the same sequences among more heads than the card has compute units, which takes the smaller workgroups: the same lists,
-    # counts and flags.  The statistics pass is cut at other places there, so its 32-bit sums of a few hundred rows differ by
+    # the same sequences among more heads than the card has compute units, one workgroup each: the same lists, counts and flags.  The statistics pass is cut at other places there, so its 32-bit sums of a few hundred rows differ by
     # rounding, the unrounded budgets by some 1e-6 and a budget next to a whole number by one.
     repeat = 40
-    many = _run(wl, repeat)
+    many = _run(wl, threads, repeat)
     seg, counts = res["seg"], res["counts"]
     for r in (0, repeat - 1):
         rows = slice(r * wl.batch, (r + 1) * wl.batch)
