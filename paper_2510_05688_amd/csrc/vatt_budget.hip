@@ -10,10 +10,12 @@ namespace {
 // the gather then reads the rows of the final sample only.
 // What bounds it: one chain per head.  Everything that the budget waits for is asked for ahead of the first batch of draws, which
 // is as large as the workgroup can make it: budgets of these targets go well beyond the base sample.
-// Kernel and whole call, us, before (the selection kernel with its top-k step left out, then a gather of all listed rows) -> now:
-// 4 x 16K tokens 19.1 -> 13, 86.8 -> 82.5; whole call 16 x 32K 373 -> 358, 32 x 8K 324 -> 311, 4 x 128K 353 -> 333, 8 x 4K paged
-// 82.4 -> 82.0, one of 2K 37.4 -> 37.2.
-template <int NT, bool OPTIONS>
+// Whole call, us, before (the selection kernel with its top-k step left out, then a gather of all listed rows), with this kernel and
+// the gather of the final sample alone, and now (two workgroups per head in phase 1, PRE): 4 x 16K tokens 86.8, 82.5, 79.7; 16 x 32K
+// 373, 358, 359; 32 x 8K 324, 311, 312; 4 x 128K 353, 333, 326; 8 x 4K paged 82.5, 82.0, 81.8; 2 x 9K of 16 heads 50.7, 50.7, 46.8;
+// one of 2K 37.4, 37.2, 35.1.
+// PRE: the first batch of draws comes from the second workgroups of phase 1.
+template <int NT, bool OPTIONS, bool PRE>
 __global__ __launch_bounds__(NT, 4) void budget_kernel(HeadArgs A) {
   touch_args<HeadArgs>();
   if constexpr (!OPTIONS) {
@@ -33,6 +35,12 @@ __global__ __launch_bounds__(NT, 4) void budget_kernel(HeadArgs A) {
   // everything that can be asked for before the sizes are known
   const HeadRec rec = A.head_rec[bh];
   const uint64_t seed = A.seq_seeds[seq];
+  uint4 pre_t = make_uint4(0u, 0u, 0u, 0u);
+  uint32_t pre_f = 0u;
+  if constexpr (PRE) {
+    pre_t = A.pre_tok[(int64_t)bh * NT + tid];
+    pre_f = A.pre_flags[(int64_t)bh * NT + tid];
+  }
   int32_t* c = A.out_counts + (int64_t)bh * 8;
   int flags = c[7];
   int32_t* idx = A.out_idx + (int64_t)bh * A.idx_cap;
@@ -112,13 +120,22 @@ __global__ __launch_bounds__(NT, 4) void budget_kernel(HeadArgs A) {
   S.m = rec.m;
   S.dbg = nullptr;
   DrawBatch spec = {};
-  // From 12K residual tokens on, 512 threads make 2048 draws at first, where the other targets' kernel has 1024; fewer tokens are drawn
-  // too often for that (us per call, 1024 / 2048 draws: 4 x 16K tokens 86.4 / 84.4, 32 x 8K 311 / 308, but 8 x 4K 85.1 / 85.3, 2 x 9K
-  // 53.1 / 53.9; workgroups of 1024 threads with 4096 draws 84.9, 334, 88.2, 56.5).
   const int plan_batch = ahead_blocks<NT>(A.small_batches, hs, final_draws(hs));
-  const int first_batch = OPTIONS || hs.n_s < 12288 ? plan_batch : likely_blocks(NT, hs, final_draws(hs));
+  const int first_batch = OPTIONS ? plan_batch : budget_blocks<NT>(hs);
   const bool want = hs.n_s > 0 && !A.nested;  // (a nested final sample rarely draws at all)
-  if (want) O::make_batch(spec, S, hs, 0u, first_batch, false, false, sm, tid);
+  if (want && PRE) {
+    spec.blocks = first_batch;
+    spec.ok = pre_ok(pre_f);
+    spec.first = pre_first(pre_f);
+    const uint32_t tk[4] = {pre_t.x, pre_t.y, pre_t.z, pre_t.w};
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      spec.tok[e] = min(max(tk[e], (uint32_t)hs.mid_lo), (uint32_t)max(hs.mid_hi - 1, hs.mid_lo));
+      if ((spec.ok >> e) & 1u) O::mark_bit(S.taken, spec.tok[e]);
+    }
+  } else if (want) {
+    O::make_batch(spec, S, hs, 0u, first_batch, false, false, sm, tid);
+  }
   constexpr bool kPlace = NT >= 1024;  // (as in the selection-only kernel)
   if (want && kPlace && A.splits == 1) {  // (else the second workgroup of phase 1 has left them)
 #pragma unroll
@@ -152,9 +169,9 @@ __global__ __launch_bounds__(NT, 4) void budget_kernel(HeadArgs A) {
       ask(s0);
       take(s0);
     }
-    A.fixed_sums[(int64_t)bh * kFixedSums + 1 + tid] = nf;
+    A.fixed_sums[(int64_t)bh * kFixedStride + 1 + tid] = nf;
   }
-  if (tid == 0) A.fixed_sums[(int64_t)bh * kFixedSums] = D_f;
+  if (tid == 0) A.fixed_sums[(int64_t)bh * kFixedStride] = D_f;
   double sigma2 = 0.0, b_star = 0.0, tr_sigma = 0.0, nhat_sq = 0.0, D_hat = D_f;
   int bfin = 0;
   if (hs.n_s > 0) {
@@ -214,9 +231,10 @@ __global__ __launch_bounds__(NT, 4) void budget_kernel(HeadArgs A) {
 }
 
 typedef void (*BudgetKernel)(HeadArgs);
-BudgetKernel budget_kernel_for(int threads, bool options) {
-  if (threads == kHeadThreadsLong) return options ? budget_kernel<kHeadThreadsLong, true> : budget_kernel<kHeadThreadsLong, false>;
-  return options ? budget_kernel<kHeadThreads, true> : budget_kernel<kHeadThreads, false>;
+BudgetKernel budget_kernel_for(int threads, bool options, bool pre) {
+  if (threads == kHeadThreadsLong) return options ? budget_kernel<kHeadThreadsLong, true, false> : budget_kernel<kHeadThreadsLong, false, false>;
+  if (options) return budget_kernel<kHeadThreads, true, false>;
+  return pre ? budget_kernel<kHeadThreads, false, true> : budget_kernel<kHeadThreads, false, false>;
 }
 
 }  // namespace
@@ -224,11 +242,12 @@ BudgetKernel budget_kernel_for(int threads, bool options) {
 hipError_t set_budget_kernel_attributes() {
   // (as for the selection kernels: the limit belongs to the kernel, so it is raised to all a CU has)
   for (const int threads : {kHeadThreads, kHeadThreadsLong})
-    for (const bool options : {false, true}) {
-      const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(budget_kernel_for(threads, options)),
-                                               hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
-      if (e != hipSuccess) return e;
-    }
+    for (const bool options : {false, true})
+      for (const bool pre : {false, true}) {
+        const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(budget_kernel_for(threads, options, pre)),
+                                                 hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
+        if (e != hipSuccess) return e;
+      }
   return hipSuccess;
 }
 
@@ -239,8 +258,10 @@ hipError_t launch_budget(const Plan& pl, const int32_t* seq_lens, const uint64_t
   const vatt_params& p = pl.p;
   const int threads = pl.head_threads;
   A.splits = head_pair(pl, 1) ? 2 : 1;
+  A.pre_tok = reinterpret_cast<uint4*>(static_cast<char*>(ws) + pl.off_pre_tok);
+  A.pre_flags = reinterpret_cast<uint32_t*>(static_cast<char*>(ws) + pl.off_pre_flags);
   const size_t lds = sizeof(uint32_t) * (threads == kHeadThreadsLong ? sampler_lds<kHeadThreadsLong>(p.n_max) : sampler_lds<kHeadThreads>(p.n_max)).end;
-  hipLaunchKernelGGL(budget_kernel_for(threads, head_options(pl)), dim3(p.n_q_heads, pl.vbatch), dim3(threads), lds, st, A);
+  hipLaunchKernelGGL(budget_kernel_for(threads, head_options(pl), A.splits == 2), dim3(p.n_q_heads, pl.vbatch), dim3(threads), lds, st, A);
   return hipGetLastError();
 }
 

@@ -296,7 +296,7 @@ __global__ __launch_bounds__(D) void tail_merge_kernel(const float* __restrict__
   const int h = head_of_block((int)blockIdx.x, Hq, Hkv, group_major), b = blockIdx.y, bh = b * Hq + h;
   const int c = threadIdx.x;
   const float* p = part + (int64_t)bh * splits * (D + 4);
-  const double* fixed = fixed_sums + (int64_t)bh * kFixedSums;
+  const double* fixed = fixed_sums + (int64_t)bh * kFixedStride;
   const HeadRec r = head_rec[bh];
   constexpr int U = 16;
   double dtot = fixed[0], a = fixed[1 + c];
@@ -358,7 +358,7 @@ hipError_t launch_gather_d(const Plan& pl, const void* v, const int32_t* block_t
   constexpr int step_rows = (kGatherThreads / (D / 8)) * 8;
   if constexpr (PART == kTail) {
     hipLaunchKernelGGL((tail_merge_kernel<D>), dim3(p.n_q_heads, pl.vbatch), dim3(D), 0, st, A.part,
-                       reinterpret_cast<const double*>(w + pl.off_pre_tok), A.head_rec, A.splits, p.n_q_heads, out_o, out_lse,
+                       reinterpret_cast<const double*>(w + pl.off_pre_flags), A.head_rec, A.splits, p.n_q_heads, out_o, out_lse,
                        pl.group_major, p.n_kv_heads, step_rows);
     return hipGetLastError();
   }

@@ -15,9 +15,10 @@ constexpr int kSubTile = 8;            // keys per sub-tile maximum
 constexpr int kHeadThreads = 512;      // workgroup size of the per-head kernel
 constexpr int kHeadThreadsLong = 1024; // ... for rows whose 8-key maxima do not fit the registers of 512 threads
 constexpr int kGatherThreads = 256;
-// Targets N and SDPA: the doubles that the budget kernel leaves of a head for the merge: D_f, and N_f from the second on.
-constexpr int kFixedSums = 1 + 128;
-static_assert(kFixedSums * sizeof(double) <= kHeadThreads * sizeof(uint4), "it lies in the region of the draws made ahead");
+// Targets N and SDPA: the doubles that the budget kernel leaves of a head for the merge, D_f and then N_f.  They take the place of the
+// flags of the head's own draws made ahead, which the kernel has read by then.
+constexpr int kFixedStride = kHeadThreads * sizeof(uint32_t) / sizeof(double);
+static_assert(1 + 128 <= kFixedStride, "a column each");
 // Launch orders of the score pass (see the score kernel); the values of VATT_OPT_SCORE_ORDER.
 constexpr int kScoreOrderTile = 0, kScoreOrderKvHead = 1, kScoreOrderBlocks = 2;
 constexpr int kDenseThreads = 256;

@@ -29,7 +29,7 @@ struct HeadArgs {
   HeadRec* head_rec;
   HeadRec* given_rec;  // caller-supplied path, gather apart: the second phase's record, beside the first's, which others are reading
   const double* vstat_part;  // [B*Hq][vstat_splits][2d+2] (targets N, SDPA)
-  double* fixed_sums;        // [B*Hq][kFixedSums]: see there (targets N, SDPA)
+  double* fixed_sums;        // [B*Hq][kFixedStride]: D_f and N_f (targets N, SDPA)
   const float* given_vstat;  // [B*Hq][given_splits][2d+4]: N_f[d], R1[d], R2, maximum (given-top-k path)
   int given_splits;
   int32_t* out_idx;
@@ -510,6 +510,15 @@ inline bool head_options(const Plan& pl) {
          pl.budget_multiple != 1;
 }
 
+// Philox blocks of the budget kernel's first batch of draws.
+// From 12K residual tokens on, 512 threads make 2048 draws at first, where the other targets' kernel has 1024; fewer tokens are drawn
+// too often for that (us per call, 1024 / 2048 draws: 4 x 16K tokens 86.4 / 84.4, 32 x 8K 311 / 308, but 8 x 4K 85.1 / 85.3, 2 x 9K
+// 53.1 / 53.9; workgroups of 1024 threads with 4096 draws 84.9, 334, 88.2, 56.5).
+template <int NT>
+__device__ __forceinline__ int budget_blocks(const HeadSizes& hs) {
+  return hs.n_s < 12288 ? ahead_blocks<NT>(0, hs, final_draws(hs)) : likely_blocks(NT, hs, final_draws(hs));
+}
+
 // Whether the selection-only kernel has a second workgroup per head: as long as all of them have a compute unit to themselves, for long
 // rows and for the first phase of the targets N and SDPA.
 inline bool head_pair(const Plan& pl, int phase) {
@@ -555,7 +564,7 @@ inline void fill_head_args(HeadArgs& A, const Plan& pl, const int32_t* seq_lens,
   A.draw_cap = pl.sampler_draw_cap;
   A.large_budgets = (pl.z_half / pl.eps) * (pl.z_half / pl.eps) > 5000.0;
   A.vstat_splits = pl.vstat_splits;
-  A.fixed_sums = reinterpret_cast<double*>(w + pl.off_pre_tok);  // (those targets have no batches made ahead)
+  A.fixed_sums = reinterpret_cast<double*>(w + pl.off_pre_flags);
   A.head_dim = p.head_dim;
   A.k_max = pl.k_max;
   A.b0_max = pl.b0_max;

@@ -95,7 +95,7 @@ __global__ __launch_bounds__(NT, FD > 0 ? 1 : 4) void head_kernel(HeadArgs A) {
   uint4 pre_t = make_uint4(0u, 0u, 0u, 0u);
   uint32_t pre_f = 0u;
   bool pre_made = false;
-  if (NT == kHeadThreads && A.pre_tok) {
+  if (NT == kHeadThreads && PHASE == 0 && A.pre_tok) {
     pre_t = A.pre_tok[(int64_t)bh * NT + tid];
     pre_f = A.pre_flags[(int64_t)bh * NT + tid];
     pre_made = pre_made_of(A.pre_flags[(int64_t)bh * NT]);  // one word for the whole workgroup: uniform
@@ -285,6 +285,12 @@ __global__ __launch_bounds__(NT, FD > 0 ? 1 : 4) void head_kernel(HeadArgs A) {
     pair_made = true;
   } else if (want0) {
     O::make_batch(spec0, S0, hs, 0u, ahead_blocks<NT>(A.small_batches, hs, base_draws(hs)), false, true, sm, tid);
+  } else if (kPair && PHASE == 1 && kTwoStreams && second && hs.n_s > 0) {
+    // (the budget kernel's first batch, which stood in its chain; it depends on the length only)
+    DrawBatch mine = {};
+    O::make_batch(mine, S1, hs, 0u, budget_blocks<NT>(hs), false, false, sm, tid);
+    A.pre_tok[(int64_t)bh * NT + tid] = make_uint4(mine.tok[0], mine.tok[1], mine.tok[2], mine.tok[3]);
+    A.pre_flags[(int64_t)bh * NT + tid] = pre_pack(mine, true);
   } else if (second && want1) {
     O::make_batch(spec1, S1, hs, 0u, ahead_blocks<NT>(A.small_batches, hs, final_draws(hs)), false, true, sm, tid);
     spec1_made = true;
@@ -1318,6 +1324,10 @@ hipError_t launch_head(const Plan& pl, int phase, const int32_t* seq_lens, const
   const vatt_params& p = pl.p;
   const bool options = head_options(pl);
   A.splits = head_pair(pl, phase) ? 2 : 1;
+  if (phase == 1) {  // (from its second workgroups to the budget kernel)
+    A.pre_tok = reinterpret_cast<uint4*>(static_cast<char*>(ws) + pl.off_pre_tok);
+    A.pre_flags = reinterpret_cast<uint32_t*>(static_cast<char*>(ws) + pl.off_pre_flags);
+  }
   hipLaunchKernelGGL(head_kernel_for(pl.head_threads, phase, options), dim3(p.n_q_heads, pl.vbatch, A.splits), dim3(pl.head_threads), pl.head_lds_bytes, st, A);
   return hipGetLastError();
 }

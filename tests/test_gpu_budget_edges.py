@@ -20,8 +20,8 @@ CASES = [
 
 
 def _run(wl, threads, repeat=1):
-    from paper_2510_05688_amd import binding as vb
     from paper_2510_05688_amd.session import DecodeSession
+    from paper_2510_05688_amd import binding as vb
     params = dict(plan_params(wl), batch=wl.batch * repeat)
     sess = DecodeSession(params)
     vb.vatt_plan_set_option(sess.plan, vb.VATT_OPT_HEAD_THREADS, threads)
