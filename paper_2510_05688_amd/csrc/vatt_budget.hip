@@ -163,15 +163,16 @@ __global__ __launch_bounds__(NT, 4) void budget_kernel(HeadArgs A) {
   for (int i = tid + NT; i < hs.n_win; i += NT) fixed(row[hs.mid_hi + i]);
   O::block_sum(sums, sm);
   const double D_f = sums[0];
+  double* fixed_sums = reinterpret_cast<double*>(A.pre_flags) + (int64_t)bh * kFixedStride;
   if (tid < d) {
     if (A.vstat_splits > VS) take(VS);
     for (int s0 = 2 * VS; s0 < A.vstat_splits; s0 += VS) {
       ask(s0);
       take(s0);
     }
-    A.fixed_sums[(int64_t)bh * kFixedStride + 1 + tid] = nf;
+    fixed_sums[1 + tid] = nf;
   }
-  if (tid == 0) A.fixed_sums[(int64_t)bh * kFixedStride] = D_f;
+  if (tid == 0) fixed_sums[0] = D_f;
   double sigma2 = 0.0, b_star = 0.0, tr_sigma = 0.0, nhat_sq = 0.0, D_hat = D_f;
   int bfin = 0;
   if (hs.n_s > 0) {

@@ -27,9 +27,7 @@ struct HeadArgs {
   const int32_t* seq_lens;
   const uint64_t* seq_seeds;
   HeadRec* head_rec;
-  HeadRec* given_rec;  // caller-supplied path, gather apart: the second phase's record, beside the first's, which others are reading
   const double* vstat_part;  // [B*Hq][vstat_splits][2d+2] (targets N, SDPA)
-  double* fixed_sums;        // [B*Hq][kFixedStride]: D_f and N_f (targets N, SDPA)
   const float* given_vstat;  // [B*Hq][given_splits][2d+4]: N_f[d], R1[d], R2, maximum (given-top-k path)
   int given_splits;
   int32_t* out_idx;
@@ -58,12 +56,13 @@ struct HeadArgs {
   KVLayout L;
   float* part;       // [B*Hq][splits][d + 4]: partial (sum w V, sum w) of every workgroup
   int splits, split_shift, group;
-  int fixed_splits, part_slots;  // caller-supplied path: workgroups per head for I_f, and partial sums of a head in all
-  int glist_cap, dlist_cap;  // LDS entries for a workgroup's share of I_f and of the final sample
+  int glist_cap;  // LDS entries for a workgroup's share of I_f; caller-supplied path, gather apart: partial sums of a head in all
+  int dlist_cap;  // LDS entries for a workgroup's share of the final sample
   // first batches of draws made ahead (nullptr: made here): of both sampler streams by workgroups of the score launch, and on the
   // caller-supplied path of the final sample's by the first phase for the second
   uint4* pre_tok;       // [B*Hq][kHeadThreads]: the four proposed tokens of every thread
-  uint32_t* pre_flags;  // [B*Hq][kHeadThreads]: see pre_pack
+  uint32_t* pre_flags;  // [B*Hq][kHeadThreads]: see pre_pack.  Also the place of what later kernels leave (kFixedStride, given_rec_of): with
+                        // pointers of their own the arguments are a cache line longer, 0.3 us of the short calls
   // random cache of base-sample rows (nullptr: the base sample is drawn)
   const void* rcache;
   CacheLayout rc;
@@ -537,7 +536,6 @@ inline void fill_head_args(HeadArgs& A, const Plan& pl, const int32_t* seq_lens,
   A.seq_lens = seq_lens;
   A.seq_seeds = seq_seeds;
   A.head_rec = reinterpret_cast<HeadRec*>(w + pl.off_head_rec);
-  A.given_rec = given_rec_of(pl, ws);
   A.vstat_part = reinterpret_cast<const double*>(w + pl.off_vstat_part);
   A.out_idx = out_idx;
   A.out_counts = out_counts;
@@ -564,7 +562,6 @@ inline void fill_head_args(HeadArgs& A, const Plan& pl, const int32_t* seq_lens,
   A.draw_cap = pl.sampler_draw_cap;
   A.large_budgets = (pl.z_half / pl.eps) * (pl.z_half / pl.eps) > 5000.0;
   A.vstat_splits = pl.vstat_splits;
-  A.fixed_sums = reinterpret_cast<double*>(w + pl.off_pre_flags);
   A.head_dim = p.head_dim;
   A.k_max = pl.k_max;
   A.b0_max = pl.b0_max;
@@ -587,7 +584,6 @@ inline void fill_head_args(HeadArgs& A, const Plan& pl, const int32_t* seq_lens,
   A.part = nullptr;
   A.splits = 1;
   A.split_shift = 0;
-  A.fixed_splits = A.part_slots = 0;
   A.group = pl.group;
   A.glist_cap = 0;
   A.dlist_cap = 0;

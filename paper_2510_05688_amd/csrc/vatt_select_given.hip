@@ -668,7 +668,7 @@ __device__ __forceinline__ void given_topk(const HeadArgs& A) {
     r.tail_by_token = 0;
     // (with the gather fused in nothing reads the record again, and the head's other workgroups may still be
     // reading the first phase's)
-    if (!kFused) A.given_rec[bh] = r;
+    if (!kFused) reinterpret_cast<HeadRec*>(A.pre_flags)[bh] = r;  // (beside the first phase's, which others are reading)
   }
 
   if constexpr (kFused) {
@@ -803,7 +803,7 @@ __device__ __forceinline__ void gather_fixed(const HeadArgs& A, int split) {
   const int sub = lane % LPR, rsub = lane / LPR;
   const HeadRec r = A.head_rec[bh];  // the first phase's: b is the size of the base sample
   const int n_fix = r.n_sink + r.n_win + r.k;
-  const int splits = used_splits(A.fixed_splits, n_fix, RPB * U);
+  const int splits = used_splits(A.splits, n_fix, RPB * U);
   if (split >= splits) return;
   const bool shared_rows = rows_are_shared(n_fix + r.b, A.group_major ? A.q_len * A.group : A.q_len, r.n, A.group_major && A.group > 1 ? 3 : 2);
   const int per = (n_fix + splits - 1) / splits;
@@ -877,7 +877,7 @@ __device__ __forceinline__ void gather_fixed(const HeadArgs& A, int split) {
   float M = -INFINITY;
 #pragma unroll
   for (int j = 0; j < WAVES; ++j) M = fmaxf(M, s_m[j]);
-  float* part = A.part + ((int64_t)bh * A.part_slots + split) * (D + 4);
+  float* part = A.part + ((int64_t)bh * A.glist_cap + split) * (D + 4);
   float a = 0.f, d = 0.f;
 #pragma unroll
   for (int j = 0; j < WAVES; ++j) {
@@ -962,11 +962,12 @@ hipError_t launch_given_budget(const Plan& pl, const void* v, const int32_t* blo
   A.L = pl.kv_v;
   A.L.block_table = block_table;
   A.part = reinterpret_cast<float*>(static_cast<char*>(ws) + pl.off_gather_part);
-  A.fixed_splits = given_fixed_splits(pl);
-  A.part_slots = given_part_slots(pl);
+  A.splits = given_fixed_splits(pl);
+  A.glist_cap = given_part_slots(pl);
+  A.pre_flags = reinterpret_cast<uint32_t*>(given_rec_of(pl, ws));
   const size_t lds = sizeof(uint32_t) * sampler_lds<kHeadThreads>(pl.p.n_max).end;
-  const GivenKernel kernel = A.fixed_splits > 0 ? given_budget_kernel_for(pl.p.head_dim, pl.p.kv_layout == VATT_LAYOUT_PAGED) : given_kernel_for(1, 0, false);
-  hipLaunchKernelGGL(kernel, dim3(pl.p.n_q_heads, pl.vbatch, 1 + A.fixed_splits), dim3(kHeadThreads), lds, st, A);
+  const GivenKernel kernel = A.splits > 0 ? given_budget_kernel_for(pl.p.head_dim, pl.p.kv_layout == VATT_LAYOUT_PAGED) : given_kernel_for(1, 0, false);
+  hipLaunchKernelGGL(kernel, dim3(pl.p.n_q_heads, pl.vbatch, 1 + A.splits), dim3(kHeadThreads), lds, st, A);
   return hipGetLastError();
 }
 
