@@ -42,7 +42,10 @@ namespace {
 // OPTIONS: a plan with an option set that the usual call does without (head_options) has a kernel of its own; without them the
 // selection-only kernel, which is at its register limit, takes 33.6 instead of 36.5 us for 16 x 32K tokens, the fused one 20.0 instead
 // of 20.4 for 1 x 32K and 12.7 instead of 13.4 for one head of 1K.
-template <int NT, int FD, bool PAGED, bool ALONE, int PHASE, bool OPTIONS>
+// PAIR: two workgroups per head (head_pair).  A form of its own, too: as a run-time branch it made the forms with one workgroup per head
+// spill, which then took (whole call, us, branch -> form of its own) 263.0 -> 262.4 for 8 x 64K tokens, 145.2 -> 143.6 for 6 x 40K at
+// epsilon 0.02, 89.1 -> 88.1 for 1 x 32K with 16 query tokens; and with two workgroups 4 x 128K 250.3 -> 249.3, 1 x 60K 57.5 -> 56.8.
+template <int NT, int FD, bool PAGED, bool ALONE, int PHASE, bool OPTIONS, bool PAIR>
 __global__ __launch_bounds__(NT, FD > 0 ? 1 : 4) void head_kernel(HeadArgs A) {
   touch_args<HeadArgs>();
   if constexpr (FD > 0 || !OPTIONS) A.nested = A.ascending = 0;  // (in the fused kernel too: what it does not serve has no code there, 0.3 us)
@@ -67,18 +70,17 @@ __global__ __launch_bounds__(NT, FD > 0 ? 1 : 4) void head_kernel(HeadArgs A) {
   constexpr bool kSplit = kFused && !ALONE;
   const uint32_t split = kSplit ? blockIdx.z : 0u, shift = kSplit ? (uint32_t)A.split_shift : 0u;
   const uint32_t smask = (1u << shift) - 1u;
-  // No more heads than half the compute units, and long rows or the first phase (head_pair): a second workgroup per head (A.splits == 2) repeats the top-k step and
-  // writes what the first would make the base sample wait for, the lists of I_f, and what it would make the budget wait for, the
-  // scores of the final sample's proposals at the list places.  Nothing is exchanged: it writes the scores of all accepted draws of the
+  // PAIR: the second workgroup of a head repeats the top-k step and writes what the first would make the base sample wait for, the
+  // lists of I_f, and what it would make the budget wait for: the scores of the final sample's proposals at the list places (long rows)
+  // or the budget kernel's first batch of draws.  Nothing is exchanged: it writes the scores of all accepted draws of the
   // first batch, and the first workgroup says in the record whether the sample is the beginning of them.  A compute unit takes
   // four to five clocks per scattered 4-byte read, and with one workgroup per head half of the units pulled all of them.
   // Whole call, us, one -> two: 4 x 128K tokens 250.5 -> 245.0, 1 x 128K 113.6 -> 103.0, 2 of 9K - 100K paged 108.5 -> 99.1, 4 x 50K with
   // k and b0 of 5 % 151.6 -> 145.4, 1 x 60K at epsilon 0.02 59.5 -> 57.3, 1 x 91K with 3 query tokens 109.4 -> 99.1.
   // Targets N and SDPA: 4 x 16K 82.5 -> 80.5, 1 x 32K 86.8 -> 84.4, 2 x 9K of 16 heads 50.7 -> 47.8, 4 x 128K 333 -> 327, 1 x 100K 155 -> 152.7.
-  constexpr bool kPair = !kFused && !OPTIONS && (NT >= 1024 || PHASE == 1);
-  const bool paired = kPair && A.splits == 2;
-  const bool second = paired && blockIdx.z == 1u;
-  const bool lister = !paired || second;            // this workgroup writes the lists of I_f
+  static_assert(!PAIR || (!kFused && !OPTIONS && (NT >= 1024 || PHASE == 1)), "what head_pair asks for");
+  const bool second = PAIR && blockIdx.z == 1u;
+  const bool lister = !PAIR || second;              // this workgroup writes the lists of I_f
   const bool writer = split == 0u && !second;       // this workgroup writes the head's other outputs
   // The sub-tile maxima the score kernel left are requested first of all, before even the sequence length is
   // known (what lies beyond the row's own sub-tiles is masked once it is): the kernel starts with a chain of
@@ -285,7 +287,7 @@ __global__ __launch_bounds__(NT, FD > 0 ? 1 : 4) void head_kernel(HeadArgs A) {
     pair_made = true;
   } else if (want0) {
     O::make_batch(spec0, S0, hs, 0u, ahead_blocks<NT>(A.small_batches, hs, base_draws(hs)), false, true, sm, tid);
-  } else if (kPair && PHASE == 1 && kTwoStreams && second && hs.n_s > 0) {
+  } else if (PAIR && PHASE == 1 && kTwoStreams && second && hs.n_s > 0) {
     // (the budget kernel's first batch, which stood in its chain; it depends on the length only)
     DrawBatch mine = {};
     O::make_batch(mine, S1, hs, 0u, budget_blocks<NT>(hs), false, false, sm, tid);
@@ -759,7 +761,7 @@ __global__ __launch_bounds__(NT, FD > 0 ? 1 : 4) void head_kernel(HeadArgs A) {
   if constexpr (kFused) my_nf = (int)(g_hi - g_lo);
 
   VATT_STAMP(A.dbg, 32);
-  if (want1 && !spec1_made) O::make_batch(spec1, S1, hs, 0u, ahead_blocks<NT>(A.small_batches, hs, final_draws(hs)), false, false, sm, tid);
+  if (!(PAIR && PHASE == 1) && want1 && !spec1_made) O::make_batch(spec1, S1, hs, 0u, ahead_blocks<NT>(A.small_batches, hs, final_draws(hs)), false, false, sm, tid);
 
   // ---- I_bs (Algorithm 2, base sample) and the sums over it ----
   int flags = topk_flag;
@@ -1003,7 +1005,7 @@ __global__ __launch_bounds__(NT, FD > 0 ? 1 : 4) void head_kernel(HeadArgs A) {
   // short of registers, the same cost more than the gather gains: a sample that its shortcut above does not
   // cover is read by token.)
   constexpr bool kEmitScores = !kFused && NT >= 1024;
-  if (kEmitScores && want1 && !spec1.have_sc && !paired) {
+  if (kEmitScores && !PAIR && want1 && !spec1.have_sc) {
 #pragma unroll
     for (int e = 0; e < 4; ++e) spec1.sc[e] = row[min(spec1.tok[e], (uint32_t)(n - 1))];
     spec1.have_sc = true;
@@ -1019,8 +1021,10 @@ __global__ __launch_bounds__(NT, FD > 0 ? 1 : 4) void head_kernel(HeadArgs A) {
   const double D_f = sums[0];
   double b_star = 0.0;
   int bfin = 0;
-  if (hs.n_s > 0) {
-    const Budget bud = algorithm2_budget(A, hs.n_s, hs.b0, D_f, sums[1], sums[2], 0.0, w_range);
+  int n_s = hs.n_s;
+  asm("" : "+s"(n_s));  // (worked out anew: its double, which the sizes at the start need too, was kept to the end and spilled)
+  if (n_s > 0) {
+    const Budget bud = algorithm2_budget(A, n_s, hs.b0, D_f, sums[1], sums[2], 0.0, w_range);
     b_star = bud.b_star;
     bfin = bud.b;
     const double D_hat = bud.D_hat;
@@ -1090,7 +1094,7 @@ __global__ __launch_bounds__(NT, FD > 0 ? 1 : 4) void head_kernel(HeadArgs A) {
                                        more_dyn ? tot1 : 0u, more_dyn ? (uint32_t)spec1.blocks : 0u);
     flags |= ((f & 1) ? kFlagDynComplement : 0) | ((f & 2) ? kFlagDynBatches : 0) | ((f & 4) ? kFlagDrawCap : 0);
     // (one batch made ahead with its scores held the whole sample, and the list stays in acceptance order)
-    dyn_placed = kEmitScores && !A.nested && !A.ascending && want1 && (spec1.have_sc || paired) && f == 0;
+    dyn_placed = kEmitScores && !A.nested && !A.ascending && want1 && (spec1.have_sc || PAIR) && f == 0;
     if (!kFused && A.ascending && !A.nested && !(f & 1))
       O::sort_ascending(idx + A.seg_dyn, (uint32_t)min(bfin, A.b_max), scratch, wpre, n, sm);
     VATT_STAMP(A.dbg, 8);
@@ -1108,7 +1112,7 @@ __global__ __launch_bounds__(NT, FD > 0 ? 1 : 4) void head_kernel(HeadArgs A) {
     if (A.out_budget_raw) A.out_budget_raw[bh] = b_star;
     HeadRec r;
     r.m = m;
-    r.scale = bfin > 0 ? (float)((double)hs.n_s / (double)bfin) : 0.f;
+    r.scale = bfin > 0 ? (float)((double)n_s / (double)bfin) : 0.f;
     r.n = n;
     r.n_sink = hs.n_sink;
     r.n_win = hs.n_win;
@@ -1256,8 +1260,8 @@ typedef void (*HeadKernel)(HeadArgs);
 // The instantiation for a plan: workgroup size; with the fused gather also head dimension and cache layout.
 template <int D, bool PAGED>
 HeadKernel fused_kernel_for(bool alone, bool options) {
-  if (alone) return options ? head_kernel<kHeadThreads, D, PAGED, true, 0, true> : head_kernel<kHeadThreads, D, PAGED, true, 0, false>;
-  return options ? head_kernel<kHeadThreads, D, PAGED, false, 0, true> : head_kernel<kHeadThreads, D, PAGED, false, 0, false>;
+  if (alone) return options ? head_kernel<kHeadThreads, D, PAGED, true, 0, true, false> : head_kernel<kHeadThreads, D, PAGED, true, 0, false, false>;
+  return options ? head_kernel<kHeadThreads, D, PAGED, false, 0, true, false> : head_kernel<kHeadThreads, D, PAGED, false, 0, false, false>;
 }
 HeadKernel fused_kernel_for(int d, bool paged, bool alone, bool options) {
   if (d == 128) return paged ? fused_kernel_for<128, true>(alone, options) : fused_kernel_for<128, false>(alone, options);
@@ -1265,9 +1269,13 @@ HeadKernel fused_kernel_for(int d, bool paged, bool alone, bool options) {
 }
 template <int NT, bool OPTIONS>
 HeadKernel head_kernel_for(int phase) {
-  return phase == 0 ? head_kernel<NT, 0, false, false, 0, OPTIONS> : head_kernel<NT, 0, false, false, 1, OPTIONS>;
+  return phase == 0 ? head_kernel<NT, 0, false, false, 0, OPTIONS, false> : head_kernel<NT, 0, false, false, 1, OPTIONS, false>;
 }
-HeadKernel head_kernel_for(int threads, int phase, bool options) {
+// pair: as head_pair says (never with options, nor for phase 0 with 512 threads)
+HeadKernel head_kernel_for(int threads, int phase, bool options, bool pair) {
+  if (pair && threads == kHeadThreadsLong)
+    return phase == 0 ? head_kernel<kHeadThreadsLong, 0, false, false, 0, false, true> : head_kernel<kHeadThreadsLong, 0, false, false, 1, false, true>;
+  if (pair) return head_kernel<kHeadThreads, 0, false, false, 1, false, true>;
   if (threads == kHeadThreadsLong) return options ? head_kernel_for<kHeadThreadsLong, true>(phase) : head_kernel_for<kHeadThreadsLong, false>(phase);
   return options ? head_kernel_for<kHeadThreads, true>(phase) : head_kernel_for<kHeadThreads, false>(phase);
 }
@@ -1284,8 +1292,11 @@ hipError_t set_kernel_attributes(const Plan& pl) {
   for (const int threads : {kHeadThreads, kHeadThreadsLong})
     for (const int phase : {0, 1})
       for (const bool options : {false, true}) {
-        const hipError_t e = raise(head_kernel_for(threads, phase, options));
+        const hipError_t e = raise(head_kernel_for(threads, phase, options, false));
         if (e != hipSuccess) return e;
+        if (options || (threads == kHeadThreads && phase == 0)) continue;
+        const hipError_t e2 = raise(head_kernel_for(threads, phase, false, true));
+        if (e2 != hipSuccess) return e2;
       }
   for (const int d : {64, 128})
     for (const bool paged : {false, true})
@@ -1322,13 +1333,13 @@ hipError_t launch_head(const Plan& pl, int phase, const int32_t* seq_lens, const
   HeadArgs A;
   fill_head_args(A, pl, seq_lens, seq_seeds, ws, out_idx, out_counts, out_budget_raw, out_stats);
   const vatt_params& p = pl.p;
-  const bool options = head_options(pl);
-  A.splits = head_pair(pl, phase) ? 2 : 1;
+  const bool pair = head_pair(pl, phase);
+  A.splits = pair ? 2 : 1;
   if (phase == 1) {  // (from its second workgroups to the budget kernel)
     A.pre_tok = reinterpret_cast<uint4*>(static_cast<char*>(ws) + pl.off_pre_tok);
     A.pre_flags = reinterpret_cast<uint32_t*>(static_cast<char*>(ws) + pl.off_pre_flags);
   }
-  hipLaunchKernelGGL(head_kernel_for(pl.head_threads, phase, options), dim3(p.n_q_heads, pl.vbatch, A.splits), dim3(pl.head_threads), pl.head_lds_bytes, st, A);
+  hipLaunchKernelGGL(head_kernel_for(pl.head_threads, phase, head_options(pl), pair), dim3(p.n_q_heads, pl.vbatch, A.splits), dim3(pl.head_threads), pl.head_lds_bytes, st, A);
   return hipGetLastError();
 }
 
