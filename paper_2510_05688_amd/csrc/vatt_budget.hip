@@ -33,7 +33,8 @@ __global__ __launch_bounds__(NT, 4) void budget_kernel(HeadArgs A) {
   const int bh = b * A.Hq + h, tid = threadIdx.x;
   const int seq = seq_of_pair(b, A.q_len);
   // everything that can be asked for before the sizes are known
-  const HeadRec rec = A.head_rec[bh];
+  const int n = A.head_rec[bh].n;
+  const float m = A.head_rec[bh].m;
   const uint64_t seed = A.seq_seeds[seq];
   uint4 pre_t = make_uint4(0u, 0u, 0u, 0u);
   uint32_t pre_f = 0u;
@@ -77,7 +78,6 @@ __global__ __launch_bounds__(NT, 4) void budget_kernel(HeadArgs A) {
   else if (tid - d < A.vstat_splits) r2 = vp[(tid - d) * stride + 2 * d];  // (at most 32)
   for (int w = tid; w < 3 * (bitmap_words(A.n_max) / 4); w += NT)
     reinterpret_cast<uint4*>(bm_f)[w] = make_uint4(0u, 0u, 0u, 0u);  // the three bitmaps follow each other
-  const int n = rec.n;
   const HeadSizes hs = head_sizes(n, A.sp);
   const float* row = A.scores + (int64_t)bh * A.n_pad;
   // scores of the listed tokens, -inf where a thread has none (exp(-inf) = 0)
@@ -117,7 +117,7 @@ __global__ __launch_bounds__(NT, 4) void budget_kernel(HeadArgs A) {
     const uint64_t dflt = 64ull * (uint64_t)S.L + 4096ull;
     S.cap = (uint32_t)min(A.draw_cap ? (uint64_t)A.draw_cap : dflt, 0x80000000ull);
   }
-  S.m = rec.m;
+  S.m = m;
   S.dbg = nullptr;
   DrawBatch spec = {};
   const int plan_batch = ahead_blocks<NT>(A.small_batches, hs, final_draws(hs));
@@ -144,9 +144,9 @@ __global__ __launch_bounds__(NT, 4) void budget_kernel(HeadArgs A) {
   }
 
   double sums[3] = {0.0, 0.0, 0.0};  // D_f, and the base sample's weights and their squares
-  auto fixed = [&](float sc) { sums[0] += (double)__expf(sc - rec.m); };
+  auto fixed = [&](float sc) { sums[0] += (double)__expf(sc - m); };
   auto sampled = [&](float sc) {
-    const double w = (double)__expf(sc - rec.m);
+    const double w = (double)__expf(sc - m);
     sums[1] += w;
     sums[2] += w * w;
   };
@@ -222,12 +222,11 @@ __global__ __launch_bounds__(NT, 4) void budget_kernel(HeadArgs A) {
     c[6] = n;
     c[7] = flags;
     if (A.out_budget_raw) A.out_budget_raw[bh] = b_star;
-    HeadRec r = rec;
+    HeadRec& r = A.head_rec[bh];  // (the rest stays as phase 1 has written it: a copy of it went through scratch memory, 0.5 us of the call)
     r.scale = bfin > 0 ? (float)((double)hs.n_s / (double)bfin) : 0.f;
     r.b = bfin;
     r.b_keep = (A.nested && bfin > 0) ? hs.b0 : 0;
     r.tail_by_token = dyn_placed ? 0 : 1;
-    A.head_rec[bh] = r;
   }
 }
 
