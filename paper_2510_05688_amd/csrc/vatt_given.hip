@@ -46,9 +46,11 @@ struct GivenArgs {
   float* vstat;       // [B*Hq][splits][2d + 4]: N_f[d], R1[d], R2, maximum (numerator statistics, targets N / SDPA)
   float* out_o;
   float* out_lse;
-  int64_t seg_sink, seg_win, seg_topk, seg_base, seg_dyn, idx_cap;
+  // (the sink segment starts at place 0: with a field of its own, what the score kernels read goes on into a further line of arguments,
+  // 0.5 us of the short calls)
+  int64_t seg_win, seg_topk, seg_base, seg_dyn, idx_cap;
   int Hq, group, splits;
-  int part_slots, first_slot;  // partial sums of a head in all; the first of this kernel's
+  int part_slots, first_slot;  // partial sums of a head in all; the first of the gather's
   int group_major;  // see head_of_block (the KV head count is Hq / group)
   int q_len;  // query tokens per sequence: blockIdx.z = sequence * q_len + query token
   float sm_scale;
@@ -110,12 +112,12 @@ __global__ __launch_bounds__(kGatherThreads, 8) void sparse_score_kernel(GivenAr
   const int32_t* slots_of = A.base_slot + (int64_t)bh * A.b0_max;
   const uint16_t* k_head = PAGED ? A.k : A.k + (int64_t)seq * A.Lk.seq_stride + (int64_t)kvh * A.Lk.head_stride;
   const int n_sw = r.n_sink + r.n_win, n_fix = n_sw + r.k;
-  const uint32_t seg_sink = (uint32_t)A.seg_sink, seg_win = (uint32_t)A.seg_win, seg_topk = (uint32_t)A.seg_topk;
+  const uint32_t seg_win = (uint32_t)A.seg_win, seg_topk = (uint32_t)A.seg_topk;
   const uint32_t seg_base = (uint32_t)A.seg_base;
   const int mine = (lane / RPW) * RPB + wave * RPW + lane % RPW;  // the row of a step that this lane prepares
   auto place_of = [&](int p0) {
     const int pc = min(p0 + mine, p_hi - 1), t2 = pc - n_sw, t3 = pc - n_fix;
-    const uint32_t edge = pc < r.n_sink ? seg_sink + (uint32_t)pc : seg_win + (uint32_t)(pc - r.n_sink);
+    const uint32_t edge = pc < r.n_sink ? (uint32_t)pc : seg_win + (uint32_t)(pc - r.n_sink);
     return t3 >= 0 ? seg_base + (uint32_t)t3 : t2 >= 0 ? seg_topk + (uint32_t)t2 : edge;
   };
   // a row in the cache is known by its slot, with the top bit set
@@ -213,7 +215,7 @@ __global__ __launch_bounds__(kGatherThreads) void sparse_stats_kernel(GivenArgs 
         valid[u] = p < hi;
         const int pc = min(p, hi - 1);
         place[u] = kTail ? A.seg_base + (pc - n_fix)
-                         : fixed_place(pc, r.n_sink, r.n_win, A.seg_sink, A.seg_win, A.seg_topk);
+                         : fixed_place(pc, r.n_sink, r.n_win, 0, A.seg_win, A.seg_topk);
       }
 #pragma unroll
       for (int u = 0; u < U; ++u) {
@@ -325,7 +327,7 @@ __global__ __launch_bounds__(kGatherThreads) void sparse_stats_kernel(GivenArgs 
 // lane, list entries and known scores are requested one step ahead, all rows of a step are in flight together.  Rows of newly
 // drawn tokens bring their K row along; lane u of a group keeps the score of the group's row u and passes it to the row's
 // own lane.  A wave has one running maximum, raised once per step.
-template <int D, bool PAGED>
+template <int D, bool PAGED, bool BESIDE>
 __global__ __launch_bounds__(kGatherThreads) void given_gather_kernel(GivenArgs A) {
   constexpr int LPR = D / 8;
   constexpr int RPW = kWave / LPR;
@@ -343,7 +345,7 @@ __global__ __launch_bounds__(kGatherThreads) void given_gather_kernel(GivenArgs 
   uint32_t qw[4];
   load_q<D>(A, bh, sub, qw);
   const int n_fix = r.n_sink + r.n_win + r.k, total = n_fix + r.b;
-  const int first = A.first_slot > 0 ? n_fix : 0, count = total - first;
+  const int first = BESIDE ? n_fix : 0, count = total - first;
   const int splits = used_splits(A.splits, count, RPB * U);
   if (split >= splits) return;
   const bool shared_rows = rows_are_shared(total, A.group_major ? A.q_len * A.group : A.q_len, r.n, A.group_major && A.group > 1 ? 3 : 2);
@@ -356,7 +358,7 @@ __global__ __launch_bounds__(kGatherThreads) void given_gather_kernel(GivenArgs 
   const float tail_bias = r.scale > 0.f ? __logf(r.scale) : 0.f;  // ln(n_s / b): sampled tokens weigh n_s / b
   const int n_sw = r.n_sink + r.n_win;
   const int n_kept = n_fix + min(max(r.b_keep, 0), r.b);  // (nested samples: these have their scores in the base sample's places)
-  const uint32_t seg_sink = (uint32_t)A.seg_sink, seg_win = (uint32_t)A.seg_win, seg_topk = (uint32_t)A.seg_topk;
+  const uint32_t seg_win = (uint32_t)A.seg_win, seg_topk = (uint32_t)A.seg_topk;
   const uint32_t seg_base = (uint32_t)A.seg_base, seg_dyn = (uint32_t)A.seg_dyn;
   const int mine = (lane / RPW) * RPB + wave * RPW + lane % RPW;  // the row of a step that this lane prepares
 
@@ -364,7 +366,7 @@ __global__ __launch_bounds__(kGatherThreads) void given_gather_kernel(GivenArgs 
   float sc_next = 0.f;
   auto request = [&](int p0) {  // (beyond the range: its last place once more)
     const int pc = min(p0 + mine, p_hi - 1), t2 = pc - n_sw, t3 = pc - n_fix;
-    const uint32_t edge = pc < r.n_sink ? seg_sink + (uint32_t)pc : seg_win + (uint32_t)(pc - r.n_sink);
+    const uint32_t edge = pc < r.n_sink ? (uint32_t)pc : seg_win + (uint32_t)(pc - r.n_sink);
     const uint32_t fixed = t2 >= 0 ? seg_topk + (uint32_t)t2 : edge;
     entry_next = idx[t3 >= 0 ? seg_dyn + (uint32_t)t3 : fixed];
     sc_next = pc < n_kept ? sp[t3 >= 0 ? seg_base + (uint32_t)t3 : fixed] : 0.f;
@@ -460,7 +462,7 @@ __global__ __launch_bounds__(kGatherThreads) void given_gather_kernel(GivenArgs 
   float M = -INFINITY;
 #pragma unroll
   for (int j = 0; j < WAVES; ++j) M = fmaxf(M, s_m[j]);
-  float* part = A.part + ((int64_t)bh * A.part_slots + A.first_slot + split) * (D + 4);
+  float* part = A.part + ((int64_t)bh * A.part_slots + (BESIDE ? A.first_slot : 0) + split) * (D + 4);
   float a = 0.f, d = 0.f;
 #pragma unroll
   for (int j = 0; j < WAVES; ++j) {
@@ -475,14 +477,14 @@ __global__ __launch_bounds__(kGatherThreads) void given_gather_kernel(GivenArgs 
   }
 }
 
-// Combines the per-split (maximum, D, N) partials of a head in split order: O = N / D, lse = M + ln D.  step_rows > 0: the first
-// fixed_splits are those of I_f (from workgroups twice the size), the others the final sample's, and only those that took part
-// (used_splits) have written theirs.  Bound by the trip to memory: the first 16 are requested beside the head record.
-template <int D>
+// Combines the per-split (maximum, D, N) partials of a head in split order: O = N / D, lse = M + ln D.  APART: only the splits that took
+// part (used_splits) have written theirs; the first fixed_splits are those of I_f beside the second selection phase, the others the
+// gather's.  Bound by the trip to memory: the first 16 are requested beside the head record.
+template <int D, bool APART, bool BESIDE>
 __global__ __launch_bounds__(D) void given_merge_kernel(const float* __restrict__ part, const HeadRec* __restrict__ head_rec,
                                                         int splits, int Hq, float* __restrict__ out_o,
-                                                        float* __restrict__ out_lse, int group_major, int Hkv, int step_rows,
-                                                        int fixed_splits, int part_slots) {
+                                                        float* __restrict__ out_lse, int group_major, int Hkv, int fixed_splits,
+                                                        int part_slots) {
   const int h = head_of_block((int)blockIdx.x, Hq, Hkv, group_major), b = blockIdx.y, bh = b * Hq + h;
   const int c = threadIdx.x;
   const float* p = part + (int64_t)bh * part_slots * (D + 4);
@@ -498,11 +500,13 @@ __global__ __launch_bounds__(D) void given_merge_kernel(const float* __restrict_
   if (splits > U) load(v2, U);
   const int s = c & (kWave - 1);
   bool mine = s < splits;
-  if (step_rows > 0) {
+  if constexpr (APART) {
+    constexpr int step_rows = kGatherThreads / (D / 8) * 8;
     const HeadRec r = head_rec[bh];
     const int n_fix = r.n_sink + r.n_win + r.k;
-    mine = s < fixed_splits ? s < used_splits(fixed_splits, n_fix, 2 * step_rows)
-                            : s - fixed_splits < used_splits(splits - fixed_splits, fixed_splits > 0 ? r.b : n_fix + r.b, step_rows) && s < splits;
+    const int fixed = BESIDE ? fixed_splits : 0;
+    mine = s < fixed ? s < used_splits(fixed, n_fix, fixed_step_rows(D))
+                     : s - fixed < used_splits(splits - fixed, BESIDE ? r.b : n_fix + r.b, step_rows) && s < splits;
   }
   const uint64_t took_part = __ballot(mine);
   const float M = wave_max(mine ? dm.y : -INFINITY);
@@ -518,13 +522,19 @@ __global__ __launch_bounds__(D) void given_merge_kernel(const float* __restrict_
     }
   };
   add(v, 0);
-  if (splits > U) add(v2, U);
-  for (int s0 = 2 * U; s0 < splits; s0 += U) {
+  if (took_part >> U) add(v2, U);
+  for (int s0 = 2 * U; s0 < splits && took_part >> s0; s0 += U) {
     load(v, s0);
     add(v, s0);
   }
   out_o[(int64_t)bh * D + c] = a / dtot;
   if (c == 0 && out_lse) out_lse[bh] = M + logf(dtot);
+}
+
+template <int D>
+auto given_gather_for(bool paged, bool beside) {
+  if (paged) return beside ? given_gather_kernel<D, true, true> : given_gather_kernel<D, true, false>;
+  return beside ? given_gather_kernel<D, false, true> : given_gather_kernel<D, false, false>;
 }
 
 template <int D>
@@ -548,7 +558,6 @@ hipError_t launch_given_d(const Plan& pl, int stage, const void* q, const void* 
   A.vstat = reinterpret_cast<float*>(w + pl.off_vstat_part);
   A.out_o = out_o;
   A.out_lse = out_lse;
-  A.seg_sink = pl.seg_off[0];
   A.seg_win = pl.seg_off[1];
   A.seg_topk = pl.seg_off[2];
   A.seg_base = pl.seg_off[3];
@@ -558,8 +567,7 @@ hipError_t launch_given_d(const Plan& pl, int stage, const void* q, const void* 
   A.group = pl.group;
   A.splits = stage == 0 ? pl.given_splits : given_tail_splits(pl);
   A.first_slot = given_fixed_splits(pl);
-  A.part_slots = given_part_slots(pl);
-  if (stage != 0) A.head_rec = given_rec_of(pl, ws);
+  A.part_slots = A.first_slot > 0 ? given_part_slots(pl) : A.splits;
   A.q_len = pl.q_len;
   A.group_major = pl.group_major;
   A.sm_scale = pl.sm_scale;
@@ -578,13 +586,12 @@ hipError_t launch_given_d(const Plan& pl, int stage, const void* q, const void* 
     else hipLaunchKernelGGL((sparse_score_kernel<D, false>), grid, dim3(kGatherThreads), 0, st, A);
     return hipGetLastError();
   }
-  if (paged) hipLaunchKernelGGL((given_gather_kernel<D, true>), grid, dim3(kGatherThreads), 0, st, A);
-  else hipLaunchKernelGGL((given_gather_kernel<D, false>), grid, dim3(kGatherThreads), 0, st, A);
+  const bool beside = A.first_slot > 0;
+  hipLaunchKernelGGL((given_gather_for<D>(paged, beside)), grid, dim3(kGatherThreads), 0, st, A);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL((given_merge_kernel<D>), dim3(p.n_q_heads, pl.vbatch), dim3(D), 0, st, A.part, A.head_rec,
-                     A.first_slot + A.splits, p.n_q_heads, out_o, out_lse, pl.group_major, p.n_kv_heads, (kGatherThreads / (D / 8)) * 8,
-                     A.first_slot, A.part_slots);
+  hipLaunchKernelGGL((beside ? given_merge_kernel<D, true, true> : given_merge_kernel<D, true, false>), dim3(p.n_q_heads, pl.vbatch), dim3(D), 0, st,
+                     A.part, A.head_rec, A.first_slot + A.splits, p.n_q_heads, out_o, out_lse, pl.group_major, p.n_kv_heads, A.first_slot, A.part_slots);
   return hipGetLastError();
 }
 
@@ -603,11 +610,11 @@ hipError_t launch_given_merge(const Plan& pl, void* ws, int splits, float* out_o
   const float* part = reinterpret_cast<const float*>(static_cast<char*>(ws) + pl.off_gather_part);
   const HeadRec* rec = reinterpret_cast<const HeadRec*>(static_cast<char*>(ws) + pl.off_head_rec);
   if (p.head_dim == 128)
-    hipLaunchKernelGGL((given_merge_kernel<128>), dim3(p.n_q_heads, pl.vbatch), dim3(128), 0, st, part, rec, splits,
-                       p.n_q_heads, out_o, out_lse, pl.group_major, p.n_kv_heads, 0, 0, splits);
+    hipLaunchKernelGGL((given_merge_kernel<128, false, false>), dim3(p.n_q_heads, pl.vbatch), dim3(128), 0, st, part, rec, splits,
+                       p.n_q_heads, out_o, out_lse, pl.group_major, p.n_kv_heads, 0, splits);
   else if (p.head_dim == 64)
-    hipLaunchKernelGGL((given_merge_kernel<64>), dim3(p.n_q_heads, pl.vbatch), dim3(64), 0, st, part, rec, splits,
-                       p.n_q_heads, out_o, out_lse, pl.group_major, p.n_kv_heads, 0, 0, splits);
+    hipLaunchKernelGGL((given_merge_kernel<64, false, false>), dim3(p.n_q_heads, pl.vbatch), dim3(64), 0, st, part, rec, splits,
+                       p.n_q_heads, out_o, out_lse, pl.group_major, p.n_kv_heads, 0, splits);
   else
     return hipErrorInvalidValue;
   return hipGetLastError();

@@ -117,30 +117,42 @@ struct Plan {
 };
 
 // Caller-supplied top-k, gather apart: workgroups per head that gather I_f beside the second selection phase, in its launch (0: the
-// gather behind it takes the whole list), and workgroups of the gather behind it; their partial sums share a region of at least 16 per
-// head.  Beside it where every head's phase has a compute unit to itself: with two of them on each, the rows wait for their slots
-// and the launch takes as long as the two one after the other.  Whole step, us, behind -> beside: 128 heads of 128K tokens 99.6 -> 94.2,
-// 192 of 32K (3 query tokens) 56.1 -> 52.1; but 512 heads of 32K 111.0 -> 113.2, of 4K 47.8 -> 49.0, 1024 of 0.3K - 1.5K paged 61.3 ->
-// 65.4.  Where query tokens share the rows, two of them on a unit still gain on longer rows: 512 heads of 9K (16 query tokens) 58.5 ->
-// 55.5, 32K (16) 85.9 -> 84.6, 16K (2) 76.5 -> 74.2, 20K (4) at epsilon 0.02 164 -> 156; but of 1K (16) 44.1 -> 44.7, 960 of 3K (3)
-// 84.9 -> 86.2, 1024 of 8K (8) 88.1 -> 89.2.
-inline int given_part_slots(const Plan& pl) { return pl.split_cap > 16 ? pl.split_cap : 16; }
-inline bool given_beside(const Plan& pl) {
-  const int heads = pl.vbatch * pl.p.n_q_heads;
-  return heads <= pl.num_cus || (pl.q_len > 1 && heads <= 2 * pl.num_cus && pl.p.n_max >= 4096);
+// gather behind it takes the whole list).  The host knows the plan's capacity, not the lengths: the lines lie where they do for sequences
+// of about that length.  Whole step, us, behind -> beside:
+// Heads: where every head's phase has a compute unit to itself, 128 heads of 128K tokens 101.3 -> 94.9, 192 of 12K 34.5 -> 33.0; with more
+// of them the rows wait for slots and the launch takes as long as the two one after the other, 512 heads of 32K 111.0 -> 113.2, 1024 of
+// 0.3K - 1.5K paged 61.3 -> 65.4.  Where query tokens share the rows two phases on a unit still gain on longer rows: 512 heads of 9K (16
+// query tokens) 58.9 -> 54.7, 32K with lists of 0.2 of it 219 -> 195; but of 1.5K with such lists 38.8 -> 40.5, 960 of 3K 84.9 -> 86.2.
+// Rows: below some 400 the two launches are as long as they were, 192 heads of 1.5K (293 rows) 26.2 -> 26.6, of 6K (406) 31.4 -> 30.9; with
+// few heads, whose phases are shorter, 32 of 4K (356) 24.4 -> 24.9, of 0.9K (526) 22.8 -> 23.5, of 16K (656) 22.9 -> 22.8.
+// Budgets: where (z / epsilon)^2 is large beside the length the sample is most of the residual, the phase takes long and the rows saved are
+// few: 192 heads of 9K at epsilon 0.005 78.2 -> 81.9, 512 at 0.01 135.3 -> 137.5, but 192 of 30K at 0.01 129.7 -> 124.4.  So it
+// is with the targets N and SDPA, by the values: 128 heads of 9K 91.7 -> 94.0, of 32K at epsilon 0.2 71.7 -> 67.9.
+// Workgroups: up to 6 per head and some two per unit in all, with 4 steps each at most; more of them slow the phases beside them (256
+// heads of 30K with 2 / 4 58.6 / 61.3, 192 of 24K with 2 / 4 44.7 / 45.4, 32 of 100K with 6 / 11 39.2 / 41.2), and fewer steps than
+// a list has are idle launches.
+// Sequences far shorter than a long capacity lose up to 2 %, longer ones gain: 512 heads (16 query tokens), capacity 32K, of 1K 48.3 -> 49.2,
+// 2K 59.6 -> 60.5, 3K 68.1 -> 68.3, 4K 75.4 -> 74.4, 6K 84.7 -> 82.9, 24K 179.7 -> 171.0.
+constexpr int kFixedLeast = 400, kFixedLeastFew = 640, kFixedWorkgroups = 576, kFixedMost = 6;
+__host__ __device__ constexpr int fixed_step_rows(int head_dim) { return kHeadThreads / (head_dim / 8) * 8; }  // rows of one of them per step
+constexpr int given_part_slots(const Plan& pl) { return pl.split_cap > 16 ? pl.split_cap : 16; }  // partial sums of a head in all
+constexpr int given_fixed_splits(const Plan& pl) {
+  const int heads = pl.vbatch * pl.p.n_q_heads, step = fixed_step_rows(pl.p.head_dim);
+  const int rows = pl.p.sink + pl.p.window + pl.k_max;
+  if (heads > pl.num_cus && (pl.q_len == 1 || heads > 2 * pl.num_cus || pl.p.n_max < 4096)) return 0;
+  if (pl.p.target != VATT_TARGET_D || rows < (2 * heads > pl.num_cus ? kFixedLeast : kFixedLeastFew)) return 0;
+  if ((pl.z_half / pl.eps) * (pl.z_half / pl.eps) > 4.0 * pl.p.n_max) return 0;
+  const int steps = (rows + step - 1) / step;
+  int splits = kFixedWorkgroups / heads;
+  splits = splits > kFixedMost ? kFixedMost : splits < 2 ? 2 : splits;
+  splits = splits < (steps + 3) / 4 ? (steps + 3) / 4 : splits > steps ? steps : splits;
+  const int left = given_part_slots(pl) - (pl.given_splits < given_part_slots(pl) ? pl.given_splits : given_part_slots(pl) - 1);
+  return splits < left ? splits : left;
 }
-inline int given_tail_splits(const Plan& pl) {
-  if (!given_beside(pl)) return pl.given_splits;
-  return pl.given_splits < given_part_slots(pl) ? pl.given_splits : given_part_slots(pl) - 1;
+// Workgroups per head of the gather behind it.
+constexpr int given_tail_splits(const Plan& pl) {
+  return given_fixed_splits(pl) > 0 && pl.given_splits >= given_part_slots(pl) ? given_part_slots(pl) - 1 : pl.given_splits;
 }
-inline int given_fixed_splits(const Plan& pl) {
-  if (!given_beside(pl)) return 0;
-  const int left = given_part_slots(pl) - given_tail_splits(pl);
-  return pl.given_splits < left ? pl.given_splits : left;
-}
-// Where the second phase leaves its record.
-inline HeadRec* given_rec_of(const Plan& pl, void* ws) { return reinterpret_cast<HeadRec*>(static_cast<char*>(ws) + pl.off_pre_flags); }
-static_assert(sizeof(HeadRec) <= kHeadThreads * sizeof(uint32_t), "it lies in the region of the draws made ahead");
 
 // Bytes of score rows a call writes, and the size from which on they are taken to outgrow the last-level cache beside
 // what else passes through it.
@@ -189,7 +201,7 @@ hipError_t launch_given_fused(const Plan& pl, int phase, const void* q, const vo
                               const int32_t* given_idx, const int32_t* given_cnt, const void* rcache, void* ws,
                               int32_t* out_idx, int32_t* out_counts, double* out_budget_raw, float* out_stats,
                               hipStream_t st);
-// The second selection phase with the gather of I_f beside it, in one launch.
+// The second selection phase, with the gather of I_f beside it in the same launch where given_fixed_splits says so.
 hipError_t launch_given_budget(const Plan& pl, const void* v, const int32_t* block_table, const int32_t* seq_lens,
                                const uint64_t* seq_seeds, void* ws, int32_t* out_idx, int32_t* out_counts, double* out_budget_raw,
                                float* out_stats, hipStream_t st);

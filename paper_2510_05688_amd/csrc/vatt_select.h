@@ -56,12 +56,15 @@ struct HeadArgs {
   KVLayout L;
   float* part;       // [B*Hq][splits][d + 4]: partial (sum w V, sum w) of every workgroup
   int splits, split_shift, group;
-  int glist_cap;  // LDS entries for a workgroup's share of I_f; caller-supplied path, gather apart: partial sums of a head in all
+  union {
+    int glist_cap;   // fused gathers: LDS entries for a workgroup's share of I_f
+    int part_slots;  // caller-supplied path, gather apart: partial sums of a head in all
+  };
   int dlist_cap;  // LDS entries for a workgroup's share of the final sample
   // first batches of draws made ahead (nullptr: made here): of both sampler streams by workgroups of the score launch, and on the
   // caller-supplied path of the final sample's by the first phase for the second
   uint4* pre_tok;       // [B*Hq][kHeadThreads]: the four proposed tokens of every thread
-  uint32_t* pre_flags;  // [B*Hq][kHeadThreads]: see pre_pack.  Also the place of what later kernels leave (kFixedStride, given_rec_of): with
+  uint32_t* pre_flags;  // [B*Hq][kHeadThreads]: see pre_pack.  Also the place of what the budget kernel leaves (kFixedStride): with
                         // pointers of their own the arguments are a cache line longer, 0.3 us of the short calls
   // random cache of base-sample rows (nullptr: the base sample is drawn)
   const void* rcache;

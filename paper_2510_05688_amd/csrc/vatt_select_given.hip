@@ -38,7 +38,7 @@ __device__ __forceinline__ bool draw_ahead(const HeadArgs& A, const HeadSizes& h
 // (N, D, maximum) per workgroup for given_merge_kernel.
 // PHASE is a constant of the kernel: what both phases could share is little, and values that only one of them loads would be
 // waited for where the paths meet.
-template <int NT, int FD, bool PAGED, int PHASE>
+template <int NT, int FD, bool PAGED, int PHASE, bool BESIDE = false>
 __device__ __forceinline__ void given_topk(const HeadArgs& A) {
   using O = HeadOps<NT>;
   using HeadSmem = typename O::HeadSmem;
@@ -81,12 +81,10 @@ __device__ __forceinline__ void given_topk(const HeadArgs& A) {
   // What can be asked for before anything is worked out comes first, and the first batch of draws, which depends on the seed,
   // the head and the length only, is made while it is under way.
   HeadRec rec = {};
-  int flags_before = 0;
   uint4 pre_t = make_uint4(0u, 0u, 0u, 0u);
   uint32_t pre_f = 0u, pre_all = 0u;
   if constexpr (PHASE != 0) {
     rec = A.head_rec[bh];
-    flags_before = A.out_counts[(int64_t)bh * 8 + 7];  // (at the end it would be a trip of its own)
     if constexpr (kFused) {
       pre_t = A.pre_tok[(int64_t)bh * NT + tid];
       pre_f = A.pre_flags[(int64_t)bh * NT + tid];
@@ -644,7 +642,7 @@ __device__ __forceinline__ void given_topk(const HeadArgs& A) {
     c[4] = bfin;
     c[5] = hs.n_s;
     c[6] = n;
-    c[7] = flags_before | flags;
+    c[7] = c[7] | flags;
     if (A.out_budget_raw) A.out_budget_raw[bh] = b_star;
     if (A.out_stats) {
       float* st = A.out_stats + (int64_t)bh * 4;
@@ -668,7 +666,15 @@ __device__ __forceinline__ void given_topk(const HeadArgs& A) {
     r.tail_by_token = 0;
     // (with the gather fused in nothing reads the record again, and the head's other workgroups may still be
     // reading the first phase's)
-    if (!kFused) reinterpret_cast<HeadRec*>(A.pre_flags)[bh] = r;  // (beside the first phase's, which others are reading)
+    HeadRec* to = A.head_rec + bh;
+    if (BESIDE) {  // (the other fields stay the first phase's: gather_fixed is reading them; written whole it is 0.2 us faster where nobody is)
+      to->m = r.m;
+      to->scale = r.scale;
+      to->b = r.b;
+      to->b_keep = r.b_keep;
+    } else if (!kFused) {
+      *to = r;
+    }
   }
 
   if constexpr (kFused) {
@@ -801,11 +807,11 @@ __device__ __forceinline__ void gather_fixed(const HeadArgs& A, int split) {
   const int bh = b * A.Hq + h, kvh = div_group(h, A.group), seq = seq_of_pair(b, A.q_len);
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int sub = lane % LPR, rsub = lane / LPR;
-  const HeadRec r = A.head_rec[bh];  // the first phase's: b is the size of the base sample
+  const HeadRec& r = A.head_rec[bh];  // (the second phase is writing m, scale, b and b_keep)
   const int n_fix = r.n_sink + r.n_win + r.k;
-  const int splits = used_splits(A.splits, n_fix, RPB * U);
+  const int splits = used_splits(A.splits, n_fix, fixed_step_rows(D));
   if (split >= splits) return;
-  const bool shared_rows = rows_are_shared(n_fix + r.b, A.group_major ? A.q_len * A.group : A.q_len, r.n, A.group_major && A.group > 1 ? 3 : 2);
+  const bool shared_rows = rows_are_shared(n_fix + (r.n_s > 0 ? base_count_of(r.n_s, A.sp) : 0), A.group_major ? A.q_len * A.group : A.q_len, r.n, A.group_major && A.group > 1 ? 3 : 2);
   const int per = (n_fix + splits - 1) / splits;
   const int p_lo = split * per, p_hi = min(p_lo + per, n_fix);
   const int32_t* idx = A.out_idx + (int64_t)bh * A.idx_cap;
@@ -877,7 +883,7 @@ __device__ __forceinline__ void gather_fixed(const HeadArgs& A, int split) {
   float M = -INFINITY;
 #pragma unroll
   for (int j = 0; j < WAVES; ++j) M = fmaxf(M, s_m[j]);
-  float* part = A.part + ((int64_t)bh * A.glist_cap + split) * (D + 4);
+  float* part = A.part + ((int64_t)bh * A.part_slots + split) * (D + 4);
   float a = 0.f, d = 0.f;
 #pragma unroll
   for (int j = 0; j < WAVES; ++j) {
@@ -892,12 +898,12 @@ __device__ __forceinline__ void gather_fixed(const HeadArgs& A, int split) {
   }
 }
 
-// The second phase of a step whose gather is apart (given_fixed_splits), and beside it, in the same launch and behind the workgroups of
+// The second phase of a step whose gather is apart, and beside it (given_fixed_splits) in the same launch and behind the workgroups of
 // the phase, the first of the third grid dimension, the gather of I_f, which waits for nothing that the phase finds out: a phase
 // is a chain of 9 us that leaves memory idle.
 template <int D, bool PAGED>
 __global__ __launch_bounds__(kHeadThreads) void given_budget_kernel(HeadArgs A) {
-  if (blockIdx.z == 0) given_topk<kHeadThreads, 0, false, 1>(A);
+  if (blockIdx.z == 0) given_topk<kHeadThreads, 0, false, 1, true>(A);
   else gather_fixed<D, PAGED>(A, (int)blockIdx.z - 1);
 }
 
@@ -963,8 +969,7 @@ hipError_t launch_given_budget(const Plan& pl, const void* v, const int32_t* blo
   A.L.block_table = block_table;
   A.part = reinterpret_cast<float*>(static_cast<char*>(ws) + pl.off_gather_part);
   A.splits = given_fixed_splits(pl);
-  A.glist_cap = given_part_slots(pl);
-  A.pre_flags = reinterpret_cast<uint32_t*>(given_rec_of(pl, ws));
+  A.part_slots = given_part_slots(pl);
   const size_t lds = sizeof(uint32_t) * sampler_lds<kHeadThreads>(pl.p.n_max).end;
   const GivenKernel kernel = A.splits > 0 ? given_budget_kernel_for(pl.p.head_dim, pl.p.kv_layout == VATT_LAYOUT_PAGED) : given_kernel_for(1, 0, false);
   hipLaunchKernelGGL(kernel, dim3(pl.p.n_q_heads, pl.vbatch, 1 + A.splits), dim3(kHeadThreads), lds, st, A);

@@ -268,11 +268,15 @@ def test_an_empty_list_is_not_interpreted():
     sess.close()
 
 
-# (tokens, sink, window, k, b0, epsilon): I_f empty, around one step of a 512-thread workgroup (256 rows of 128 columns), of many steps;
-# no residual; a whole residual
+# (tokens, sink, window, k, b0, epsilon).  In one launch where I_f can have 640 rows or more (few heads): around that line, around one
+# step each of three workgroups (256 rows of 128 columns) and of six, more rows than that, no residual, budgets beyond the first draws.
+# Behind it in both forms: I_f empty, around one step, no residual, a whole residual.
+BESIDE = [(2000, 100, 100, 439, 64, 0.05), (2000, 100, 100, 440, 64, 0.05), (4000, 100, 100, 567, 64, 0.05), (4000, 100, 100, 568, 64, 0.05),
+          (4000, 100, 100, 569, 64, 0.05), (4000, 100, 100, 1336, 64, 0.05), (4000, 100, 100, 1337, 64, 0.05), (1000, 150, 150, 700, 8, 0.1),
+          (7000, 128, 900, 1500, 300, 0.014)]
 @pytest.mark.parametrize("paged", [False, True])
 @pytest.mark.parametrize("case", [(900, 0, 0, 0, 40, 0.1), (2000, 100, 100, 55, 64, 0.05), (2000, 100, 100, 56, 64, 0.05), (2000, 100, 100, 57, 64, 0.05),
-                                  (300, 150, 150, 9, 8, 0.1), (6000, 128, 900, 2500, 300, 0.005)], ids=lambda c: "-".join(map(str, c)))
+                                  (300, 150, 150, 9, 8, 0.1), (6000, 128, 900, 2500, 300, 0.005)] + BESIDE, ids=lambda c: "-".join(map(str, c)))
 def test_gather_of_the_fixed_set_beside_the_budget_and_behind_it(case, paged):
     from paper_2510_05688_amd import binding as vb
     from paper_2510_05688_amd.session import DecodeSession
@@ -282,7 +286,7 @@ def test_gather_of_the_fixed_set_beside_the_budget_and_behind_it(case, paged):
                                  plant_frac=0.003)
     supplied = {h: _oracle_topk(wl, 0, h) for h in range(4)}
     got = []
-    for batch in (1, 70):  # 4 heads: beside the second phase; 280, more than the card has compute units: behind it
+    for batch in (1, 70):  # 280 heads, more than the card has compute units: behind the second phase
         params = dict(plan_params(wl), batch=batch)
         tile = lambda a: np.concatenate([a] * batch)
         if paged:
