@@ -61,3 +61,53 @@ def test_budgets_at_the_edges_of_their_sizes(case, head_dim, threads):
                 n_dyn = int(min(one[4], other[4]))
                 if not int(one[7]) & 2:  # (a complement leaves out another token if one fewer is left out)
                     assert np.array_equal(many["idx"][r * wl.batch + b, h, seg[4]:seg[4] + n_dyn], res["idx"][b, h, seg[4]:seg[4] + n_dyn])
+
+
+def _launches(sess):
+    """Kernels of one decode call: the nodes of a graph that it is captured into."""
+    import ctypes
+    import torch
+    side = torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    graph = torch.cuda.CUDAGraph(keep_graph=True)
+    with torch.cuda.graph(graph, stream=side):
+        sess.decode()
+    count = ctypes.c_size_t(0)
+    hip = ctypes.CDLL("libamdhip64.so")
+    assert hip.hipGraphGetNodes(ctypes.c_void_p(graph.raw_cuda_graph()), None, ctypes.byref(count)) == 0
+    return count.value
+
+
+@pytest.mark.parametrize("paged", [False, True])
+@pytest.mark.parametrize("head_dim", [64, 128])
+def test_one_gather_workgroup_per_head_finishes_it(head_dim, paged):
+    """Sixteen heads per compute unit and more: the gather of the final sample adds the sums over I_f itself, with an empty sample (30
+    tokens) too, and no merge is launched."""
+    from paper_2510_05688_amd.session import DecodeSession
+    p = default_params(head_dim, sink=4, window=28, topk_abs=20, topk_frac=0.0, base_abs=16, base_frac=0.0, epsilon=0.3, target=2)
+    wl = workloads.make_workload("alone", batch=2, n_q_heads=4, n_kv_heads=2, head_dim=head_dim, n_max=320, seq_lens=[317, 30], seed=9, params=p,
+                                 v_mean=1.0)
+    k_bits, v_bits, table = workloads.to_paged(wl, 16) if paged else (wl.k_bits, wl.v_bits, None)
+    repeat, got, launches = 512, [], []
+    for times in (1, repeat):
+        tile = lambda a: np.concatenate([a] * times)
+        sess = DecodeSession(dict(plan_params(wl, paged=paged, num_blocks=len(k_bits) if paged else 0), batch=2 * times))
+        # (the copies of a sequence read the same pages)
+        sess.upload(tile(wl.q_bits), k_bits if paged else tile(k_bits), v_bits if paged else tile(v_bits), tile(wl.seq_lens), tile(wl.seeds),
+                    tile(table) if paged else None)
+        sess.workspace.fill_(0xff)
+        sess.out_idx.zero_()
+        sess.decode()
+        got.append(sess.results_host())
+        launches.append(_launches(sess))
+        sess.close()
+    one, many = got
+    check_all(wl, one, label="alone")
+    assert launches == [6, 5]
+    assert not one["counts"][1, :, 4].any() and (one["counts"][0, :, 4] > 0).all()
+    for r in range(0, repeat, 73):
+        rows = slice(2 * r, 2 * r + 2)
+        assert np.array_equal(many["counts"][rows], one["counts"])
+        # (sums of some hundred 32-bit products cut at other places: a few units in the last place of the largest value)
+        np.testing.assert_allclose(many["O"][rows], one["O"], rtol=0, atol=4e-6 * np.abs(one["O"]).max())
+        np.testing.assert_allclose(many["lse"][rows], one["lse"], rtol=0, atol=4e-6)
