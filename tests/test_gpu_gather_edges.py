@@ -154,15 +154,17 @@ def test_budgets_beyond_the_first_draws_are_paged_as_they_are_contiguous(d, epsi
             assert np.linalg.norm(got[1]["O"][b, h] - want) <= 2e-6 * np.linalg.norm(want)
 
 
-def _decode(wl, paged, splits, v_bits):
+def _decode(wl, paged, splits, v_bits, copies=1):
     from paper_2510_05688_amd import binding as vb
     from paper_2510_05688_amd.session import DecodeSession
     kept, wl.v_bits = wl.v_bits, v_bits
     k_bits, v_bits, table = workloads.to_paged(wl, 16) if paged else (wl.k_bits, wl.v_bits, None)
     wl.v_bits = kept
-    sess = DecodeSession(plan_params(wl, paged=paged, num_blocks=k_bits.shape[0] if paged else 0))
+    sess = DecodeSession(dict(plan_params(wl, paged=paged, num_blocks=k_bits.shape[0] if paged else 0), batch=wl.batch * copies))
     vb.vatt_plan_set_option(sess.plan, vb.VATT_OPT_FUSED_GATHER, splits)
-    sess.upload(wl.q_bits, k_bits, v_bits, wl.seq_lens, wl.seeds, table)
+    tile = lambda a: np.concatenate([a] * copies)
+    sess.upload(tile(wl.q_bits), k_bits if paged else tile(k_bits), v_bits if paged else tile(v_bits), tile(wl.seq_lens), tile(wl.seeds),
+                tile(table) if paged else None)
     sess.decode()
     res = sess.results_host()
     sess.close()
@@ -207,16 +209,20 @@ def test_an_inf_in_a_listed_row_stays_an_inf(d, n, paged, splits):
 @pytest.mark.parametrize("paged", [False, True])
 @pytest.mark.parametrize("d", [64, 128])
 def test_an_inf_in_the_last_base_sample_row_stays_an_inf(d, paged):
-    """Output target: the statistics pass reads the base sample's rows last.  A base sample that is the whole residual ends
-    with the largest token before the window; an Inf in its V row makes the numerator's norm Inf, not NaN."""
+    """Output target: the statistics pass reads the base sample's rows last, the gather behind it the final sample's.  Both are the whole
+    residual here and end with the largest token before the window; an Inf in its V row makes the numerator's norm and the output
+    Inf, not NaN, with several gather workgroups per head and with one."""
     n = 300
     p = default_params(d, sink=16, window=48, topk_abs=8, topk_frac=0.0, base_abs=n, base_frac=0.0, target=2)
     wl = workloads.make_workload("inf_base", batch=1, n_q_heads=4, n_kv_heads=2, head_dim=d, n_max=304, seq_lens=[n], seed=3, params=p)
     spoilt = wl.v_bits.copy()
     spoilt[0, :, n - 49, 7] = 0x7F80
-    res = _decode(wl, paged, 0, spoilt)
-    last = [res["idx"][0, h, res["seg"][3] + res["counts"][0, h, 3] - 1] for h in range(4)]
-    heads = [h for h in range(4) if last[h] == n - 49]
-    assert heads
-    for h in heads:
-        assert res["stats"][0, h, 3] == np.inf and res["O"][0, h, 7] == np.inf
+    for copies in (1, 1024):  # (4096 heads have one workgroup each)
+        res = _decode(wl, paged, 0, spoilt, copies)
+        seg, counts, idx = res["seg"], res["counts"][-1], res["idx"][-1]
+        heads = [h for h in range(4) if idx[h, seg[3] + counts[h, 3] - 1] == n - 49]
+        assert heads
+        for h in heads:
+            assert idx[h, seg[4] + counts[h, 4] - 1] == n - 49
+            assert res["stats"][-1, h, 3] == np.inf and res["O"][-1, h, 7] == np.inf
+            assert np.isfinite(np.delete(res["O"][-1, h], 7)).all()
