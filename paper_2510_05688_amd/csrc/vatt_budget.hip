@@ -163,7 +163,7 @@ __global__ __launch_bounds__(NT, 4) void budget_kernel(HeadArgs A) {
   for (int i = tid + NT; i < hs.n_win; i += NT) fixed(row[hs.mid_hi + i]);
   O::block_sum(sums, sm);
   const double D_f = sums[0];
-  double* fixed_sums = reinterpret_cast<double*>(A.pre_flags) + (int64_t)bh * kFixedStride;
+  double* fixed_sums = A.fixed_sums + (int64_t)bh * kFixedStride;  // (this workgroup has read the head's flags)
   if (tid < d) {
     if (A.vstat_splits > VS) take(VS);
     for (int s0 = 2 * VS; s0 < A.vstat_splits; s0 += VS) {

@@ -341,7 +341,7 @@ hipError_t launch_gather_d(const Plan& pl, const void* v, const int32_t* block_t
   A.head_rec = reinterpret_cast<const HeadRec*>(w + pl.off_head_rec);
   A.idx = out_idx;
   A.part = reinterpret_cast<float*>(w + pl.off_gather_part);
-  A.fixed_sums = reinterpret_cast<const double*>(w + pl.off_pre_flags);
+  A.fixed_sums = fixed_sums_of(pl, ws);
   A.vpart = reinterpret_cast<double*>(w + pl.off_vstat_part);
   A.out_o = out_o;
   A.out_lse = out_lse;

@@ -154,6 +154,8 @@ constexpr int given_tail_splits(const Plan& pl) {
   return given_fixed_splits(pl) > 0 && pl.given_splits >= given_part_slots(pl) ? given_part_slots(pl) - 1 : pl.given_splits;
 }
 
+inline double* fixed_sums_of(const Plan& pl, void* ws) { return reinterpret_cast<double*>(static_cast<char*>(ws) + pl.off_pre_flags); }
+
 // Bytes of score rows a call writes, and the size from which on they are taken to outgrow the last-level cache beside
 // what else passes through it.
 inline size_t score_bytes(const Plan& pl) { return (size_t)pl.vbatch * pl.p.n_q_heads * pl.p.n_max * sizeof(float); }

@@ -64,8 +64,10 @@ struct HeadArgs {
   // first batches of draws made ahead (nullptr: made here): of both sampler streams by workgroups of the score launch, and on the
   // caller-supplied path of the final sample's by the first phase for the second
   uint4* pre_tok;       // [B*Hq][kHeadThreads]: the four proposed tokens of every thread
-  uint32_t* pre_flags;  // [B*Hq][kHeadThreads]: see pre_pack.  Also the place of what the budget kernel leaves (kFixedStride): with
-                        // pointers of their own the arguments are a cache line longer, 0.3 us of the short calls
+  union {                  // (with a pointer of its own for each the arguments are a cache line longer, 0.3 us of the short calls)
+    uint32_t* pre_flags;   // [B*Hq][kHeadThreads]: see pre_pack
+    double* fixed_sums;    // the same place (fixed_sums_of), [B*Hq][kFixedStride]: what the budget kernel leaves
+  };
   // random cache of base-sample rows (nullptr: the base sample is drawn)
   const void* rcache;
   CacheLayout rc;
