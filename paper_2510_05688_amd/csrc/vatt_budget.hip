@@ -10,10 +10,9 @@ namespace {
 // the gather then reads the rows of the final sample only.
 // What bounds it: one chain per head.  Everything that the budget waits for is asked for ahead of the first batch of draws, which
 // is as large as the workgroup can make it: budgets of these targets go well beyond the base sample.
-// Whole call, us, before (the selection kernel with its top-k step left out, then a gather of all listed rows), with this kernel and
-// the gather of the final sample alone, and now (two workgroups per head in phase 1, PRE): 4 x 16K tokens 86.8, 82.5, 79.7; 16 x 32K
-// 373, 358, 359; 32 x 8K 324, 311, 312; 4 x 128K 353, 333, 326; 8 x 4K paged 82.5, 82.0, 81.8; 2 x 9K of 16 heads 50.7, 50.7, 46.8;
-// one of 2K 37.4, 37.2, 35.1.
+// Whole call, us, before (the selection kernel with its top-k step left out, then a gather of all listed rows) and now (this kernel, the
+// gather of the final sample alone, and with few heads two workgroups each in phase 1, PRE): 4 x 16K tokens 87.6 -> 80.2, 16 x 32K
+// 375 -> 359, 32 x 8K 328 -> 313, 4 x 128K 350 -> 325, 8 x 4K paged 83.3 -> 80.7, 2 x 9K of 16 heads 50.9 -> 47.5, one of 2K 34.5 -> 30.5.
 // PRE: the first batch of draws comes from the second workgroups of phase 1.
 template <int NT, bool OPTIONS, bool PRE>
 __global__ __launch_bounds__(NT, 4) void budget_kernel(HeadArgs A) {

@@ -75,8 +75,8 @@ __global__ __launch_bounds__(NT, FD > 0 ? 1 : 4) void head_kernel(HeadArgs A) {
   // or the budget kernel's first batch of draws.  Nothing is exchanged: it writes the scores of all accepted draws of the
   // first batch, and the first workgroup says in the record whether the sample is the beginning of them.  A compute unit takes
   // four to five clocks per scattered 4-byte read, and with one workgroup per head half of the units pulled all of them.
-  // Whole call, us, one -> two: 4 x 128K tokens 250.5 -> 245.0, 1 x 128K 113.6 -> 103.0, 2 of 9K - 100K paged 108.5 -> 99.1, 4 x 50K with
-  // k and b0 of 5 % 151.6 -> 145.4, 1 x 60K at epsilon 0.02 59.5 -> 57.3, 1 x 91K with 3 query tokens 109.4 -> 99.1.
+  // Whole call, us, one -> two: 4 x 128K tokens 250.4 -> 244.1, 1 x 128K 112.1 -> 102.3, 2 of 9K - 100K paged 108.5 -> 99.1, 4 x 50K with
+  // k and b0 of 5 % 152.0 -> 145.8, 1 x 60K at epsilon 0.02 59.2 -> 56.4, 1 x 91K with 3 query tokens 108.9 -> 98.4.
   // Targets N and SDPA: 4 x 16K 82.5 -> 80.5, 1 x 32K 86.8 -> 84.4, 2 x 9K of 16 heads 50.7 -> 47.8, 4 x 128K 333 -> 327, 1 x 100K 155 -> 152.7.
   static_assert(!PAIR || (!kFused && !OPTIONS && (NT >= 1024 || PHASE == 1)), "what head_pair asks for");
   const bool second = PAIR && blockIdx.z == 1u;
